@@ -591,10 +591,33 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
   a.has_linear = pl.NL > 0; a.P = pl.P; a.act = pl.act_q;
   a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
   a.scale_log2e = pl.scale * kLog2e;
-  // block_size 128: 8 waves x 32 queries, ring of 8 key blocks, barrier every 64 keys (one workgroup per CU);
-  // block_size 64: 4 waves x 32 queries, ring of 4 key blocks, barrier every 32 keys (two workgroups per CU).
-  const bool big = pl.KT == 128;
-  a.n_qtiles = pl.n_qtiles;
+  // Two tilings of one computation (every query column sees the same keys in the same order: the same bits): 8 waves x
+  // 32 queries with a ring of 8 key blocks and a barrier every 64 keys, one workgroup per CU, or 4 waves x 32 queries
+  // with a ring of 4 and a barrier every 32 keys, two workgroups per CU.  The variants' tiles are part of their
+  // definition, so block_size decides there; for the plain operator the sizes do.  Query kernel, H = 12, R = 4, in us,
+  // 8 waves against 4:
+  //   d = 128, 128-wide maps    N = 256: 20 / 24, 1560: 29 / 35, 5003: 55 / 69, 12000: 260 / 258, 32760: 1386 / 1493
+  //   d = 128, 256-wide maps    N = 256: 64 / 73, 5003: 98 / 116, 32760: 1634 / 1701; fp32, B = 2, N = 5003: 198 / 282
+  //   d = 64                    N = 256: 12 / 15, 5003 (240 workgroups): 33 / 37, 8000 (384): 79 / 70, 32760: 838 / 818
+  //   linear part precomputed   N = 1560: 20 / 16, 3000 (288 small workgroups): 30 / 31, 20000: 546 / 573
+  //   R = 1, B H = 10, N = 230 (whole call): 14.6 / 12.3
+  // The 4-wave kernel reads the epilogue's operands from L2 instead of LDS and fetches every key block twice as often;
+  // with d = 64 both are small, and its two independent workgroups per CU fill each other's gaps once there is more
+  // than one round of them.  With the linear part precomputed or absent it has no operands to fetch: it is 5 % slower
+  // over whole rounds of the chip (N = 20000, 32760 above), but a last round of at most one small workgroup per CU takes
+  // 0.6 of a round instead of a whole one (N = 8000, 768 small workgroups: 106 / 117; 12000: 225 / 243), which `few` adds up
+  // in twentieths of a round.
+  const auto wgs = [&](int qt) { return (int64_t)((pl.N + qt - 1) / qt) * pl.B * pl.H; };
+  bool big;
+  if (pl.LW > 0 || pl.CC > 0) big = pl.KT == 128;
+  else if ((wide || pl.NL == 0) && (pl.D == 128 || wgs(128) <= 256)) {
+    const int64_t tail = wgs(128) % 512;
+    const int64_t few = wgs(128) / 512 * 21 + (tail == 0 ? 0 : tail <= 256 ? 13 : 21);
+    big = (wgs(256) + 255) / 256 * 20 <= few;
+  } else if (pl.D == 64) big = wgs(256) <= 256;
+  else big = true;
+  const int qt = big ? 256 : 128;
+  a.n_qtiles = (pl.N + qt - 1) / qt;
   a.total_wg = a.n_qtiles * pl.B * pl.H;
   dim3 grid(((a.total_wg + 7) / 8) * 8);
 #define HA_QUERY(DD, HH, FF, F32) \
@@ -607,7 +630,7 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
       else query_kernel_ring<DD, HH, FF, 4, 4, 1, F32, false, 1><<<grid, 256, 0, st>>>(a); \
     } else { \
       if (big) query_kernel_ring<DD, HH, FF, 8, 8, 2, F32><<<grid, 512, 0, st>>>(a); \
-      else query_kernel_ring<DD, HH, FF, 4, 4, 1, F32><<<grid, 256, 0, st>>>(a); \
+      else if constexpr (HH <= 128) query_kernel_ring<DD, HH, FF, 4, 4, 1, F32><<<grid, 256, 0, st>>>(a); \
     } \
   } while (0)
   if (wide) {
