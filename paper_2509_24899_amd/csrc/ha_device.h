@@ -52,6 +52,11 @@ static __device__ __forceinline__ float xhalf_sum(float x) {
   return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
 
+// max(x, 0) in one instruction: fmaxf first quiets an operand the compiler cannot vouch for (a matrix-core result), which
+// is a second v_max per value.  A NaN gives 0 here, as it does there.  (The upper bound is not INFINITY because the
+// compiler turns that into fmaxf again; an infinite hidden activation overflows the hi + lo split either way.)
+static __device__ __forceinline__ float relu(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, 3.402823466e+38f); }
+
 static __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // 8 consecutive elements of a row in the io dtype -> 8 bf16 (fp32 is rounded to nearest even).

@@ -46,7 +46,7 @@ static __device__ __forceinline__ void mlp128_pipelined(const bf16x8 (&xf)[8], l
   };
   // registers x, x + 1 of a finished layer-1 tile -> ReLU -> hi + lo (8 vector instructions)
   auto conv2 = [&](const f32x16 &hh, int hb, int x) {
-    const float a = fmaxf(hh[x], 0.f), b = fmaxf(hh[x + 1], 0.f);
+    const float a = relu(hh[x]), b = relu(hh[x + 1]);
     const unsigned hi = pack_bf16(a, b);
     h_hi[hb][x >> 3][(x & 7) >> 1] = hi;
     h_lo[hb][x >> 3][(x & 7) >> 1] = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));

@@ -64,6 +64,11 @@ static inline bool state_compacts_softmax_keys(const Plan &pl) {
   return state_uses_pipelined_kernel(pl) && !pl.f32 && pl.CC == 0 && pl.LW == 0 && pl.NS > 0 && pl.NL > 0 && pl.n_chunks > 0;
 }
 
+// Purely linear attention with the 128-wide maps has a query-side kernel of its own (ha_linear.hip).
+static inline bool query_side_is_linear(const Plan &pl) {
+  return pl.NS == 0 && pl.CC == 0 && pl.LW == 0 && pl.DM == 0 && state_uses_pipelined_kernel(pl);
+}
+
 // Fills `pl` from a validated problem.  Pure host arithmetic.
 void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl);
 
@@ -85,6 +90,9 @@ hipError_t launch_state_reduce(const Plan &pl, void *ws, hipStream_t st);
 hipError_t launch_state_reduce_with_prep(const Plan &pl, const ha_feature_map &phi_q, void *ws, hipStream_t st);
 hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi_q, void *out, float *row_den, void *ws,
                         hipStream_t st, const WidePlan *wide = nullptr);
+// ha_linear.hip: the query side where there is no softmax token at all
+hipError_t launch_linear_query(const Plan &pl, const void *q, const ha_feature_map &phi_q, void *out, float *row_den, void *ws,
+                               hipStream_t st);
 // ha_wide.hip
 void make_wide_plan(const Plan &pl, size_t base_off, WidePlan &wp);
 hipError_t launch_wide_key_side(const Plan &pl, const WidePlan &wp, const void *k, const void *v, const ha_feature_map &phi_k,

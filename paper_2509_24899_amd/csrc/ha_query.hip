@@ -569,6 +569,7 @@ __global__ __launch_bounds__(64 * NW, 2) void query_kernel_ring(QueryArgs a) {
 
 hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi_q, void *out, float *row_den, void *ws,
                         hipStream_t st, const WidePlan *wide) {
+  if (!wide && query_side_is_linear(pl)) return launch_linear_query(pl, q, *phi_q, out, row_den, ws, st);
   QueryArgs a;
   a.q = q;
   a.out = out;
