@@ -141,10 +141,11 @@ ha_status hybrid_attn_forward(const ha_problem *p, const void *q, const void *k,
  * array inside the library instead of a caller workspace.  The array is HA_STATIC_SCRATCH_MIB MiB; every GPU the
  * library runs on holds its own copy until the process ends, and its address on a GPU is looked up at the first
  * call on that GPU.  The call allocates nothing, frees nothing and does not synchronise; apart from the workspace
- * it takes the arguments of hybrid_attn_forward and returns the same result bit for bit.  A problem whose
- * hybrid_attn_workspace_bytes() exceeds hybrid_attn_static_scratch_bytes() is refused with HA_ERR_WORKSPACE before
- * any HIP call (at the 480p / 81-frame shape with 12 heads the workspace is about 75 MB, so that shape does not fit;
- * 12 heads of 16 K tokens at rate 4 do).  All calls on one GPU share the one array, whose contents are undefined
+ * it takes the arguments of hybrid_attn_forward and returns the same result bit for bit.  A problem whose scratch
+ * exceeds hybrid_attn_static_scratch_bytes() is refused with HA_ERR_WORKSPACE before any HIP call (at the 480p /
+ * 81-frame shape with 12 heads the workspace is about 75 MB, so that shape does not fit; 12 heads of 16 K tokens at
+ * rate 4 do; with the 256-wide maps less is needed here than hybrid_attn_workspace_bytes() says: intermediate results
+ * of the queries are then formed a part at a time).  All calls on one GPU share the one array, whose contents are undefined
  * between calls (nothing in it has to start at zero): calls on one GPU must be ordered on one stream, or
  * otherwise not overlap; calls that overlap on one GPU race. */
 #define HA_STATIC_SCRATCH_MIB 64
@@ -165,7 +166,7 @@ ha_status hybrid_attn_linear_state(const ha_problem *p, const void *k, const voi
  * one set on its stream around its stages (record i uses set i % n); n = 0 switches the tap off and
  * destroys the events.  hybrid_attn_profile_read waits for record `index` to finish and returns the
  * stage durations in milliseconds: ms[0] softmax-key compaction, ms[1] key-side feature map + state
- * pass + state reduction, ms[2] query-side weight re-ordering, ms[3] the fused query kernel (softmax
+ * pass + state reduction, ms[2] query-side weight re-ordering, ms[3] the query kernel (softmax
  * tile loop, phi_q, contraction with the state and merge), ms[4] the whole forward.  Stages that did
  * not run report 0.  HA_ERR_SHAPE for an index that was never recorded.  Host memory only.
  * A negative count, hybrid_attn_profile_enable(-n), creates n sets as well but records only the pair of events around

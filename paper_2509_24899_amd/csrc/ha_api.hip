@@ -89,7 +89,7 @@ static ha_status validate(const ha_problem *p, const ha_feature_map *phi_q, cons
   return HA_OK;
 }
 
-void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl) {
+void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl, size_t limit) {
   std::memset(&pl, 0, sizeof(pl));
   pl.B = p.B; pl.H = p.H; pl.N = p.N; pl.D = p.d_head; pl.R = p.hybrid_rate;
   pl.f32 = p.dtype == HA_F32;
@@ -163,6 +163,23 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
   pl.off_sthi = take(BH * pl.n_cc * pl.F * pl.D * 2);
   pl.off_stlo = take(BH * pl.n_cc * pl.F * pl.D * 2);
   pl.total = off;
+  pl.split_linear = has_linear && pl.HD == 256 && pl.F == 256 && pl.DM == 0 && pl.CC == 0 && pl.LW == 0;
+  if (pl.split_linear) {
+    // whole tiles of 256 queries, the larger of the two the pass uses; n in fp32, then e
+    const size_t tile = BH * 256 * (pl.D + 1) * 4, tiles = ((size_t)pl.N + 255) / 256;
+    pl.lin_rows = pl.N;
+    pl.off_lin = off;
+    if (off + tiles * tile <= limit) {
+      take(tiles * tile);
+      pl.total = off;
+    } else {
+      pl.off_lin = pl.off_part;
+      const size_t fit = (pl.off_S - pl.off_part) / tile;   // at least one: a partial state is larger than a tile's results
+      if (fit < tiles) pl.lin_rows = (int)(fit * 256);
+    }
+    pl.n_tb = (pl.lin_rows + 255) / 256 * 8;
+    pl.off_e = pl.off_lin + BH * pl.n_tb * 32 * pl.D * 4;
+  }
 }
 
 // Feature maps outside the fused kernels' widths take the layer-by-layer path.
@@ -174,8 +191,8 @@ static bool needs_wide_path(const Plan &pl) {
 
 // Plan of the forward plus, where needed, the layer-by-layer path's buffers behind it; returns the workspace size.
 static size_t full_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl, WidePlan &wp,
-                        bool &wide) {
-  make_plan(p, phi_q, phi_k, pl);
+                        bool &wide, size_t limit = SIZE_MAX) {
+  make_plan(p, phi_q, phi_k, pl, limit);
   wide = phi_q && phi_k && needs_wide_path(pl);
   if (!wide) return pl.total;
   make_wide_plan(pl, pl.total, wp);
@@ -234,7 +251,7 @@ size_t hybrid_attn_workspace_bytes(const ha_problem *p, const ha_feature_map *ph
 
 static ha_status forward_impl(const ha_problem *p, const void *q, const void *k, const void *v,
                               const ha_feature_map *phi_q, const ha_feature_map *phi_k, void *out, float *row_den,
-                              void *workspace, size_t workspace_bytes, void *hip_stream) {
+                              void *workspace, size_t workspace_bytes, void *hip_stream, size_t limit = SIZE_MAX) {
   ha_status s = ha::validate(p, phi_q, phi_k);
   if (s != HA_OK) return s;
   if (!q || !k || !v || !out) return HA_ERR_NULL;
@@ -242,7 +259,7 @@ static ha_status forward_impl(const ha_problem *p, const void *q, const void *k,
   ha::Plan pl;
   ha::WidePlan wp;
   bool wide;
-  const size_t need = ha::full_plan(*p, phi_q, phi_k, pl, wp, wide);
+  const size_t need = ha::full_plan(*p, phi_q, phi_k, pl, wp, wide, limit);
   if (!workspace || workspace_bytes < need) return HA_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return HA_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -259,8 +276,20 @@ static ha_status forward_impl(const ha_problem *p, const void *q, const void *k,
     return ha::device_error(e);
   }
   if (ev && (e = hipEventRecord(ev[3], st)) != hipSuccess) return ha::device_error(e);
-  if ((e = ha::launch_query(pl, q, phi_q, out, row_den, workspace, st, wide ? &wp : nullptr)) != hipSuccess)
+  if (pl.split_linear) {
+    // (in one piece unless the workspace is of fixed size: see make_plan)
+    const size_t row = (size_t)p->stride_n * (pl.f32 ? 4 : 2);
+    ha::Plan part = pl;
+    for (int n0 = 0; n0 < pl.N; n0 += pl.lin_rows) {
+      part.N = pl.N - n0 < pl.lin_rows ? pl.N - n0 : pl.lin_rows;
+      const void *qn = static_cast<const char *>(q) + n0 * row;
+      void *on = static_cast<char *>(out) + n0 * row;
+      if ((e = ha::launch_linear256(part, qn, *phi_q, workspace, st)) != hipSuccess) return ha::device_error(e);
+      if ((e = ha::launch_query(part, qn, phi_q, on, row_den, workspace, st)) != hipSuccess) return ha::device_error(e);
+    }
+  } else if ((e = ha::launch_query(pl, q, phi_q, out, row_den, workspace, st, wide ? &wp : nullptr)) != hipSuccess) {
     return ha::device_error(e);
+  }
   if (ev) {
     if ((e = hipEventRecord(ev[4], st)) != hipSuccess) return ha::device_error(e);
     ++ha::g_prof.count;
@@ -315,12 +344,12 @@ ha_status hybrid_attn_forward_static(const ha_problem *p, const void *q, const v
   ha::WidePlan wp;
   bool wide;
   // the size check is host arithmetic: a problem beyond the static array is refused before any HIP call
-  if (ha::full_plan(*p, phi_q, phi_k, pl, wp, wide) > ha::kStaticScratchBytes) return HA_ERR_WORKSPACE;
+  if (ha::full_plan(*p, phi_q, phi_k, pl, wp, wide, ha::kStaticScratchBytes) > ha::kStaticScratchBytes) return HA_ERR_WORKSPACE;
   if (!q || !k || !v || !out) return HA_ERR_NULL;
   void *ws = nullptr;
   hipError_t e = ha::static_scratch(&ws);
   if (e != hipSuccess) return ha::device_error(e);
-  return forward_impl(p, q, k, v, phi_q, phi_k, out, nullptr, ws, ha::kStaticScratchBytes, hip_stream);
+  return forward_impl(p, q, k, v, phi_q, phi_k, out, nullptr, ws, ha::kStaticScratchBytes, hip_stream, ha::kStaticScratchBytes);
 }
 
 ha_status hybrid_attn_profile_enable(int n_records) {

@@ -25,6 +25,11 @@ struct Plan {
   int CH, n_chunks, n_state_tiles;
   // workspace byte offsets (all multiples of 256)
   size_t off_w1q, off_w2q, off_w1k, off_w2k, off_ks, off_vs, off_part, off_S, off_z, off_sthi, off_stlo, total;
+  // 128 -> 256 -> 256 maps, plain operator: the linear part of the query side is a pass of its own (ha_linear256.hip), whose
+  // results (n_tb 32-query blocks per (batch, head)) the query kernel adds; lin_rows queries of every head at a time
+  bool split_linear;
+  int n_tb, lin_rows;
+  size_t off_lin, off_e;
 };
 
 // Workspace of the value-distillation gradient beyond the forward's: operand fragments of W2^T, S and dS, the
@@ -69,8 +74,10 @@ static inline bool query_side_is_linear(const Plan &pl) {
   return pl.NS == 0 && pl.CC == 0 && pl.LW == 0 && pl.DM == 0 && state_uses_pipelined_kernel(pl);
 }
 
-// Fills `pl` from a validated problem.  Pure host arithmetic.
-void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl);
+// Fills `pl` from a validated problem.  Pure host arithmetic.  limit: size of a workspace that cannot grow; where the
+// results of the 256-wide maps' linear pass (516 bytes per query and head) do not fit it, they take the place of the state
+// partials, which are spent by then, as many queries at a time as that holds.
+void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl, size_t limit = SIZE_MAX);
 
 // Kernel launchers (ha_kernels.hip).  Each enqueues on `st` and returns the launch status.
 hipError_t launch_weight_prep(const Plan &pl, const ha_feature_map &fm, bool is_query, void *ws, hipStream_t st);
@@ -93,6 +100,8 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
 // ha_linear.hip: the query side where there is no softmax token at all
 hipError_t launch_linear_query(const Plan &pl, const void *q, const ha_feature_map &phi_q, void *out, float *row_den, void *ws,
                                hipStream_t st);
+// ha_linear256.hip: n = phi_q(q) S and e = phi_q(q) . z of the 128 -> 256 -> 256 maps
+hipError_t launch_linear256(const Plan &pl, const void *q, const ha_feature_map &phi_q, void *ws, hipStream_t st);
 // ha_wide.hip
 void make_wide_plan(const Plan &pl, size_t base_off, WidePlan &wp);
 hipError_t launch_wide_key_side(const Plan &pl, const WidePlan &wp, const void *k, const void *v, const ha_feature_map &phi_k,

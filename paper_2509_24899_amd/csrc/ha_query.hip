@@ -574,9 +574,10 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
   a.q = q;
   a.out = out;
   a.row_den = row_den;
-  a.lin = wide ? ws_ptr<f32x4>(ws, wide->off_lin) : nullptr;
-  a.lin_e = wide ? ws_ptr<float>(ws, wide->off_e) : nullptr;
-  a.n_tb = wide ? wide->n_tb_q : 0;
+  const bool lin = wide || pl.split_linear;               // the linear part arrives precomputed
+  a.lin = wide ? ws_ptr<f32x4>(ws, wide->off_lin) : lin ? ws_ptr<f32x4>(ws, pl.off_lin) : nullptr;
+  a.lin_e = wide ? ws_ptr<float>(ws, wide->off_e) : lin ? ws_ptr<float>(ws, pl.off_e) : nullptr;
+  a.n_tb = wide ? wide->n_tb_q : pl.n_tb;
   a.ks_frag = ws_ptr<bf16x8>(ws, pl.off_ks);
   a.vs_frag = ws_ptr<bf16x8>(ws, pl.off_vs);
   a.w1f = ws_ptr<bf16x8>(ws, pl.off_w1q);
@@ -611,7 +612,7 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
   const auto wgs = [&](int qt) { return (int64_t)((pl.N + qt - 1) / qt) * pl.B * pl.H; };
   bool big;
   if (pl.LW > 0 || pl.CC > 0) big = pl.KT == 128;
-  else if ((wide || pl.NL == 0) && (pl.D == 128 || wgs(128) <= 256)) {
+  else if ((lin || pl.NL == 0) && (pl.D == 128 || wgs(128) <= 256)) {
     const int64_t tail = wgs(128) % 512;
     const int64_t few = wgs(128) / 512 * 21 + (tail == 0 ? 0 : tail <= 256 ? 13 : 21);
     big = (wgs(256) + 255) / 256 * 20 <= few;
@@ -634,7 +635,7 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
       else if constexpr (HH <= 128) query_kernel_ring<DD, HH, FF, 4, 4, 1, F32><<<grid, 256, 0, st>>>(a); \
     } \
   } while (0)
-  if (wide) {
+  if (lin) {
     if (big) {
       if (pl.f32) query_kernel_ring<128, 128, 128, 8, 8, 2, true, true><<<grid, 512, 0, st>>>(a);
       else query_kernel_ring<128, 128, 128, 8, 8, 2, false, true><<<grid, 512, 0, st>>>(a);
