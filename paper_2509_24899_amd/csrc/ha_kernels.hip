@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256) void compact_kernel(const void *__restrict__ k
 }
 
 // ------------------------------------------------------------------------------------------------
-// state_kernel: grid (n_chunks, B*H), 4 waves.  A chunk is CH linear tokens, walked in tiles of 128.
+// state_kernel (d = 64; ha_state.hip and ha_state256.hip serve d = 128): grid (n_chunks, B*H), 4 waves.  A chunk is CH linear tokens, walked in tiles of 128.
 // Per tile every wave runs the phi_k MLP on its 32 tokens (tokens are C columns), the four waves
 // park phi_k(k)^T and V^T in LDS with tokens contiguous, then the output tiles of
 // [S | z] = phi_k(K)^T [V | 1] are dealt round-robin to the waves and contracted over the tokens.
@@ -102,43 +102,21 @@ __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ 
   constexpr int TPW = RPW * NCB;              // output tiles per such wave
   constexpr int CG = D / 32;                  // groups of four 16-byte chunks per V row
   constexpr int VPT = (TOK / 16) * CG / 4;    // V chunks per thread per tile
-  // the MLP weight fragments of this head live in LDS when they fit next to the two transposing arrays
-  constexpr bool WLDS = (HD * D + F * HD) * 2 <= 64 * 1024;
-  // Wider maps: the weights do not fit next to the two transposing arrays, but those are idle while the MLP runs.
-  // One raw area serves both: per tile W1 and the first half of W2 are staged into it (direct-to-LDS, one fetch
-  // per workgroup instead of one per wave), the second half of W2 follows once layer 1 is done, and only then
-  // the area becomes phi^T and V^T.
-  constexpr bool WIDE = F > 128;
-  constexpr int NW1 = HD * D / 8, NW2 = F * HD / 8;            // bf16x8 per head
-  constexpr int RAW = WIDE ? (NW1 + NW2 / 2 > (F + D) * PITCH / 8 ? NW1 + NW2 / 2 : (F + D) * PITCH / 8) : 1;
-  static_assert(!WIDE || (NW2 / 2 <= NW1 && (F / 32) % 2 == 0 && RAW * 16 <= 150 * 1024), "staging plan does not fit");
-  __shared__ __align__(16) __bf16 ft_s[WIDE ? 1 : F][PITCH];
-  __shared__ __align__(16) __bf16 vt_s[WIDE ? 1 : D][PITCH];
-  __shared__ bf16x8 raw[RAW];
-  __shared__ bf16x8 wlds[WLDS ? (HD * D + F * HD) / 8 : 1];
+  // the MLP weight fragments of this head live in LDS next to the two transposing arrays
+  static_assert((HD * D + F * HD) * 2 <= 64 * 1024, "the weights live in LDS");
+  __shared__ __align__(16) __bf16 ft_s[F][PITCH];
+  __shared__ __align__(16) __bf16 vt_s[D][PITCH];
+  __shared__ bf16x8 wlds[(HD * D + F * HD) / 8];
   __shared__ __align__(16) __bf16 et[WEIGHTED ? 2 : 1][WEIGHTED ? PITCH : 8];
-  static_assert(!WEIGHTED || F <= 128, "the weighted pass is built for the narrow maps only");
   const int chunk = blockIdx.x, bh = blockIdx.y, h = bh % H;
   const int64_t base = (int64_t)(bh / H) * sb + (int64_t)h * sh;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, kept scalar
   const bf16x8 *w1g = w1f_all + (int64_t)h * (HD * D / 8);
   const bf16x8 *w2g = w2f_all + (int64_t)h * (F * HD / 8);
-  if constexpr (WLDS) {
-    for (int i = tid; i < HD * D / 8; i += 256) wlds[i] = w1g[i];
-    for (int i = tid; i < F * HD / 8; i += 256) wlds[HD * D / 8 + i] = w2g[i];
-    // visible to all waves after the first barrier inside the tile loop; layer 1 of the first tile
-    // must not start before that, so synchronise once here
-    __syncthreads();
-  }
-  std::conditional_t<WLDS, lds_frag_ptr, GlobalFrags> w1f, w2f;
-  if constexpr (WLDS) {
-    w1f = (lds_frag_ptr)&wlds[0];
-    w2f = (lds_frag_ptr)&wlds[HD * D / 8];
-  } else {
-    w1f = global_frags(w1g, HD * D * 2);
-    w2f = global_frags(w2g, F * HD * 2);
-  }
+  for (int i = tid; i < HD * D / 8; i += 256) wlds[i] = w1g[i];
+  for (int i = tid; i < F * HD / 8; i += 256) wlds[HD * D / 8 + i] = w2g[i];
+  const lds_frag_ptr w1f = (lds_frag_ptr)&wlds[0], w2f = (lds_frag_ptr)&wlds[HD * D / 8];
   // the biases of this head sit in LDS (zeros when absent): their reads queue up with the weight reads
   // instead of exposing a vector-memory round trip in front of every chain of matrix instructions
   __shared__ float blds[HD + F];
@@ -171,8 +149,8 @@ __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ 
   const int vsw = (lane >> 4) << 1;                       // sw of rows 8 c8 + i, c8 % 4 = lane / 16
   const int vrow0 = 8 * (lane >> 4) * PITCH;
   const int rsw = ((r >> 3) & 3) << 1;                    // sw of operand rows 32 blk + r
-  __bf16 *ftp = WIDE ? reinterpret_cast<__bf16 *>(&raw[0]) : &ft_s[0][0];
-  __bf16 *vtp = WIDE ? reinterpret_cast<__bf16 *>(&raw[0]) + F * PITCH : &vt_s[0][0];
+  __bf16 *ftp = &ft_s[0][0];
+  __bf16 *vtp = &vt_s[0][0];
 
   // this workgroup's range of linear tokens: chunk number `chunk` of CH tokens, or (chunk-causal variant) piece
   // chunk % nsub of the linear tokens of causal chunk chunk / nsub
@@ -194,7 +172,6 @@ __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ 
   for (int t0 = lt_begin; t0 < lt_end; t0 += TOK) {
     // V rows of this tile: pass p of wave w covers tokens 16 ((4p + w) % 8) .. + 15 and the four
     // 16-byte chunks 4 (p / 2) .. + 3 of each (64 contiguous bytes per row)
-    // (wide maps: the MLP needs the registers, so V is requested only once the hidden activations are dead)
     bf16x8 vreg[VPT];
     auto load_v = [&]() {
 #pragma unroll
@@ -205,7 +182,7 @@ __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ 
         else vreg[p] = load8<F32>(v, base + (int64_t)tok * sn + c8 * 8);
       }
     };
-    if constexpr (!WIDE) load_v();
+    load_v();
     __builtin_amdgcn_sched_barrier(0);
     // phi_k on this wave's 32 tokens; the K rows of the next tile are requested as soon as layer 1
     // has consumed the current ones
@@ -213,50 +190,24 @@ __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ 
       bf16x8 phi[FB][2];
       {
         bf16x8 h_hi[HD / 32][2], h_lo[HD / 32][2];
-        if constexpr (WIDE) {
-          // the previous tile's contraction is over (barrier at the end of the loop body): the area is free
-          dma_to_lds(w1g, &raw[0], NW1 / 64, w, 4, lane);
-          dma_to_lds(w2g, &raw[NW1], NW2 / 2 / 64, w, 4, lane);
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          __syncthreads();
-          feature_mlp_layer1<D, HD, true>(xf, (lds_frag_ptr)&raw[0], b1, lane, g, h_hi, h_lo);
-        } else {
-          feature_mlp_layer1<D, HD, true>(xf, w1f, b1, lane, g, h_hi, h_lo);
-        }
+        feature_mlp_layer1<D, HD, true>(xf, w1f, b1, lane, g, h_hi, h_lo);
         __builtin_amdgcn_sched_barrier(0);
         load_k(t0 + TOK, xf);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (WIDE) {
-          PhiState<FB> st;
-          feature_layer2_phi_tiles<HD, F, 0, FB / 2, false>(h_hi, h_lo, (lds_frag_ptr)&raw[NW1], 0, b2, lane, g, act, P, Dp, st,
-                                                           phi);
-          __syncthreads();                                  // every wave is done with W1: the second half of W2 replaces it
-          dma_to_lds(w2g + NW2 / 2, &raw[0], NW2 / 2 / 64, w, 4, lane);
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          __syncthreads();
-          feature_layer2_phi_tiles<HD, F, FB / 2, FB, false>(h_hi, h_lo, (lds_frag_ptr)&raw[0], (FB / 2) * (HD / 32) * 2, b2,
-                                                            lane, g, act, P, Dp, st, phi);
-          feature_phi_finish<F>(st, act, P, Dp, phi);
-        } else {
-          f32x16 u[FB];
-          feature_mlp_layer2<HD, F, true>(h_hi, h_lo, w2f, b2, lane, g, u);
-          feature_activation<FB>(u, g, act, P, Dp);
-          float rs = 1.f;
-          if constexpr (WEIGHTED) rs = rs_all[(int64_t)bh * NL + lmap.token(min(t0 + tf, NL - 1))];
+        f32x16 u[FB];
+        feature_mlp_layer2<HD, F, true>(h_hi, h_lo, w2f, b2, lane, g, u);
+        feature_activation<FB>(u, g, act, P, Dp);
+        float rs = 1.f;
+        if constexpr (WEIGHTED) rs = rs_all[(int64_t)bh * NL + lmap.token(min(t0 + tf, NL - 1))];
 #pragma unroll
-          for (int fb = 0; fb < FB; ++fb)
+        for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
-            for (int sp = 0; sp < 2; ++sp) {
-              f32x8 t8;
+          for (int sp = 0; sp < 2; ++sp) {
+            f32x8 t8;
 #pragma unroll
-              for (int i = 0; i < 8; ++i) t8[i] = WEIGHTED ? u[fb][8 * sp + i] * rs : u[fb][8 * sp + i];
-              phi[fb][sp] = __builtin_convertvector(t8, bf16x8);
-            }
-        }
-      }
-      if constexpr (WIDE) {
-        load_v();
-        __syncthreads();                                    // the weights have been read by every wave: the area becomes phi^T | V^T
+            for (int i = 0; i < 8; ++i) t8[i] = WEIGHTED ? u[fb][8 * sp + i] * rs : u[fb][8 * sp + i];
+            phi[fb][sp] = __builtin_convertvector(t8, bf16x8);
+          }
       }
       if (t0 + TOK > lt_end) {                             // ragged end of the range: padded tokens add nothing
         const bool valid = t0 + tf < lt_end;
@@ -524,15 +475,14 @@ hipError_t launch_compact(const Plan &pl, const void *k, const void *v, void *ws
 hipError_t launch_state(const Plan &pl, const void *k, const void *v, const ha_feature_map &fm, void *ws,
                         hipStream_t st) {
   if (state_uses_pipelined_kernel(pl)) return launch_state_pipelined(pl, k, v, fm, ws, st);   // ha_state.hip
+  if (pl.D == 128) return launch_state256(pl, k, v, fm, ws, st);                              // ha_state256.hip
   dim3 grid(pl.n_chunks, pl.B * pl.H);
   const bf16x8 *w1f = ws_ptr<bf16x8>(ws, pl.off_w1k), *w2f = ws_ptr<bf16x8>(ws, pl.off_w2k);
   float *part = ws_ptr<float>(ws, pl.off_part);
 #define HA_STATE(DD, HH, FF, F32) \
   state_kernel<DD, HH, FF, F32><<<grid, 256, 0, st>>>(k, v, w1f, w2f, fm.b1, fm.b2, part, pl.H, pl.NL, pl.R, pl.G, pl.CH, \
                                                      pl.P, pl.act_k, pl.sb, pl.sh, pl.sn, nullptr, nullptr, pl.N, pl.CC, pl.nsub)
-  if (pl.D == 64) { if (pl.f32) HA_STATE(64, 64, 64, true); else HA_STATE(64, 64, 64, false); }
-  else if (pl.HD == 128) { if (pl.f32) HA_STATE(128, 128, 128, true); else HA_STATE(128, 128, 128, false); }
-  else { if (pl.f32) HA_STATE(128, 256, 256, true); else HA_STATE(128, 256, 256, false); }
+  if (pl.f32) HA_STATE(64, 64, 64, true); else HA_STATE(64, 64, 64, false);
 #undef HA_STATE
   return hipGetLastError();
 }
@@ -548,8 +498,7 @@ hipError_t launch_weighted_state(const Plan &pl, const void *q, const void *gsig
 #define HA_WSTATE(DD, F32) \
   state_kernel<DD, DD, DD, F32, true><<<grid, 256, 0, st>>>(q, gsign, w1f, w2f, fm.b1, fm.b2, part, pl.H, pl.N, 0, 1, CH, pl.P, \
                                                             pl.act_q, pl.sb, pl.sh, pl.sn, rs, wp)
-  if (pl.D == 64) { if (pl.f32) HA_WSTATE(64, true); else HA_WSTATE(64, false); }
-  else { if (pl.f32) HA_WSTATE(128, true); else HA_WSTATE(128, false); }
+  if (pl.f32) HA_WSTATE(64, true); else HA_WSTATE(64, false);
 #undef HA_WSTATE
   return hipGetLastError();
 }

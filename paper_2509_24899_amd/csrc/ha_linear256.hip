@@ -5,13 +5,10 @@
 //
 // As the query kernel's epilogue this costs 57 us per round of workgroups at 480p / 81 frames (340 us of 1627): hidden
 // activations, accumulators and features of 256 channels do not fit the registers the softmax accumulators leave, and the
-// operands (W1 64 KiB, W2 128 KiB, S hi + lo 128 KiB per head) pass through the ring in three exposed rounds.  Here a
-// token's 256 pre-activations are the accumulators: the hidden layer is walked in blocks of 32 units, each of which is
-// formed (8 matrix instructions), split into hi + lo and contracted into all 8 output tiles (32 instructions) before the
-// next one starts, so one hidden block is all that is ever held and the softmax sees fp32 values of all channels (one
-// rounding of phi to bf16 instead of two).  Operands stream through an LDS ring in that very order, 24 KiB per hidden block
-// (its rows of W1, its columns of W2), then 16 KiB per feature block of S; the stream runs ahead over the tiles and heads
-// of a workgroup, one barrier per slab.
+// operands (W1 64 KiB, W2 128 KiB, S hi + lo 128 KiB per head) pass through the ring in three exposed rounds.  Here the map is
+// evaluated a hidden block at a time (ha_mlp256.h), so the softmax sees fp32 values of all channels (one rounding of phi to
+// bf16 instead of two), and the operands stream through an LDS ring in that very order, 24 KiB per hidden block, then 16 KiB
+// per feature block of S; the stream runs ahead over the tiles and heads of a workgroup, one barrier per slab.
 //
 // Bound: matrix cores, 448 instructions of 32 cycles per 32-query block (28.7 k cycles per 256-query tile), next to 9 k
 // cycles of exponentials and packing and the conversion of each hidden block, which the barrier keeps both waves of a SIMD
@@ -20,7 +17,7 @@
 // side); B = 2, H = 12, N = 5003, fp32, R = 3: 198 us -> 79 + 127 us in a round and a half less exposed epilogue (355 -> 329
 // us); the fixed cost of a small call falls from 64 to about 25 us.
 #include "ha_device.h"
-#include "ha_mlp128.h"
+#include "ha_mlp256.h"
 #include "ha_plan.h"
 
 namespace ha {
@@ -43,7 +40,7 @@ struct Linear256Args {
 template <int NW, int NBUF, bool F32, bool ACT0, bool P2>
 __global__ __launch_bounds__(64 * NW, 2) void linear256_kernel(Linear256Args a) {
   constexpr int D = 128, HD = 256, F = 256, KS = D / 16, HB = HD / 32, FB = F / 32, RB = D / 32;
-  constexpr int WCH = KS + 2 * FB, SCH = RB * 4;          // 1 KiB chunks per slab: of the weights, of S
+  constexpr int WCH = kSlabChunks, SCH = RB * 4;          // 1 KiB chunks per slab: of the weights, of S
   constexpr int SLOT = WCH * 64, STEPS = HB + FB;
   constexpr int NW1 = HD * D / 8, NW2 = F * HD / 8, NST = D * F / 8;
   static_assert(NBUF >= 3 && NBUF <= STEPS && WCH % NW == 0 && SCH % NW == 0, "slabs are dealt evenly");
@@ -70,10 +67,7 @@ __global__ __launch_bounds__(64 * NW, 2) void linear256_kernel(Linear256Args a) 
 #pragma unroll
       for (int i = 0; i < WCH / NW; ++i) {
         const int c = i * NW + w;
-        // chunks 0 .. 7: the fragments of 32 rows of W1; 8 + 2 fb + half: those 32 columns of W2
-        const bf16x8 *gp = c < KS ? a.w1f + (int64_t)h * NW1 + (s * KS + c) * 64
-                                  : a.w2f + (int64_t)h * NW2 + ((((c - KS) >> 1) * HB + s) * 2 + ((c - KS) & 1)) * 64;
-        dma(gp, c);
+        dma(slab_chunk(a.w1f + (int64_t)h * NW1, a.w2f + (int64_t)h * NW2, s, c), c);
       }
     } else {
 #pragma unroll
@@ -110,12 +104,6 @@ __global__ __launch_bounds__(64 * NW, 2) void linear256_kernel(Linear256Args a) 
   load_q(t_lo, xf);
 #pragma unroll
   for (int s = 0; s < NBUF - 1; ++s) request(bh, s, s);
-  auto tile_of = [&](const float *b, int blk) {           // 32 consecutive values as a C tile's column
-    const f32x4 *src = reinterpret_cast<const f32x4 *>(b + 32 * blk + 4 * g);
-    const f32x8 lo = __builtin_shufflevector(src[0], src[2], 0, 1, 2, 3, 4, 5, 6, 7);
-    const f32x8 hi = __builtin_shufflevector(src[4], src[6], 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-  };
   const float *b1 = &vecs[0], *b2 = &vecs[HD], *zz = &vecs[HD + F];
 
   int bh_vecs = -1;
@@ -133,83 +121,20 @@ __global__ __launch_bounds__(64 * NW, 2) void linear256_kernel(Linear256Args a) 
     // ---------------- the map: u = W2 relu(W1 x + b1) + b2, one hidden block per slab
     f32x16 u[FB];
 #pragma unroll
-    for (int fb = 0; fb < FB; ++fb) u[fb] = tile_of(b2, fb);
+    for (int fb = 0; fb < FB; ++fb) u[fb] = column_tile(b2, fb, g);
 #pragma unroll 1
     for (int hb = 0; hb < HB; ++hb) {
       advance(hb, t > t_lo);
       const lds_frag_ptr sl = (lds_frag_ptr)&ring[slot * SLOT];
       slot = slot + 1 == NBUF ? 0 : slot + 1;
-      f32x16 hh = tile_of(b1, hb);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) hh = mfma32(frag_at(sl, ks, lane), xf[ks], hh);
-      u32x4 h_hi[2], h_lo[2];
-#pragma unroll
-      for (int x = 0; x < 16; x += 2) {
-        const float v0 = relu(hh[x]), v1 = relu(hh[x + 1]);
-        const unsigned hi = pack_bf16(v0, v1);
-        h_hi[x >> 3][(x & 7) >> 1] = hi;
-        h_lo[x >> 3][(x & 7) >> 1] = pack_bf16(v0 - __uint_as_float(hi << 16), v1 - __uint_as_float(hi & 0xffff0000u));
-      }
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int fb = 0; fb < FB; fb += 2) {
-          const bf16x8 lo8 = __builtin_bit_cast(bf16x8, h_lo[s]), hi8 = __builtin_bit_cast(bf16x8, h_hi[s]);
-          const bf16x8 wa = frag_at(sl, KS + 2 * fb + s, lane), wb = frag_at(sl, KS + 2 * (fb + 1) + s, lane);
-          u[fb] = mfma32(wa, lo8, u[fb]);
-          u[fb + 1] = mfma32(wb, lo8, u[fb + 1]);
-          u[fb] = mfma32(wa, hi8, u[fb]);
-          u[fb + 1] = mfma32(wb, hi8, u[fb + 1]);
-        }
+      mlp256_hidden_block(sl, b1, hb, xf, lane, g, u);
     }
     load_q(t + 1 < t_hi ? t + 1 : t, xf);                 // the next tile's rows travel under everything below
     // ---------------- output stage: positive activation over all channels, slice powers, bf16
-    if constexpr (ACT0) {
-      float m = u[0][0];
-#pragma unroll
-      for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-        for (int x = 0; x < 16; x += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, u[fb][x]), u[fb][x + 1]);
-      const float off = -xhalf_max(m) * kLog2e;
-      float sum0 = 0.f, sum1 = 0.f;
-#pragma unroll
-      for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-        for (int x = 0; x < 16; x += 2) {
-          u[fb][x] = fast_exp2(__builtin_fmaf(u[fb][x], kLog2e, off));
-          u[fb][x + 1] = fast_exp2(__builtin_fmaf(u[fb][x + 1], kLog2e, off));
-          sum0 += u[fb][x];
-          sum1 += u[fb][x + 1];
-        }
-      const float inv = 1.0f / xhalf_sum(sum0 + sum1);
-#pragma unroll
-      for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-        for (int x = 0; x < 16; ++x) u[fb][x] *= inv;
-    } else {
-#pragma unroll
-      for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-        for (int x = 0; x < 16; ++x) u[fb][x] = a.act == 1 ? fast_exp2(u[fb][x] * kLog2e) : relu(u[fb][x]);
-    }
+    phi256_output<ACT0, P2>(u, a.act, a.P);
     u32x4 gb[FB][2];                                      // word i of half s: channels crow(8 s + 2 i, g) and the next
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb) {
-      if constexpr (P2) {                                 // the default degree: the upper half of the channels is squared
-        if (fb >= FB / 2)
-#pragma unroll
-          for (int x = 0; x < 16; ++x) u[fb][x] *= u[fb][x];
-      } else {
-#pragma unroll
-        for (int x = 0; x < 16; ++x) {
-          const int extra = ((32 * fb + 8 * (x >> 2)) * a.P) / F;        // slice = power - 1 in 0 .. 7; wave-uniform
-          const float t0 = u[fb][x], t2 = t0 * t0;
-          float y = (extra & 1) ? t2 : t0;
-          y = (extra & 2) ? y * t2 : y;
-          y = (extra & 4) ? y * (t2 * t2) : y;
-          u[fb][x] = y;
-        }
-      }
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll

@@ -23,6 +23,17 @@ static __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
 // is the source's.  The kernel below places its matrix instructions, LDS reads and vector work by hand with it.
 #define HA_FENCE() __builtin_amdgcn_sched_barrier(0)
 
+// Row-major [token][column] bf16 tile in LDS with rows of 2 D bytes.  The 16-byte pieces of a row are XOR-swizzled by
+// the row so that the transposing reads (4 rows x 32 bytes per 16 lanes) and the row-wise writes spread over the
+// banks.  The swizzle only has to be the same function everywhere the tile is addressed.
+template <int D>
+struct RowTile {
+  static constexpr int ROWB = 2 * D;        // bytes per row
+  static constexpr int PPR = ROWB / 16;     // 16-byte pieces per row
+  static __device__ __forceinline__ int sw(int row) { return D >= 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+  // byte offset of 16-byte piece p of `row`
+  static __device__ __forceinline__ int piece(int row, int p) { return row * ROWB + ((p ^ sw(row)) << 4); }
+};
 
 // xf: the B-operand fragments of the 32 token rows (natural slot order over d); w1f / w2f: A-operand fragments of the
 // weights in LDS (W1 natural order, W2 in the order of the C registers of layer 1); b1, b2: the biases in LDS.

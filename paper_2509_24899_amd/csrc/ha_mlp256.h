@@ -1,0 +1,107 @@
+// Pieces of the feature map phi of Sec. 3.2 for the widths 128 -> 256 -> 256 on one 32-token column block, shared by the state
+// pass and the query side.  gfx950 only.
+//
+// A token's 256 pre-activations are eight accumulator tiles; the hidden layer is walked in blocks of 32 units, each formed
+// (8 matrix instructions), split into hi + lo and contracted into all eight tiles (32 instructions) before the next one
+// starts, so one hidden block is all that is ever held.  The operands of a hidden block form a 24 KiB slab: the 8
+// fragments of its rows of W1, then for every 32-channel output tile the two of its columns of W2.
+#pragma once
+#include "ha_mlp128.h"
+
+namespace ha {
+
+constexpr int kSlabChunks = 8 + 2 * 8;                    // 1 KiB chunks of a weight slab
+// Chunk c of the slab of hidden block hb, from one head's prepared fragments (W1 natural, W2 chained order).
+static __device__ __forceinline__ const bf16x8 *slab_chunk(const bf16x8 *w1f, const bf16x8 *w2f, int hb, int c) {
+  return c < 8 ? w1f + (hb * 8 + c) * 64 : w2f + ((((c - 8) >> 1) * 8 + hb) * 2 + ((c - 8) & 1)) * 64;
+}
+
+// 32 consecutive values (LDS) as one column of a C tile: four 16-byte reads, no vector instruction.
+static __device__ __forceinline__ f32x16 column_tile(const float *b, int blk, int g) {
+  const f32x4 *src = reinterpret_cast<const f32x4 *>(b + 32 * blk + 4 * g);
+  const f32x8 lo = __builtin_shufflevector(src[0], src[2], 0, 1, 2, 3, 4, 5, 6, 7);
+  const f32x8 hi = __builtin_shufflevector(src[4], src[6], 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+}
+
+// u += W2[:, block] relu(W1[block, :] x + b1[block]) from the block's slab in LDS.
+static __device__ __forceinline__ void mlp256_hidden_block(lds_frag_ptr sl, const float *b1, int hb, const bf16x8 (&xf)[8],
+                                                           int lane, int g, f32x16 (&u)[8]) {
+  f32x16 hh = column_tile(b1, hb, g);
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) hh = mfma32(frag_at(sl, ks, lane), xf[ks], hh);
+  u32x4 h_hi[2], h_lo[2];
+#pragma unroll
+  for (int x = 0; x < 16; x += 2) {
+    const float v0 = relu(hh[x]), v1 = relu(hh[x + 1]);
+    const unsigned hi = pack_bf16(v0, v1);
+    h_hi[x >> 3][(x & 7) >> 1] = hi;
+    h_lo[x >> 3][(x & 7) >> 1] = pack_bf16(v0 - __uint_as_float(hi << 16), v1 - __uint_as_float(hi & 0xffff0000u));
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const bf16x8 lo8 = __builtin_bit_cast(bf16x8, h_lo[s]), hi8 = __builtin_bit_cast(bf16x8, h_hi[s]);
+#pragma unroll
+    for (int fb = 0; fb < 8; fb += 2) {
+      const bf16x8 wa = frag_at(sl, 8 + 2 * fb + s, lane), wb = frag_at(sl, 8 + 2 * (fb + 1) + s, lane);
+      u[fb] = mfma32(wa, lo8, u[fb]);
+      u[fb + 1] = mfma32(wb, lo8, u[fb + 1]);
+      u[fb] = mfma32(wa, hi8, u[fb]);
+      u[fb + 1] = mfma32(wb, hi8, u[fb + 1]);
+    }
+  }
+}
+
+// The output stage in place: positive activation over all channels, slice powers.  ACT0: softmax over the channels; otherwise
+// `act` picks exp (1) or ReLU.  P2: the degree is 2, the paper's default.
+template <bool ACT0, bool P2>
+static __device__ __forceinline__ void phi256_output(f32x16 (&u)[8], int act, int P) {
+  if constexpr (ACT0) {
+    float m = u[0][0];
+#pragma unroll
+    for (int fb = 0; fb < 8; ++fb)
+#pragma unroll
+      for (int x = 0; x < 16; x += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, u[fb][x]), u[fb][x + 1]);
+    const float off = -xhalf_max(m) * kLog2e;
+    float sum0 = 0.f, sum1 = 0.f;
+#pragma unroll
+    for (int fb = 0; fb < 8; ++fb)
+#pragma unroll
+      for (int x = 0; x < 16; x += 2) {
+        u[fb][x] = fast_exp2(__builtin_fmaf(u[fb][x], kLog2e, off));
+        u[fb][x + 1] = fast_exp2(__builtin_fmaf(u[fb][x + 1], kLog2e, off));
+        sum0 += u[fb][x];
+        sum1 += u[fb][x + 1];
+      }
+    const float inv = 1.0f / xhalf_sum(sum0 + sum1);
+#pragma unroll
+    for (int fb = 0; fb < 8; ++fb)
+#pragma unroll
+      for (int x = 0; x < 16; ++x) u[fb][x] *= inv;
+  } else {
+#pragma unroll
+    for (int fb = 0; fb < 8; ++fb)
+#pragma unroll
+      for (int x = 0; x < 16; ++x) u[fb][x] = act == 1 ? fast_exp2(u[fb][x] * kLog2e) : relu(u[fb][x]);
+  }
+#pragma unroll
+  for (int fb = 0; fb < 8; ++fb) {
+    if constexpr (P2) {                                   // the upper half of the channels is squared
+      if (fb >= 4)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) u[fb][x] *= u[fb][x];
+    } else {
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const int extra = ((32 * fb + 8 * (x >> 2)) * P) / 256;          // slice = power - 1 in 0 .. 7; wave-uniform
+        const float t0 = u[fb][x], t2 = t0 * t0;
+        float y = (extra & 1) ? t2 : t0;
+        y = (extra & 2) ? y * t2 : y;
+        y = (extra & 4) ? y * (t2 * t2) : y;
+        u[fb][x] = y;
+      }
+    }
+  }
+}
+
+}  // namespace ha

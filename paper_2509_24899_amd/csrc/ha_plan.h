@@ -84,6 +84,8 @@ hipError_t launch_weight_prep(const Plan &pl, const ha_feature_map &fm, bool is_
 hipError_t launch_compact(const Plan &pl, const void *k, const void *v, void *ws, hipStream_t st);
 hipError_t launch_state(const Plan &pl, const void *k, const void *v, const ha_feature_map &phi_k, void *ws,
                         hipStream_t st);
+hipError_t launch_state256(const Plan &pl, const void *k, const void *v, const ha_feature_map &phi_k, void *ws,
+                           hipStream_t st);   // ha_state256.hip: 128 -> 256 -> 256
 hipError_t launch_state_pipelined(const Plan &pl, const void *k, const void *v, const ha_feature_map &phi_k, void *ws,
                                   hipStream_t st);
 hipError_t launch_state_pipelined_weighted(const Plan &pl, const void *q, const void *gsign, const float *rs, const float *wp,

@@ -26,18 +26,6 @@
 
 namespace ha {
 
-// Row-major [token][column] bf16 tile in LDS with rows of 2 D bytes.  The 16-byte pieces of a row are XOR-swizzled by
-// the row so that the transposing reads (4 rows x 32 bytes per 16 lanes) and the row-wise writes spread over the
-// banks.  The swizzle only has to be the same function everywhere the tile is addressed.
-template <int D>
-struct RowTile {
-  static constexpr int ROWB = 2 * D;        // bytes per row
-  static constexpr int PPR = ROWB / 16;     // 16-byte pieces per row
-  static __device__ __forceinline__ int sw(int row) { return D >= 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
-  // byte offset of 16-byte piece p of `row`
-  static __device__ __forceinline__ int piece(int row, int p) { return row * ROWB + ((p ^ sw(row)) << 4); }
-};
-
 // ACT0: the output activation is the softmax over the channels (the default of the paper's maps), scheduled by hand;
 // the other activations (exp, ReLU: no reduction over channels) take a plain epilogue of layer 2.
 // Softmax-key compaction inside the state pass (COMPACT; bf16, the plain operator).  The softmax tokens T_S (Sec. 3.2)
