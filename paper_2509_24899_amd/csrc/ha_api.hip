@@ -195,7 +195,7 @@ static size_t full_plan(const ha_problem &p, const ha_feature_map *phi_q, const 
   make_plan(p, phi_q, phi_k, pl, limit);
   wide = phi_q && phi_k && needs_wide_path(pl);
   if (!wide) return pl.total;
-  make_wide_plan(pl, pl.total, wp);
+  make_wide_plan(pl, pl.total, wp, false);
   return wp.total;
 }
 
@@ -510,7 +510,7 @@ static void grad_layout(const ha_problem &p, const ha_feature_map *phi_q, const 
   gl.total = base;
   if (gl.student.NL == 0) return;
   if (gl.layered) {
-    ha::make_wide_plan(gl.student, base, gl.wp);
+    ha::make_wide_plan(gl.student, base, gl.wp, true);
     ha::make_wide_grad_plan(gl.student, gl.wp, gl.wp.total, gl.wgp);
     gl.total = gl.wgp.total;
   } else {

@@ -24,32 +24,51 @@ static __device__ __forceinline__ f32x16 column_tile(const float *b, int blk, in
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
 }
 
-// u += W2[:, block] relu(W1[block, :] x + b1[block]) from the block's slab in LDS.
-static __device__ __forceinline__ void mlp256_hidden_block(lds_frag_ptr sl, const float *b1, int hb, const bf16x8 (&xf)[8],
-                                                           int lane, int g, f32x16 (&u)[8]) {
+// ReLU of a finished hidden tile as hi + lo bf16 pairs: the B operands of the next product.
+static __device__ __forceinline__ void relu_hi_lo(const f32x16 &t, u32x4 (&hi)[2], u32x4 (&lo)[2]) {
+#pragma unroll
+  for (int x = 0; x < 16; x += 2) {
+    const float v0 = relu(t[x]), v1 = relu(t[x + 1]);
+    const unsigned p = pack_bf16(v0, v1);
+    hi[x >> 3][(x & 7) >> 1] = p;
+    lo[x >> 3][(x & 7) >> 1] = pack_bf16(v0 - __uint_as_float(p << 16), v1 - __uint_as_float(p & 0xffff0000u));
+  }
+}
+
+// relu(W1[block, :] x + b1[block]) of hidden block hb from the head of its slab.
+static __device__ __forceinline__ void hidden_block(lds_frag_ptr sl, const float *b1, int hb, const bf16x8 (&xf)[8], int lane, int g,
+                                                    u32x4 (&h_hi)[2], u32x4 (&h_lo)[2]) {
   f32x16 hh = column_tile(b1, hb, g);
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) hh = mfma32(frag_at(sl, ks, lane), xf[ks], hh);
-  u32x4 h_hi[2], h_lo[2];
-#pragma unroll
-  for (int x = 0; x < 16; x += 2) {
-    const float v0 = relu(hh[x]), v1 = relu(hh[x + 1]);
-    const unsigned hi = pack_bf16(v0, v1);
-    h_hi[x >> 3][(x & 7) >> 1] = hi;
-    h_lo[x >> 3][(x & 7) >> 1] = pack_bf16(v0 - __uint_as_float(hi << 16), v1 - __uint_as_float(hi & 0xffff0000u));
-  }
+  relu_hi_lo(hh, h_hi, h_lo);
+}
+
+// u += W[:, block] h of the block's 32 inputs for NT output tiles; wsl: two fragments per tile.
+template <int NT>
+static __device__ __forceinline__ void hidden_to_outputs(lds_frag_ptr wsl, bf16x8 hi0, bf16x8 hi1, bf16x8 lo0, bf16x8 lo1, int lane,
+                                                         f32x16 (&u)[NT]) {
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
-    const bf16x8 lo8 = __builtin_bit_cast(bf16x8, h_lo[s]), hi8 = __builtin_bit_cast(bf16x8, h_hi[s]);
+    const bf16x8 hi8 = s ? hi1 : hi0, lo8 = s ? lo1 : lo0;
 #pragma unroll
-    for (int fb = 0; fb < 8; fb += 2) {
-      const bf16x8 wa = frag_at(sl, 8 + 2 * fb + s, lane), wb = frag_at(sl, 8 + 2 * (fb + 1) + s, lane);
+    for (int fb = 0; fb < NT; fb += 2) {
+      const bf16x8 wa = frag_at(wsl, 2 * fb + s, lane), wb = frag_at(wsl, 2 * (fb + 1) + s, lane);
       u[fb] = mfma32(wa, lo8, u[fb]);
       u[fb + 1] = mfma32(wb, lo8, u[fb + 1]);
       u[fb] = mfma32(wa, hi8, u[fb]);
       u[fb + 1] = mfma32(wb, hi8, u[fb + 1]);
     }
   }
+}
+
+// u += W2[:, block] relu(W1[block, :] x + b1[block]) from the block's slab in LDS.
+static __device__ __forceinline__ void mlp256_hidden_block(lds_frag_ptr sl, const float *b1, int hb, const bf16x8 (&xf)[8],
+                                                           int lane, int g, f32x16 (&u)[8]) {
+  u32x4 h_hi[2], h_lo[2];
+  hidden_block(sl, b1, hb, xf, lane, g, h_hi, h_lo);
+  hidden_to_outputs<8>(sl + 8 * 64, __builtin_bit_cast(bf16x8, h_hi[0]), __builtin_bit_cast(bf16x8, h_hi[1]),
+                       __builtin_bit_cast(bf16x8, h_lo[0]), __builtin_bit_cast(bf16x8, h_lo[1]), lane, u);
 }
 
 // The output stage in place: positive activation over all channels, slice powers.  ACT0: softmax over the channels; otherwise

@@ -40,11 +40,12 @@ struct GradPlan {
 };
 
 // Workspace of the layer-by-layer path for feature maps beyond the fused kernels' widths (beyond the forward's):
-// hidden activations (hi + lo), fp32 pre-activations, phi, and for the queries n = phi_q S and e = phi_q . z.
+// hidden activations (hi + lo where another layer reads them), fp32 pre-activations, and for the queries n = phi_q S and
+// e = phi_q . z.
 struct WidePlan {
   int n_tb_q, n_tb_k;      // 32-token blocks of the query tokens / the linear key tokens
   size_t off_w1, off_wm, off_w2;   // weight fragments of the map being evaluated (key side, then query side)
-  size_t off_hhi, off_hlo, off_h2hi, off_h2lo, off_u, off_stat, off_phi, off_lin, off_e, total;
+  size_t off_hhi, off_h2hi, off_h2lo, off_u, off_stat, off_phi, off_lin, off_e, total;
 };
 
 // Number of softmax tokens among the first t tokens: the first G of every R G tokens (Sec. 3.2 with G = 1).
@@ -105,7 +106,8 @@ hipError_t launch_linear_query(const Plan &pl, const void *q, const ha_feature_m
 // ha_linear256.hip: n = phi_q(q) S and e = phi_q(q) . z of the 128 -> 256 -> 256 maps
 hipError_t launch_linear256(const Plan &pl, const void *q, const ha_feature_map &phi_q, void *ws, hipStream_t st);
 // ha_wide.hip
-void make_wide_plan(const Plan &pl, size_t base_off, WidePlan &wp);
+// backward: with the images only a backward pass reads (first hidden layer, phi)
+void make_wide_plan(const Plan &pl, size_t base_off, WidePlan &wp, bool backward);
 hipError_t launch_wide_key_side(const Plan &pl, const WidePlan &wp, const void *k, const void *v, const ha_feature_map &phi_k,
                                 void *ws, hipStream_t st);
 hipError_t launch_wide_query_side(const Plan &pl, const WidePlan &wp, const void *q, const ha_feature_map &phi_q, void *ws,
@@ -128,9 +130,21 @@ hipError_t launch_value_distill_backward(const Plan &pl, const GradPlan &gp, con
 hipError_t launch_vd_rows(const Plan &pl, const void *y_teacher, const void *y_student, const float *row_den, void *gsign,
                           float *rs, float *wp, hipStream_t st, double *l1_partial = nullptr, double *loss = nullptr);
 hipError_t launch_natural_frags(const float *M, void *hi, void *lo, int rows, int cols, int n_mat, hipStream_t st);
-// ha_wide.hip / ha_wide_grad.hip
+// ha_wide_mlp.hip: one layer of a map that goes layer by layer.  x given: the input is the first hidden layer
+// relu(W1 x + b1), formed on the way (its bf16 image is left in h_hi if that is given); otherwise the images in_hi, in_lo.
+// out_u, out_stat given: the last layer; otherwise out_hi, out_lo.
+struct WideMlpLayer {
+  const void *x, *in_hi, *in_lo, *w1f, *wf;
+  const float *b1, *bias;
+  void *h_hi, *out_hi, *out_lo, *out_u;
+  float *out_stat;
+  int K, NOUT, n_tok, R;
+};
+hipError_t launch_wide_mlp(const Plan &pl, const WideMlpLayer &l, hipStream_t st);
+// ha_wide.hip / ha_wide_grad.hip.  keep_hidden: leave the first hidden layer's image in the workspace (a backward pass
+// reads it).
 hipError_t launch_wide_map(const Plan &pl, const WidePlan &wp, const void *x, const ha_feature_map &fm, bool is_query, void *ws,
-                           hipStream_t st);
+                           hipStream_t st, bool keep_hidden);
 void make_wide_grad_plan(const Plan &pl, const WidePlan &wp, size_t base_off, WideGradPlan &gp);
 hipError_t launch_wide_value_distill_backward(const Plan &pl, const WidePlan &wp, const WideGradPlan &gp, const void *q,
                                               const void *k, const void *v, const ha_feature_map &phi_q,

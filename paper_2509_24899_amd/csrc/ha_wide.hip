@@ -4,8 +4,8 @@
 // activations travel through HBM, in exactly the register image the next product wants:
 //
 //   wide_prep_kernel       one weight matrix -> A-operand fragments (natural order for layer 1, chained after it)
-//   wide_layer1_kernel     h^T = relu(W1 x^T + b1)                     x from q / k, h as hi + lo bf16
-//   wide_layer_kernel      h'^T = relu(W h^T + b)  or  u^T = W h^T + b  (last layer: fp32 pre-activations)
+//   (ha_wide_mlp.hip)      h^T = relu(W1 x^T + b1) on the way into  h'^T = relu(W h^T + b)  or  u^T = W h^T + b  (last
+//                          layer: fp32 pre-activations); h' as hi + lo bf16
 //   (output stage)         softmax / exp / relu over all channels of a token, slice powers, bf16: applied by the two
 //                          consumers below while they read the pre-activations, so phi never visits HBM
 //   wide_state_kernel      [S | z] += phi_k^T [V | 1], one 128-channel slab of S per workgroup
@@ -20,18 +20,6 @@
 #include "ha_plan.h"
 
 namespace ha {
-
-struct WideArgs {
-  const void *x;                 // layer 1: q or k (io dtype, strided)
-  const bf16x8 *in_hi, *in_lo;   // later layers / consumers: activations of the previous pass
-  const bf16x8 *wf;              // weight fragments of this layer, all heads
-  const float *bias;             // [H][NOUT] or null
-  bf16x8 *out_hi, *out_lo;       // hidden layers
-  f32x4 *out_u;                  // last layer
-  float *out_stat;               // last layer: [bh][tb][256-channel block][2][64] running maximum and sum of exponentials
-  int H, K, NOUT, n_tok, n_tb, R, G;
-  int64_t sb, sh, sn;
-};
 
 // ------------------------------------------------------------------------------------------------
 // wide_prep_kernel: grid (ceil(NOUT*K / 256), H).  W [H][NOUT][K] (io dtype) ->
@@ -61,182 +49,6 @@ __global__ __launch_bounds__(256) void wide_prep_kernel(const void *__restrict__
   if constexpr (F32) val = static_cast<const float *>(wsrc)[src];
   else val = static_cast<float>(static_cast<const __bf16 *>(wsrc)[src]);
   wf[(int64_t)h * NOUT * K + e] = static_cast<__bf16>(val);
-}
-
-// ------------------------------------------------------------------------------------------------
-// wide_layer1_kernel: grid (ceil(n_tb / 4), NOUT / 128, B*H), 4 waves, one 32-token block per wave and four
-// 32-channel output blocks per workgroup row.  W1 fragments in natural order (weight_prep_kernel).
-template <int D, bool F32>
-__global__ __launch_bounds__(256) void wide_layer1_kernel(WideArgs a) {
-  constexpr int KS = D / 16;
-  const int bh = blockIdx.z, h = bh % a.H;
-  const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
-  const int tb = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (tb >= a.n_tb) return;
-  const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)h * a.sh;
-  const LinearMap lmap(a.R, a.G);
-  const int tok = lmap.token(min(32 * tb + r, a.n_tok - 1));
-  bf16x8 xf[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) xf[ks] = load8<F32>(a.x, base + (int64_t)tok * a.sn + 16 * ks + 8 * g);
-  const GlobalFrags wf = global_frags(a.wf + (int64_t)h * (a.NOUT * D / 8), a.NOUT * D * 2);
-  const int HB = a.NOUT / 32;
-  for (int j = 0; j < 4; ++j) {
-    const int hb = blockIdx.y * 4 + j;
-    f32x16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = a.bias ? a.bias[(int64_t)h * a.NOUT + 32 * hb + crow(v, g)] : 0.f;
-    bf16x8 w8[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) w8[ks] = frag_at(wf, hb * KS + ks, lane);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) acc = mfma32(w8[ks], xf[ks], acc);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      f32x8 t, lo;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) t[i] = fmaxf(acc[8 * s + i], 0.f);
-      const bf16x8 hi = __builtin_convertvector(t, bf16x8);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) lo[i] = t[i] - static_cast<float>(hi[i]);
-      const int64_t o = ((((int64_t)bh * a.n_tb + tb) * HB + hb) * 2 + s) * 64 + lane;
-      a.out_hi[o] = hi;
-      a.out_lo[o] = __builtin_convertvector(lo, bf16x8);
-    }
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// wide_layer_kernel: grid (ceil(n_tb / 4), ceil(NOUT / 256), B*H), 4 waves.  Input activations as hi + lo C images
-// (width K), weights [NOUT x K] as fragments in chained order.  LAST: fp32 pre-activations out; otherwise relu
-// and hi + lo bf16.  Every wave owns one 32-token block and all (up to eight) 32-channel output tiles of the
-// workgroup, so an activation fragment is read once per 256 output channels; the weight fragments are the same
-// for the four waves and pass through LDS, two 32-channel input blocks per stage, the next stage in flight
-// (direct-to-LDS) while the 64 matrix instructions of the current one run.
-// FULL: NOUT is a multiple of 256, every workgroup has all eight output tiles: the inner loops carry no tile-count
-// tests, so the weight fragments of a half step are requested together ahead of their matrix instructions.
-template <bool LAST, bool FULL>
-__global__ __launch_bounds__(256, 2) void wide_layer_kernel(WideArgs a) {
-  constexpr int NT = 8, KCH = 2, STG = NT * KCH * 2 * 64;       // bf16x8 per stage buffer (32 KiB)
-  __shared__ bf16x8 wl[2][STG];
-  const int bh = blockIdx.z, h = bh % a.H;
-  const int lane = threadIdx.x & 63, g = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool live = blockIdx.x * 4 + w < a.n_tb;                 // idle waves keep staging and synchronising
-  const int tb = live ? blockIdx.x * 4 + w : a.n_tb - 1;
-  const int KB = a.K / 32, OB = a.NOUT / 32;
-  const int ob0 = blockIdx.y * NT;
-  const int nt = FULL ? NT : min(NT, OB - ob0);
-  const bf16x8 *wg = a.wf + (int64_t)h * ((int64_t)a.NOUT * a.K / 8);
-  const bf16x8 *bhi = a.in_hi + ((int64_t)bh * a.n_tb + tb) * KB * 128 + lane;
-  const bf16x8 *blo = a.in_lo + ((int64_t)bh * a.n_tb + tb) * KB * 128 + lane;
-  f32x16 acc[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[j][v] = (a.bias && j < nt) ? a.bias[(int64_t)h * a.NOUT + 32 * (ob0 + j) + crow(v, g)] : 0.f;
-  auto stage = [&](int c, int buf) {              // input blocks c KCH .. c KCH + KCH - 1 of every output tile
-    for (int j = 0; j < nt; ++j)
-      dma_to_lds(wg + (((int64_t)(ob0 + j) * KB + c * KCH) * 2) * 64, &wl[buf][j * KCH * 2 * 64], KCH * 2, w, 4, lane);
-  };
-  bf16x8 cb_hi[2], cb_lo[2], nb_hi[2], nb_lo[2];
-  auto request_b = [&](int kb, bf16x8 (&hi)[2], bf16x8 (&lo)[2]) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      hi[s] = bhi[(kb * 2 + s) * 64];
-      lo[s] = blo[(kb * 2 + s) * 64];
-    }
-  };
-  stage(0, 0);
-  request_b(0, cb_hi, cb_lo);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  const int n_stages = KB / KCH;
-  for (int c = 0; c < n_stages; ++c) {
-    if (c + 1 < n_stages) stage(c + 1, (c + 1) & 1);
-    const bf16x8 *wbuf = &wl[c & 1][lane];
-#pragma unroll
-    for (int kbl = 0; kbl < KCH; ++kbl) {
-      const int kb = c * KCH + kbl;
-      if (kb + 1 < KB) request_b(kb + 1, nb_hi, nb_lo);
-      if constexpr (FULL) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-          for (int j0 = 0; j0 < NT; j0 += 4) {
-            bf16x8 af[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) af[j] = wbuf[((j0 + j) * KCH * 2 + kbl * 2 + s) * 64];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              acc[j0 + j] = mfma32(af[j], cb_lo[s], acc[j0 + j]);
-              acc[j0 + j] = mfma32(af[j], cb_hi[s], acc[j0 + j]);
-            }
-          }
-      } else {
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-          for (int j = 0; j < NT; ++j)
-            if (j < nt) {
-              const bf16x8 af = wbuf[(j * KCH * 2 + kbl * 2 + s) * 64];
-              acc[j] = mfma32(af, cb_lo[s], acc[j]);
-              acc[j] = mfma32(af, cb_hi[s], acc[j]);
-            }
-      }
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        cb_hi[s] = nb_hi[s];
-        cb_lo[s] = nb_lo[s];
-      }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();                               // the next stage has landed; this one may be overwritten
-  }
-  if (!live) return;
-  if constexpr (LAST) {
-    // per token: maximum of this workgroup's channels and the sum of exponentials against it, so that the output
-    // stage can form the softmax over all channels with a single sweep over the pre-activations
-    float m = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-      if (j < nt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) m = fmaxf(m, acc[j][v]);
-    m = xhalf_max(m);
-    float sum = 0.f;
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-      if (j < nt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sum += fast_exp2((acc[j][v] - m) * kLog2e);
-    sum = xhalf_sum(sum);
-    float *st = a.out_stat + ((((int64_t)bh * a.n_tb + tb) * gridDim.y + blockIdx.y) * 2) * 64 + lane;
-    st[0] = m;
-    st[64] = sum;
-  }
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    if (j >= nt) break;
-    const int64_t blk = ((int64_t)bh * a.n_tb + tb) * OB + ob0 + j;
-    if constexpr (LAST) {
-#pragma unroll
-      for (int x4 = 0; x4 < 4; ++x4)
-        a.out_u[(blk * 4 + x4) * 64 + lane] = f32x4{acc[j][4 * x4], acc[j][4 * x4 + 1], acc[j][4 * x4 + 2], acc[j][4 * x4 + 3]};
-    } else {
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        f32x8 t, lo;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t[i] = fmaxf(acc[j][8 * s + i], 0.f);
-        const bf16x8 hi = __builtin_convertvector(t, bf16x8);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) lo[i] = t[i] - static_cast<float>(hi[i]);
-        a.out_hi[(blk * 2 + s) * 64 + lane] = hi;
-        a.out_lo[(blk * 2 + s) * 64 + lane] = __builtin_convertvector(lo, bf16x8);
-      }
-    }
-  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -463,7 +275,7 @@ template <typename T>
 static inline T *ws_ptr(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(ws) + off); }
 static inline size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
-void make_wide_plan(const Plan &pl, size_t base_off, WidePlan &wp) {
+void make_wide_plan(const Plan &pl, size_t base_off, WidePlan &wp, bool backward) {
   const size_t BH = (size_t)pl.B * pl.H;
   wp.n_tb_q = (pl.N + 31) / 32;
   wp.n_tb_k = (pl.NL + 31) / 32;
@@ -474,13 +286,12 @@ void make_wide_plan(const Plan &pl, size_t base_off, WidePlan &wp) {
   wp.off_w1 = take((size_t)pl.H * pl.HD * pl.D * 2);
   wp.off_wm = take((size_t)pl.H * pl.DM * pl.HD * 2);
   wp.off_w2 = take((size_t)pl.H * pl.F * KL * 2);
-  wp.off_hhi = take(BH * n_tb * 32 * pl.HD * 2);
-  wp.off_hlo = take(BH * n_tb * 32 * pl.HD * 2);
+  wp.off_hhi = take(backward ? BH * n_tb * 32 * pl.HD * 2 : 0);
   wp.off_h2hi = take(BH * n_tb * 32 * pl.DM * 2);
   wp.off_h2lo = take(BH * n_tb * 32 * pl.DM * 2);
   wp.off_u = take(BH * n_tb * 32 * (size_t)pl.F * 4);
   wp.off_stat = take(BH * n_tb * ((pl.F + 255) / 256) * 2 * 64 * sizeof(float));
-  wp.off_phi = take(BH * n_tb * 32 * (size_t)pl.F * 2);
+  wp.off_phi = take(backward ? BH * n_tb * 32 * (size_t)pl.F * 2 : 0);
   wp.off_lin = take(BH * n_tb * 32 * (size_t)pl.D * 4);
   wp.off_e = take(BH * (size_t)pl.N * 4);
   wp.total = off;
@@ -490,9 +301,8 @@ void make_wide_plan(const Plan &pl, size_t base_off, WidePlan &wp) {
 // pre-activations and the softmax statistics; the output stage belongs to whoever reads them next.  is_query: all N
 // tokens of q; otherwise the linear tokens of k.
 hipError_t launch_wide_map(const Plan &pl, const WidePlan &wp, const void *x, const ha_feature_map &fm, bool is_query,
-                           void *ws, hipStream_t st) {
-  const int BH = pl.B * pl.H;
-  const int n_tok = is_query ? pl.N : pl.NL, n_tb = is_query ? wp.n_tb_q : wp.n_tb_k;
+                           void *ws, hipStream_t st, bool keep_hidden) {
+  const int n_tok = is_query ? pl.N : pl.NL;
   hipError_t e;
   const int KL = pl.DM > 0 ? pl.DM : pl.HD;
   // weight fragments of this map
@@ -513,54 +323,39 @@ hipError_t launch_wide_map(const Plan &pl, const WidePlan &wp, const void *x, co
     prep(fm.w2, wp.off_w2, pl.F, KL, true);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  WideArgs a;
-  a.x = x;
-  a.H = pl.H; a.n_tok = n_tok; a.n_tb = n_tb; a.R = is_query ? 0 : pl.R; a.G = pl.G;
-  a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
-  a.in_hi = a.in_lo = nullptr;
-  a.out_u = nullptr;
-  a.out_stat = nullptr;
-  // layer 1: d -> HD
-  a.wf = ws_ptr<bf16x8>(ws, wp.off_w1);
-  a.bias = fm.b1; a.K = pl.D; a.NOUT = pl.HD;
-  a.out_hi = ws_ptr<bf16x8>(ws, wp.off_hhi); a.out_lo = ws_ptr<bf16x8>(ws, wp.off_hlo);
-  {
-    dim3 grid((n_tb + 3) / 4, pl.HD / 128, BH);
-    if (pl.f32) wide_layer1_kernel<128, true><<<grid, 256, 0, st>>>(a);
-    else wide_layer1_kernel<128, false><<<grid, 256, 0, st>>>(a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  a.in_hi = ws_ptr<bf16x8>(ws, wp.off_hhi); a.in_lo = ws_ptr<bf16x8>(ws, wp.off_hlo);
+  // x -> first hidden layer (-> middle layer, hi + lo images) -> fp32 pre-activations and softmax statistics
+  WideMlpLayer l = {};
+  l.x = x;
+  l.n_tok = n_tok; l.R = is_query ? 0 : pl.R;
+  l.w1f = ws_ptr<void>(ws, wp.off_w1);
+  l.b1 = fm.b1;
+  l.K = pl.HD;
+  if (keep_hidden) l.h_hi = ws_ptr<void>(ws, wp.off_hhi);
   if (pl.DM > 0) {
-    // middle layer of a three-layer map: HD -> DM, relu, hi + lo
-    a.wf = ws_ptr<bf16x8>(ws, wp.off_wm);
-    a.bias = fm.b_mid; a.K = pl.HD; a.NOUT = pl.DM;
-    a.out_hi = ws_ptr<bf16x8>(ws, wp.off_h2hi); a.out_lo = ws_ptr<bf16x8>(ws, wp.off_h2lo);
-    dim3 grid((n_tb + 3) / 4, (pl.DM + 255) / 256, BH);
-    if (pl.DM % 256 == 0) wide_layer_kernel<false, true><<<grid, 256, 0, st>>>(a);
-    else wide_layer_kernel<false, false><<<grid, 256, 0, st>>>(a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    a.in_hi = ws_ptr<bf16x8>(ws, wp.off_h2hi); a.in_lo = ws_ptr<bf16x8>(ws, wp.off_h2lo);
+    l.wf = ws_ptr<void>(ws, wp.off_wm);
+    l.bias = fm.b_mid;
+    l.NOUT = pl.DM;
+    l.out_hi = ws_ptr<void>(ws, wp.off_h2hi);
+    l.out_lo = ws_ptr<void>(ws, wp.off_h2lo);
+    if ((e = launch_wide_mlp(pl, l, st)) != hipSuccess) return e;
+    l.x = nullptr;
+    l.h_hi = nullptr;
+    l.in_hi = l.out_hi; l.in_lo = l.out_lo;
+    l.out_hi = l.out_lo = nullptr;
+    l.K = pl.DM;
   }
-  // last layer: -> F, fp32 pre-activations
-  a.wf = ws_ptr<bf16x8>(ws, wp.off_w2);
-  a.bias = fm.b2; a.K = KL; a.NOUT = pl.F;
-  a.out_hi = a.out_lo = nullptr;
-  a.out_u = ws_ptr<f32x4>(ws, wp.off_u);
-  a.out_stat = ws_ptr<float>(ws, wp.off_stat);
-  {
-    dim3 grid((n_tb + 3) / 4, (pl.F + 255) / 256, BH);
-    if (pl.F % 256 == 0) wide_layer_kernel<true, true><<<grid, 256, 0, st>>>(a);
-    else wide_layer_kernel<true, false><<<grid, 256, 0, st>>>(a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  return hipSuccess;
+  l.wf = ws_ptr<void>(ws, wp.off_w2);
+  l.bias = fm.b2;
+  l.NOUT = pl.F;
+  l.out_u = ws_ptr<void>(ws, wp.off_u);
+  l.out_stat = ws_ptr<float>(ws, wp.off_stat);
+  return launch_wide_mlp(pl, l, st);
 }
 
 // Key side: phi_k over the linear tokens, then [S | z] (partials + the forward's reduction).
 hipError_t launch_wide_key_side(const Plan &pl, const WidePlan &wp, const void *k, const void *v, const ha_feature_map &phi_k,
                                 void *ws, hipStream_t st) {
-  hipError_t e = launch_wide_map(pl, wp, k, phi_k, false, ws, st);
+  hipError_t e = launch_wide_map(pl, wp, k, phi_k, false, ws, st, false);
   if (e != hipSuccess) return e;
   dim3 grid(pl.n_chunks, pl.B * pl.H, pl.F / 128);
   if (pl.f32)
@@ -578,7 +373,7 @@ hipError_t launch_wide_key_side(const Plan &pl, const WidePlan &wp, const void *
 // Query side: phi_q over all tokens, e = phi_q . z, n = phi_q S; the query kernel picks both up in its epilogue.
 hipError_t launch_wide_query_side(const Plan &pl, const WidePlan &wp, const void *q, const ha_feature_map &phi_q, void *ws,
                                   hipStream_t st) {
-  hipError_t e = launch_wide_map(pl, wp, q, phi_q, true, ws, st);
+  hipError_t e = launch_wide_map(pl, wp, q, phi_q, true, ws, st, false);
   if (e != hipSuccess) return e;
   dim3 grid((wp.n_tb_q + 3) / 4, pl.B * pl.H);
   wide_lin_kernel<128><<<grid, 256, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat),

@@ -1,0 +1,259 @@
+// Layers of the feature maps that go layer by layer through HBM (ha_wide.hip), as one streaming kernel.  gfx950 only.
+//
+// One workgroup, 8 waves of 32 tokens, walks a contiguous run of work items (tile of 256 tokens, block of 32 NT output
+// channels).  A wave's accumulators are the NT output tiles of its tokens; the contraction runs over the input width in
+// blocks of 32, each of which is
+//   from x      formed on the spot: relu(W1 x + b1) of 32 hidden units (8 matrix instructions), split into hi + lo, so that
+//               the first hidden layer never visits HBM (its 8 instructions per block are repeated for every block of output
+//               channels: a quarter of the 32 that consume it, against 4 bytes per unit and token written and read back), or
+//   from HBM    fetched as the hi + lo register images the previous layer left, three blocks ahead.
+// The weights of a block (its rows of W1, its columns of the layer's matrix) are one slab of an LDS ring that all waves
+// share; requests run ahead across items, one barrier per block.  Output blocks of a tile are consecutive items, so an
+// image is read from HBM once and then from the cache behind it.
+//
+// Bound: matrix cores at the clock the power limit allows: 1.05 PFLOP/s of matrix instructions in both forms, where a large
+// library product of the same type reaches 1.3.  Measured with the 768-wide three-layer maps at 480p / 81 frames, 12 heads,
+// R = 8: first hidden layer + middle layer as passes of their own 324 + 777 us (keys) and 375 + 928 us (queries), 939 and
+// 1050 us here; the last layer, whose input comes from HBM in either case, 772 -> 788 and 926 -> 913 us; the 256-wide maps'
+// two layers ahead of a backward pass 111 + 174 -> 185 us (queries), 87 + 131 -> 145 us (keys).
+#include "ha_mlp256.h"
+#include "ha_plan.h"
+
+namespace ha {
+
+struct WideMlpArgs {
+  const void *x;                 // from x: q or k (io dtype, strided)
+  const bf16x8 *in_hi, *in_lo;   // from HBM: the previous layer's images, width K
+  const bf16x8 *w1f, *wf;        // fragments, all heads: W1 (natural order), this layer's matrix [NOUT x K] (chained)
+  const float *b1, *bias;        // [H][K], [H][NOUT], or null
+  bf16x8 *h_hi;                  // from x: the hidden layer's bf16 image, if somebody needs it (or null)
+  bf16x8 *out_hi, *out_lo;       // hidden layer out
+  f32x4 *out_u;                  // last layer: fp32 pre-activations
+  float *out_stat;               // last layer: [bh][tb][256-channel block][2][64] maximum and sum of exponentials
+  int H, K, NOUT, n_tok, n_tb, R, G;
+  int ob_first, n_ob;            // first output tile, blocks of NT tiles
+  int n_tiles, total;            // 256-token tiles per (batch, head), items overall
+  int64_t sb, sh, sn;
+};
+
+// SRC: 0 from x in bf16, 1 from x in fp32, 2 from HBM.  LAST: fp32 pre-activations out; otherwise relu, hi + lo bf16.
+template <int NT, int SRC, bool LAST>
+__global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
+  constexpr bool X = SRC != 2;
+  constexpr int D = 128, KS = D / 16, NW = 8, NBUF = 5;
+  constexpr int CH = (X ? KS : 0) + 2 * NT, PW = CH / NW, SLOT = CH * 64;      // 1 KiB chunks per slab, per wave
+  constexpr int WMAX = 768;
+  static_assert(CH % NW == 0, "slabs are dealt evenly");
+  __shared__ bf16x8 ring[NBUF * SLOT];
+  __shared__ __align__(16) float vecs[(X ? WMAX : 0) + WMAX];                  // b1, bias of the whole layer
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nwg = gridDim.x;                                                   // a multiple of 8
+  const int wg = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
+  const int i_lo = (int)((int64_t)wg * a.total / nwg), i_hi = (int)((int64_t)(wg + 1) * a.total / nwg);
+  if (i_lo >= i_hi) return;
+  const int KB = a.K / 32, OB = a.NOUT / 32;                                   // KB: a multiple of 4
+  const int per_head = a.n_tiles * a.n_ob;
+  const LinearMap lmap(a.R, a.G);
+
+  struct Item { int bh, tb, ob0; };                                            // tb: this wave's 32-token block
+  auto item_of = [&](int i) {
+    Item it;
+    it.bh = i / per_head;
+    const int rem = i - it.bh * per_head, tile = rem / a.n_ob;
+    it.tb = tile * NW + w;
+    it.ob0 = a.ob_first + (rem - tile * a.n_ob) * NT;
+    return it;
+  };
+  const unsigned lane_off = lane * 16;
+  auto request = [&](const Item &it, int kb, int slot) {
+    const int h = it.bh % a.H;
+    const bf16x8 *w1 = X ? a.w1f + (int64_t)h * (a.K * D / 8) + kb * KS * 64 : nullptr;
+    const bf16x8 *wm = a.wf + (int64_t)h * ((int64_t)a.NOUT * a.K / 8);
+#pragma unroll
+    for (int i = 0; i < PW; ++i) {
+      const int c = i * NW + w;
+      const int cc = c - (X ? KS : 0);
+      const bf16x8 *gp = X && c < KS ? w1 + c * 64 : wm + (((int64_t)(it.ob0 + (cc >> 1)) * KB + kb) * 2 + (cc & 1)) * 64;
+      const unsigned l = __builtin_amdgcn_readfirstlane(
+          (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)(&ring[slot * SLOT + c * 64]));
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(gp) : "memory");
+    }
+  };
+  Item cur = item_of(i_lo), nxt = cur;
+  int slot = 0, ahead = NBUF - 1;                  // slot of the current slab; slot the next request goes to
+  bool stored = false;                             // this wave wrote its outputs at the end of the item before
+  // Barrier ahead of a slab: this wave's share has landed and so has everybody's, and everybody is done with the slab
+  // before it, whose slot takes the request NBUF - 1 slabs ahead.  Newer than the slab's own request are at least the
+  // NBUF - 2 requests after it (and from HBM as many groups of four image loads), and, for slabs requested before this
+  // wave's outputs, those 4 NT stores (loads and stores retire in order).
+  constexpr int FLY = (NBUF - 2) * (PW + (X ? 0 : 4));
+  static_assert(FLY + 4 * NT < 63, "vmcnt immediate too large");
+  auto advance = [&](int kb) {
+    if (stored && kb < NBUF - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FLY + 4 * NT) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FLY) : "memory");
+    __syncthreads();
+    const int s = kb + NBUF - 1;
+    request(s < KB ? cur : nxt, s < KB ? s : s - KB, ahead);                   // (past the last item: a slab nobody reads)
+    ahead = ahead + 1 == NBUF ? 0 : ahead + 1;
+  };
+  auto next_slab = [&]() {
+    const lds_frag_ptr sl = (lds_frag_ptr)&ring[slot * SLOT];
+    slot = slot + 1 == NBUF ? 0 : slot + 1;
+    return sl;
+  };
+
+  bf16x8 xf[X ? KS : 1];
+  auto load_x = [&](const Item &it) {
+    const int h = it.bh % a.H;
+    const int64_t base = (int64_t)(it.bh / a.H) * a.sb + (int64_t)h * a.sh;
+    const int tok = lmap.token(min(32 * it.tb + r, a.n_tok - 1));              // rows past the end repeat the last token
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) xf[ks] = load8<SRC == 1>(a.x, base + (int64_t)tok * a.sn + 16 * ks + 8 * g);
+  };
+  bf16x8 im_hi[X ? 1 : 4][2], im_lo[X ? 1 : 4][2];                             // input blocks kb .. kb + 3, buffer kb % 4
+  auto load_image = [&](const Item &it, int kb, bf16x8 (&hi)[2], bf16x8 (&lo)[2]) {
+    const int64_t at = (((int64_t)it.bh * a.n_tb + min(it.tb, a.n_tb - 1)) * KB + kb) * 128 + lane;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      hi[s] = a.in_hi[at + s * 64];
+      lo[s] = a.in_lo[at + s * 64];
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < NBUF - 1; ++s) request(cur, s, s);                       // (KB >= NBUF - 1)
+  if constexpr (!X) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s) load_image(cur, s, im_hi[s], im_lo[s]);
+  }
+  const float *b1 = &vecs[0], *bias = &vecs[X ? WMAX : 0];
+
+  int bh_vecs = -1;
+  for (int i = i_lo; i < i_hi; ++i) {
+    nxt = item_of(i + 1 < i_hi ? i + 1 : i);
+    if constexpr (X) load_x(cur);
+    if (cur.bh != bh_vecs) {                       // workgroup-uniform: the first item, or the head changes
+      const int h = cur.bh % a.H;
+      __syncthreads();                             // every wave is done with the previous head's biases
+      if constexpr (X)
+        for (int j = tid; j < a.K; j += 512) vecs[j] = a.b1 ? a.b1[(int64_t)h * a.K + j] : 0.f;
+      for (int j = tid; j < a.NOUT; j += 512) vecs[(X ? WMAX : 0) + j] = a.bias ? a.bias[(int64_t)h * a.NOUT + j] : 0.f;
+      bh_vecs = cur.bh;
+      __syncthreads();
+    }
+    const bool live = cur.tb < a.n_tb;             // idle waves keep staging and synchronising
+    f32x16 acc[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[j] = column_tile(bias, cur.ob0 + j, g);
+    if constexpr (X) {
+      const bool keep = a.h_hi && cur.ob0 == 0 && live;
+#pragma unroll 1
+      for (int kb = 0; kb < KB; ++kb) {
+        advance(kb);
+        const lds_frag_ptr sl = next_slab();
+        u32x4 h_hi[2], h_lo[2];
+        hidden_block(sl, b1, kb, xf, lane, g, h_hi, h_lo);
+        if (keep) {
+          const int64_t at = (((int64_t)cur.bh * a.n_tb + cur.tb) * KB + kb) * 128 + lane;
+#pragma unroll
+          for (int s = 0; s < 2; ++s) a.h_hi[at + s * 64] = __builtin_bit_cast(bf16x8, h_hi[s]);
+        }
+        hidden_to_outputs<NT>(sl + KS * 64, __builtin_bit_cast(bf16x8, h_hi[0]), __builtin_bit_cast(bf16x8, h_hi[1]),
+                              __builtin_bit_cast(bf16x8, h_lo[0]), __builtin_bit_cast(bf16x8, h_lo[1]), lane, acc);
+      }
+    } else {
+#pragma unroll 1
+      for (int kb = 0; kb < KB; kb += 4) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          advance(kb + q);
+          const lds_frag_ptr sl = next_slab();
+          const int s = kb + q + 3;
+          load_image(s < KB ? cur : nxt, s < KB ? s : s - KB, im_hi[(q + 3) & 3], im_lo[(q + 3) & 3]);
+          hidden_to_outputs<NT>(sl, im_hi[q][0], im_hi[q][1], im_lo[q][0], im_lo[q][1], lane, acc);
+        }
+      }
+    }
+    stored = live;
+    if (live) {
+      const int64_t blk0 = ((int64_t)cur.bh * a.n_tb + cur.tb) * OB + cur.ob0;
+      if constexpr (LAST) {
+        // per token: maximum of this block's channels and the sum of exponentials against it, so that the output stage
+        // can form the softmax over all channels with a single sweep over the pre-activations
+        float m = acc[0][0];
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; v += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, acc[j][v]), acc[j][v + 1]);
+        m = xhalf_max(m);
+        const float off = -m * kLog2e;
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) sum += fast_exp2(__builtin_fmaf(acc[j][v], kLog2e, off));
+        sum = xhalf_sum(sum);
+        float *st = a.out_stat + ((((int64_t)cur.bh * a.n_tb + cur.tb) * ((OB + 7) / 8) + cur.ob0 / 8) * 2) * 64 + lane;
+        st[0] = m;
+        st[64] = sum;
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int x4 = 0; x4 < 4; ++x4)
+            a.out_u[((blk0 + j) * 4 + x4) * 64 + lane] = f32x4{acc[j][4 * x4], acc[j][4 * x4 + 1], acc[j][4 * x4 + 2], acc[j][4 * x4 + 3]};
+      } else {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          u32x4 hi[2], lo[2];
+          relu_hi_lo(acc[j], hi, lo);
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            a.out_hi[((blk0 + j) * 2 + s) * 64 + lane] = __builtin_bit_cast(bf16x8, hi[s]);
+            a.out_lo[((blk0 + j) * 2 + s) * 64 + lane] = __builtin_bit_cast(bf16x8, lo[s]);
+          }
+        }
+      }
+    }
+    cur = nxt;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be on its way into this workgroup's LDS
+}
+
+hipError_t launch_wide_mlp(const Plan &pl, const WideMlpLayer &l, hipStream_t st) {
+  WideMlpArgs a;
+  a.x = l.x;
+  a.in_hi = static_cast<const bf16x8 *>(l.in_hi); a.in_lo = static_cast<const bf16x8 *>(l.in_lo);
+  a.w1f = static_cast<const bf16x8 *>(l.w1f); a.wf = static_cast<const bf16x8 *>(l.wf);
+  a.b1 = l.b1; a.bias = l.bias;
+  a.h_hi = static_cast<bf16x8 *>(l.h_hi);
+  a.out_hi = static_cast<bf16x8 *>(l.out_hi); a.out_lo = static_cast<bf16x8 *>(l.out_lo);
+  a.out_u = static_cast<f32x4 *>(l.out_u); a.out_stat = l.out_stat;
+  a.H = pl.H; a.K = l.K; a.NOUT = l.NOUT;
+  a.n_tok = l.n_tok; a.n_tb = (l.n_tok + 31) / 32; a.R = l.R; a.G = pl.G;
+  a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
+  a.n_tiles = (a.n_tb + 7) / 8;
+  const int src = !l.x ? 2 : pl.f32 ? 1 : 0;
+  // blocks of eight output tiles, then a block of four where the width is an odd multiple of 128
+  for (int nt : {8, 4}) {
+    const int OB = a.NOUT / 32;
+    a.ob_first = nt == 8 ? 0 : OB / 8 * 8;
+    a.n_ob = nt == 8 ? OB / 8 : (OB - a.ob_first) / 4;
+    if (a.n_ob == 0) continue;
+    if (nt == 4 && a.ob_first > 0) a.h_hi = nullptr;                           // written with the first block
+    a.total = a.n_tiles * a.n_ob * pl.B * pl.H;
+    const int nwg = a.total < 256 ? (a.total + 7) / 8 * 8 : 256;               // one workgroup per CU
+#define HA_WIDE_MLP(NT, SRC) \
+  do { \
+    if (l.out_u) wide_mlp_kernel<NT, SRC, true><<<nwg, 512, 0, st>>>(a); \
+    else wide_mlp_kernel<NT, SRC, false><<<nwg, 512, 0, st>>>(a); \
+  } while (0)
+    if (nt == 8) { if (src == 0) HA_WIDE_MLP(8, 0); else if (src == 1) HA_WIDE_MLP(8, 1); else HA_WIDE_MLP(8, 2); }
+    else { if (src == 0) HA_WIDE_MLP(4, 0); else if (src == 1) HA_WIDE_MLP(4, 1); else HA_WIDE_MLP(4, 2); }
+#undef HA_WIDE_MLP
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+}  // namespace ha
