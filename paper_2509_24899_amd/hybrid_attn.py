@@ -125,6 +125,10 @@ def _lib():
     return _LIB
 
 
+def _mismatch(what):
+    raise ValueError(f"feature map does not match the problem: {what}")
+
+
 @dataclass
 class FeatureMap:
     """Device tensors of one feature map: w1 [H, Hd, d], b1 [H, Hd] fp32 or None, w2 [H, F, Hd],
@@ -143,27 +147,35 @@ class FeatureMap:
         """The C ABI reads these tensors through raw pointers with the shapes and dtype it derives from the problem;
         a mismatch would be garbage or an out-of-bounds device read, so every dimension, dtype and device is checked
         here against the problem's (H heads of width d_head, io dtype, device of q)."""
-        def need(cond, what):
-            if not cond:
-                raise ValueError(f"feature map does not match the problem: {what}")
-        Hd = self.w1.shape[1] if self.w1.dim() == 3 else -1
-        need(self.w1.dim() == 3 and tuple(self.w1.shape) == (H, Hd, d_head), f"w1 must be [H={H}, d_hidden, d_head={d_head}], got {tuple(self.w1.shape)}")
+        w1, w2, mid = self.w1, self.w2, self.w_mid
+        w1s, w2s, mids = tuple(w1.shape), tuple(w2.shape), tuple(mid.shape) if mid is not None else None
+        Hd = w1s[1] if len(w1s) == 3 else -1
+        if w1s != (H, Hd, d_head):
+            _mismatch(f"w1 must be [H={H}, d_hidden, d_head={d_head}], got {w1s}")
         kl = Hd
-        if self.w_mid is not None:
-            need(self.w_mid.dim() == 3 and tuple(self.w_mid.shape[::2]) == (H, Hd), f"w_mid must be [H={H}, d_mid, d_hidden={Hd}], got {tuple(self.w_mid.shape)}")
-            kl = self.w_mid.shape[1]
-        need(self.w2.dim() == 3 and self.w2.shape[0] == H and self.w2.shape[2] == kl, f"w2 must be [H={H}, d_out, {kl}], got {tuple(self.w2.shape)}")
-        F = self.w2.shape[1]
+        if mid is not None:
+            if len(mids) != 3 or mids[::2] != (H, Hd):
+                _mismatch(f"w_mid must be [H={H}, d_mid, d_hidden={Hd}], got {mids}")
+            kl = mids[1]
+        if len(w2s) != 3 or w2s[0] != H or w2s[2] != kl:
+            _mismatch(f"w2 must be [H={H}, d_out, {kl}], got {w2s}")
+        F = w2s[1]
         for name, b, width in (("b1", self.b1, Hd), ("b2", self.b2, F), ("b_mid", self.b_mid, kl)):
             if b is not None:
-                need(name != "b_mid" or self.w_mid is not None, "b_mid given without w_mid")
-                need(tuple(b.shape) == (H, width), f"{name} must be [H={H}, {width}], got {tuple(b.shape)}")
-                need(b.device == device, f"{name} is on {b.device}, q on {device}")
-        for name, t in (("w1", self.w1), ("w2", self.w2), ("w_mid", self.w_mid)):
+                if name == "b_mid" and mid is None:
+                    _mismatch("b_mid given without w_mid")
+                if tuple(b.shape) != (H, width):
+                    _mismatch(f"{name} must be [H={H}, {width}], got {tuple(b.shape)}")
+                if b.device != device:
+                    _mismatch(f"{name} is on {b.device}, q on {device}")
+        for name, t in (("w1", w1), ("w2", w2), ("w_mid", mid)):
             if t is not None:
-                need(t.dtype == dtype, f"{name} is {t.dtype}, q is {dtype}")
-                need(t.device == device, f"{name} is on {t.device}, q on {device}")
-        need(self.poly_degree >= 1 and F % self.poly_degree == 0, f"poly_degree {self.poly_degree} must divide d_out {F}")
+                if t.dtype != dtype:
+                    _mismatch(f"{name} is {t.dtype}, q is {dtype}")
+                if t.device != device:
+                    _mismatch(f"{name} is on {t.device}, q on {device}")
+        if self.poly_degree < 1 or F % self.poly_degree != 0:
+            _mismatch(f"poly_degree {self.poly_degree} must divide d_out {F}")
 
     def c_struct(self) -> ha_feature_map:
         for t in (self.w1, self.w2, self.w_mid):
@@ -237,6 +249,12 @@ def _alloc_on(stream):
     return torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext()
 
 
+def _stream_handle(stream, tensor) -> int:
+    """hipStream_t of the given stream, or of torch's current stream on the tensor's device.  (The current stream's raw
+    handle: building the torch.cuda.Stream object around it costs 1.7 us, as much as the rest of a small call.)"""
+    return stream.cuda_stream if stream is not None else torch._C._cuda_getCurrentRawStream(tensor.get_device())
+
+
 def hybrid_attn_validate(problem: ha_problem, phi_q=None, phi_k=None) -> int:
     _, pq = _fm_ptr(phi_q)
     _, pk = _fm_ptr(phi_k)
@@ -284,7 +302,7 @@ def hybrid_attn_mfma_probe(random_operands: bool, iters: int, launches: int, sin
     flops = ctypes.c_double(0.0)
     st = _lib().hybrid_attn_mfma_probe(int(bool(random_operands)), iters, launches, sink.data_ptr(),
                                        sink.numel() * sink.element_size(), ctypes.byref(flops),
-                                       torch.cuda.current_stream(sink.device).cuda_stream)
+                                       _stream_handle(None, sink))
     if st != HA_OK:
         raise HybridAttnError(st, "hybrid_attn_mfma_probe")
     return flops.value
@@ -356,7 +374,7 @@ def hybrid_attn_forward(q, k, v, phi_q: Optional[FeatureMap], phi_k: Optional[Fe
     if workspace is None:
         with _alloc_on(stream):
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    stream_handle = (stream if stream is not None else torch.cuda.current_stream(q.device)).cuda_stream
+    stream_handle = _stream_handle(stream, q)
     st = lib.hybrid_attn_forward(ctypes.byref(prob), q.data_ptr(), k.data_ptr(), v.data_ptr(), pq, pk,
                                  out.data_ptr(), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                  stream_handle)
@@ -381,7 +399,7 @@ def hybrid_attn_forward_static(q, k, v, phi_q: Optional[FeatureMap], phi_k: Opti
     prob = make_problem(q, hybrid_rate, block_size, softmax_scale)
     sq, pq = _fm_ptr(phi_q, q)
     sk, pk = _fm_ptr(phi_k, q)
-    stream_handle = (stream if stream is not None else torch.cuda.current_stream(q.device)).cuda_stream
+    stream_handle = _stream_handle(stream, q)
     st = _lib().hybrid_attn_forward_static(ctypes.byref(prob), q.data_ptr(), k.data_ptr(), v.data_ptr(), pq, pk,
                                            out.data_ptr(), stream_handle)
     if st != HA_OK:
@@ -417,7 +435,7 @@ def hybrid_attn_value_distill_loss(q, k, v, phi_q: Optional[FeatureMap], phi_k: 
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
     loss = torch.empty(1 + q.shape[0] * q.shape[1], dtype=torch.float64, device=q.device)
-    stream_handle = (stream if stream is not None else torch.cuda.current_stream(q.device)).cuda_stream
+    stream_handle = _stream_handle(stream, q)
     st = lib.hybrid_attn_value_distill_loss(ctypes.byref(prob), q.data_ptr(), k.data_ptr(), v.data_ptr(), pq, pk,
                                             int(teacher_is_cached), y_teacher.data_ptr(), y_student.data_ptr(),
                                             loss.data_ptr(), workspace.data_ptr(),
@@ -475,7 +493,7 @@ def hybrid_attn_value_distill_grad(q, k, v, phi_q: FeatureMap, phi_k: FeatureMap
 
     gq, cq = grads_of(phi_q)
     gk, ck = grads_of(phi_k)
-    stream_handle = (stream if stream is not None else torch.cuda.current_stream(q.device)).cuda_stream
+    stream_handle = _stream_handle(stream, q)
     st = lib.hybrid_attn_value_distill_grad(ctypes.byref(prob), q.data_ptr(), k.data_ptr(), v.data_ptr(), pq, pk,
                                             int(teacher_is_cached), int(student_is_cached), y_teacher.data_ptr(),
                                             y_student.data_ptr(), row_den.data_ptr(), loss.data_ptr(), ctypes.byref(cq),
@@ -501,7 +519,7 @@ def hybrid_attn_param_update(master, grad, lr: float, kind: int = HA_OPT_SGD, m=
             raise ValueError("param_io must be contiguous and of master's size")
         io_code = _dtype_code(param_io)
     opt = ha_optimizer(kind, step, lr, grad_scale, beta1, beta2, eps, weight_decay)
-    stream_handle = (stream if stream is not None else torch.cuda.current_stream(master.device)).cuda_stream
+    stream_handle = _stream_handle(stream, master)
     st = _lib().hybrid_attn_param_update(ctypes.byref(opt), master.numel(), master.data_ptr(), grad.data_ptr(),
                                          m.data_ptr() if m is not None else None, v.data_ptr() if v is not None else None,
                                          param_io.data_ptr() if param_io is not None else None, io_code, stream_handle)
@@ -526,7 +544,7 @@ def hybrid_attn_linear_state(k, v, phi_k: FeatureMap, hybrid_rate: int, block_si
     B, H, N, d = k.shape
     S = torch.empty(B, H, sk.d_out, d, dtype=torch.float32, device=k.device)
     z = torch.empty(B, H, sk.d_out, dtype=torch.float32, device=k.device)
-    stream_handle = (stream if stream is not None else torch.cuda.current_stream(k.device)).cuda_stream
+    stream_handle = _stream_handle(stream, k)
     st = lib.hybrid_attn_linear_state(ctypes.byref(prob), k.data_ptr(), v.data_ptr(), pk, S.data_ptr(), z.data_ptr(),
                                       workspace.data_ptr(), workspace.numel(), stream_handle)
     if st != HA_OK:
