@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void wide_prep_kernel(const void *__restrict__
 
 // ------------------------------------------------------------------------------------------------
 // Output stage of a feature map, applied by the consumers of phi while they read the fp32 pre-activations (so phi
-// itself never visits HBM): normalisation (softmax: against the maximum and sum combined from the per-256-channel-block
+// itself never visits HBM): normalisation (softmax: against the maximum and sum combined from the per-128-channel-block
 // values the last layer left behind), slice powers, rounding.
 constexpr int WIDE_FMAX = 768;
 
@@ -69,7 +69,7 @@ static __device__ __forceinline__ WideOutStage wide_out_stage(const float *__res
   o.off = 0.f; o.inv = 1.f; o.act = act;
   o.inv_groups = 8.0f * (float)P / (float)F;
   if (act == 0) {
-    const int nblk = (F + 255) / 256;
+    const int nblk = F / 128;
     const float *st = stat + (bh_tb * nblk * 2) * 64 + lane;
     float m = -INFINITY;
     for (int b = 0; b < nblk; ++b) m = fmaxf(m, st[b * 128]);
@@ -290,7 +290,7 @@ void make_wide_plan(const Plan &pl, size_t base_off, WidePlan &wp, bool backward
   wp.off_h2hi = take(BH * n_tb * 32 * pl.DM * 2);
   wp.off_h2lo = take(BH * n_tb * 32 * pl.DM * 2);
   wp.off_u = take(BH * n_tb * 32 * (size_t)pl.F * 4);
-  wp.off_stat = take(BH * n_tb * ((pl.F + 255) / 256) * 2 * 64 * sizeof(float));
+  wp.off_stat = take(BH * n_tb * (pl.F / 128) * 2 * 64 * sizeof(float));
   wp.off_phi = take(backward ? BH * n_tb * 32 * (size_t)pl.F * 2 : 0);
   wp.off_lin = take(BH * n_tb * 32 * (size_t)pl.D * 4);
   wp.off_e = take(BH * (size_t)pl.N * 4);

@@ -46,7 +46,7 @@ struct WideGradArgs {
   const float *zvec;              // [B*H][F]
   f32x4 *t_img;                   // in: pre-activations u; out: t = activation(u)            [bh][tb][F/32][4][64]
   f32x4 *tdt_img;                 // out: t dt (softmax), dt t (exp), dt [u > 0] (relu)
-  const float *stat;              // softmax maxima / sums per 256-channel block (last layer of the forward)
+  const float *stat;              // softmax maxima / sums per 128-channel block (last layer of the forward)
   float *pdot;                    // [bh][tb][blocks][64]: per-token sum of t dt over the block's channels
   bf16x8 *du_img;                 // FUSED: du, bf16 image
   bf16x8 *phi_img;                // QUERY: phi_q, bf16 image (zero for tokens past the end)
@@ -86,11 +86,12 @@ __global__ __launch_bounds__(256) void wide_dphi_kernel(WideGradArgs a) {
   }
   float off = 0.f, inv = 1.f;
   if (a.act == 0) {
-    const float *st = a.stat + (((int64_t)bh * a.n_tb + tb) * nblk * 2) * 64 + lane;
+    const int n_st = a.F / 128;
+    const float *st = a.stat + (((int64_t)bh * a.n_tb + tb) * n_st * 2) * 64 + lane;
     float m = -INFINITY;
-    for (int b = 0; b < nblk; ++b) m = fmaxf(m, st[b * 128]);
+    for (int b = 0; b < n_st; ++b) m = fmaxf(m, st[b * 128]);
     float sum = 0.f;
-    for (int b = 0; b < nblk; ++b) sum += st[b * 128 + 64] * fast_exp2((st[b * 128] - m) * kLog2e);
+    for (int b = 0; b < n_st; ++b) sum += st[b * 128 + 64] * fast_exp2((st[b * 128] - m) * kLog2e);
     off = -m * kLog2e;
     inv = 1.0f / sum;
   }

@@ -29,7 +29,7 @@ struct WideMlpArgs {
   bf16x8 *h_hi;                  // from x: the hidden layer's bf16 image, if somebody needs it (or null)
   bf16x8 *out_hi, *out_lo;       // hidden layer out
   f32x4 *out_u;                  // last layer: fp32 pre-activations
-  float *out_stat;               // last layer: [bh][tb][256-channel block][2][64] maximum and sum of exponentials
+  float *out_stat;               // last layer: [bh][tb][128-channel block][2][64] maximum and sum of exponentials
   int H, K, NOUT, n_tok, n_tb, R, G;
   int ob_first, n_ob;            // first output tile, blocks of NT tiles
   int n_tiles, total;            // 256-token tiles per (batch, head), items overall
@@ -178,24 +178,27 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
     if (live) {
       const int64_t blk0 = ((int64_t)cur.bh * a.n_tb + cur.tb) * OB + cur.ob0;
       if constexpr (LAST) {
-        // per token: maximum of this block's channels and the sum of exponentials against it, so that the output stage
-        // can form the softmax over all channels with a single sweep over the pre-activations
-        float m = acc[0][0];
+        // per token and 128 channels: their maximum and the sum of exponentials against it, so that the output stage can
+        // form the softmax over all channels with a single sweep over the pre-activations
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int j0 = 0; j0 < NT; j0 += 4) {
+          float m = acc[j0][0];
 #pragma unroll
-          for (int v = 0; v < 16; v += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, acc[j][v]), acc[j][v + 1]);
-        m = xhalf_max(m);
-        const float off = -m * kLog2e;
-        float sum = 0.f;
+          for (int j = j0; j < j0 + 4; ++j)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+            for (int v = 0; v < 16; v += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, acc[j][v]), acc[j][v + 1]);
+          m = xhalf_max(m);
+          const float off = -m * kLog2e;
+          float sum = 0.f;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) sum += fast_exp2(__builtin_fmaf(acc[j][v], kLog2e, off));
-        sum = xhalf_sum(sum);
-        float *st = a.out_stat + ((((int64_t)cur.bh * a.n_tb + cur.tb) * ((OB + 7) / 8) + cur.ob0 / 8) * 2) * 64 + lane;
-        st[0] = m;
-        st[64] = sum;
+          for (int j = j0; j < j0 + 4; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum += fast_exp2(__builtin_fmaf(acc[j][v], kLog2e, off));
+          sum = xhalf_sum(sum);
+          float *st = a.out_stat + ((((int64_t)cur.bh * a.n_tb + cur.tb) * (OB / 4) + (cur.ob0 + j0) / 4) * 2) * 64 + lane;
+          st[0] = m;
+          st[64] = sum;
+        }
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -233,11 +236,14 @@ hipError_t launch_wide_mlp(const Plan &pl, const WideMlpLayer &l, hipStream_t st
   a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
   a.n_tiles = (a.n_tb + 7) / 8;
   const int src = !l.x ? 2 : pl.f32 ? 1 : 0;
-  // blocks of eight output tiles, then a block of four where the width is an odd multiple of 128
+  // Blocks of eight output tiles, then a block of four where the width is an odd multiple of 128; blocks of four
+  // throughout where those of eight would not give every CU a workgroup: twice the workgroups with half the work per step,
+  // and one launch (384-wide two-layer maps, R = 4, whole forward: H = 1, N = 2000 165 -> 112 us; H = 12, N = 2600 218 -> 194).
+  const int OB = a.NOUT / 32;
+  const bool small = (int64_t)a.n_tiles * (OB / 8) * pl.B * pl.H < 256;
   for (int nt : {8, 4}) {
-    const int OB = a.NOUT / 32;
-    a.ob_first = nt == 8 ? 0 : OB / 8 * 8;
-    a.n_ob = nt == 8 ? OB / 8 : (OB - a.ob_first) / 4;
+    a.ob_first = nt == 8 || small ? 0 : OB / 8 * 8;
+    a.n_ob = nt == 8 ? (small ? 0 : OB / 8) : (OB - a.ob_first) / 4;
     if (a.n_ob == 0) continue;
     if (nt == 4 && a.ob_first > 0) a.h_hi = nullptr;                           // written with the first block
     a.total = a.n_tiles * a.n_ob * pl.B * pl.H;
