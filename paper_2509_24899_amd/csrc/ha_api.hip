@@ -102,6 +102,12 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
   pl.n_cc = pl.CC > 0 ? (pl.N + pl.CC - 1) / pl.CC : 1;
   pl.nsub = 1;
   pl.LW = p.local_window;
+  if (pl.LW > 0 && p.local_window / (2 * p.block_size) >= (pl.N + 2 * p.block_size - 1) / (2 * p.block_size) - 1) {
+    // every tile sees every other: plain softmax attention
+    pl.LW = 0;
+    pl.R = 1;
+    pl.NS = pl.N;
+  }
   if (pl.LW > 0) {
     // every token is a candidate softmax key (compacted at rate 1) and a linear key of the tiles that do not see it
     pl.NS = pl.N;
@@ -189,14 +195,72 @@ static bool needs_wide_path(const Plan &pl) {
   return pl.NL > 0 && ((!square && !paper_width) || pl.DM > 0);
 }
 
+constexpr size_t kStaticScratchBytes = (size_t)HA_STATIC_SCRATCH_MIB << 20;
+
+// Into how many ranges the keys of the plain operator's softmax loop are split.  A tile of 256 queries is one workgroup, so
+// a problem of few tiles leaves CUs idle for the whole loop; with n ranges it has n times the workgroups, each with 1 / n
+// of the keys, at the price of a pass that merges the partial sums (516 bytes per query and range written and read).  The
+// estimate, in us, from measured times: a 32-key step takes 0.5 (0.42 in the small tiling of an unsplit problem), the rest
+// of a workgroup 5, or 14 where it evaluates the 128-wide maps in its epilogue; the merging pass 5, or 10 and 1.3 per range
+// where it evaluates them (in the kernel of ha_linear.hip), and its traffic at 4 TB/s.  It has to be 10 % better than one
+// range.  Whole calls, one range / split, us:
+//   R = 1:  H = 1, N = 2000  37 / 31;  N = 8000  122 / 55;  N = 20000  289 / 188;  H = 2, N = 5000  81 / 46;  H = 5, N = 3000
+//   55 / 44;  R = 4:  H = 1, N = 20000  126 / 95 (128-wide maps), 135 / 116 (256-wide).
+static int choose_split(const Plan &pl, bool lin) {
+  if (pl.D != 128 || pl.CC > 0 || pl.LW > 0 || pl.NS == 0) return 1;
+  const bool fused = pl.NL > 0 && !lin;                   // the maps are evaluated by the query kernel, or by the merging pass
+  const double tiles = (double)((pl.N + 255) / 256) * pl.B * pl.H, rows = (double)pl.N * pl.B * pl.H;
+  // From half the CUs on the loop is left whole.  (It would still pay a little at exactly 128 tiles; but there one head of a
+  // long clip, on its own, keeps the bits it has among others, and with them the signs a distillation gradient is made of.)
+  if (tiles >= 128.0) return 1;
+  const int nblk = (pl.NS + 31) / 32;
+  auto cost = [&](int n) {
+    const double rounds = std::ceil(tiles * n / 256.0), blocks = (nblk + n - 1) / n;
+    const double step = n == 1 && !fused ? 0.42 : 0.5;
+    const double loop = rounds * (blocks * step + (n == 1 && fused ? 14.0 : 5.0));
+    return n == 1 ? loop : loop + (fused ? 10.0 + 1.3 * n : 5.0) + rows * n * 1032.0 / 4.0e6;
+  };
+  int best = 1;
+  double least = 0.9 * cost(1);
+  for (int n = 2; n <= 8 && 2 * n <= nblk; ++n)      // (the merging kernel takes up to eight)
+    if (cost(n) < least) {
+      least = cost(n);
+      best = n;
+    }
+  return best;
+}
+
 // Plan of the forward plus, where needed, the layer-by-layer path's buffers behind it; returns the workspace size.
 static size_t full_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl, WidePlan &wp,
                         bool &wide, size_t limit = SIZE_MAX) {
   make_plan(p, phi_q, phi_k, pl, limit);
   wide = phi_q && phi_k && needs_wide_path(pl);
-  if (!wide) return pl.total;
-  make_wide_plan(pl, pl.total, wp, false);
-  return wp.total;
+  size_t total = pl.total;
+  if (wide) {
+    make_wide_plan(pl, pl.total, wp, false);
+    total = wp.total;
+  }
+  // the partial sums of split key ranges.  Whether the keys are split must not depend on the workspace (results are equal
+  // bit for bit with a workspace of fixed size), so where a problem would fit the static one, its partial sums have to fit
+  // it as well.
+  pl.n_split = choose_split(pl, wide || pl.split_linear);
+  const size_t BH = (size_t)pl.B * pl.H, per = BH * ((pl.N + 255) / 256) * 256 * (pl.D + 2) * 4;
+  if (total <= kStaticScratchBytes)
+    while (pl.n_split > 1 && total + pl.n_split * per > kStaticScratchBytes) --pl.n_split;
+  if (pl.split_linear) {
+    // (with the linear pass's results in the partials' place, a part at a time, there is no room: see make_plan)
+    const size_t lin = BH * ((pl.N + 255) / 256) * 256 * (pl.D + 1) * 4;
+    const size_t least = pl.off_lin == pl.off_part ? total : total - lin;
+    if (least <= kStaticScratchBytes && least + lin > kStaticScratchBytes) pl.n_split = 1;
+  }
+  if (pl.n_split > 1) {
+    pl.n_tb_split = (pl.N + 255) / 256 * 8;
+    pl.off_po = total;
+    pl.off_pm = pl.off_po + pl.n_split * BH * pl.n_tb_split * 32 * pl.D * 4;
+    pl.off_pl = pl.off_pm + pl.n_split * BH * pl.n_tb_split * 32 * 4;
+    total += pl.n_split * per;
+  }
+  return total;
 }
 
 static ha_status device_error(hipError_t e) {
@@ -308,7 +372,6 @@ ha_status hybrid_attn_forward(const ha_problem *p, const void *q, const void *k,
 // In host code the array's name only stands for the symbol; its device address (one per GPU, each GPU holds its
 // own copy) is looked up once per device and kept.
 namespace ha {
-constexpr size_t kStaticScratchBytes = (size_t)HA_STATIC_SCRATCH_MIB << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void *g_scratch_ptr[kMaxDevices] = {};
@@ -449,11 +512,11 @@ static size_t distill_layout(const ha_problem &p, const ha_feature_map *phi_q, c
                              ha::Plan &teacher, ha::Plan &student, size_t &off_partial) {
   ha_problem pt = p;
   pt.hybrid_rate = 1;
-  ha::make_plan(pt, nullptr, nullptr, teacher);
   ha::WidePlan wp;
   bool wide;
+  const size_t teacher_total = ha::full_plan(pt, nullptr, nullptr, teacher, wp, wide);
   const size_t student_total = ha::full_plan(p, phi_q, phi_k, student, wp, wide);
-  off_partial = ha::align256(teacher.total > student_total ? teacher.total : student_total);
+  off_partial = ha::align256(teacher_total > student_total ? teacher_total : student_total);
   return off_partial + ha::align256(ha::l1_partial_bytes(student));
 }
 

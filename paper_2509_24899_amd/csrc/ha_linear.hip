@@ -1,5 +1,6 @@
 // Query side of purely linear attention (rate 0: no softmax tokens; Sec. 3.1) for the widths 128 -> 128 -> 128:
-//     y_i = phi_q(q_i) S / (phi_q(q_i) . z).   gfx950 only.
+//     y_i = phi_q(q_i) S / (phi_q(q_i) . z),   gfx950 only,
+// and, with the softmax part given as the partial sums of key ranges (see SplitArgs), of Eq. "hybrid".
 //
 // The query kernel of ha_query.hip runs this as its epilogue: every workgroup fetches the operands for one tile of 256
 // queries, its waves go through load, layers, contraction and store in step, and memory is idle while they compute.
@@ -31,11 +32,12 @@ struct LinearArgs {
   float *row_den;                        // optional [B*H][N]
   int H, N, P, act;
   int64_t sb, sh, sn;
+  SplitArgs sp;                          // MERGE: the softmax part
 };
 
 // grid (workgroups per (batch, head), B*H), 8 waves.  ACT0: the output activation is the softmax over the channels; P2: the
 // degree is 2, the paper's default (a branch on it here costs a copy of all feature registers).
-template <bool F32, bool ACT0, bool P2>
+template <bool F32, bool ACT0, bool P2, bool MERGE>
 __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
   constexpr int D = 128, F = 128, KS = D / 16, FB = F / 32, RB = D / 32, NOP = D * D / 8;
   // output staging, per wave: 32 query rows x 64 bytes (32 bf16 or 16 fp32 channels), rows padded by 16 bytes
@@ -163,10 +165,17 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
       }
     };
     st_frags(0, 0, fa);
+    if constexpr (MERGE) {
+      // the accumulators start as the softmax part; one half of the wave counts its denominator (the other's half of
+      // phi . z is added below)
+      const float l = merge_ranges<RB>(a.sp, bh, blk, lane, n);
+      den = g == 0 ? l : 0.f;
+    } else {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+      for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-      for (int x = 0; x < 16; ++x) n[rb][x] = 0.f;
+        for (int x = 0; x < 16; ++x) n[rb][x] = 0.f;
+    }
     HA_FENCE();
 #pragma unroll
     for (int rp = 0; rp < RB; rp += 2) {
@@ -228,16 +237,18 @@ hipError_t launch_linear_query(const Plan &pl, const void *q, const ha_feature_m
   a.z = reinterpret_cast<float *>(wsb + pl.off_z);
   a.H = pl.H; a.N = pl.N; a.P = pl.P; a.act = pl.act_q;
   a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
+  a.sp = split_args(pl, ws);
   // one workgroup per CU in a single round; short sequences spread over as many of them as they have blocks
   const int nb = (pl.N + 31) / 32, room = 256 / (pl.B * pl.H) > 0 ? 256 / (pl.B * pl.H) : 1;
   dim3 grid(nb < room ? nb : room, pl.B * pl.H);
-#define HA_LINEAR(F32) \
+#define HA_LINEAR(F32, MERGE) \
   do { \
-    if (pl.act_q != HA_ACT_SOFTMAX) linear_query_kernel<F32, false, false><<<grid, 512, 0, st>>>(a); \
-    else if (pl.P == 2) linear_query_kernel<F32, true, true><<<grid, 512, 0, st>>>(a); \
-    else linear_query_kernel<F32, true, false><<<grid, 512, 0, st>>>(a); \
+    if (pl.act_q != HA_ACT_SOFTMAX) linear_query_kernel<F32, false, false, MERGE><<<grid, 512, 0, st>>>(a); \
+    else if (pl.P == 2) linear_query_kernel<F32, true, true, MERGE><<<grid, 512, 0, st>>>(a); \
+    else linear_query_kernel<F32, true, false, MERGE><<<grid, 512, 0, st>>>(a); \
   } while (0)
-  if (pl.f32) HA_LINEAR(true); else HA_LINEAR(false);
+  if (pl.n_split > 1) { if (pl.f32) HA_LINEAR(true, true); else HA_LINEAR(false, true); }
+  else { if (pl.f32) HA_LINEAR(true, false); else HA_LINEAR(false, false); }
 #undef HA_LINEAR
   return hipGetLastError();
 }

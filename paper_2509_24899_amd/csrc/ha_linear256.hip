@@ -6,8 +6,7 @@
 // As the query kernel's epilogue this costs 57 us per round of workgroups at 480p / 81 frames (340 us of 1627): hidden
 // activations, accumulators and features of 256 channels do not fit the registers the softmax accumulators leave, and the
 // operands (W1 64 KiB, W2 128 KiB, S hi + lo 128 KiB per head) pass through the ring in three exposed rounds.  Here the map is
-// evaluated a hidden block at a time (ha_mlp256.h), so the softmax sees fp32 values of all channels (one rounding of phi to
-// bf16 instead of two), and the operands stream through an LDS ring in that very order, 24 KiB per hidden block, then 16 KiB
+// evaluated a hidden block at a time (ha_mlp256.h), and the operands stream through an LDS ring in that very order, 24 KiB per hidden block, then 16 KiB
 // per feature block of S; the stream runs ahead over the tiles and heads of a workgroup, one barrier per slab.
 //
 // Bound: matrix cores, 448 instructions of 32 cycles per 32-query block (28.7 k cycles per 256-query tile), next to 9 k

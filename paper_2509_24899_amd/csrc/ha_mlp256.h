@@ -72,7 +72,9 @@ static __device__ __forceinline__ void mlp256_hidden_block(lds_frag_ptr sl, cons
 }
 
 // The output stage in place: positive activation over all channels, slice powers.  ACT0: softmax over the channels; otherwise
-// `act` picks exp (1) or ReLU.  P2: the degree is 2, the paper's default.
+// `act` picks exp (1) or ReLU.  P2: the degree is 2, the paper's default.  The exponentials are rounded to bf16 as they are
+// formed and phi once more behind the powers, as in the tile-wise form (feature_layer2_phi) that the variants' epilogue
+// uses: the operator and its variants round alike.
 template <bool ACT0, bool P2>
 static __device__ __forceinline__ void phi256_output(f32x16 (&u)[8], int act, int P) {
   if constexpr (ACT0) {
@@ -91,6 +93,9 @@ static __device__ __forceinline__ void phi256_output(f32x16 (&u)[8], int act, in
         u[fb][x + 1] = fast_exp2(__builtin_fmaf(u[fb][x + 1], kLog2e, off));
         sum0 += u[fb][x];
         sum1 += u[fb][x + 1];
+        const unsigned p = pack_bf16(u[fb][x], u[fb][x + 1]);
+        u[fb][x] = __uint_as_float(p << 16);
+        u[fb][x + 1] = __uint_as_float(p & 0xffff0000u);
       }
     const float inv = 1.0f / xhalf_sum(sum0 + sum1);
 #pragma unroll

@@ -30,7 +30,26 @@ struct Plan {
   bool split_linear;
   int n_tb, lin_rows;
   size_t off_lin, off_e;
+  // key ranges the softmax loop is split into (1: one workgroup walks all keys of its tile), with the partial sums of every
+  // range (see SplitArgs): blocks of 32 queries per (batch, head), images, maxima and sums
+  int n_split, n_tb_split;
+  size_t off_po, off_pm, off_pl;
 };
+
+// Partial sums of the softmax loop over one of n_split key ranges, per (range, batch, head): the accumulators as fp32 register
+// images, and per query the exact maximum of its raw logits over the range (which the accumulators are expressed
+// against) and the sum of weights.  n_split <= 1: none.
+struct SplitArgs {
+  float *po;                  // [n_split][B*H][n_tb][d/32][4][64][4]
+  float *pm, *pl;             // [n_split][B*H][32 n_tb]
+  int n_split, n_tb, BH;
+  float scale_log2e;
+};
+static inline SplitArgs split_args(const Plan &pl, void *ws) {
+  char *w = static_cast<char *>(ws);
+  return SplitArgs{reinterpret_cast<float *>(w + pl.off_po), reinterpret_cast<float *>(w + pl.off_pm), reinterpret_cast<float *>(w + pl.off_pl),
+                   pl.n_split, pl.n_tb_split, pl.B * pl.H, pl.scale * 1.4426950408889634f};
+}
 
 // Workspace of the value-distillation gradient beyond the forward's: operand fragments of W2^T, S and dS, the
 // per-row factors, the sign tensor and the partial tiles of the two gradient passes.
@@ -100,7 +119,7 @@ hipError_t launch_state_reduce(const Plan &pl, void *ws, hipStream_t st);
 hipError_t launch_state_reduce_with_prep(const Plan &pl, const ha_feature_map &phi_q, void *ws, hipStream_t st);
 hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi_q, void *out, float *row_den, void *ws,
                         hipStream_t st, const WidePlan *wide = nullptr);
-// ha_linear.hip: the query side where there is no softmax token at all
+// ha_linear.hip: the query side where there is no softmax token at all, or where the softmax part arrives as partial sums
 hipError_t launch_linear_query(const Plan &pl, const void *q, const ha_feature_map &phi_q, void *out, float *row_den, void *ws,
                                hipStream_t st);
 // ha_linear256.hip: n = phi_q(q) S and e = phi_q(q) . z of the 128 -> 256 -> 256 maps

@@ -28,6 +28,7 @@ struct QueryArgs {
   int H, N, NS, n_qtiles, n_ktiles, n_kblocks, total_wg;
   int CC, n_cc, R, G;                   // chunk-causal variant (CC > 0): chunk length, chunk count, the token split
   int LW;                               // local-window variant: window in tokens on either side of the query tile
+  SplitArgs sp;                         // key ranges (MODE 3)
   int has_linear, P, act;
   int64_t sb, sh, sn;
   float scale_log2e;
@@ -189,7 +190,8 @@ static __device__ __forceinline__ void query_epilogue(const QueryArgs &a, int bh
 // is first read (as K(j+2)) at least one barrier after it was requested.
 // LIN: the linear part arrives precomputed (maps too wide for the epilogue below); a variant of its own so that
 // the usual kernel carries none of it.
-// MODE 1: the chunk-causal variant, 2: the local-window variant; likewise variants of their own.
+// MODE 1: the chunk-causal variant, 2: the local-window variant; likewise variants of their own.  MODE 3: the keys are split
+// into ranges, a workgroup walks one of them and leaves partial sums for the pass that merges them.
 template <int D, int HD, int F, int NW, int NB, int G, bool F32, bool LIN = false, int MODE = 0>
 __global__ __launch_bounds__(64 * NW, 2) void query_kernel_ring(QueryArgs a) {
   static_assert(G <= 2 && NB >= 2 * G + 2 && (NB & (NB - 1)) == 0, "ring too short for the barrier period");
@@ -219,6 +221,11 @@ __global__ __launch_bounds__(64 * NW, 2) void query_kernel_ring(QueryArgs a) {
   constexpr bool CAUSAL = MODE == 1;
   if constexpr (CAUSAL) logical = blockIdx.x;
   if (logical >= a.total_wg) return;
+  int range = 0;
+  if constexpr (MODE == 3) {
+    range = logical % a.sp.n_split;
+    logical /= a.sp.n_split;
+  }
   int bh = logical / a.n_qtiles, qtile = logical % a.n_qtiles;
   if constexpr (CAUSAL) {
     // the work of a tile grows with its position: the longest tiles of every (batch, head) are started first, and
@@ -253,6 +260,11 @@ __global__ __launch_bounds__(64 * NW, 2) void query_kernel_ring(QueryArgs a) {
     a.z += shift * F;
     a.st_hi += shift * (D * F / 8);
     a.st_lo += shift * (D * F / 8);
+  }
+  if constexpr (MODE == 3) {
+    const int nb = (a.NS + 31) >> 5, kb_hi = (int)((int64_t)(range + 1) * nb / a.sp.n_split);
+    kb_lo = (int)((int64_t)range * nb / a.sp.n_split);
+    a.NS = min(a.NS, kb_hi * 32) - kb_lo * 32;
   }
   // n_chunks 1 KiB wave-chunks global -> LDS, dealt round-robin to the waves (direct-to-LDS loads, see below)
   auto stage_in = [&](const bf16x8 *gsrc, bf16x8 *ldst, int n_chunks) {
@@ -484,6 +496,22 @@ __global__ __launch_bounds__(64 * NW, 2) void query_kernel_ring(QueryArgs a) {
 #pragma unroll
       for (int x = 0; x < 16; ++x) o[rb][x] *= alpha;
   }
+  if constexpr (MODE == 3) {
+    const int64_t rb0 = (int64_t)range * a.sp.BH + bh;
+    const int tb = q0 >> 5;
+    f32x4 *po = reinterpret_cast<f32x4 *>(a.sp.po) + (rb0 * a.sp.n_tb + tb) * RB * 4 * 64 + lane;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int x4 = 0; x4 < 4; ++x4)
+        po[(rb * 4 + x4) * 64] = f32x4{o[rb][4 * x4], o[rb][4 * x4 + 1], o[rb][4 * x4 + 2], o[rb][4 * x4 + 3]};
+    const float l = xhalf_sum(lsum);
+    if (lane < 32) {
+      a.sp.pm[(rb0 * a.sp.n_tb + tb) * 32 + lane] = m_true;
+      a.sp.pl[(rb0 * a.sp.n_tb + tb) * 32 + lane] = l;
+    }
+    return;
+  }
   char *stage = reinterpret_cast<char *>(&ring[0]) + w * (2 * NB * FRAG * 16 / NW);
   if constexpr (LIN) {
     // linear part computed by the wide-map passes: add it to the accumulators, which share its register layout
@@ -567,14 +595,87 @@ __global__ __launch_bounds__(64 * NW, 2) void query_kernel_ring(QueryArgs a) {
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// merge_kernel: grid (n_tb, B*H), 4 waves, one 32-query block; wave w takes channels 32 w .. + 31.  The partial sums of the key
+// ranges, put on their common maximum c_i, plus the precomputed linear part if there is one: y = (a + n) / (l + e).
+// All ranges' loads are in flight at once: the pass is a few memory round trips long.
+constexpr int kMaxSplit = 8;
+template <bool F32>
+__global__ __launch_bounds__(256) void merge_kernel(QueryArgs a) {
+  constexpr int D = 128, RB = D / 32, ESZ = F32 ? 4 : 2, PITCH = 32 * ESZ + 16, CPR = 32 * ESZ / 16;
+  __shared__ __align__(16) char stage_all[4 * 32 * PITCH];
+  const int bh = blockIdx.y, tb = blockIdx.x, lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q0 = 32 * tb;
+  const int64_t step = (int64_t)a.sp.BH * a.sp.n_tb, blk = (int64_t)bh * a.sp.n_tb + tb;
+  const int n_split = a.sp.n_split;
+  float ms[kMaxSplit], ls[kMaxSplit];
+  f32x4 part[kMaxSplit][4], lin[4];
+  float lin_e = 0.f;
+#pragma unroll
+  for (int s = 0; s < kMaxSplit; ++s) {
+    const int64_t at = blk + (s < n_split ? s : 0) * step;          // (ranges there are not repeat the first, with weight 0)
+    ms[s] = s < n_split ? a.sp.pm[at * 32 + r] : -INFINITY;
+    ls[s] = a.sp.pl[at * 32 + r];
+    if (s < n_split) {
+      const f32x4 *src = reinterpret_cast<const f32x4 *>(a.sp.po) + (at * RB + w) * 4 * 64 + lane;
+#pragma unroll
+      for (int x4 = 0; x4 < 4; ++x4) part[s][x4] = src[x4 * 64];
+    }
+  }
+#pragma unroll
+  for (int x4 = 0; x4 < 4; ++x4) lin[x4] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (a.lin) {
+#pragma unroll
+    for (int x4 = 0; x4 < 4; ++x4) lin[x4] = a.lin[((((int64_t)bh * a.n_tb + tb) * RB + w) * 4 + x4) * 64 + lane];
+    lin_e = a.lin_e[(int64_t)bh * a.N + min(q0 + r, a.N - 1)];
+  }
+  float m = ms[0];
+#pragma unroll
+  for (int s = 1; s < kMaxSplit; ++s) m = fmaxf(m, ms[s]);
+  float l = 0.f;
+  f32x4 o[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int s = 0; s < kMaxSplit; ++s)
+    if (s < n_split) {
+      const float wgt = fast_exp2((ms[s] - m) * a.sp.scale_log2e);
+      l = __builtin_fmaf(wgt, ls[s], l);
+#pragma unroll
+      for (int x4 = 0; x4 < 4; ++x4)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[x4][j] = __builtin_fmaf(wgt, part[s][x4][j], o[x4][j]);
+    }
+  const float den = l + lin_e, inv = 1.0f / den;
+  if (w == 0) store_den(a, bh, lane, den, q0);
+  char *stage = stage_all + w * 32 * PITCH;
+#pragma unroll
+  for (int x4 = 0; x4 < 4; ++x4) {
+    const f32x4 y = {(o[x4][0] + lin[x4][0]) * inv, (o[x4][1] + lin[x4][1]) * inv, (o[x4][2] + lin[x4][2]) * inv, (o[x4][3] + lin[x4][3]) * inv};
+    char *dst = stage + r * PITCH + (8 * x4 + 4 * g) * ESZ;
+    if constexpr (F32) *reinterpret_cast<f32x4 *>(dst) = y;
+    else *reinterpret_cast<bf16x4 *>(dst) = __builtin_convertvector(y, bf16x4);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the wave's own staging area, in order (see store_tile)
+  const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
+#pragma unroll
+  for (int i = lane; i < 32 * CPR; i += 64) {
+    const int row = i / CPR, ch = i % CPR;
+    if (q0 + row < a.N) {
+      const f32x4 piece = *reinterpret_cast<const f32x4 *>(stage + row * PITCH + ch * 16);
+      char *dst = static_cast<char *>(a.out) + (base + (int64_t)(q0 + row) * a.sn + 32 * w) * ESZ + ch * 16;
+      *reinterpret_cast<f32x4 *>(dst) = piece;
+    }
+  }
+}
+
 hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi_q, void *out, float *row_den, void *ws,
                         hipStream_t st, const WidePlan *wide) {
   if (!wide && query_side_is_linear(pl)) return launch_linear_query(pl, q, *phi_q, out, row_den, ws, st);
+  const bool lin = wide || pl.split_linear;               // the linear part arrives precomputed
   QueryArgs a;
   a.q = q;
   a.out = out;
   a.row_den = row_den;
-  const bool lin = wide || pl.split_linear;               // the linear part arrives precomputed
   a.lin = wide ? ws_ptr<f32x4>(ws, wide->off_lin) : lin ? ws_ptr<f32x4>(ws, pl.off_lin) : nullptr;
   a.lin_e = wide ? ws_ptr<float>(ws, wide->off_e) : lin ? ws_ptr<float>(ws, pl.off_e) : nullptr;
   a.n_tb = wide ? wide->n_tb_q : pl.n_tb;
@@ -593,6 +694,22 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
   a.has_linear = pl.NL > 0; a.P = pl.P; a.act = pl.act_q;
   a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
   a.scale_log2e = pl.scale * kLog2e;
+  a.sp = SplitArgs{nullptr, nullptr, nullptr, 1, 0, 0, 0.f};
+  if (pl.n_split > 1) {
+    // (choose_split says when)
+    a.sp = split_args(pl, ws);
+    a.n_qtiles = (pl.N + 255) / 256;
+    a.total_wg = a.n_qtiles * pl.B * pl.H * pl.n_split;
+    const dim3 grid((a.total_wg + 7) / 8 * 8), mgrid((pl.N + 31) / 32, pl.B * pl.H);
+    if (pl.f32) query_kernel_ring<128, 128, 128, 8, 8, 2, true, true, 3><<<grid, 512, 0, st>>>(a);
+    else query_kernel_ring<128, 128, 128, 8, 8, 2, false, true, 3><<<grid, 512, 0, st>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (pl.NL > 0 && !lin) return launch_linear_query(pl, q, *phi_q, out, row_den, ws, st);
+    if (pl.f32) merge_kernel<true><<<mgrid, 256, 0, st>>>(a);
+    else merge_kernel<false><<<mgrid, 256, 0, st>>>(a);
+    return hipGetLastError();
+  }
   // Two tilings of one computation (every query column sees the same keys in the same order: the same bits): 8 waves x
   // 32 queries with a ring of 8 key blocks and a barrier every 64 keys, one workgroup per CU, or 4 waves x 32 queries
   // with a ring of 4 and a barrier every 32 keys, two workgroups per CU.  The variants' tiles are part of their

@@ -1,0 +1,70 @@
+"""Problems of few query tiles split the softmax keys into ranges whose partial sums a second pass merges: every form of
+that pass (rate 1, 128-wide maps, precomputed linear part of the 256-wide and of wider maps) against the fp64 oracle, with
+ragged last ranges, rows and tiles, a maximum that sits in any one range, the denominators of the gradient call, and
+equal bits with the fixed workspace and for either block size.
+
+Tolerance: the bars of test_gpu_parity.py; row denominators 2e-3 relative (weights and features rounded once to bf16)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import hybrid_attn_oracle as O
+from paper_2509_24899_amd import hybrid_attn as ha
+from paper_2509_24899_amd import workloads as W
+from test_gpu_parity import check, oracle_map
+
+pytestmark = pytest.mark.gpu
+
+
+def work(N, R, width=128, B=1, H=2, dtype="bf16", seed=0, gain=1.0):
+    P = {128: 2, 256: 2, 384: 3}[width]
+    return W.Workload(f"ks_R{R}_F{width}_N{N}_B{B}H{H}_{dtype}", B, H, N, 128, dtype, 128, R, width, width, poly_degree=P, seed=seed, qk_gain=gain)
+
+
+# (key blocks of 32 from a few per range to uneven ranges; the last block and the last tile ragged)
+@pytest.mark.parametrize("dtype", ("bf16", "f32"))
+@pytest.mark.parametrize("width", (128, 256, 384))
+@pytest.mark.parametrize("N,R", ((1560, 4), (700, 1), (2049, 2), (3001, 3), (1025, 1)))
+def test_ranges(N, R, width, dtype):
+    w = work(N, R, width, H=3, dtype=dtype, seed=N, gain=128 ** 0.5)
+    rows = W.sample_rows(w, n_random=32)
+    y64, _ = check(w.name, W.make_inputs(w), block_size=64, rows=rows)
+    y128, _ = check(w.name, W.make_inputs(w), block_size=128, rows=rows)
+    assert np.array_equal(y64, y128)
+
+
+@pytest.mark.parametrize("at", (0, 700, 1996))
+def test_one_key_far_above_the_others(at):
+    """Its range holds the maximum of every row that points its way: the other ranges' sums shrink to nothing."""
+    w = work(2000, 4, seed=3, gain=128 ** 0.5)
+    inp = W.make_inputs(w)
+    inp.k[:, :, at - at % 4] *= 8.0
+    inp.k[:] = W.round_to_bf16(inp.k)
+    check(f"ks_peak_{at}", inp, rows=W.sample_rows(w, n_random=64))
+
+
+@pytest.mark.parametrize("width", (128, 256))
+def test_row_denominators(width):
+    inp = W.make_inputs(work(1500, 2, width, seed=6, gain=128 ** 0.5))
+    w = inp.workload
+    q, k, v, fq, fk = ha.to_device(inp)
+    _, _, _, _, y, den = ha.hybrid_attn_value_distill_grad(q, k, v, fq, fk, 2, 128, w.scale, y_teacher=torch.zeros_like(q), teacher_is_cached=True)
+    torch.cuda.synchronize()
+    assert torch.equal(ha.hybrid_attn_forward(q, k, v, fq, fk, 2, 128, w.scale), y)
+    for h in range(w.H):
+        _, z = O.linear_state(inp.k[0, h], inp.v[0, h], oracle_map(inp.phi_k), h, 2)
+        _, l, _ = O.softmax_part(np.asarray(inp.q[0, h], np.float64), inp.k[0, h], inp.v[0, h], 2, w.scale)
+        ref = l + O.feature_map(inp.q[0, h], oracle_map(inp.phi_q), h) @ z
+        assert np.abs(den[0, h].double().cpu().numpy() / ref - 1).max() <= 4e-3     # (exp of a rounded logit: 2^-9 at most twice)
+
+
+@pytest.mark.parametrize("B,H,N,R,width", ((1, 12, 1560, 4, 128), (1, 1, 20000, 2, 256), (1, 2, 12000, 4, 256), (1, 2, 16000, 1, 128)))
+def test_fixed_workspace_gives_the_same_bits(B, H, N, R, width):
+    w = work(N, R, width, B, H, seed=N)
+    q, k, v, fq, fk = ha.to_device(W.make_inputs(w))
+    maps = (None, None) if R == 1 else (fq, fk)
+    ref = ha.hybrid_attn_forward(q, k, v, *maps, R, 128, w.scale)
+    out = torch.full_like(q, float("nan"))
+    ha.hybrid_attn_forward_static(q, k, v, *maps, R, out, 128, w.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)
