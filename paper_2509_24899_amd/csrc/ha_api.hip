@@ -169,10 +169,21 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
   pl.off_sthi = take(BH * pl.n_cc * pl.F * pl.D * 2);
   pl.off_stlo = take(BH * pl.n_cc * pl.F * pl.D * 2);
   pl.total = off;
-  pl.split_linear = has_linear && pl.HD == 256 && pl.F == 256 && pl.DM == 0 && pl.CC == 0 && pl.LW == 0;
+  // whole tiles of 256 queries, the larger of the two the pass of the 256-wide maps uses; n in fp32, then e
+  const size_t tile = BH * 256 * (pl.D + 1) * 4, tiles = ((size_t)pl.N + 255) / 256;
+  const bool plain = has_linear && pl.DM == 0 && pl.CC == 0 && pl.LW == 0 && pl.D == 128;
+  pl.split_linear = plain && pl.HD == 256 && pl.F == 256;
+  // With the 128-wide maps the query kernel's epilogue is 11 us at the end of every workgroup; a pass of its own over blocks
+  // of 32 queries is one more launch, but leaves the query kernel free to split the keys and to use small tiles.  That pays
+  // for few heads, whose operands all workgroups share (whole calls, epilogue / pass, us, R = 4: H = 1, N = 2000  38.5 / 36.0,
+  // 8000  69.5 / 51.0, 20000  127 / 90; H = 2, N = 5000  55.6 / 49.4; H = 5, N = 3000  48.8 / 44.4), and not for many
+  // (H = 12, N = 1560  42.9 / 42.7, 2600  49.4 / 51.0; H = 24, N = 1000  41.5 / 44.0; at R = 16 up to 9 % worse), nor once
+  // 128-query tiles are more than one per CU.  The rule must not depend on the workspace (results are equal bit for bit
+  // with one of fixed size), so its results have to fit the static one if the rest does.
+  if (plain && pl.HD == 128 && pl.F == 128 && pl.NS > 0 && BH <= 5 && ((size_t)pl.N + 127) / 128 * BH <= 256 &&
+      (off + tiles * tile <= kStaticScratchBytes || off > kStaticScratchBytes))
+    pl.split_linear = true;
   if (pl.split_linear) {
-    // whole tiles of 256 queries, the larger of the two the pass uses; n in fp32, then e
-    const size_t tile = BH * 256 * (pl.D + 1) * 4, tiles = ((size_t)pl.N + 255) / 256;
     pl.lin_rows = pl.N;
     pl.off_lin = off;
     if (off + tiles * tile <= limit) {
@@ -195,20 +206,16 @@ static bool needs_wide_path(const Plan &pl) {
   return pl.NL > 0 && ((!square && !paper_width) || pl.DM > 0);
 }
 
-constexpr size_t kStaticScratchBytes = (size_t)HA_STATIC_SCRATCH_MIB << 20;
-
 // Into how many ranges the keys of the plain operator's softmax loop are split.  A tile of 256 queries is one workgroup, so
 // a problem of few tiles leaves CUs idle for the whole loop; with n ranges it has n times the workgroups, each with 1 / n
 // of the keys, at the price of a pass that merges the partial sums (516 bytes per query and range written and read).  The
 // estimate, in us, from measured times: a 32-key step takes 0.5 (0.42 in the small tiling of an unsplit problem), the rest
-// of a workgroup 5, or 14 where it evaluates the 128-wide maps in its epilogue; the merging pass 5, or 10 and 1.3 per range
-// where it evaluates them (in the kernel of ha_linear.hip), and its traffic at 4 TB/s.  It has to be 10 % better than one
-// range.  Whole calls, one range / split, us:
+// of a workgroup 5; the merging pass 5 and its traffic at 4 TB/s.  It has to be 10 % better than one range.  (Where the query
+// kernel would evaluate the maps in its epilogue, there is no pass that could merge.)  Whole calls, one range / split, us:
 //   R = 1:  H = 1, N = 2000  37 / 31;  N = 8000  122 / 55;  N = 20000  289 / 188;  H = 2, N = 5000  81 / 46;  H = 5, N = 3000
 //   55 / 44;  R = 4:  H = 1, N = 20000  126 / 95 (128-wide maps), 135 / 116 (256-wide).
 static int choose_split(const Plan &pl, bool lin) {
-  if (pl.D != 128 || pl.CC > 0 || pl.LW > 0 || pl.NS == 0) return 1;
-  const bool fused = pl.NL > 0 && !lin;                   // the maps are evaluated by the query kernel, or by the merging pass
+  if (pl.D != 128 || pl.CC > 0 || pl.LW > 0 || pl.NS == 0 || (pl.NL > 0 && !lin)) return 1;
   const double tiles = (double)((pl.N + 255) / 256) * pl.B * pl.H, rows = (double)pl.N * pl.B * pl.H;
   // From half the CUs on the loop is left whole.  (It would still pay a little at exactly 128 tiles; but there one head of a
   // long clip, on its own, keeps the bits it has among others, and with them the signs a distillation gradient is made of.)
@@ -216,9 +223,8 @@ static int choose_split(const Plan &pl, bool lin) {
   const int nblk = (pl.NS + 31) / 32;
   auto cost = [&](int n) {
     const double rounds = std::ceil(tiles * n / 256.0), blocks = (nblk + n - 1) / n;
-    const double step = n == 1 && !fused ? 0.42 : 0.5;
-    const double loop = rounds * (blocks * step + (n == 1 && fused ? 14.0 : 5.0));
-    return n == 1 ? loop : loop + (fused ? 10.0 + 1.3 * n : 5.0) + rows * n * 1032.0 / 4.0e6;
+    const double loop = rounds * (blocks * (n == 1 ? 0.42 : 0.5) + 5.0);
+    return n == 1 ? loop : loop + 5.0 + rows * n * 1032.0 / 4.0e6;
   };
   int best = 1;
   double least = 0.9 * cost(1);
@@ -247,7 +253,7 @@ static size_t full_plan(const ha_problem &p, const ha_feature_map *phi_q, const 
   const size_t BH = (size_t)pl.B * pl.H, per = BH * ((pl.N + 255) / 256) * 256 * (pl.D + 2) * 4;
   if (total <= kStaticScratchBytes)
     while (pl.n_split > 1 && total + pl.n_split * per > kStaticScratchBytes) --pl.n_split;
-  if (pl.split_linear) {
+  if (pl.split_linear && pl.F == 256) {
     // (with the linear pass's results in the partials' place, a part at a time, there is no room: see make_plan)
     const size_t lin = BH * ((pl.N + 255) / 256) * 256 * (pl.D + 1) * 4;
     const size_t least = pl.off_lin == pl.off_part ? total : total - lin;
@@ -348,7 +354,9 @@ static ha_status forward_impl(const ha_problem *p, const void *q, const void *k,
       part.N = pl.N - n0 < pl.lin_rows ? pl.N - n0 : pl.lin_rows;
       const void *qn = static_cast<const char *>(q) + n0 * row;
       void *on = static_cast<char *>(out) + n0 * row;
-      if ((e = ha::launch_linear256(part, qn, *phi_q, workspace, st)) != hipSuccess) return ha::device_error(e);
+      if ((e = pl.F == 256 ? ha::launch_linear256(part, qn, *phi_q, workspace, st)
+                           : ha::launch_linear_query(part, qn, *phi_q, nullptr, nullptr, workspace, st)) != hipSuccess)
+        return ha::device_error(e);
       if ((e = ha::launch_query(part, qn, phi_q, on, row_den, workspace, st)) != hipSuccess) return ha::device_error(e);
     }
   } else if ((e = ha::launch_query(pl, q, phi_q, out, row_den, workspace, st, wide ? &wp : nullptr)) != hipSuccess) {

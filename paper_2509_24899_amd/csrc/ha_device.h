@@ -72,36 +72,6 @@ static __device__ __forceinline__ bf16x8 load8(const void *base, int64_t elem_of
   }
 }
 
-// The partial sums of the key ranges of 32-query block tb (see SplitArgs), expressed against the maximum over all of them:
-// the accumulators in o, the sum of weights of this lane's query returned (both halves of the wave hold it).
-template <int RB, typename SPLIT>
-static __device__ __forceinline__ float merge_ranges(const SPLIT &sp, int bh, int tb, int lane, f32x16 (&o)[RB]) {
-  const int64_t step = (int64_t)sp.BH * sp.n_tb, blk = (int64_t)bh * sp.n_tb + tb;
-  const int r = lane & 31;
-  float m = -INFINITY;
-  for (int s = 0; s < sp.n_split; ++s) m = fmaxf(m, sp.pm[(blk + s * step) * 32 + r]);
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int x = 0; x < 16; ++x) o[rb][x] = 0.f;
-  float l = 0.f;
-  for (int s = 0; s < sp.n_split; ++s) {
-    const int64_t at = blk + s * step;
-    const f32x4 *src = reinterpret_cast<const f32x4 *>(sp.po) + at * RB * 4 * 64 + lane;
-    const float wgt = fast_exp2((sp.pm[at * 32 + r] - m) * sp.scale_log2e);
-    l = __builtin_fmaf(wgt, sp.pl[at * 32 + r], l);
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int x4 = 0; x4 < 4; ++x4) {
-        const f32x4 t = src[(rb * 4 + x4) * 64];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[rb][4 * x4 + j] = __builtin_fmaf(wgt, t[j], o[rb][4 * x4 + j]);
-      }
-  }
-  return l;
-}
-
 // Linear-token index -> token index: the tokens outside the softmax set in increasing order (R = 0: all).  With
 // groups of G tokens, every R-th group being softmax tokens, linear token i lies in group-of-R-groups i / ((R - 1) G)
 // and i + (that quotient + 1) G is its token index.  The quotient is exact for every int32 i: a double-precision

@@ -1,6 +1,6 @@
 // Query side of purely linear attention (rate 0: no softmax tokens; Sec. 3.1) for the widths 128 -> 128 -> 128:
 //     y_i = phi_q(q_i) S / (phi_q(q_i) . z),   gfx950 only,
-// and, with the softmax part given as the partial sums of key ranges (see SplitArgs), of Eq. "hybrid".
+// and, for small problems with softmax tokens, its numerator and denominator alone, which the query kernel adds.
 //
 // The query kernel of ha_query.hip runs this as its epilogue: every workgroup fetches the operands for one tile of 256
 // queries, its waves go through load, layers, contraction and store in step, and memory is idle while they compute.
@@ -32,12 +32,14 @@ struct LinearArgs {
   float *row_den;                        // optional [B*H][N]
   int H, N, P, act;
   int64_t sb, sh, sn;
-  SplitArgs sp;                          // MERGE: the softmax part
+  f32x4 *lin;                            // PART: n^T as [B*H][n_tb][D/32][4][64], e as [B*H][N], instead of out
+  float *lin_e;
+  int n_tb;
 };
 
 // grid (workgroups per (batch, head), B*H), 8 waves.  ACT0: the output activation is the softmax over the channels; P2: the
 // degree is 2, the paper's default (a branch on it here costs a copy of all feature registers).
-template <bool F32, bool ACT0, bool P2, bool MERGE>
+template <bool F32, bool ACT0, bool P2, bool PART>
 __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
   constexpr int D = 128, F = 128, KS = D / 16, FB = F / 32, RB = D / 32, NOP = D * D / 8;
   // output staging, per wave: 32 query rows x 64 bytes (32 bf16 or 16 fp32 channels), rows padded by 16 bytes
@@ -155,6 +157,10 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
         if (q_first + row < a.N) *reinterpret_cast<f32x4 *>(dst) = piece[i];
       }
     };
+    auto store_part = [&](int rb, int x4) {                 // registers 4 x4 .. 4 x4 + 3 of row block rb
+      a.lin[((((int64_t)bh * a.n_tb + blk) * RB + rb) * 4 + x4) * 64 + lane] =
+          f32x4{n[rb][4 * x4], n[rb][4 * x4 + 1], n[rb][4 * x4 + 2], n[rb][4 * x4 + 3]};
+    };
     constexpr int PASSES = 32 / CPP, SPP = 16 / PASSES;   // passes per row block, matrix-instruction slots per pass
     bf16x8 fa[2][2], fbuf[2][2];
     auto st_frags = [&](int rp, int t, bf16x8 (&dst)[2][2]) {
@@ -165,17 +171,10 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
       }
     };
     st_frags(0, 0, fa);
-    if constexpr (MERGE) {
-      // the accumulators start as the softmax part; one half of the wave counts its denominator (the other's half of
-      // phi . z is added below)
-      const float l = merge_ranges<RB>(a.sp, bh, blk, lane, n);
-      den = g == 0 ? l : 0.f;
-    } else {
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int x = 0; x < 16; ++x) n[rb][x] = 0.f;
-    }
+      for (int x = 0; x < 16; ++x) n[rb][x] = 0.f;
     HA_FENCE();
 #pragma unroll
     for (int rp = 0; rp < RB; rp += 2) {
@@ -193,6 +192,8 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
           }
           if (rp == 0) {
             if (slot >= 2) den_slice(t, slot - 2);
+          } else if constexpr (PART) {
+            if (t < 2) store_part(slot >> 1, 2 * (slot & 1) + t);       // the image of the first pair
           } else {
             const int c = t * 4 + slot, q = c / SPP, rb = q / PASSES, p = q % PASSES, at = c % SPP;
             if (at < CPP / 8) put(rb, p, at);
@@ -205,9 +206,15 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
       if (rp == 0) {
         den = xhalf_sum(den);
         if (a.row_den && lane < 32 && q_first + lane < a.N) a.row_den[(int64_t)bh * a.N + q_first + lane] = den;
+        if (PART && lane < 32 && q_first + lane < a.N) a.lin_e[(int64_t)bh * a.N + q_first + lane] = den;
         inv = 1.0f / den;
         HA_FENCE();
       }
+    }
+    if constexpr (PART) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) store_part(2 + (i >> 2), i & 3);
+      continue;
     }
 #pragma unroll
     for (int rb = 2; rb < RB; ++rb)
@@ -237,17 +244,20 @@ hipError_t launch_linear_query(const Plan &pl, const void *q, const ha_feature_m
   a.z = reinterpret_cast<float *>(wsb + pl.off_z);
   a.H = pl.H; a.N = pl.N; a.P = pl.P; a.act = pl.act_q;
   a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
-  a.sp = split_args(pl, ws);
+  const bool part = pl.split_linear;
+  a.lin = part ? reinterpret_cast<f32x4 *>(wsb + pl.off_lin) : nullptr;
+  a.lin_e = part ? reinterpret_cast<float *>(wsb + pl.off_e) : nullptr;
+  a.n_tb = pl.n_tb;
   // one workgroup per CU in a single round; short sequences spread over as many of them as they have blocks
   const int nb = (pl.N + 31) / 32, room = 256 / (pl.B * pl.H) > 0 ? 256 / (pl.B * pl.H) : 1;
   dim3 grid(nb < room ? nb : room, pl.B * pl.H);
-#define HA_LINEAR(F32, MERGE) \
+#define HA_LINEAR(F32, PART) \
   do { \
-    if (pl.act_q != HA_ACT_SOFTMAX) linear_query_kernel<F32, false, false, MERGE><<<grid, 512, 0, st>>>(a); \
-    else if (pl.P == 2) linear_query_kernel<F32, true, true, MERGE><<<grid, 512, 0, st>>>(a); \
-    else linear_query_kernel<F32, true, false, MERGE><<<grid, 512, 0, st>>>(a); \
+    if (pl.act_q != HA_ACT_SOFTMAX) linear_query_kernel<F32, false, false, PART><<<grid, 512, 0, st>>>(a); \
+    else if (pl.P == 2) linear_query_kernel<F32, true, true, PART><<<grid, 512, 0, st>>>(a); \
+    else linear_query_kernel<F32, true, false, PART><<<grid, 512, 0, st>>>(a); \
   } while (0)
-  if (pl.n_split > 1) { if (pl.f32) HA_LINEAR(true, true); else HA_LINEAR(false, true); }
+  if (part) { if (pl.f32) HA_LINEAR(true, true); else HA_LINEAR(false, true); }
   else { if (pl.f32) HA_LINEAR(true, false); else HA_LINEAR(false, false); }
 #undef HA_LINEAR
   return hipGetLastError();

@@ -25,8 +25,9 @@ struct Plan {
   int CH, n_chunks, n_state_tiles;
   // workspace byte offsets (all multiples of 256)
   size_t off_w1q, off_w2q, off_w1k, off_w2k, off_ks, off_vs, off_part, off_S, off_z, off_sthi, off_stlo, total;
-  // 128 -> 256 -> 256 maps, plain operator: the linear part of the query side is a pass of its own (ha_linear256.hip), whose
-  // results (n_tb 32-query blocks per (batch, head)) the query kernel adds; lin_rows queries of every head at a time
+  // 128 -> 256 -> 256 maps, plain operator, and small problems with the 128-wide maps: the linear part of the query side is a
+  // pass of its own (ha_linear256.hip, ha_linear.hip), whose results (n_tb 32-query blocks per (batch, head)) the query
+  // kernel adds; lin_rows queries of every head at a time
   bool split_linear;
   int n_tb, lin_rows;
   size_t off_lin, off_e;
@@ -97,6 +98,7 @@ static inline bool query_side_is_linear(const Plan &pl) {
 // Fills `pl` from a validated problem.  Pure host arithmetic.  limit: size of a workspace that cannot grow; where the
 // results of the 256-wide maps' linear pass (516 bytes per query and head) do not fit it, they take the place of the state
 // partials, which are spent by then, as many queries at a time as that holds.
+constexpr size_t kStaticScratchBytes = (size_t)HA_STATIC_SCRATCH_MIB << 20;
 void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl, size_t limit = SIZE_MAX);
 
 // Kernel launchers (ha_kernels.hip).  Each enqueues on `st` and returns the launch status.
@@ -119,7 +121,7 @@ hipError_t launch_state_reduce(const Plan &pl, void *ws, hipStream_t st);
 hipError_t launch_state_reduce_with_prep(const Plan &pl, const ha_feature_map &phi_q, void *ws, hipStream_t st);
 hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi_q, void *out, float *row_den, void *ws,
                         hipStream_t st, const WidePlan *wide = nullptr);
-// ha_linear.hip: the query side where there is no softmax token at all, or where the softmax part arrives as partial sums
+// ha_linear.hip: the query side where there is no softmax token at all; with pl.split_linear its n = phi_q(q) S and e only
 hipError_t launch_linear_query(const Plan &pl, const void *q, const ha_feature_map &phi_q, void *out, float *row_den, void *ws,
                                hipStream_t st);
 // ha_linear256.hip: n = phi_q(q) S and e = phi_q(q) . z of the 128 -> 256 -> 256 maps

@@ -705,7 +705,6 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
     else query_kernel_ring<128, 128, 128, 8, 8, 2, false, true, 3><<<grid, 512, 0, st>>>(a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (pl.NL > 0 && !lin) return launch_linear_query(pl, q, *phi_q, out, row_den, ws, st);
     if (pl.f32) merge_kernel<true><<<mgrid, 256, 0, st>>>(a);
     else merge_kernel<false><<<mgrid, 256, 0, st>>>(a);
     return hipGetLastError();

@@ -1,5 +1,5 @@
 """Problems of few query tiles split the softmax keys into ranges whose partial sums a second pass merges: every form of
-that pass (rate 1, 128-wide maps, precomputed linear part of the 256-wide and of wider maps) against the fp64 oracle, with
+that pass (rate 1, precomputed linear part of the 128-wide, 256-wide and wider maps) against the fp64 oracle, with
 ragged last ranges, rows and tiles, a maximum that sits in any one range, the denominators of the gradient call, and
 equal bits with the fixed workspace and for either block size.
 
@@ -56,6 +56,14 @@ def test_row_denominators(width):
         _, l, _ = O.softmax_part(np.asarray(inp.q[0, h], np.float64), inp.k[0, h], inp.v[0, h], 2, w.scale)
         ref = l + O.feature_map(inp.q[0, h], oracle_map(inp.phi_q), h) @ z
         assert np.abs(den[0, h].double().cpu().numpy() / ref - 1).max() <= 4e-3     # (exp of a rounded logit: 2^-9 at most twice)
+
+
+@pytest.mark.parametrize("H", (5, 6))                  # five heads: linear part ahead of the query kernel; six: in its epilogue
+@pytest.mark.parametrize("N,P,act", ((1, 2, 0), (33, 1, 0), (257, 4, 0), (6528, 2, 0), (6529, 2, 0), (300, 8, 1), (300, 2, 2)))
+def test_linear_part_of_the_narrow_maps(N, P, act, H):
+    """51 and 52 tiles of 128 queries per head: the border of the rule at five heads."""
+    w = W.replace(work(N, 4 if N > 4 else 0, H=H, seed=N), poly_degree=P)
+    check(f"ks_lin128_H{H}_N{N}_P{P}_a{act}", W.make_inputs(w), act=act, rows=W.sample_rows(w, n_random=16) if N > 600 else None)
 
 
 @pytest.mark.parametrize("B,H,N,R,width", ((1, 12, 1560, 4, 128), (1, 1, 20000, 2, 256), (1, 2, 12000, 4, 256), (1, 2, 16000, 1, 128)))
