@@ -22,7 +22,7 @@
 namespace ha {
 
 // ------------------------------------------------------------------------------------------------
-// weight_prep_kernel: grid (ceil(max(HD*D, F*HD) / 256), H); see weight_prep_body
+// weight_prep_kernel: grid (weight_prep_blocks, H); see weight_prep_body
 template <bool F32>
 __global__ __launch_bounds__(256) void weight_prep_kernel(const void *__restrict__ w1, const void *__restrict__ w2,
                                                           __bf16 *__restrict__ w1f, __bf16 *__restrict__ w2f,
@@ -31,19 +31,31 @@ __global__ __launch_bounds__(256) void weight_prep_kernel(const void *__restrict
 }
 
 // ------------------------------------------------------------------------------------------------
-// compact_kernel: grid (n_kblocks, B*H); one workgroup builds one 32-key block of both fragment arrays.
+// compact_kernel: grid (n_kblocks, B*H); one workgroup builds one 32-key block of both fragment arrays.  With weights to
+// re-order (wp.w1), in the same launch: rows B*H + h of the grid prepare those of head h (two small independent jobs; as
+// launches of their own each waits for the one before to drain, 2 to 3 us).
 //   ks_frag[bh][kb][ks][lane]          = K[token(32kb + r)][16ks + 8g .. +7]
 //   vs_frag[bh][kb][rb][s][lane][t]    = V[token(32kb + crow(8s + t, g))][32rb + r]
 // token(key) = key * R, or with groups of G tokens (key / G) R G + key % G; keys >= NS are zero padding.
+struct WeightPrep {
+  const void *w1, *w2;
+  __bf16 *w1f, *w2f;
+  int HD, F;
+};
 template <int D, bool F32>
 __global__ __launch_bounds__(256) void compact_kernel(const void *__restrict__ k, const void *__restrict__ v,
                                                       bf16x8 *__restrict__ ks_frag, bf16x8 *__restrict__ vs_frag,
                                                       int H, int NS, int R, int G, int n_kblocks, int64_t sb,
-                                                      int64_t sh, int64_t sn) {
+                                                      int64_t sh, int64_t sn, int BH, WeightPrep wp) {
   constexpr int CPR = D / 8;            // 16-byte chunks per row
   constexpr int FRAG = D * 4;           // bf16x8 per 32-key block (= D*32*2/16)
   __shared__ __align__(16) __bf16 vt[32][D + 8];
   const int kb = blockIdx.x, bh = blockIdx.y;
+  if (bh >= BH) {
+    weight_prep_body<F32>(wp.w1, wp.w2, wp.w1f, wp.w2f, D, wp.HD, wp.F, bh - BH, blockIdx.x * 256 + threadIdx.x);
+    return;
+  }
+  if (kb >= n_kblocks) return;
   const int64_t base = (int64_t)(bh / H) * sb + (int64_t)(bh % H) * sh;
   bf16x8 *kdst = ks_frag + ((int64_t)bh * n_kblocks + kb) * FRAG;
   bf16x8 *vdst = vs_frag + ((int64_t)bh * n_kblocks + kb) * FRAG;
@@ -451,8 +463,7 @@ template <typename T>
 static inline T *ws_ptr(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(ws) + off); }
 
 hipError_t launch_weight_prep(const Plan &pl, const ha_feature_map &fm, bool is_query, void *ws, hipStream_t st) {
-  const int n = (pl.HD * pl.D > pl.F * pl.HD) ? pl.HD * pl.D : pl.F * pl.HD;
-  dim3 grid((n + 255) / 256, pl.H);
+  dim3 grid(weight_prep_blocks(pl.D, pl.HD, pl.F), pl.H);
   __bf16 *w1f = ws_ptr<__bf16>(ws, is_query ? pl.off_w1q : pl.off_w1k);
   __bf16 *w2f = ws_ptr<__bf16>(ws, is_query ? pl.off_w2q : pl.off_w2k);
   if (pl.f32) weight_prep_kernel<true><<<grid, 256, 0, st>>>(fm.w1, fm.w2, w1f, w2f, pl.D, pl.HD, pl.F);
@@ -460,12 +471,18 @@ hipError_t launch_weight_prep(const Plan &pl, const ha_feature_map &fm, bool is_
   return hipGetLastError();
 }
 
-hipError_t launch_compact(const Plan &pl, const void *k, const void *v, void *ws, hipStream_t st) {
+hipError_t launch_compact(const Plan &pl, const void *k, const void *v, void *ws, hipStream_t st, const ha_feature_map *prep_k) {
   dim3 grid(pl.n_kblocks, pl.B * pl.H);
+  WeightPrep wp = {};
+  if (prep_k) {
+    wp = WeightPrep{prep_k->w1, prep_k->w2, ws_ptr<__bf16>(ws, pl.off_w1k), ws_ptr<__bf16>(ws, pl.off_w2k), pl.HD, pl.F};
+    const unsigned need = weight_prep_blocks(pl.D, pl.HD, pl.F);
+    grid = dim3(grid.x > need ? grid.x : need, grid.y + pl.H);
+  }
   bf16x8 *ksf = ws_ptr<bf16x8>(ws, pl.off_ks), *vsf = ws_ptr<bf16x8>(ws, pl.off_vs);
 #define HA_COMPACT(DD, FF) \
   compact_kernel<DD, FF><<<grid, 256, 0, st>>>(k, v, ksf, vsf, pl.H, pl.NS, pl.LW > 0 ? 1 : pl.R, pl.G, pl.n_kblocks, pl.sb, \
-                                               pl.sh, pl.sn)
+                                               pl.sh, pl.sn, pl.B * pl.H, wp)
   if (pl.D == 64) { if (pl.f32) HA_COMPACT(64, true); else HA_COMPACT(64, false); }
   else { if (pl.f32) HA_COMPACT(128, true); else HA_COMPACT(128, false); }
 #undef HA_COMPACT
@@ -504,7 +521,7 @@ hipError_t launch_weighted_state(const Plan &pl, const void *q, const void *gsig
 }
 
 hipError_t launch_state_reduce_with_prep(const Plan &pl, const ha_feature_map &phi_q, void *ws, hipStream_t st) {
-  const int n_prep = ((pl.HD * pl.D > pl.F * pl.HD ? pl.HD * pl.D : pl.F * pl.HD) + 255) / 256;
+  const int n_prep = weight_prep_blocks(pl.D, pl.HD, pl.F);
   const int n_red = pl.n_state_tiles * 1024 / 256;
   dim3 grid(n_red > n_prep ? n_red : n_prep, pl.B * pl.H + pl.H);
 #define HA_RP(F32) \

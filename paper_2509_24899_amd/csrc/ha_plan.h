@@ -103,7 +103,8 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
 
 // Kernel launchers (ha_kernels.hip).  Each enqueues on `st` and returns the launch status.
 hipError_t launch_weight_prep(const Plan &pl, const ha_feature_map &fm, bool is_query, void *ws, hipStream_t st);
-hipError_t launch_compact(const Plan &pl, const void *k, const void *v, void *ws, hipStream_t st);
+// prep_k (optional): the key-side map, whose weights are re-ordered in the same launch
+hipError_t launch_compact(const Plan &pl, const void *k, const void *v, void *ws, hipStream_t st, const ha_feature_map *prep_k);
 hipError_t launch_state(const Plan &pl, const void *k, const void *v, const ha_feature_map &phi_k, void *ws,
                         hipStream_t st);
 hipError_t launch_state256(const Plan &pl, const void *k, const void *v, const ha_feature_map &phi_k, void *ws,

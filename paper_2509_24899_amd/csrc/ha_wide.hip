@@ -22,33 +22,12 @@
 namespace ha {
 
 // ------------------------------------------------------------------------------------------------
-// wide_prep_kernel: grid (ceil(NOUT*K / 256), H).  W [H][NOUT][K] (io dtype) ->
-//   natural:  wf[h][ob][ks][lane][t]    = W[h][32 ob + r][16 ks + 8 g + t]
-//   chained:  wf[h][ob][kb][s][lane][t] = W[h][32 ob + r][32 kb + crow(8 s + t, g)]
+// wide_prep_kernel: grid (ceil(NOUT*K / 2048), H).  W [H][NOUT][K] (io dtype) -> fragments, see weight_piece
 template <bool F32, bool CHAINED>
-__global__ __launch_bounds__(256) void wide_prep_kernel(const void *__restrict__ wsrc, __bf16 *__restrict__ wf, int NOUT, int K) {
-  const int h = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= NOUT * K) return;
-  const int t = e & 7, lane = (e >> 3) & 63, rest = e >> 9;
-  const int r = lane & 31, g = lane >> 5;
-  int row, col;
-  if constexpr (CHAINED) {
-    const int KB = K / 32;
-    const int s = rest & 1, kb = (rest >> 1) % KB, ob = (rest >> 1) / KB;
-    row = 32 * ob + r;
-    col = 32 * kb + crow(8 * s + t, g);
-  } else {
-    const int KS = K / 16;
-    const int ks = rest % KS, ob = rest / KS;
-    row = 32 * ob + r;
-    col = 16 * ks + 8 * g + t;
-  }
-  const int64_t src = ((int64_t)h * NOUT + row) * K + col;
-  float val;
-  if constexpr (F32) val = static_cast<const float *>(wsrc)[src];
-  else val = static_cast<float>(static_cast<const __bf16 *>(wsrc)[src]);
-  wf[(int64_t)h * NOUT * K + e] = static_cast<__bf16>(val);
+__global__ __launch_bounds__(256) void wide_prep_kernel(const void *__restrict__ wsrc, bf16x8 *__restrict__ wf, int NOUT, int K) {
+  const int piece = blockIdx.x * 256 + threadIdx.x;
+  const int64_t n = (int64_t)NOUT * K, base = blockIdx.y * n;
+  if (piece < n / 8) wf[base / 8 + piece] = weight_piece<F32, CHAINED>(wsrc, base, K, piece);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -308,8 +287,8 @@ hipError_t launch_wide_map(const Plan &pl, const WidePlan &wp, const void *x, co
   // weight fragments of this map
   {
     auto prep = [&](const void *wsrc, size_t off, int nout, int kdim, bool chained) {
-      dim3 grid((nout * kdim + 255) / 256, pl.H);
-      __bf16 *dst = ws_ptr<__bf16>(ws, off);
+      dim3 grid((nout * kdim / 8 + 255) / 256, pl.H);
+      bf16x8 *dst = ws_ptr<bf16x8>(ws, off);
       if (pl.f32) {
         if (chained) wide_prep_kernel<true, true><<<grid, 256, 0, st>>>(wsrc, dst, nout, kdim);
         else wide_prep_kernel<true, false><<<grid, 256, 0, st>>>(wsrc, dst, nout, kdim);
