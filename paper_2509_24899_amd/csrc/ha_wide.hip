@@ -69,11 +69,15 @@ static __device__ __forceinline__ void wide_phi_tile(const f32x4 (&raw)[4], int 
   for (int x4 = 0; x4 < 4; ++x4)
 #pragma unroll
     for (int j = 0; j < 4; ++j) u[4 * x4 + j] = raw[x4][j];
+  if (o.act == 0) {                                            // one branch per tile, not one per value
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    if (o.act == 0) u[v] = fast_exp2(__builtin_fmaf(u[v], kLog2e, o.off)) * o.inv;
-    else if (o.act == 1) u[v] = fast_exp2(u[v] * kLog2e);
-    else u[v] = fmaxf(u[v], 0.f);
+    for (int v = 0; v < 16; ++v) u[v] = fast_exp2(__builtin_fmaf(u[v], kLog2e, o.off)) * o.inv;
+  } else if (o.act == 1) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) u[v] = fast_exp2(u[v] * kLog2e);
+  } else {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) u[v] = fmaxf(u[v], 0.f);
   }
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
@@ -186,57 +190,89 @@ __global__ __launch_bounds__(256, 1) void wide_state_kernel(const f32x4 *__restr
 }
 
 // ------------------------------------------------------------------------------------------------
-// wide_lin_kernel: grid (ceil(n_tb / 4), B*H).  Output stage of phi_q and the linear part of Eq. "hybrid" per 32-query
-// block: n^T = S^T phi_q^T (A operand = S^T as hi + lo fragments in chained order, state_reduce_kernel's layout; B
-// operand = phi_q, formed tile by tile from the fp32 pre-activations) and e = phi_q . z with the rounded phi_q, as the
-// numerator uses it.  Output: n as an fp32 C image of width D, i.e. the layout of the query kernel's accumulators;
-// e[bh][token].
+// wide_lin_kernel: grid (ceil(n_tb / 8), B*H), 8 waves.  Output stage of phi_q and the linear part of
+// Eq. "hybrid" per 32-query block: n^T = S^T phi_q^T (A operand = S^T as hi + lo fragments in chained order,
+// state_reduce_kernel's layout; B operand = phi_q, formed tile by tile from the fp32 pre-activations) and e = phi_q . z
+// with the rounded phi_q, as the numerator uses it.  Output: n as an fp32 C image of width D, i.e. the layout of the query
+// kernel's accumulators; e[bh][token].
+// The 16 fragments of S a 32-channel tile meets are the same for all waves: a slab of an LDS ring, one barrier per tile
+// (every wave reading its own from L2, 4.7 GB of them: 460 us at 480p / 81 frames, 768 wide, 12 heads; now 355).  The wave's own tile of
+// pre-activations comes with it, two tiles ahead: the bound is HBM, 1.2 GB of them, and 64 KiB per CU are on their way.
+// All loads of the loop are LDS-DMA so that the counts below are the only waits.
 template <int D>
-__global__ __launch_bounds__(256) void wide_lin_kernel(const f32x4 *__restrict__ u_img, const float *__restrict__ stat,
-                                                       const bf16x8 *__restrict__ st_hi, const bf16x8 *__restrict__ st_lo,
-                                                       const float *__restrict__ z, f32x4 *__restrict__ lin,
-                                                       float *__restrict__ e_out, int F, int n_tok, int n_tb, int act, int P) {
-  constexpr int RB = D / 32;
-  __shared__ float zl[WIDE_FMAX];
+__global__ __launch_bounds__(512, 2) void wide_lin_kernel(const f32x4 *u_img, const float *stat, const bf16x8 *st_hi,
+                                                          const bf16x8 *st_lo, const float *z, f32x4 *lin, float *e_out, int F,
+                                                          int n_tok, int n_tb, int act, int P) {
+  constexpr int RB = D / 32, NBUF = 3, SLOT = RB * 4 * 64;
+  static_assert(RB * 4 == 16, "two chunks of a slab per wave: the wait below counts them");
+  __shared__ bf16x8 ring[NBUF * SLOT];
+  __shared__ f32x4 tile[NBUF * 8 * 4 * 64];             // [slot][wave][piece]
+  __shared__ __align__(16) float zl[WIDE_FMAX];
   const int bh = blockIdx.y;
-  for (int i = threadIdx.x; i < F; i += 256) zl[i] = z[(int64_t)bh * F + i];
-  __syncthreads();
+  for (int i = threadIdx.x; i < F; i += 512) zl[i] = z[(int64_t)bh * F + i];
   const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
-  const int tb = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (tb >= n_tb) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool live = blockIdx.x * 8 + w < n_tb;          // idle waves keep staging and synchronising
+  const int tb = live ? blockIdx.x * 8 + w : n_tb - 1;
   const int FB = F / 32;
   const bool valid = 32 * tb + r < n_tok;
+  const unsigned lane_off = lane * 16;
+  const f32x4 *usrc = u_img + ((int64_t)bh * n_tb + tb) * FB * 256;
+  auto dma = [&](const void *to, const void *from) {
+    const unsigned l = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)to);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(from) : "memory");
+  };
+  // slab fb: chunk (rb, s, hi / lo) = fragment (rb, fb, s) of either array; past the last one it is fetched again, so that
+  // a request is always six loads
+  auto request = [&](int fb, int slot) {
+    const int src = min(fb, FB - 1);
+#pragma unroll
+    for (int x4 = 0; x4 < 4; ++x4) dma(&tile[((slot * 8 + w) * 4 + x4) * 64], usrc + (src * 4 + x4) * 64);
+#pragma unroll
+    for (int i = 0; i < RB * 4 / 8; ++i) {
+      const int c = i * 8 + w;
+      const bf16x8 *gp = ((c & 1) ? st_lo : st_hi) + (int64_t)bh * (D * F / 8) + (((c >> 2) * FB + src) * 2 + ((c >> 1) & 1)) * 64;
+      dma(&ring[slot * SLOT + c * 64], gp);
+    }
+  };
   const WideOutStage os = wide_out_stage(stat, (int64_t)bh * n_tb + tb, F, act, P, lane);
-  const f32x4 *usrc = u_img + ((int64_t)bh * n_tb + tb) * FB * 256 + lane;
-  const GlobalFrags shi = global_frags(st_hi + (int64_t)bh * (D * F / 8), D * F * 2);
-  const GlobalFrags slo = global_frags(st_lo + (int64_t)bh * (D * F / 8), D * F * 2);
+  request(0, 0);
+  request(1, 1);
   f32x16 acc[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[rb][v] = 0.f;
   float dot = 0.f;
+  int slot = 0;
+#pragma unroll 1
   for (int fb = 0; fb < FB; ++fb) {
-    bf16x8 b[2], ahi[RB][2], alo[RB][2];
+    asm volatile("s_waitcnt vmcnt(6)" ::: "memory");    // the request behind this tile's
+    __syncthreads();                                    // this tile's slab is there, the last tile's slot is free
+    request(fb + 2, slot == 0 ? 2 : slot - 1);
+    const lds_frag_ptr sl = (lds_frag_ptr)&ring[slot * SLOT];
+    f32x4 raw[4];
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        ahi[rb][s] = frag_at(shi, (rb * FB + fb) * 2 + s, lane);
-        alo[rb][s] = frag_at(slo, (rb * FB + fb) * 2 + s, lane);
-      }
-    wide_phi_tile(usrc, fb, os, valid, b);
+    for (int x4 = 0; x4 < 4; ++x4) raw[x4] = tile[((slot * 8 + w) * 4 + x4) * 64 + lane];
+    bf16x8 b[2];
+    wide_phi_tile(raw, fb, os, valid, b);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) dot += static_cast<float>(b[s][i]) * zl[32 * fb + crow(8 * s + i, g)];
+      for (int x = 0; x < 2; ++x) {
+        const f32x4 z4 = *reinterpret_cast<const f32x4 *>(&zl[32 * fb + 16 * s + 8 * x + 4 * g]);
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        acc[rb] = mfma32(alo[rb][s], b[s], acc[rb]);
-        acc[rb] = mfma32(ahi[rb][s], b[s], acc[rb]);
+        for (int j = 0; j < 4; ++j) dot += static_cast<float>(b[s][4 * x + j]) * z4[j];
       }
+#pragma unroll
+      for (int lo = 1; lo >= 0; --lo)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[rb] = mfma32(frag_at(sl, rb * 4 + s * 2 + lo, lane), b[s], acc[rb]);
     }
+    slot = slot == 2 ? 0 : slot + 1;
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing may still be on its way into this workgroup's LDS
+  if (!live) return;
   dot = xhalf_sum(dot);
   if (g == 0 && valid) e_out[(int64_t)bh * n_tok + 32 * tb + r] = dot;
 #pragma unroll
@@ -354,8 +390,8 @@ hipError_t launch_wide_query_side(const Plan &pl, const WidePlan &wp, const void
                                   hipStream_t st) {
   hipError_t e = launch_wide_map(pl, wp, q, phi_q, true, ws, st, false);
   if (e != hipSuccess) return e;
-  dim3 grid((wp.n_tb_q + 3) / 4, pl.B * pl.H);
-  wide_lin_kernel<128><<<grid, 256, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat),
+  dim3 grid((wp.n_tb_q + 7) / 8, pl.B * pl.H);
+  wide_lin_kernel<128><<<grid, 512, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat),
                                              ws_ptr<bf16x8>(ws, pl.off_sthi), ws_ptr<bf16x8>(ws, pl.off_stlo),
                                              ws_ptr<float>(ws, pl.off_z), ws_ptr<f32x4>(ws, wp.off_lin),
                                              ws_ptr<float>(ws, wp.off_e), pl.F, pl.N, wp.n_tb_q, pl.act_q, pl.P);
