@@ -55,20 +55,35 @@ struct WideGradArgs {
 };
 
 // ------------------------------------------------------------------------------------------------
-// wide_dphi_kernel: grid (ceil(n_tb / 4), ceil(F / 256), B*H), one 32-token block per wave.
+// wide_dphi_kernel: grid (ceil(n_tb / 8), ceil(F / 256), B*H), 8 waves of one 32-token block each.
+// The eight output tiles' fragments of M (128 KiB hi + lo) are the same for all waves: one fetch per workgroup into LDS, all
+// of it ahead of the walk, and z beside it; the pre-activations of the next tile travel under the current one.  ACT0:
+// softmax.  (With every wave of four reading M from L2 and the pre-activations where they are used, 407 us over the queries
+// and 294 over the keys for the 256-wide maps at 480p / 81 frames, 12 heads; now 244 and 175.)  Bound: HBM, the fp32
+// pre-activations in, du (and phi_q) out, 0.9 GB over the queries.
 // FUSED (every case but a softmax over more than one 256-channel block): the sum of the softmax Jacobian is complete
 // inside the workgroup's block, so du is formed here (t dt of the eight tiles waits in registers for the sum, t is
 // recomputed from the pre-activations, which the wave has just read) and written as the bf16 image; the fp32 side
 // images and wide_du_kernel are not needed.  QUERY: phi_q = t^p is written as a bf16 image for the dS product.
-template <int D, bool F32, bool QUERY, bool FUSED>
-__global__ __launch_bounds__(256) void wide_dphi_kernel(WideGradArgs a) {
+template <int D, bool F32, bool QUERY, bool FUSED, bool ACT0>
+__global__ __launch_bounds__(512, 2) void wide_dphi_kernel(WideGradArgs a) {
   constexpr int KS = D / 16, NT = 8;
+  __shared__ bf16x8 m_lds[NT * KS * 2 * 64];              // [tile][k-step][hi, lo]
+  __shared__ __align__(16) float z_lds[NT * 32];
   const int bh = blockIdx.z, h = bh % a.H;
   const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
-  const int tb = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (tb >= a.n_tb) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool live = blockIdx.x * 8 + w < a.n_tb;
+  const int tb = live ? blockIdx.x * 8 + w : a.n_tb - 1;
   const int FB = a.F / 32, nblk = (a.F + 255) / 256;
   const int fb0 = blockIdx.y * NT, nt = min(NT, FB - fb0);
+  const unsigned lane_off = lane * 16;
+  for (int c = w; c < nt * KS * 2; c += 8) {
+    const bf16x8 *gp = ((c & 1) ? a.m_lo : a.m_hi) + (int64_t)bh * ((int64_t)a.F * D / 8) + (fb0 * KS + (c >> 1)) * 64;
+    const unsigned l = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)(&m_lds[c * 64]));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(gp) : "memory");
+  }
+  if (threadIdx.x < nt * 32) z_lds[threadIdx.x] = a.zvec[(int64_t)bh * a.F + 32 * fb0 + threadIdx.x];
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)h * a.sh;
   const LinearMap lmap(QUERY ? 0 : a.R, a.G);
   const bool valid = 32 * tb + r < a.n_tok;
@@ -85,7 +100,7 @@ __global__ __launch_bounds__(256) void wide_dphi_kernel(WideGradArgs a) {
     wz_ = a.wp[(int64_t)bh * a.N + tok] * rs_;
   }
   float off = 0.f, inv = 1.f;
-  if (a.act == 0) {
+  if constexpr (ACT0) {
     const int n_st = a.F / 128;
     const float *st = a.stat + (((int64_t)bh * a.n_tb + tb) * n_st * 2) * 64 + lane;
     float m = -INFINITY;
@@ -95,14 +110,20 @@ __global__ __launch_bounds__(256) void wide_dphi_kernel(WideGradArgs a) {
     off = -m * kLog2e;
     inv = 1.0f / sum;
   }
-  const GlobalFrags mhi = global_frags(a.m_hi + (int64_t)bh * ((int64_t)a.F * D / 8), a.F * D * 2);
-  const GlobalFrags mlo = global_frags(a.m_lo + (int64_t)bh * ((int64_t)a.F * D / 8), a.F * D * 2);
   const float inv_groups = 8.0f * (float)a.P / (float)a.F;
   auto activation = [&](float u) {
-    if (a.act == 0) return fast_exp2(__builtin_fmaf(u, kLog2e, off)) * inv;
-    if (a.act == 1) return fast_exp2(u * kLog2e);
-    return fmaxf(u, 0.f);
+    if constexpr (ACT0) return fast_exp2(__builtin_fmaf(u, kLog2e, off)) * inv;
+    else return a.act == 1 ? fast_exp2(u * kLog2e) : fmaxf(u, 0.f);
   };
+  f32x4 uq_cur[4], uq_nxt[4];
+  auto load_tile = [&](int fb, f32x4 (&dst)[4]) {
+#pragma unroll
+    for (int x4 = 0; x4 < 4; ++x4) dst[x4] = a.t_img[((((int64_t)bh * a.n_tb + tb) * FB + fb) * 4 + x4) * 64 + lane];
+  };
+  load_tile(fb0, uq_nxt);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();                                        // M and z are in LDS; no wave waits for another from here on
+  if (!live) return;
   float pdot = 0.f;
   f32x16 keep[FUSED ? NT : 1];
 #pragma unroll
@@ -112,28 +133,26 @@ __global__ __launch_bounds__(256) void wide_dphi_kernel(WideGradArgs a) {
     f32x16 acc;
 #pragma unroll
     for (int x = 0; x < 16; ++x) acc[x] = 0.f;
-    bf16x8 fl[KS], fh[KS];
+#pragma unroll
+    for (int x4 = 0; x4 < 4; ++x4) uq_cur[x4] = uq_nxt[x4];
+    if (j + 1 < NT && j + 1 < nt) load_tile(fb + 1, uq_nxt);
+    const lds_frag_ptr m = (lds_frag_ptr)&m_lds[j * KS * 2 * 64];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      fl[ks] = frag_at(mlo, fb * KS + ks, lane);
-      fh[ks] = frag_at(mhi, fb * KS + ks, lane);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      acc = mfma32(fl[ks], uf[ks], acc);
-      acc = mfma32(fh[ks], uf[ks], acc);
+      acc = mfma32(frag_at(m, 2 * ks + 1, lane), uf[ks], acc);
+      acc = mfma32(frag_at(m, 2 * ks, lane), uf[ks], acc);
     }
     const int64_t img = (((int64_t)bh * a.n_tb + tb) * FB + fb) * 4;
     f32x16 phi;
 #pragma unroll
     for (int x4 = 0; x4 < 4; ++x4) {
-      const f32x4 uq = a.t_img[(img + x4) * 64 + lane];
+      const f32x4 uq = uq_cur[x4];
+      const f32x4 z4 = *reinterpret_cast<const f32x4 *>(&z_lds[32 * j + 8 * x4 + 4 * g]);
       const int extra = (int)(((float)(4 * fb + x4) + 0.5f) * inv_groups);        // slice power - 1, wave-uniform
       f32x4 tq, dq;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int c = 32 * fb + crow(4 * x4 + i, g);
-        const float dphi = rs_ * acc[4 * x4 + i] + wz_ * a.zvec[(int64_t)bh * a.F + c];
+        const float dphi = rs_ * acc[4 * x4 + i] + wz_ * z4[i];
         const float t = activation(uq[i]);
         const float t2 = t * t;
         float pw = (extra & 1) ? t : 1.f;                                        // t^extra
@@ -141,7 +160,7 @@ __global__ __launch_bounds__(256) void wide_dphi_kernel(WideGradArgs a) {
         pw = (extra & 4) ? pw * (t2 * t2) : pw;
         const float dt = dphi * (float)(extra + 1) * pw;
         float v;
-        if (a.act == 2) v = uq[i] > 0.f ? dt : 0.f;
+        if (!ACT0 && a.act == 2) v = uq[i] > 0.f ? dt : 0.f;
         else v = t * dt;
         v = valid ? v : 0.f;
         tq[i] = t;
@@ -171,12 +190,12 @@ __global__ __launch_bounds__(256) void wide_dphi_kernel(WideGradArgs a) {
   if constexpr (!FUSED) {
     a.pdot[(((int64_t)bh * a.n_tb + tb) * nblk + blockIdx.y) * 64 + lane] = pdot;
   } else {
-    const float dot = a.act == 0 ? pdot : 0.f;
+    const float dot = ACT0 ? pdot : 0.f;
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
       if (j >= nt) break;
       const int64_t img = (((int64_t)bh * a.n_tb + tb) * FB + fb0 + j) * 4;
-      if (a.act == 0) {
+      if constexpr (ACT0) {
 #pragma unroll
         for (int x4 = 0; x4 < 4; ++x4) {
           const f32x4 uq = a.t_img[(img + x4) * 64 + lane];
@@ -594,11 +613,12 @@ hipError_t launch_wide_value_distill_backward(const Plan &pl, const WidePlan &wp
     const bool fused = a.act != 0 || F <= 256;       // the softmax Jacobian's sum stays inside one workgroup
     a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
     {
-      dim3 grid((n_tb + 3) / 4, (F + 255) / 256, BH);
-#define HA_DPHI(F32, QUERY)                                                      \
-  do {                                                                          \
-    if (fused) wide_dphi_kernel<128, F32, QUERY, true><<<grid, 256, 0, st>>>(a); \
-    else wide_dphi_kernel<128, F32, QUERY, false><<<grid, 256, 0, st>>>(a);      \
+      dim3 grid((n_tb + 7) / 8, (F + 255) / 256, BH);
+#define HA_DPHI(F32, QUERY)                                                                       \
+  do {                                                                                           \
+    if (a.act != HA_ACT_SOFTMAX) wide_dphi_kernel<128, F32, QUERY, true, false><<<grid, 512, 0, st>>>(a); \
+    else if (fused) wide_dphi_kernel<128, F32, QUERY, true, true><<<grid, 512, 0, st>>>(a);       \
+    else wide_dphi_kernel<128, F32, QUERY, false, true><<<grid, 512, 0, st>>>(a);                 \
   } while (0)
       if (is_query) { if (pl.f32) HA_DPHI(true, true); else HA_DPHI(false, true); }
       else { if (pl.f32) HA_DPHI(true, false); else HA_DPHI(false, false); }
