@@ -196,8 +196,9 @@ __global__ __launch_bounds__(256, 1) void wide_state_kernel(const f32x4 *__restr
 // with the rounded phi_q, as the numerator uses it.  Output: n as an fp32 C image of width D, i.e. the layout of the query
 // kernel's accumulators; e[bh][token].
 // The 16 fragments of S a 32-channel tile meets are the same for all waves: a slab of an LDS ring, one barrier per tile
-// (every wave reading its own from L2, 4.7 GB of them: 460 us at 480p / 81 frames, 768 wide, 12 heads; now 355).  The wave's own tile of
-// pre-activations comes with it, two tiles ahead: the bound is HBM, 1.2 GB of them, and 64 KiB per CU are on their way.
+// (every wave reading its own from L2, 4.7 GB of them: 460 us at 480p / 81 frames, 768 wide, 12 heads; now 355).  The
+// wave's own tile of pre-activations comes with it, two tiles ahead: the bound is HBM, 1.2 GB of them, and 64 KiB per CU
+// are on their way.
 // All loads of the loop are LDS-DMA so that the counts below are the only waits.
 template <int D>
 __global__ __launch_bounds__(512, 2) void wide_lin_kernel(const f32x4 *u_img, const float *stat, const bf16x8 *st_hi,

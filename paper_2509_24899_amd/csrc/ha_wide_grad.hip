@@ -316,13 +316,17 @@ __global__ __launch_bounds__(256, 2) void wide_back_layer_kernel(const bf16x8 *_
 }
 
 // ------------------------------------------------------------------------------------------------
-// wide_contract_kernel: grid (n_chunks, B*H, (WA / 128) * (WB / 128)), 4 waves.  Per 128-token tile the A slab
+// wide_contract_kernel: grid n_chunks * B*H * slabs, slabs = (WA / 128) * (WB / 128), 4 waves.  Per 128-token tile the A slab
 // (128 rows of the A image, tokens as columns) and the B slab (128 columns) are parked in LDS with tokens contiguous,
 // as in the state pass, and wave w contracts row block w of the slab with the four column blocks and the extra
 // column block.  BSRC 0: B from a bf16 image of width WB; 1: rows of an io-dtype tensor behind the token map (q / k,
 // width D); 2: rows of the dense bf16 sign tensor.  a_scale (optional, [B*H][N]): per-token factor on A before it is
 // rounded (the 1 / den_i of the dS product).  Extra column block: ones, or with wcol the (hi, lo) pair of wcol's entry.
 // Partial tiles: part[bh][chunk][slab pair][w][5][16][64].
+// Bound: memory; the images of A and B are read once per slab they meet.  The slabs of one chunk therefore sit next to each
+// other on one XCD (workgroup ids eight apart), walk its tokens together and share them in that L2, and the next tile
+// is on its way to registers while this one is contracted (480p / 81 frames, 12 heads, 256 wide: (du, h) 128 -> 115 us as
+// the mean of both sides, (dpre, x) 73 -> 69, the dS product 90 - 94 either way).
 struct ContractArgs {
   const bf16x8 *a_img;       // [bh][tb][WA/32][2][64]
   const float *a_scale;      // or null
@@ -332,6 +336,7 @@ struct ContractArgs {
   float *part;
   int H, N, WA, WB, n_tok, n_tb, R, G, CH;
   int64_t sb, sh, sn;
+  int n_chunks, BH;          // set where the kernel is launched
 };
 
 template <int BSRC, bool F32>
@@ -341,8 +346,13 @@ __global__ __launch_bounds__(256, 1) void wide_contract_kernel(ContractArgs a) {
   __shared__ __align__(16) __bf16 ft[128][PITCH];
   __shared__ __align__(16) __bf16 vt[128][PITCH];
   __shared__ __align__(16) __bf16 et[2][PITCH];
-  const int chunk = blockIdx.x, bh = blockIdx.y, h = bh % a.H;
-  const int nbs = a.WB / 128, as = blockIdx.z / nbs, bs = blockIdx.z % nbs;
+  // workgroup id -> (chunk and head, slab): groups of eight (chunk, head) pairs, slab by slab; the last group may be smaller
+  const int nbs = a.WB / 128, n_slab = (a.WA / 128) * nbs;
+  const int grp = blockIdx.x / (8 * n_slab), in_grp = blockIdx.x % (8 * n_slab);
+  const int width = min(8, a.n_chunks * a.BH - 8 * grp);
+  const int pair = 8 * grp + in_grp % width, slab = in_grp / width;
+  const int chunk = pair % a.n_chunks, bh = pair / a.n_chunks, h = bh % a.H;
+  const int as = slab / nbs, bs = slab % nbs;
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)h * a.sh;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -366,18 +376,36 @@ __global__ __launch_bounds__(256, 1) void wide_contract_kernel(ContractArgs a) {
   const bf16x8 ones = bf16x8{one, one, one, one, one, one, one, one};
   const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
   const int t_begin = chunk * a.CH, t_end = min(t_begin + a.CH, a.n_tok);
-  for (int t0 = t_begin; t0 < t_end; t0 += TOK) {
+  // a tile: A, four 32-row blocks of the image; B, four of its image, or rows: pass p of wave w covers tokens
+  // 16 ((4 p + w) % 8) .. + 15 and the four 16-byte chunks 4 (p / 2) .. + 3
+  constexpr int NPB = BSRC == 0 ? 8 : VPT;
+  bf16x8 pa[4][2], pb[NPB];
+  auto load_tile = [&](int t0) {
     const int tb = t0 / 32 + w;
     const bool have = tb < a.n_tb;
-    const bool valid = t0 + tf < a.n_tok;
-    const int tok = lmap.token(min(t0 + tf, a.n_tok - 1));
-    // A slab: four 32-row blocks of the image, scaled per token where asked for
-    bf16x8 pa[4][2];
 #pragma unroll
     for (int fb = 0; fb < 4; ++fb)
 #pragma unroll
       for (int s = 0; s < 2; ++s)
         pa[fb][s] = have ? a.a_img[((((int64_t)bh * a.n_tb + tb) * AB + 4 * as + fb) * 2 + s) * 64 + lane] : zero;
+    if constexpr (BSRC == 0) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) pb[x] = have ? a.b_img[((((int64_t)bh * a.n_tb + tb) * BB + 4 * bs) * 2 + x) * 64 + lane] : zero;
+    } else {
+#pragma unroll
+      for (int p = 0; p < VPT; ++p) {
+        const int trow = 16 * ((4 * p + w) & 7) + (lane & 15), c8 = 4 * (p >> 1) + (lane >> 4);
+        const int tk = lmap.token(min(t0 + trow, a.n_tok - 1));
+        if constexpr (BSRC == 1) pb[p] = load8<F32>(a.b_rows, base + (int64_t)tk * a.sn + c8 * 8);
+        else pb[p] = static_cast<const bf16x8 *>(a.b_rows)[((int64_t)bh * a.N + tk) * (D / 8) + c8];
+      }
+    }
+  };
+  load_tile(t_begin);
+  for (int t0 = t_begin; t0 < t_end; t0 += TOK) {
+    const bool valid = t0 + tf < a.n_tok;
+    const int tok = lmap.token(min(t0 + tf, a.n_tok - 1));
+    // A slab, scaled per token where asked for
     if (a.a_scale) {
       const float sc = valid ? a.a_scale[(int64_t)bh * a.N + tok] : 0.f;
 #pragma unroll
@@ -396,28 +424,18 @@ __global__ __launch_bounds__(256, 1) void wide_contract_kernel(ContractArgs a) {
       for (int x = 0; x < 16; ++x) ftp[(32 * fb + 8 * (x >> 2) + (x & 3)) * PITCH + fcol[x >> 2]] = pa[fb][x >> 3][x & 7];
     // B slab
     if constexpr (BSRC == 0) {
-      bf16x8 pb[4][2];
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
-          pb[cb][s] = have ? a.b_img[((((int64_t)bh * a.n_tb + tb) * BB + 4 * bs + cb) * 2 + s) * 64 + lane] : zero;
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int x = 0; x < 16; ++x) vtp[(32 * cb + 8 * (x >> 2) + (x & 3)) * PITCH + fcol[x >> 2]] = pb[cb][x >> 3][x & 7];
+        for (int x = 0; x < 16; ++x)
+          vtp[(32 * cb + 8 * (x >> 2) + (x & 3)) * PITCH + fcol[x >> 2]] = pb[2 * cb + (x >> 3)][x & 7];
     } else {
-      // rows: pass p of wave w covers tokens 16 ((4 p + w) % 8) .. + 15 and the four 16-byte chunks 4 (p / 2) .. + 3
 #pragma unroll
       for (int p = 0; p < VPT; ++p) {
-        const int trow = 16 * ((4 * p + w) & 7) + (lane & 15), c8 = 4 * (p >> 1) + (lane >> 4);
-        const int tk = lmap.token(min(t0 + trow, a.n_tok - 1));
-        bf16x8 v8;
-        if constexpr (BSRC == 1) v8 = load8<F32>(a.b_rows, base + (int64_t)tk * a.sn + c8 * 8);
-        else v8 = static_cast<const bf16x8 *>(a.b_rows)[((int64_t)bh * a.N + tk) * (D / 8) + c8];
+        const int trow = 16 * ((4 * p + w) & 7) + (lane & 15);
         const int col = (((trow >> 3) ^ vsw) << 3) | (trow & 7);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) vtp[(32 * (p >> 1) + i) * PITCH + vrow0 + col] = v8[i];
+        for (int i = 0; i < 8; ++i) vtp[(32 * (p >> 1) + i) * PITCH + vrow0 + col] = pb[p][i];
       }
     }
     if (a.wcol && g == 0) {
@@ -427,6 +445,7 @@ __global__ __launch_bounds__(256, 1) void wide_contract_kernel(ContractArgs a) {
       et[1][tf] = static_cast<__bf16>(wv - static_cast<float>(whi));
     }
     __syncthreads();
+    if (t0 + TOK < t_end) load_tile(t0 + TOK);
 #pragma unroll
     for (int ks = 0; ks < TOK / 16; ++ks) {
       const int col = ((2 * ks + g) ^ rsw) << 3;
@@ -444,7 +463,7 @@ __global__ __launch_bounds__(256, 1) void wide_contract_kernel(ContractArgs a) {
     }
     __syncthreads();
   }
-  float *dst = a.part + ((((int64_t)bh * gridDim.x + chunk) * gridDim.z + blockIdx.z) * 4 + w) * NCB * 1024;
+  float *dst = a.part + ((((int64_t)bh * a.n_chunks + chunk) * n_slab + slab) * 4 + w) * NCB * 1024;
 #pragma unroll
   for (int i = 0; i < NCB; ++i)
 #pragma unroll
@@ -553,7 +572,9 @@ template <int BSRC>
 static hipError_t contract_and_reduce(const Plan &pl, ContractArgs c, int n_chunks, bool per_head, float *mat, float *vec,
                                       hipStream_t st) {
   const int BH = pl.B * pl.H;
-  dim3 grid(n_chunks, BH, (c.WA / 128) * (c.WB / 128));
+  c.n_chunks = n_chunks;
+  c.BH = BH;
+  const unsigned grid = (unsigned)n_chunks * BH * (c.WA / 128) * (c.WB / 128);
   if (pl.f32) wide_contract_kernel<BSRC, true><<<grid, 256, 0, st>>>(c);
   else wide_contract_kernel<BSRC, false><<<grid, 256, 0, st>>>(c);
   hipError_t e = hipGetLastError();
