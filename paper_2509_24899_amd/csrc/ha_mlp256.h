@@ -72,36 +72,36 @@ static __device__ __forceinline__ void mlp256_hidden_block(lds_frag_ptr sl, cons
 }
 
 // The output stage in place: positive activation over all channels, slice powers.  ACT0: softmax over the channels; otherwise
-// `act` picks exp (1) or ReLU.  P2: the degree is 2, the paper's default.  The exponentials are rounded to bf16 as they are
-// formed and phi once more behind the powers, as in the tile-wise form (feature_layer2_phi) that the variants' epilogue
-// uses: the operator and its variants round alike.
+// `act` picks exp (1) or ReLU.  P2: the degree is 2, the paper's default.  Tile by tile against the running maximum, the
+// exponentials rounded to bf16 as they are formed and phi once more behind the powers: value for value what the tile-wise form
+// (feature_layer2_phi_tiles, feature_phi_finish) does, which the variants' epilogue uses.
 template <bool ACT0, bool P2>
 static __device__ __forceinline__ void phi256_output(f32x16 (&u)[8], int act, int P) {
+  float factor[8];
   if constexpr (ACT0) {
-    float m = u[0][0];
+    float m_run = -INFINITY, sum = 0.f;
 #pragma unroll
-    for (int fb = 0; fb < 8; ++fb)
+    for (int fb = 0; fb < 8; ++fb) {
+      float t = u[fb][0];
 #pragma unroll
-      for (int x = 0; x < 16; x += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, u[fb][x]), u[fb][x + 1]);
-    const float off = -xhalf_max(m) * kLog2e;
-    float sum0 = 0.f, sum1 = 0.f;
-#pragma unroll
-    for (int fb = 0; fb < 8; ++fb)
+      for (int x = 1; x < 16; ++x) t = fmaxf(t, u[fb][x]);
+      const float m_new = fmaxf(m_run, xhalf_max(t));
+      sum *= fast_exp2((m_run - m_new) * kLog2e);         // exp2(-inf) = 0 on the first tile
+      const float off = -m_new * kLog2e;
 #pragma unroll
       for (int x = 0; x < 16; x += 2) {
-        u[fb][x] = fast_exp2(__builtin_fmaf(u[fb][x], kLog2e, off));
-        u[fb][x + 1] = fast_exp2(__builtin_fmaf(u[fb][x + 1], kLog2e, off));
-        sum0 += u[fb][x];
-        sum1 += u[fb][x + 1];
-        const unsigned p = pack_bf16(u[fb][x], u[fb][x + 1]);
+        const float e0 = fast_exp2(__builtin_fmaf(u[fb][x], kLog2e, off)), e1 = fast_exp2(__builtin_fmaf(u[fb][x + 1], kLog2e, off));
+        sum += e0;
+        sum += e1;
+        const unsigned p = pack_bf16(e0, e1);
         u[fb][x] = __uint_as_float(p << 16);
         u[fb][x + 1] = __uint_as_float(p & 0xffff0000u);
       }
-    const float inv = 1.0f / xhalf_sum(sum0 + sum1);
+      factor[fb] = m_run = m_new;
+    }
+    const float inv = 1.0f / xhalf_sum(sum);
 #pragma unroll
-    for (int fb = 0; fb < 8; ++fb)
-#pragma unroll
-      for (int x = 0; x < 16; ++x) u[fb][x] *= inv;
+    for (int fb = 0; fb < 8; ++fb) factor[fb] = fast_exp2((factor[fb] - m_run) * kLog2e) * inv;
   } else {
 #pragma unroll
     for (int fb = 0; fb < 8; ++fb)
@@ -110,19 +110,25 @@ static __device__ __forceinline__ void phi256_output(f32x16 (&u)[8], int act, in
   }
 #pragma unroll
   for (int fb = 0; fb < 8; ++fb) {
+    if constexpr (ACT0) {
+#pragma unroll
+      for (int x = 0; x < 16; ++x) u[fb][x] *= factor[fb];
+    }
     if constexpr (P2) {                                   // the upper half of the channels is squared
       if (fb >= 4)
 #pragma unroll
         for (int x = 0; x < 16; ++x) u[fb][x] *= u[fb][x];
     } else {
 #pragma unroll
-      for (int x = 0; x < 16; ++x) {
-        const int extra = ((32 * fb + 8 * (x >> 2)) * P) / 256;          // slice = power - 1 in 0 .. 7; wave-uniform
-        const float t0 = u[fb][x], t2 = t0 * t0;
-        float y = (extra & 1) ? t2 : t0;
-        y = (extra & 2) ? y * t2 : y;
-        y = (extra & 4) ? y * (t2 * t2) : y;
-        u[fb][x] = y;
+      for (int q = 0; q < 4; ++q) {
+        const int extra = ((32 * fb + 8 * q) * P) / 256;  // slice = power - 1 in 0 .. 7; wave-uniform
+        const float t0 = u[fb][4 * q], t1 = u[fb][4 * q + 1], t2 = u[fb][4 * q + 2], t3 = u[fb][4 * q + 3];
+        for (int i = 0; i < extra; ++i) {
+          u[fb][4 * q] *= t0;
+          u[fb][4 * q + 1] *= t1;
+          u[fb][4 * q + 2] *= t2;
+          u[fb][4 * q + 3] *= t3;
+        }
       }
     }
   }

@@ -62,3 +62,16 @@ def test_fixed_workspace_gives_the_same_bits(N):
     ha.hybrid_attn_forward_static(q, k, v, fq, fk, w.R, out, 128, w.scale)
     torch.cuda.synchronize()
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("P", (1, 2, 4))
+@pytest.mark.parametrize("dtype", ("bf16", "f32"))
+def test_features_round_as_in_the_variants(P, dtype):
+    """At rate 0 the last chunk of the chunk-causal variant sees what every query of the plain operator sees, through states
+    that are summed in the same order; its epilogue evaluates phi_q tile by tile.  Same features, same bits."""
+    w = work(1024, R=0, dtype=dtype, P=P, seed=11 + P)
+    q, k, v, fq, fk = ha.to_device(W.make_inputs(w))
+    plain = ha.hybrid_attn_forward(q, k, v, fq, fk, 0, 128, w.scale)
+    causal = ha.hybrid_attn_forward(q, k, v, fq, fk, (0, 0, 256), 128, w.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(plain[:, :, 768:], causal[:, :, 768:])
