@@ -489,7 +489,9 @@ __global__ __launch_bounds__(64 * NW, 2) void query_kernel_ring(QueryArgs a) {
     ring_barrier(Fa{});   // everything landed and read: the ring is free for the epilogue
     // express the accumulators against the exact c_i (Eq. "hybrid": the largest softmax weight is 1)
     m_true = xhalf_max(m_true);
-    const float alpha = fast_exp2((m - m_true) * c);
+    // (a range in which every logit of a query is -inf has no maximum; its sums are zero, and the merging pass, which has
+    // the other ranges' maxima, gives it weight zero)
+    const float alpha = MODE == 3 && m_true == -INFINITY ? 1.f : fast_exp2((m - m_true) * c);
     lsum = lacc[0] * alpha;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)

@@ -43,6 +43,19 @@ def test_one_key_far_above_the_others(at):
     check(f"ks_peak_{at}", inp, rows=W.sample_rows(w, n_random=64))
 
 
+@pytest.mark.parametrize("lo,hi", ((0.0, 0.5), (0.3, 0.7), (0.6, 1.0)))
+@pytest.mark.parametrize("N,R,width,dtype", ((2000, 1, 128, "bf16"), (2000, 1, 128, "f32"), (20000, 4, 128, "bf16"), (20000, 4, 256, "bf16"), (20000, 4, 384, "f32")))
+def test_ranges_whose_every_logit_is_minus_infinity(N, R, width, dtype, lo, hi):
+    """Keys masked with values whose products with the queries overflow to -inf, whole ranges of them: weight zero, as in
+    one range."""
+    w = work(N, R, width, H=1, dtype=dtype, seed=N + R, gain=128 ** 0.5)
+    inp = W.make_inputs(w)
+    inp.q[:] = W.round_to_bf16(np.abs(inp.q) + 1)
+    a, b = (int(x * N) // R * R for x in (lo, hi))
+    inp.k[:, :, a:b:R] = W.round_to_bf16(np.float32([-3e38]))[0]
+    check(f"ks_masked_N{N}_R{R}_F{width}_{a}_{b}", inp, rows=np.arange(0, N, N // 40))
+
+
 @pytest.mark.parametrize("width", (128, 256))
 def test_row_denominators(width):
     inp = W.make_inputs(work(1500, 2, width, seed=6, gain=128 ** 0.5))
