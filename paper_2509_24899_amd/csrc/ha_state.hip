@@ -182,11 +182,12 @@ __global__ __launch_bounds__(512, 1) void state_pipelined_kernel(const void *__r
           for (int x = 0; x < 16; ++x) u[fb][x] *= rs;
       }
       if (t0 + TOK > lt_end) {                        // ragged end of the range: padded tokens add nothing
-        const float keep = t0 + tf < lt_end ? 1.f : 0.f;
+        // (by selection: a padded row may be a token of the next causal chunk, whose features need not be finite)
+        const bool keep = t0 + tf < lt_end;
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
-          for (int x = 0; x < 16; ++x) u[fb][x] *= keep;
+          for (int x = 0; x < 16; ++x) u[fb][x] = keep ? u[fb][x] : 0.f;
       }
       // ---------------- phi -> LDS, row-major: registers 4 q .. 4 q + 3 of tile fb are channels 32 fb + 8 q + 4 g .. + 3
       typedef unsigned u32x2 __attribute__((ext_vector_type(2)));

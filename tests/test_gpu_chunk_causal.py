@@ -86,3 +86,19 @@ def test_headline_shape_chunk_causal_sampled_rows():
     inp = W.make_inputs(wl)
     rows = np.unique(np.concatenate([np.array([0, 255, 4095, 4096, 8191, 8192, 28671, 28672, 32759]), W.sample_rows(wl, n_random=40)]))
     causal_case("causal_headline_R4_C4096", inp, 4, 4096, rows=rows)
+
+
+@pytest.mark.parametrize("act,value", [(ha.HA_ACT_EXP, 1e3), (ha.HA_ACT_EXP, 1e30), (ha.HA_ACT_RELU, 3e38), (ha.HA_ACT_SOFTMAX, float("inf"))])
+@pytest.mark.parametrize("d,width,dtype", [(64, 64, "bf16"), (128, 128, "bf16"), (128, 128, "f32"), (128, 256, "bf16"), (128, 256, "f32")])
+def test_a_later_key_that_overflows_leaves_earlier_chunks_alone(d, width, dtype, act, value):
+    """Chunks of 512 tokens hold 341 linear ones at R = 3: the last 128-token tile of a chunk's state pass is filled up
+    with tokens of the next chunk, here with features that are not finite."""
+    w = W.Workload("causal_overflow", 1, 2, 1100, d, dtype, 128, 3, width, width, seed=60, qk_gain=float(d ** 0.5))
+    q, k, v, fq, fk = ha.to_device(W.make_inputs(w))
+    fq.out_act = fk.out_act = act
+    before = ha.hybrid_attn_forward(q, k, v, fq, fk, (3, 0, 512), 128, w.scale)
+    k[:, :, 514:560] = value
+    after = ha.hybrid_attn_forward(q, k, v, fq, fk, (3, 0, 512), 128, w.scale)
+    torch.cuda.synchronize()
+    assert torch.isfinite(before).all()
+    assert torch.equal(before[:, :, :512], after[:, :, :512])
