@@ -125,6 +125,11 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
   pl.KT = p.block_size;
   pl.n_ktiles = (pl.NS + pl.KT - 1) / pl.KT;
   pl.n_kblocks = pl.n_ktiles * (pl.KT / 32);
+  {
+    const size_t block = (size_t)pl.B * pl.H * 2 * 32 * pl.D * 2;      // 32 keys and values of every (batch, head)
+    pl.key_pad_64 = block * (pl.n_kblocks - (pl.NS + 63) / 64 * 2);
+    pl.key_pad_128 = block * ((pl.NS + 127) / 128 * 4 - pl.n_kblocks);
+  }
   // state pass: one workgroup per CU (256 CUs) in a single round when there is enough work,
   // chunks are whole 128-token tiles
   {
@@ -178,10 +183,9 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
   // for few heads, whose operands all workgroups share (whole calls, epilogue / pass, us, R = 4: H = 1, N = 2000  38.5 / 36.0,
   // 8000  69.5 / 51.0, 20000  127 / 90; H = 2, N = 5000  55.6 / 49.4; H = 5, N = 3000  48.8 / 44.4), and not for many
   // (H = 12, N = 1560  42.9 / 42.7, 2600  49.4 / 51.0; H = 24, N = 1000  41.5 / 44.0; at R = 16 up to 9 % worse), nor once
-  // 128-query tiles are more than one per CU.  The rule must not depend on the workspace (results are equal bit for bit
-  // with one of fixed size), so its results have to fit the static one if the rest does.
+  // 128-query tiles are more than one per CU.
   if (plain && pl.HD == 128 && pl.F == 128 && pl.NS > 0 && BH <= 5 && ((size_t)pl.N + 127) / 128 * BH <= 256 &&
-      (off + tiles * tile <= kStaticScratchBytes || off > kStaticScratchBytes))
+      route_has_room(pl, off, tiles * tile))
     pl.split_linear = true;
   if (pl.split_linear) {
     pl.lin_rows = pl.N;
@@ -246,19 +250,13 @@ static size_t full_plan(const ha_problem &p, const ha_feature_map *phi_q, const 
     make_wide_plan(pl, pl.total, wp, false);
     total = wp.total;
   }
-  // the partial sums of split key ranges.  Whether the keys are split must not depend on the workspace (results are equal
-  // bit for bit with a workspace of fixed size), so where a problem would fit the static one, its partial sums have to fit
-  // it as well.
+  // the partial sums of split key ranges, next to the linear pass's results (which a fixed workspace may hold in the state
+  // partials' place, a part of the queries at a time: see make_plan; the keys are in one range then)
+  const size_t BH = (size_t)pl.B * pl.H, rows = BH * ((pl.N + 255) / 256) * 256;
+  const size_t lin = pl.split_linear ? rows * (pl.D + 1) * 4 : 0, per = rows * (pl.D + 2) * 4;
+  const size_t base = lin && pl.off_lin != pl.off_part ? total - lin : total;
   pl.n_split = choose_split(pl, wide || pl.split_linear);
-  const size_t BH = (size_t)pl.B * pl.H, per = BH * ((pl.N + 255) / 256) * 256 * (pl.D + 2) * 4;
-  if (total <= kStaticScratchBytes)
-    while (pl.n_split > 1 && total + pl.n_split * per > kStaticScratchBytes) --pl.n_split;
-  if (pl.split_linear && pl.F == 256) {
-    // (with the linear pass's results in the partials' place, a part at a time, there is no room: see make_plan)
-    const size_t lin = BH * ((pl.N + 255) / 256) * 256 * (pl.D + 1) * 4;
-    const size_t least = pl.off_lin == pl.off_part ? total : total - lin;
-    if (least <= kStaticScratchBytes && least + lin > kStaticScratchBytes) pl.n_split = 1;
-  }
+  while (pl.n_split > 1 && !route_has_room(pl, base, lin + pl.n_split * per)) --pl.n_split;
   if (pl.n_split > 1) {
     pl.n_tb_split = (pl.N + 255) / 256 * 8;
     pl.off_po = total;

@@ -35,6 +35,8 @@ struct Plan {
   // range (see SplitArgs): blocks of 32 queries per (batch, head), images, maxima and sums
   int n_split, n_tb_split;
   size_t off_po, off_pm, off_pl;
+  // bytes by which the key fragments are larger than with block_size 64, and smaller than with 128
+  size_t key_pad_64, key_pad_128;
 };
 
 // Partial sums of the softmax loop over one of n_split key ranges, per (range, batch, head): the accumulators as fp32 register
@@ -99,6 +101,12 @@ static inline bool query_side_is_linear(const Plan &pl) {
 // results of the 256-wide maps' linear pass (516 bytes per query and head) do not fit it, they take the place of the state
 // partials, which are spent by then, as many queries at a time as that holds.
 constexpr size_t kStaticScratchBytes = (size_t)HA_STATIC_SCRATCH_MIB << 20;
+// Whether a plan of `base` bytes may take a route that needs `extra` more.  A call has the same bits with a workspace of any
+// size and with the static one, and with either block_size, so the answer must be the same in all four: a problem that fits
+// the static array with one of the block sizes has to fit it with both, the extra included.
+static inline bool route_has_room(const Plan &pl, size_t base, size_t extra) {
+  return base - pl.key_pad_64 > kStaticScratchBytes || base + pl.key_pad_128 + extra <= kStaticScratchBytes;
+}
 void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl, size_t limit = SIZE_MAX);
 
 // Kernel launchers (ha_kernels.hip).  Each enqueues on `st` and returns the launch status.

@@ -346,3 +346,20 @@ def test_binding_checks_feature_map_tensors_against_the_problem():
     q = torch.zeros(1, 3, 16, 128, dtype=torch.bfloat16)
     with pytest.raises(ValueError):
         ha._fm_ptr(_cpu_map(H=2), q)
+
+
+@pytest.mark.parametrize("width", (128, 256, 384))
+@pytest.mark.parametrize("R", (1, 2, 3, 4))
+def test_block_size_changes_nothing_but_the_padding_of_the_keys(lib, R, width):
+    """The routes a call takes (linear part as a pass of its own, number of key ranges) show in the size of its workspace.
+    Around the sizes where the 64 MiB of the fixed workspace end, both block sizes plan the same: the sizes differ by the
+    key fragments, padded to whole multiples of block_size, and by nothing else."""
+    fm = _map(width, width, 3) if width == 384 else _map(width, width)
+    maps = (None, None) if R == 1 else (fm, fm)
+    near = {"128-2": range(15300, 15552, 2), "384-2": range(6400, 9602, 7), "384-3": range(12740, 12830)}.get(f"{width}-{R}", ())
+    for H in (1, 2, 3, 5, 12):
+        for N in [*range(129, 34000, 211), *near]:
+            n_s = -(-N // R)
+            pad = H * 2 * 32 * 128 * 2 * (-(-n_s // 128) * 4 - -(-n_s // 64) * 2)
+            small, large = (ha.hybrid_attn_workspace_bytes(_problem(H=H, N=N, R=R, bs=bs), *maps) for bs in (64, 128))
+            assert large - small == pad, (H, N, R, width)

@@ -89,3 +89,19 @@ def test_fixed_workspace_gives_the_same_bits(B, H, N, R, width):
     ha.hybrid_attn_forward_static(q, k, v, *maps, R, out, 128, w.scale)
     torch.cuda.synchronize()
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("N,R,width", ((15362, 2, 128), (15488, 2, 128), (7000, 2, 384), (6402, 2, 384)))
+def test_block_sizes_agree_where_the_fixed_workspace_ends(N, R, width):
+    w = work(N, R, width, seed=N)
+    q, k, v, fq, fk = ha.to_device(W.make_inputs(w))
+    a, b = (ha.hybrid_attn_forward(q, k, v, fq, fk, R, bs, w.scale) for bs in (64, 128))
+    outs = [b]
+    for bs in (64, 128):
+        try:
+            outs.append(ha.hybrid_attn_forward_static(q, k, v, fq, fk, R, torch.full_like(q, float("nan")), bs, w.scale))
+        except ha.HybridAttnError as e:
+            assert e.status == ha.HA_ERR_WORKSPACE
+    torch.cuda.synchronize()
+    for other in outs:
+        assert torch.equal(a, other)
