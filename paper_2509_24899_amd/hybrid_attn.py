@@ -251,7 +251,8 @@ def _alloc_on(stream):
 
 def _stream_handle(stream, tensor) -> int:
     """hipStream_t of the given stream, or of torch's current stream on the tensor's device.  (The current stream's raw
-    handle: building the torch.cuda.Stream object around it costs 1.7 us, as much as the rest of a small call.)"""
+    handle: building the torch.cuda.Stream object around it costs 1.7 us, as much as the rest of a small call.  It takes a
+    CPU tensor's device index, -1, for the current GPU: every caller has refused CPU tensors first.)"""
     return stream.cuda_stream if stream is not None else torch._C._cuda_getCurrentRawStream(tensor.get_device())
 
 
@@ -299,6 +300,7 @@ def hybrid_attn_profile_count() -> int:
 def hybrid_attn_mfma_probe(random_operands: bool, iters: int, launches: int, sink: torch.Tensor) -> float:
     """Enqueue the matrix-core probe on the current stream (see the header); returns the flops of one
     launch.  `sink`: device tensor of at least 2 KiB per compute unit."""
+    _require_gpu(sink)
     flops = ctypes.c_double(0.0)
     st = _lib().hybrid_attn_mfma_probe(int(bool(random_operands)), iters, launches, sink.data_ptr(),
                                        sink.numel() * sink.element_size(), ctypes.byref(flops),

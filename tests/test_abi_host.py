@@ -363,3 +363,18 @@ def test_block_size_changes_nothing_but_the_padding_of_the_keys(lib, R, width):
             pad = H * 2 * 32 * 128 * 2 * (-(-n_s // 128) * 4 - -(-n_s // 64) * 2)
             small, large = (ha.hybrid_attn_workspace_bytes(_problem(H=H, N=N, R=R, bs=bs), *maps) for bs in (64, 128))
             assert large - small == pad, (H, N, R, width)
+
+
+def test_probe_refuses_host_memory(monkeypatch):
+    """The probe's kernel writes through the sink's address: a CPU tensor must not reach the library (a stub here)."""
+    reached = []
+
+    class Stub:
+        def hybrid_attn_mfma_probe(self, *args):
+            reached.append(args)
+            return ha.HA_OK
+    monkeypatch.setattr(ha, "_lib", lambda: Stub())
+    monkeypatch.setattr(ha.torch._C, "_cuda_getCurrentRawStream", lambda device: 0, raising=False)
+    with pytest.raises(RuntimeError):
+        ha.hybrid_attn_mfma_probe(False, 1, 1, ha.torch.zeros(1024))
+    assert not reached
