@@ -477,14 +477,4 @@ static __device__ __forceinline__ void feature_layer2_phi(const bf16x8 (&h_hi)[H
   feature_phi_finish<F>(st, act, P, Dp, phi);
 }
 
-template <int D, int HD, int F, typename WP>
-static __device__ __forceinline__ void feature_mlp(const bf16x8 (&xf)[D / 16], WP w1f,
-                                                   WP w2f, const float *b1,
-                                                   const float *b2, int lane, int g,
-                                                   f32x16 (&u)[F / 32]) {
-  bf16x8 h_hi[HD / 32][2], h_lo[HD / 32][2];
-  feature_mlp_layer1<D, HD>(xf, w1f, b1, lane, g, h_hi, h_lo);
-  feature_mlp_layer2<HD, F>(h_hi, h_lo, w2f, b2, lane, g, u);
-}
-
 }  // namespace ha

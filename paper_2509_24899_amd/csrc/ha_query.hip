@@ -717,7 +717,6 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
   // definition, so block_size decides there; for the plain operator the sizes do.  Query kernel, H = 12, R = 4, in us,
   // 8 waves against 4:
   //   d = 128, 128-wide maps    N = 256: 20 / 24, 1560: 29 / 35, 5003: 55 / 69, 12000: 260 / 258, 32760: 1386 / 1493
-  //   d = 128, 256-wide maps    N = 256: 64 / 73, 5003: 98 / 116, 32760: 1634 / 1701; fp32, B = 2, N = 5003: 198 / 282
   //   d = 64                    N = 256: 12 / 15, 5003 (240 workgroups): 33 / 37, 8000 (384): 79 / 70, 32760: 838 / 818
   //   linear part precomputed   N = 1560: 20 / 16, 3000 (288 small workgroups): 30 / 31, 20000: 546 / 573
   //   R = 1, B H = 10, N = 230 (whole call): 14.6 / 12.3
@@ -748,9 +747,11 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
     } else if (pl.CC > 0) { \
       if (big) query_kernel_ring<DD, HH, FF, 8, 8, 2, F32, false, 1><<<grid, 512, 0, st>>>(a); \
       else query_kernel_ring<DD, HH, FF, 4, 4, 1, F32, false, 1><<<grid, 256, 0, st>>>(a); \
-    } else { \
+    } else if constexpr (HH <= 128) { \
       if (big) query_kernel_ring<DD, HH, FF, 8, 8, 2, F32><<<grid, 512, 0, st>>>(a); \
-      else if constexpr (HH <= 128) query_kernel_ring<DD, HH, FF, 4, 4, 1, F32><<<grid, 256, 0, st>>>(a); \
+      else query_kernel_ring<DD, HH, FF, 4, 4, 1, F32><<<grid, 256, 0, st>>>(a); \
+    } else { \
+      return hipErrorInvalidValue;      /* the plan of the plain operator has the wider maps' linear part precomputed */ \
     } \
   } while (0)
   if (lin) {
