@@ -123,7 +123,10 @@ ha_status hybrid_attn_validate(const ha_problem *p, const ha_feature_map *phi_q,
 
 /* Bytes of device scratch hybrid_attn_forward needs for this problem (0 if the problem does not
  * validate).  Holds the compacted softmax keys / values, the MLP weights in matrix-core operand
- * order, the per-chunk partial states and the reduced state S, z.  Host only. */
+ * order, the per-chunk partial states, the reduced state S, z, and for the query side, where the
+ * linear part is a pass of its own (256-wide and wider maps, small problems), its results, 516 bytes
+ * per query and head, and where the softmax keys are split into ranges (few queries and heads) the
+ * partial sums, 520 bytes per query, head and range.  Host only. */
 size_t hybrid_attn_workspace_bytes(const ha_problem *p, const ha_feature_map *phi_q,
                                    const ha_feature_map *phi_k);
 
@@ -156,7 +159,8 @@ ha_status hybrid_attn_forward_static(const ha_problem *p, const void *q, const v
 
 /* Debug / test taps into the same pipeline: run only the key-side passes (weight re-ordering,
  * softmax-key compaction, state pass) and copy the reduced state out in plain layout.
- * state_S: device fp32 [B, H, F, d_head]; state_z: device fp32 [B, H, F]. */
+ * state_S: device fp32 [B, H, F, d_head]; state_z: device fp32 [B, H, F].  hybrid_attn_workspace_bytes() is enough; what it
+ * counts for the query side (see there) is not needed. */
 ha_status hybrid_attn_linear_state(const ha_problem *p, const void *k, const void *v,
                                    const ha_feature_map *phi_k, float *state_S, float *state_z,
                                    void *workspace, size_t workspace_bytes, void *hip_stream);

@@ -479,7 +479,9 @@ ha_status hybrid_attn_linear_state(const ha_problem *p, const void *k, const voi
   ha::Plan pl;
   ha::WidePlan wp;
   bool wide;
-  const size_t need = ha::full_plan(*p, phi_k, phi_k, pl, wp, wide);
+  ha::full_plan(*p, phi_k, phi_k, pl, wp, wide);
+  // (the query side's buffers come last: the linear part's results, partial sums of key ranges)
+  const size_t need = wide ? wp.off_lin : pl.split_linear ? pl.off_lin : pl.total;
   if (!workspace || workspace_bytes < need) return HA_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return HA_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);

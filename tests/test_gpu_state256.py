@@ -46,3 +46,19 @@ def test_degrees_and_activations(P, act):
 def test_several_tiles_per_chunk_and_more_heads_than_compute_units():
     state(5000, 4, B=2, H=12, seed=1)      # 10 chunks of 3 tiles per head, the last one ragged
     state(300, 2, B=3, H=100, seed=2)
+
+
+@pytest.mark.parametrize("width,H,N", ((256, 12, 3000), (128, 2, 3000), (128, 1, 20000), (384, 1, 12000)))
+def test_workspace_without_the_query_sides_part(width, H, N):
+    """The state tap runs the key side only: a workspace without the linear part's results (516 bytes per query and head)
+    is enough, and nothing behind it is written."""
+    w = W.Workload("s_ws", 1, H, N, 128, "bf16", 128, 4, width, width, poly_degree=3 if width == 384 else 2, seed=N)
+    _, k, v, _, fk = ha.to_device(W.make_inputs(w))
+    S, z = ha.hybrid_attn_linear_state(k, v, fk, 4)
+    need = ha.hybrid_attn_workspace_bytes(ha.make_problem(k, 4, 128, 1.0), fk, fk)
+    small = need - H * -(-N // 256) * 256 * 129 * 4 if width != 384 else need - H * -(-N // 32) * 32 * 128 * 4
+    buf = torch.full((need,), 0x5a, dtype=torch.uint8, device="cuda")
+    S2, z2 = ha.hybrid_attn_linear_state(k, v, fk, 4, workspace=buf[:small])
+    torch.cuda.synchronize()
+    assert torch.equal(S, S2) and torch.equal(z, z2)
+    assert (buf[small:] == 0x5a).all()
