@@ -35,9 +35,13 @@ struct LinearArgs {
   f32x4 *lin;                            // PART: n^T as [B*H][n_tb][D/32][4][64], e as [B*H][N], instead of out
   float *lin_e;
   int n_tb;
+  int per_bh, total;                     // workgroups per (batch, head), and overall
 };
 
-// grid (workgroups per (batch, head), B*H), 8 waves.  ACT0: the output activation is the softmax over the channels; P2: the
+// grid: total, rounded up to a multiple of 8, 8 waves.  Consecutive workgroups of one XCD (blockIdx % 8) share a (batch, head),
+// so that an XCD's L2 fetches the operands of an eighth of the heads and not of all (whole calls at rate 0 with one or two blocks
+// per wave, us, before / after: H = 32, N = 1526  44.4 / 38.9; H = 24, N = 2038  41.0 / 37.4; H = 12, N = 3318  35.7 / 34.3;
+// longer sequences the same).  ACT0: the output activation is the softmax over the channels; P2: the
 // degree is 2, the paper's default (a branch on it here costs a copy of all feature registers).
 template <bool F32, bool ACT0, bool P2, bool PART>
 __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
@@ -47,7 +51,9 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
   __shared__ bf16x8 ops[4 * NOP];                        // W1, W2, S^T hi, S^T lo
   __shared__ __align__(16) float vecs[3 * F];            // b1, b2, z
   __shared__ __align__(16) char stage_all[8 * 32 * PITCH];
-  const int bh = blockIdx.y, h = bh % a.H;
+  const int per_xcd = (a.total + 7) >> 3, logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (logical >= a.total) return;
+  const int bh = logical / a.per_bh, piece = logical % a.per_bh, h = bh % a.H;
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)h * a.sh;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -62,7 +68,7 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
   }
   // blocks of 32 queries of this workgroup, dealt to its waves
   const int nb = (a.N + 31) / 32;
-  const int b_lo = (int)((int64_t)blockIdx.x * nb / gridDim.x), b_hi = (int)((int64_t)(blockIdx.x + 1) * nb / gridDim.x);
+  const int b_lo = (int)((int64_t)piece * nb / a.per_bh), b_hi = (int)((int64_t)(piece + 1) * nb / a.per_bh);
   auto load_q = [&](int blk, bf16x8 (&dst)[KS]) {
     const int qi = min(32 * blk + r, a.N - 1);           // rows past the end repeat the last query and are not stored
 #pragma unroll
@@ -135,7 +141,7 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
     // Output, 64 bytes of every row per pass: registers 4 x .. 4 x + 3 are channels 8 x + 4 g .. + 3 of query r.  The
     // staging area is the wave's own and a wave's LDS instructions execute in order, so the compiler only has to
     // keep the reads behind the writes (and the next pass's writes behind the reads).
-    f32x4 piece[2];
+    f32x4 out_piece[2];
     auto put = [&](int rb, int p, int xl) {
       const int x4 = p * (CPP / 8) + xl;
       const f32x4 y = {n[rb][4 * x4] * inv, n[rb][4 * x4 + 1] * inv, n[rb][4 * x4 + 2] * inv, n[rb][4 * x4 + 3] * inv};
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
     auto take = [&]() {
       asm volatile("" ::: "memory");
 #pragma unroll
-      for (int i = 0; i < 2; ++i) piece[i] = *reinterpret_cast<const f32x4 *>(stage + (16 * i + (lane >> 2)) * PITCH + (lane & 3) * 16);
+      for (int i = 0; i < 2; ++i) out_piece[i] = *reinterpret_cast<const f32x4 *>(stage + (16 * i + (lane >> 2)) * PITCH + (lane & 3) * 16);
       asm volatile("" ::: "memory");
     };
     auto store = [&](int rb, int p) {
@@ -154,7 +160,7 @@ __global__ __launch_bounds__(512, 1) void linear_query_kernel(LinearArgs a) {
       for (int i = 0; i < 2; ++i) {
         const int row = 16 * i + (lane >> 2);
         char *dst = static_cast<char *>(a.out) + (base + (int64_t)(q_first + row) * a.sn + 32 * rb + CPP * p) * ESZ + (lane & 3) * 16;
-        if (q_first + row < a.N) *reinterpret_cast<f32x4 *>(dst) = piece[i];
+        if (q_first + row < a.N) *reinterpret_cast<f32x4 *>(dst) = out_piece[i];
       }
     };
     auto store_part = [&](int rb, int x4) {                 // registers 4 x4 .. 4 x4 + 3 of row block rb
@@ -250,7 +256,9 @@ hipError_t launch_linear_query(const Plan &pl, const void *q, const ha_feature_m
   a.n_tb = pl.n_tb;
   // one workgroup per CU in a single round; short sequences spread over as many of them as they have blocks
   const int nb = (pl.N + 31) / 32, room = 256 / (pl.B * pl.H) > 0 ? 256 / (pl.B * pl.H) : 1;
-  dim3 grid(nb < room ? nb : room, pl.B * pl.H);
+  a.per_bh = nb < room ? nb : room;
+  a.total = a.per_bh * pl.B * pl.H;
+  const int grid = (a.total + 7) / 8 * 8;
 #define HA_LINEAR(F32, PART) \
   do { \
     if (pl.act_q != HA_ACT_SOFTMAX) linear_query_kernel<F32, false, false, PART><<<grid, 512, 0, st>>>(a); \

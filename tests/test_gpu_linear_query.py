@@ -27,6 +27,15 @@ def test_sizes(B, H, N, dtype):
     check("lin", W.make_inputs(work(N, B, H, dtype, seed=N)))
 
 
+@pytest.mark.parametrize("dtype", ("bf16", "f32"))
+@pytest.mark.parametrize("B,H,N", ((1, 7, 97), (1, 32, 1526), (1, 129, 700), (4, 40, 1031), (3, 86, 300), (1, 257, 161)))
+def test_pieces_on_the_eight_chiplets(B, H, N, dtype):
+    """Workgroups are numbered chiplet by chiplet over pieces of heads: totals that are and are not multiples of eight, one
+    workgroup per head (more than 128 heads), and more heads than CUs."""
+    w = work(N, B, H, dtype, seed=N)
+    check("lin_pieces", W.make_inputs(w), rows=np.unique(np.r_[0:N:53, N - 33:N]))
+
+
 @pytest.mark.parametrize("act", (ha.HA_ACT_SOFTMAX, ha.HA_ACT_EXP, ha.HA_ACT_RELU))
 @pytest.mark.parametrize("P", (1, 2, 4, 8))
 def test_degrees_and_activations(P, act):
