@@ -714,27 +714,36 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
   // Two tilings of one computation (every query column sees the same keys in the same order: the same bits): 8 waves x
   // 32 queries with a ring of 8 key blocks and a barrier every 64 keys, one workgroup per CU, or 4 waves x 32 queries
   // with a ring of 4 and a barrier every 32 keys, two workgroups per CU.  The variants' tiles are part of their
-  // definition, so block_size decides there; for the plain operator the sizes do.  Query kernel, H = 12, R = 4, in us,
-  // 8 waves against 4:
-  //   d = 128, 128-wide maps    N = 256: 20 / 24, 1560: 29 / 35, 5003: 55 / 69, 12000: 260 / 258, 32760: 1386 / 1493
-  //   d = 64                    N = 256: 12 / 15, 5003 (240 workgroups): 33 / 37, 8000 (384): 79 / 70, 32760: 838 / 818
-  //   linear part precomputed   N = 1560: 20 / 16, 3000 (288 small workgroups): 30 / 31, 20000: 546 / 573
-  //   R = 1, B H = 10, N = 230 (whole call): 14.6 / 12.3
-  // The 4-wave kernel reads the epilogue's operands from L2 instead of LDS and fetches every key block twice as often;
-  // with d = 64 both are small, and its two independent workgroups per CU fill each other's gaps once there is more
-  // than one round of them.  With the linear part precomputed or absent it has no operands to fetch: it is 5 % slower
-  // over whole rounds of the chip (N = 20000, 32760 above), but a last round of at most one small workgroup per CU takes
-  // 0.6 of a round instead of a whole one (N = 8000, 768 small workgroups: 106 / 117; 12000: 225 / 243), which `few` adds up
-  // in twentieths of a round.
+  // definition, so block_size decides there; for the plain operator the sizes do.
+  //   d = 128, maps in the epilogue: the 4-wave kernel reads their operands from L2 instead of LDS and fetches every key block
+  // twice as often, so it is better only where its last round of workgroups is emptier.  In us: a round of 256 large
+  // workgroups takes 0.50 per key block and 14 beside, one of 512 small ones 0.52 and 24, a last one of at most 256 small ones
+  // 0.30 and 26 (877 problems timed with both, R = 2 .. 16, both dtypes: 63 of them take the small tiles; none is more than
+  // 0.4 % slower than with large ones throughout, none more than 2.3 % than with small ones).  Whole calls, large / small:
+  // H = 10, N = 6500, R = 2 (260 / 510 workgroups) 196 / 149; H = 20, N = 3200, R = 4 (260 / 500) 94 / 81; H = 12, N = 5504, R = 2
+  // (264 / 516) 175 / 175; H = 64, N = 5556, R = 2 (1408 / 2816) 577 / 614.  Within one round of large ones they are better.
+  //   d = 128, linear part precomputed or absent: no operands to fetch.  In hundredths of a key block a round of large workgroups
+  // takes 100 per block, one of small ones 105, a last one of at most 256 small ones 65; a short loop's start costs the large
+  // ones 65 more, and 250 with every further round (small workgroups start where one has ended).  (660 problems timed with both:
+  // the choice is on average 0.1 % off the better one, at most 4.6 %.)  Large / small, R = 1: H = 250, N = 457 (500 / 1000)
+  // 71.7 / 63.6; H = 100, N = 494 (200 / 400) 32.7 / 34.6; H = 128, N = 268 (256 / 384) 35.2 / 33.3; H = 86, N = 3975, fp32
+  // (1376 / 2752) 725 / 759; 256-wide maps: H = 48, N = 4818, R = 16 (912 / 1824) 342 / 323.
+  //   d = 64: everything is small, and two independent workgroups per CU fill each other's gaps once there is more than one round
+  // of large ones (R = 2 .. 16: large takes 0.85 - 0.97 of small's time within one round of them, 0.96 - 1.24, on average 1.06, beyond),
+  // or where small ones are at most one per CU and the loop is long (H = 1, N = 18432, R = 2, fp32: 154 / 139; 64 key blocks
+  // and less: 0.87 - 1.04).
   const auto wgs = [&](int qt) { return (int64_t)((pl.N + qt - 1) / qt) * pl.B * pl.H; };
+  const int64_t nblk = (pl.NS + 31) / 32, rounds = (wgs(256) + 255) / 256, full = wgs(128) / 512, tail = wgs(128) % 512;
   bool big;
   if (pl.LW > 0 || pl.CC > 0) big = pl.KT == 128;
   else if ((lin || pl.NL == 0) && (pl.D == 128 || wgs(128) <= 256)) {
-    const int64_t tail = wgs(128) % 512;
-    const int64_t few = wgs(128) / 512 * 21 + (tail == 0 ? 0 : tail <= 256 ? 13 : 21);
-    big = (wgs(256) + 255) / 256 * 20 <= few;
-  } else if (pl.D == 64) big = wgs(256) <= 256;
-  else big = true;
+    const int64_t len = nblk > 0 ? nblk : 1024;              // (rate 0: the rounds alone count)
+    big = rounds * (100 * len + 250) - 185 <= full * 105 * len + (tail == 0 ? 0 : tail <= 256 ? 65 : 105) * len;
+  } else if (pl.D == 64) big = wgs(256) <= 256 && (wgs(128) > 256 || nblk <= 64);
+  else {
+    const int64_t last = tail == 0 ? 0 : tail <= 256 ? 30 * nblk + 2600 : 52 * nblk + 2400;
+    big = wgs(256) <= 256 || rounds * (50 * nblk + 1400) <= full * (52 * nblk + 2400) + last;
+  }
   const int qt = big ? 256 : 128;
   a.n_qtiles = (pl.N + qt - 1) / qt;
   a.total_wg = a.n_qtiles * pl.B * pl.H;

@@ -34,3 +34,39 @@ def test_both_sides_of_the_tiling_rules(d, width, H, N, dtype):
     y64, _ = check(w.name + "_bs64", inp, block_size=64, rows=rows)
     y128, _ = check(w.name + "_bs128", inp, block_size=128, rows=rows)
     assert np.array_equal(y64, y128)
+
+
+# d = 128 with the maps in the epilogue: small tiles where the large ones' last round is nearly empty (260 / 510 and 520 / 1020
+# workgroups; 260 / 520 stays large), rate 1 with short loops and many heads (500 / 1000, 384), d = 64 with a long loop and
+# few workgroups (84 small ones)
+@pytest.mark.parametrize("d,width,H,N,R", ((128, 128, 10, 6500, 2), (128, 128, 20, 6500, 4), (128, 128, 10, 6656, 2), (128, 0, 250, 457, 1),
+                                           (128, 0, 128, 300, 1), (128, 256, 48, 1200, 16), (64, 64, 1, 10722, 2), (64, 64, 2, 17000, 4)))
+@pytest.mark.parametrize("dtype", ("bf16", "f32"))
+def test_emptier_last_rounds(d, width, H, N, R, dtype):
+    width = width or d
+    w = W.Workload(f"tiling2_d{d}_F{width}_H{H}_N{N}_{dtype}", 1, H, N, d, dtype, 64, R, width, width, seed=N)
+    check(w.name, W.make_inputs(w), rows=np.unique(np.r_[0, 127, 128, 255, 256, N // 2, N - 130:N - 126, N - 1]))
+
+
+def test_one_more_row_of_tiles_is_not_one_more_round():
+    """250 workgroups of 256 queries are one round on 256 CUs (122 us).  1.6 % more queries make 260 of them, a second round for
+    ten (194 us, 1.57 times as long), or 510 of 128, one round of two per CU (145 us; by the cost model of the rule, 7.7 against
+    6.4 units for the kernel, 1.20).  The medians of one process are compared; the line lies halfway between 1.20 and 1.57."""
+    from paper_2509_24899_amd import hybrid_attn as ha
+    times = []
+    for N in (6400, 6500):
+        w = W.Workload("rounds", 1, 10, N, 128, "bf16", 64, 2, 128, 128, seed=1)
+        q, k, v, fq, fk = ha.device_inputs(w)
+        out = torch.empty_like(q)
+        ws = torch.empty(ha.hybrid_attn_workspace_bytes(ha.make_problem(q, 2, 64, w.scale), fq, fk), dtype=torch.uint8, device="cuda")
+        ms = []
+        for i in range(25):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(8):
+                ha.hybrid_attn_forward(q, k, v, fq, fk, 2, 64, w.scale, out=out, workspace=ws)
+            b.record()
+            b.synchronize()
+            ms.append(a.elapsed_time(b))
+        times.append(float(np.median(ms[5:])))
+    assert times[1] < 1.38 * times[0], times
