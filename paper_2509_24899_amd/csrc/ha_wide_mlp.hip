@@ -32,7 +32,8 @@ struct WideMlpArgs {
   float *out_stat;               // last layer: [bh][tb][128-channel block][2][64] maximum and sum of exponentials
   int H, K, NOUT, n_tok, n_tb, R, G;
   int ob_first, n_ob;            // first output tile, blocks of NT tiles
-  int n_tiles, total;            // 256-token tiles per (batch, head), items overall
+  int n_tiles;                   // 256-token tiles per (batch, head)
+  int first, total;              // items of this launch
   int64_t sb, sh, sn;
 };
 
@@ -50,7 +51,7 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nwg = gridDim.x;                                                   // a multiple of 8
   const int wg = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
-  const int i_lo = (int)((int64_t)wg * a.total / nwg), i_hi = (int)((int64_t)(wg + 1) * a.total / nwg);
+  const int i_lo = a.first + (int)((int64_t)wg * a.total / nwg), i_hi = a.first + (int)((int64_t)(wg + 1) * a.total / nwg);
   if (i_lo >= i_hi) return;
   const int KB = a.K / 32, OB = a.NOUT / 32;                                   // KB: a multiple of 4
   const int per_head = a.n_tiles * a.n_ob;
@@ -236,24 +237,44 @@ hipError_t launch_wide_mlp(const Plan &pl, const WideMlpLayer &l, hipStream_t st
   a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
   a.n_tiles = (a.n_tb + 7) / 8;
   const int src = !l.x ? 2 : pl.f32 ? 1 : 0;
-  // Blocks of eight output tiles, then a block of four where the width is an odd multiple of 128; blocks of four
-  // throughout where those of eight would not give every CU a workgroup: twice the workgroups with half the work per step,
-  // and one launch (384-wide two-layer maps, R = 4, whole forward: H = 1, N = 2000 165 -> 112 us; H = 12, N = 2600 218 -> 194).
-  const int OB = a.NOUT / 32;
-  const bool small = (int64_t)a.n_tiles * (OB / 8) * pl.B * pl.H < 256;
-  for (int nt : {8, 4}) {
-    a.ob_first = nt == 8 || small ? 0 : OB / 8 * 8;
-    a.n_ob = nt == 8 ? (small ? 0 : OB / 8) : (OB - a.ob_first) / 4;
-    if (a.n_ob == 0) continue;
-    if (nt == 4 && a.ob_first > 0) a.h_hi = nullptr;                           // written with the first block
-    a.total = a.n_tiles * a.n_ob * pl.B * pl.H;
+  // Blocks of eight output tiles, or of four, or both: a workgroup takes whole items, so the time goes in rounds of 256 of
+  // them.  A round takes 20 units with blocks of eight, 13 with blocks of four (the first hidden layer and the barriers are not
+  // halved), a second launch 4.  Where the width is an odd multiple of 128 the last block is one of four in any case, in a
+  // launch of its own unless all are; otherwise the items beyond the last whole round may be halved and go second (item i of
+  // eight tiles is items 2 i and 2 i + 1 of four).  Whole forwards at rate 0, blocks of eight / four, us: 768-wide two-layer maps,
+  // 40 tiles (120 items of eight) 193 / 168, 60 tiles (180) 208 / 236, 129 tiles (387) 336 / 398; 512-wide three-layer maps, 129
+  // tiles (258) 371 / 358, 200 tiles (400) 412 / 484; 640-wide, 60 tiles (120 + 60) 243 / 207, 110 tiles (220 + 110) 276 / 290,
+  // 140 tiles (280 + 140) 351 / 293.
+  struct Launch { int nt, ob_first, n_ob, first, total; } launches[2];
+  int n_launches = 0;
+  {
+    const int OB = a.NOUT / 32, tiles = a.n_tiles * pl.B * pl.H, i8 = tiles * (OB / 8), i4 = tiles * (OB / 4), rest = i8 % 256;
+    const auto rounds = [](int items) { return (items + 255) / 256; };
+    const int fours = rounds(i4) * 13, eights = rounds(i8) * 20 + (OB % 8 ? rounds(tiles) * 13 + 4 : 0);
+    const bool halve = OB % 8 == 0 && i8 > 256 && rest > 0;
+    const int both = halve ? i8 / 256 * 20 + rounds(2 * rest) * 13 + 4 : eights;
+    if (OB < 8 || fours < (both < eights ? both : eights)) {
+      launches[n_launches++] = {4, 0, OB / 4, 0, i4};
+    } else if (both < eights) {
+      launches[n_launches++] = {8, 0, OB / 8, 0, i8 - rest};
+      launches[n_launches++] = {4, 0, OB / 4, 2 * (i8 - rest), 2 * rest};
+    } else {
+      launches[n_launches++] = {8, 0, OB / 8, 0, i8};
+      if (OB % 8) launches[n_launches++] = {4, OB / 8 * 8, 1, 0, tiles};
+    }
+  }
+  for (int i = 0; i < n_launches; ++i) {
+    a.ob_first = launches[i].ob_first;
+    a.n_ob = launches[i].n_ob;
+    a.first = launches[i].first;
+    a.total = launches[i].total;
     const int nwg = a.total < 256 ? (a.total + 7) / 8 * 8 : 256;               // one workgroup per CU
 #define HA_WIDE_MLP(NT, SRC) \
   do { \
     if (l.out_u) wide_mlp_kernel<NT, SRC, true><<<nwg, 512, 0, st>>>(a); \
     else wide_mlp_kernel<NT, SRC, false><<<nwg, 512, 0, st>>>(a); \
   } while (0)
-    if (nt == 8) { if (src == 0) HA_WIDE_MLP(8, 0); else if (src == 1) HA_WIDE_MLP(8, 1); else HA_WIDE_MLP(8, 2); }
+    if (launches[i].nt == 8) { if (src == 0) HA_WIDE_MLP(8, 0); else if (src == 1) HA_WIDE_MLP(8, 1); else HA_WIDE_MLP(8, 2); }
     else { if (src == 0) HA_WIDE_MLP(4, 0); else if (src == 1) HA_WIDE_MLP(4, 1); else HA_WIDE_MLP(4, 2); }
 #undef HA_WIDE_MLP
     const hipError_t e = hipGetLastError();

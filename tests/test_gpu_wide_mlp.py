@@ -7,6 +7,7 @@ Tolerance: the bars of test_gpu_parity.py."""
 import numpy as np
 import pytest
 import torch
+import torch
 
 from paper_2509_24899_amd import workloads as W
 from test_gpu_parity import check
@@ -35,3 +36,58 @@ def test_token_counts(N, mid):
 def test_many_heads():
     w = work(300, 384, 512, 256, 4, H=60, B=3, R=2, seed=9)
     check(w.name, W.make_inputs(w), rows=np.arange(0, 300, 7))
+
+
+# Work items (256 tokens x 256 channels) around whole rounds of 256: 258 = a round and two items halved (three layers: from x and
+# from HBM), 288 and 264 with more of them, 180 (one round, not halved), 270 + 135 (odd multiple of 128: blocks of four throughout)
+@pytest.mark.parametrize("B,H,N,hid,feat,mid,R", ((1, 3, 10808, 512, 512, 512, 0), (2, 12, 789, 768, 768, 768, 4), (1, 12, 5503, 384, 256, 0, 8),
+                                                  (1, 3, 5000, 768, 768, 0, 4), (1, 3, 11400, 640, 640, 0, 0)))
+@pytest.mark.parametrize("dtype", ("bf16", "f32"))
+def test_items_beyond_whole_rounds(B, H, N, hid, feat, mid, R, dtype):
+    w = work(N, hid, feat, mid, {256: 2, 512: 4, 640: 4, 768: 6}[feat], H=H, B=B, R=R, dtype=dtype, seed=N)
+    check(w.name, W.make_inputs(w), rows=np.unique(np.r_[0, 255, 256, N // 2, N - 257:N - 255, N - 1]))
+
+
+def test_hidden_image_of_halved_items():
+    """The backward pass of the 256-wide maps reads the first hidden layer as the layer kernel left it: 264 items for twelve
+    heads (eight of them halved) against 22 for one head on its own (blocks of four throughout): the same gradients up to the order
+    of fp32 sums (other chunks of tokens; the bar of the headline gradient test)."""
+    from paper_2509_24899_amd import hybrid_attn as ha
+    w = work(5503, 256, 256, H=12, R=4, seed=5)
+    q, k, v, fq, fk = ha.device_inputs(w)
+
+    def grads(a, b):
+        def sl(m):
+            return ha.FeatureMap(*(t[a:b].contiguous() for t in (m.w1, m.b1, m.w2, m.b2)), m.poly_degree)
+        yt = torch.zeros_like(q[:, a:b])
+        return ha.hybrid_attn_value_distill_grad(q[:, a:b], k[:, a:b], v[:, a:b], sl(fq), sl(fk), 4, 128, w.scale, y_teacher=yt, teacher_is_cached=True)[1:3]
+    every = grads(0, 12)
+    for h in (0, 7, 11):
+        for m, one in zip(every, grads(h, h + 1)):
+            for n in one:
+                x, y = m[n][h].double(), one[n][0].double()
+                assert float((x - y).norm() / y.norm()) <= 1e-4, (h, n)
+
+
+def test_a_second_round_of_small_items_is_not_taken():
+    """768-wide maps, one head: 40 tiles of tokens are 240 items with blocks of four output tiles, one round on 256 CUs (168 us).
+    44 tiles are 264 of them, a second round (236 us, 1.41 times as long), or 132 with blocks of eight (202 us, 1.20).  The medians
+    of one process are compared; the line lies halfway."""
+    from paper_2509_24899_amd import hybrid_attn as ha
+    times = []
+    for N in (10232, 11256):
+        w = work(N, 768, 768, H=1, R=0, seed=1)
+        q, k, v, fq, fk = ha.device_inputs(w)
+        out = torch.empty_like(q)
+        ws = torch.empty(ha.hybrid_attn_workspace_bytes(ha.make_problem(q, 0, 128, w.scale), fq, fk), dtype=torch.uint8, device="cuda")
+        ms = []
+        for i in range(25):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(8):
+                ha.hybrid_attn_forward(q, k, v, fq, fk, 0, 128, w.scale, out=out, workspace=ws)
+            b.record()
+            b.synchronize()
+            ms.append(a.elapsed_time(b))
+        times.append(float(np.median(ms[5:])))
+    assert times[1] < 1.305 * times[0], times
