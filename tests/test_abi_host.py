@@ -378,3 +378,43 @@ def test_probe_refuses_host_memory(monkeypatch):
     with pytest.raises(RuntimeError):
         ha.hybrid_attn_mfma_probe(False, 1, 1, ha.torch.zeros(1024))
     assert not reached
+
+
+def key_ranges(H, N, R, width, dtype="bf16"):
+    """Into how many ranges the softmax keys of a d = 128 problem (B = 1, block_size 128) are split, from the size of its
+    workspace: what is left beyond the buffers of the unsplit plan, in partial sums of one range.  0: not a whole number."""
+    fm = _map(width, width, 3) if width == 384 else _map(width, width)
+    need = ha.hybrid_attn_workspace_bytes(_problem(H=H, N=N, R=R, dtype=ha.HA_BF16 if dtype == "bf16" else ha.HA_F32), *((None, None) if R == 1 else (fm, fm)))
+    D, F = 128, 128 if R == 1 else width
+    n_s = -(-N // R)
+    tiles = -(-(N - n_s) // 128)
+    want = min(tiles, max(256 // H, 1))
+    chunks = -(-(N - n_s) // (-(-tiles // want) * 128)) if tiles else 0
+    rows = H * -(-N // 256) * 256
+    sizes = [H * F * D * 2, H * F * F * 2] * 2 + [H * -(-n_s // 128) * 128 * D * 2] * 2
+    sizes += [H * chunks * (F // 32) * 5 * 4096, H * F * D * 4, H * F * 4, H * F * D * 2, H * F * D * 2]
+    n_tb = -(-N // 32)
+    if R > 1 and width == 384:        # layer by layer: weights, pre-activations, statistics, linear part
+        sizes += [H * F * D * 2, H * F * F * 2, H * n_tb * 32 * F * 4, H * n_tb * (F // 128) * 512, H * n_tb * 32 * D * 4, H * N * 4]
+    unsplit = sum((x + 255) // 256 * 256 for x in sizes)
+    per = rows * (D + 2) * 4
+    for lin in (0, rows * (D + 1) * 4):       # the linear part as a pass of its own: always with 256, with 128 for few heads
+        if need == unsplit + lin:
+            return 1
+        if (need - unsplit - lin) % per == 0 and need > unsplit + lin:
+            return (need - unsplit - lin) // per
+    return 0
+
+
+# What test_gpu_key_split.py runs: (N, R, width, H) whose keys are split, with ragged last blocks, ranges, tiles and rows, two to
+# eight ranges, the linear part precomputed by each of the passes that can.
+SPLIT_SHAPES = ((1101, 1, 128, 1), (3001, 1, 128, 1), (1821, 1, 128, 3), (16001, 1, 128, 1), (30003, 1, 128, 1), (8321, 2, 128, 1),
+                (9003, 4, 128, 1), (20001, 4, 128, 1), (6003, 2, 256, 1), (9003, 2, 256, 1), (20001, 4, 256, 1), (3001, 2, 384, 1),
+                (9003, 4, 384, 1), (16001, 2, 384, 2))
+
+
+@pytest.mark.parametrize("dtype", ("bf16", "f32"))
+def test_split_shapes_are_split(lib, dtype):
+    n = [key_ranges(H, N, R, width, dtype) for N, R, width, H in SPLIT_SHAPES]
+    assert set(n) == set(range(2, 9)), n
+    assert key_ranges(12, 32760, 4, 128) == key_ranges(1, 32760, 1, 128) == key_ranges(12, 1560, 4, 256) == 1
