@@ -240,8 +240,10 @@ hipError_t launch_wide_mlp(const Plan &pl, const WideMlpLayer &l, hipStream_t st
   // Blocks of eight output tiles, or of four, or both: a workgroup takes whole items, so the time goes in rounds of 256 of
   // them.  A round takes 20 units with blocks of eight, 13 with blocks of four (the first hidden layer and the barriers are not
   // halved), a second launch 4.  Where the width is an odd multiple of 128 the last block is one of four in any case, in a
-  // launch of its own unless all are; otherwise the items beyond the last whole round may be halved and go second (item i of
-  // eight tiles is items 2 i and 2 i + 1 of four).  Whole forwards at rate 0, blocks of eight / four, us: 768-wide two-layer maps,
+  // launch of its own unless all are; otherwise the items beyond one or two whole rounds may be halved and go second (item i of
+  // eight tiles is items 2 i and 2 i + 1 of four): 1 - 5 % of the forward with 2 .. 128 of them beyond one round, 1 - 3 % beyond
+  // two, nothing or a loss of up to 4 % beyond four, where the workgroups that have one item less leave the others power.  Whole
+  // forwards at rate 0, blocks of eight / four, us: 768-wide two-layer maps,
   // 40 tiles (120 items of eight) 193 / 168, 60 tiles (180) 208 / 236, 129 tiles (387) 336 / 398; 512-wide three-layer maps, 129
   // tiles (258) 371 / 358, 200 tiles (400) 412 / 484; 640-wide, 60 tiles (120 + 60) 243 / 207, 110 tiles (220 + 110) 276 / 290,
   // 140 tiles (280 + 140) 351 / 293.
@@ -251,7 +253,7 @@ hipError_t launch_wide_mlp(const Plan &pl, const WideMlpLayer &l, hipStream_t st
     const int OB = a.NOUT / 32, tiles = a.n_tiles * pl.B * pl.H, i8 = tiles * (OB / 8), i4 = tiles * (OB / 4), rest = i8 % 256;
     const auto rounds = [](int items) { return (items + 255) / 256; };
     const int fours = rounds(i4) * 13, eights = rounds(i8) * 20 + (OB % 8 ? rounds(tiles) * 13 + 4 : 0);
-    const bool halve = OB % 8 == 0 && i8 > 256 && rest > 0;
+    const bool halve = OB % 8 == 0 && i8 > 256 && i8 < 3 * 256 && rest > 0;
     const int both = halve ? i8 / 256 * 20 + rounds(2 * rest) * 13 + 4 : eights;
     if (OB < 8 || fours < (both < eights ? both : eights)) {
       launches[n_launches++] = {4, 0, OB / 4, 0, i4};
