@@ -134,7 +134,12 @@ size_t hybrid_attn_workspace_bytes(const ha_problem *p, const ha_feature_map *ph
  * and return without waiting.  q, k, v: device, read-only.  out: device, written in full.
  * workspace: device, 256-byte aligned, at least hybrid_attn_workspace_bytes() bytes, contents
  * undefined before and after.  out and workspace must not overlap the inputs.  Two calls that
- * share a workspace must be ordered on one stream.  Returns HA_OK once everything is enqueued. */
+ * share a workspace must be ordered on one stream.  Returns HA_OK once everything is enqueued.
+ * A call's result is the same bit for bit every time, whatever the size of the workspace.  The bits of one (batch, head)
+ * may depend on how many stand beside it, to rounding: B H decides how the linear tokens' sums are cut into chunks and,
+ * for five (batch, head) pairs or fewer, which kernel forms the linear part; and below 128 tiles of 256 queries
+ * (B H ceil(N / 256)) into how many ranges the softmax keys are split, as far as the partial sums leave room in
+ * HA_STATIC_SCRATCH_MIB. */
 ha_status hybrid_attn_forward(const ha_problem *p, const void *q, const void *k, const void *v,
                               const ha_feature_map *phi_q, const ha_feature_map *phi_k,
                               void *out, void *workspace, size_t workspace_bytes, void *hip_stream);

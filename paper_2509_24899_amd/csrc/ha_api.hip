@@ -179,11 +179,12 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
   const bool plain = has_linear && pl.DM == 0 && pl.CC == 0 && pl.LW == 0 && pl.D == 128;
   pl.split_linear = plain && pl.HD == 256 && pl.F == 256;
   // With the 128-wide maps the query kernel's epilogue is 11 us at the end of every workgroup; a pass of its own over blocks
-  // of 32 queries is one more launch, but leaves the query kernel free to split the keys and to use small tiles.  That pays
-  // for few heads, whose operands all workgroups share (whole calls, epilogue / pass, us, R = 4: H = 1, N = 2000  38.5 / 36.0,
-  // 8000  69.5 / 51.0, 20000  127 / 90; H = 2, N = 5000  55.6 / 49.4; H = 5, N = 3000  48.8 / 44.4), and not for many
-  // (H = 12, N = 1560  42.9 / 42.7, 2600  49.4 / 51.0; H = 24, N = 1000  41.5 / 44.0; at R = 16 up to 9 % worse), nor once
-  // 128-query tiles are more than one per CU.
+  // of 32 queries is one more launch, but leaves the query kernel free to split the keys and to use small tiles.  Whole calls,
+  // epilogue / pass, us: R = 4, H = 1, N = 2000  38.3 / 35.3; 8000  70 / 50 (keys split; 61 without); 20000  127 / 91 (109); H = 2,
+  // N = 5000  56.0 / 49.6; H = 5, N = 3000  48.5 / 44.0; R = 16  39.1 / 36.0; R = 2  63.2 / 56.1.  From six (batch, head) pairs on it
+  // is a gain at low rates and a loss at high ones: H = 8, N = 3000  R = 2  63.3 / 58.9, R = 4  48.5 / 47.3, R = 16  38.4 / 39.9;
+  // H = 10, N = 3000, R = 16  40.0 / 42.5; H = 12, N = 1560  R = 2  52.2 / 48.7, R = 4  43.5 / 42.2, N = 2600, R = 16  40.0 / 42.6.  Five is the
+  // largest number at which no measured problem loses.  Nor does it pay once 128-query tiles are more than one per CU.
   if (plain && pl.HD == 128 && pl.F == 128 && pl.NS > 0 && BH <= 5 && ((size_t)pl.N + 127) / 128 * BH <= 256 &&
       route_has_room(pl, off, tiles * tile))
     pl.split_linear = true;
@@ -212,17 +213,20 @@ static bool needs_wide_path(const Plan &pl) {
 
 // Into how many ranges the keys of the plain operator's softmax loop are split.  A tile of 256 queries is one workgroup, so
 // a problem of few tiles leaves CUs idle for the whole loop; with n ranges it has n times the workgroups, each with 1 / n
-// of the keys, at the price of a pass that merges the partial sums (516 bytes per query and range written and read).  The
+// of the keys, at the price of a pass that merges the partial sums (520 bytes per query and range written and read).  The
 // estimate, in us, from measured times: a 32-key step takes 0.5 (0.42 in the small tiling of an unsplit problem), the rest
 // of a workgroup 5; the merging pass 5 and its traffic at 4 TB/s.  It has to be 10 % better than one range.  (Where the query
 // kernel would evaluate the maps in its epilogue, there is no pass that could merge.)  Whole calls, one range / split, us:
-//   R = 1:  H = 1, N = 2000  37 / 31;  N = 8000  122 / 55;  N = 20000  289 / 188;  H = 2, N = 5000  81 / 46;  H = 5, N = 3000
-//   55 / 44;  R = 4:  H = 1, N = 20000  126 / 95 (128-wide maps), 135 / 116 (256-wide).
+//   R = 1:  H = 1, N = 2000  37.4 / 23.4;  N = 8000  123 / 49;  N = 20000  291 / 189;  N = 32500  517 / 448;  H = 2, N = 5000  81 / 44;
+//   H = 5, N = 3000  54.7 / 41.9;  R = 4, H = 1:  N = 20000  109 / 91 (128-wide maps), 134 / 115 (256-wide);  N = 8000  61 / 50, 86 / 75.
 static int choose_split(const Plan &pl, bool lin) {
   if (pl.D != 128 || pl.CC > 0 || pl.LW > 0 || pl.NS == 0 || (pl.NL > 0 && !lin)) return 1;
   const double tiles = (double)((pl.N + 255) / 256) * pl.B * pl.H, rows = (double)pl.N * pl.B * pl.H;
-  // From half the CUs on the loop is left whole.  (It would still pay a little at exactly 128 tiles; but there one head of a
-  // long clip, on its own, keeps the bits it has among others, and with them the signs a distillation gradient is made of.)
+  // From half the CUs on the loop is left whole.  Above 128 tiles the estimate is wrong and splitting loses (R = 1, one range /
+  // split: H = 1, N = 33500  601 / 745, 36000  646 / 798, 42000  819 / 937; at other rates the estimate takes one range itself).
+  // At 128 tiles exactly it would gain at R = 1 (H = 1, N = 32760  520 / 450; H = 2, N = 16300  267 / 238; H = 4, N = 8100  142 / 131), which
+  // is given up: one head of a 480p clip (32760 tokens) on its own then has the softmax outputs it has among others, bit for
+  // bit, and with them the signs that a distillation gradient is made of.
   if (tiles >= 128.0) return 1;
   const int nblk = (pl.NS + 31) / 32;
   auto cost = [&](int n) {

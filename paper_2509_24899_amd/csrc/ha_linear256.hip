@@ -11,7 +11,7 @@
 //
 // Bound: matrix cores, 448 instructions of 32 cycles per 32-query block (28.7 k cycles per 256-query tile), next to 9 k
 // cycles of exponentials and packing and the conversion of each hidden block, which the barrier keeps both waves of a SIMD
-// in at the same time; n costs 201 MB written here and read again.  Measured at 480p / 81 frames, 12 heads: this pass 174 us
+// in at the same time (matrix cores busy for 45 % of the cycles at 2.06 GHz); n costs 201 MB written here and read again.  Measured at 480p / 81 frames, 12 heads: this pass 174 us (178 with the features rounded tile by tile)
 // and the query kernel 1413 us where the query kernel alone took 1627 on a faster box (forward 1959 -> 1858 us side by
 // side); B = 2, H = 12, N = 5003, fp32, R = 3: 198 us -> 79 + 127 us in a round and a half less exposed epilogue (355 -> 329
 // us); the fixed cost of a small call falls from 64 to about 25 us.

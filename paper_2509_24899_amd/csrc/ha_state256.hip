@@ -12,7 +12,8 @@
 //
 // Bound: matrix cores, 400 instructions of 32 cycles per SIMD and 128-token tile (12.8 k cycles), next to 5 k cycles of
 // exponentials and packing that nothing covers.  Measured at 480p / 81 frames, 12 heads, R = 4: 222 us in one role with the
-// weights staged per tile in two rounds, 128 us here; B = 2, N = 5003, R = 3, fp32: 108 -> 66 us.
+// weights staged per tile in two rounds, 128 us here (130 with the features rounded tile by tile, see phi256_output; 36 % of the
+// cycles with a matrix instruction in flight); B = 2, N = 5003, R = 3, fp32: 108 -> 66 us.
 #include "ha_mlp256.h"
 #include "ha_plan.h"
 
