@@ -8,14 +8,18 @@
 //               channels: a quarter of the 32 that consume it, against 4 bytes per unit and token written and read back), or
 //   from HBM    fetched as the hi + lo register images the previous layer left, three blocks ahead.
 // The weights of a block (its rows of W1, its columns of the layer's matrix) are one slab of an LDS ring that all waves
-// share; requests run ahead across items, one barrier per block.  Output blocks of a tile are consecutive items, so an
-// image is read from HBM once and then from the cache behind it.
+// share; requests run ahead across items, one barrier per block.  A slab is in place a block before its turn, so that under the
+// products of a block the next block's first fragments are read and (from x) the next hidden block is formed: formed at the head
+// of its own block, as eight products in series each behind an LDS read of its own, it left the matrix cores idle in both waves of a
+// SIMD at once (57 % busy, now 66 %).  From HBM the output blocks of a tile go to neighbouring workgroups of an XCD at the same
+// time, so that its image is fetched once: one after the other in one workgroup it was fetched three times (3.8 GB, now 1.5 GB).
 //
-// Bound: matrix cores at the clock the power limit allows: 1.05 PFLOP/s of matrix instructions in both forms, where a large
-// library product of the same type reaches 1.3.  Measured with the 768-wide three-layer maps at 480p / 81 frames, 12 heads,
-// R = 8: first hidden layer + middle layer as passes of their own 324 + 777 us (keys) and 375 + 928 us (queries), 939 and
-// 1050 us here; the last layer, whose input comes from HBM in either case, 772 -> 788 and 926 -> 913 us; the 256-wide maps'
-// two layers ahead of a backward pass 111 + 174 -> 185 us (queries), 87 + 131 -> 145 us (keys).
+// Bound: matrix cores at the clock the power limit allows: 1.25 PFLOP/s of matrix instructions in both forms (66 % busy at 1.83 GHz,
+// 64 % at 1.87), where a large library product of the same type reaches 1.3.  Measured with the 768-wide three-layer maps at 480p / 81
+// frames, 12 heads, R = 8, keys and queries: from x 938 and 1038 us with the hidden block at the head of its own block, 839 and 927 us
+// here; from HBM 795 and 920 us, 771 and 874 without a wait for all loads every fourth block (the order of the first image loads),
+// 679 and 752 us with the image fetched once.  The 256-wide maps' two layers ahead of a backward pass: 111 + 174 us as
+// passes of their own, 185 us here (queries).
 #include "ha_mlp256.h"
 #include "ha_plan.h"
 
@@ -44,65 +48,68 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
   constexpr int D = 128, KS = D / 16, NW = 8, NBUF = 5;
   constexpr int CH = (X ? KS : 0) + 2 * NT, PW = CH / NW, SLOT = CH * 64;      // 1 KiB chunks per slab, per wave
   constexpr int WMAX = 768;
-  static_assert(CH % NW == 0, "slabs are dealt evenly");
+  static_assert(CH % NW == 0 && KS == NW, "slabs are dealt evenly, the first chunk of a wave from W1");
   __shared__ bf16x8 ring[NBUF * SLOT];
   __shared__ __align__(16) float vecs[(X ? WMAX : 0) + WMAX];                  // b1, bias of the whole layer
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nwg = gridDim.x;                                                   // a multiple of 8
-  const int wg = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
-  const int i_lo = a.first + (int)((int64_t)wg * a.total / nwg), i_hi = a.first + (int)((int64_t)(wg + 1) * a.total / nwg);
+  // Items of this workgroup: from x a contiguous run, so that a tile's rows and first hidden block serve all its output blocks;
+  // from HBM the items of its XCD in turn, so that neighbouring workgroups read a tile's image at the same time and it leaves
+  // HBM (or the cache in front of it) once and not once per output block.
+  const int per_xcd = gridDim.x >> 3, xcd = blockIdx.x & 7, in_xcd = blockIdx.x >> 3;   // the grid is a multiple of 8
+  const int u_lo = X ? xcd * per_xcd + in_xcd : xcd, u_n = X ? gridDim.x : 8, stride = X ? 1 : per_xcd;
+  const int i_lo = a.first + (int)((int64_t)u_lo * a.total / u_n) + (X ? 0 : in_xcd), i_hi = a.first + (int)((int64_t)(u_lo + 1) * a.total / u_n);
   if (i_lo >= i_hi) return;
   const int KB = a.K / 32, OB = a.NOUT / 32;                                   // KB: a multiple of 4
   const int per_head = a.n_tiles * a.n_ob;
   const LinearMap lmap(a.R, a.G);
 
-  struct Item { int bh, tb, ob0; };                                            // tb: this wave's 32-token block
+  struct Item {
+    int bh, tb, ob0;                                                           // tb: this wave's 32-token block
+    const bf16x8 *w1, *wm;                                                     // this wave's chunks of slab 0
+    int64_t image;                                                             // from HBM: block 0 of the input's image
+  };
   auto item_of = [&](int i) {
     Item it;
     it.bh = i / per_head;
-    const int rem = i - it.bh * per_head, tile = rem / a.n_ob;
+    const int rem = i - it.bh * per_head, tile = rem / a.n_ob, h = it.bh % a.H;
     it.tb = tile * NW + w;
     it.ob0 = a.ob_first + (rem - tile * a.n_ob) * NT;
+    // chunk NW i + w of a slab is (X) chunk w of the block's W1 for i = 0, then fragment w % 2 of output tile 4 i' + w / 2
+    it.w1 = X ? a.w1f + (int64_t)h * (a.K * D / 8) + w * 64 : nullptr;
+    it.wm = a.wf + (int64_t)h * ((int64_t)a.NOUT * a.K / 8) + ((int64_t)(it.ob0 + (w >> 1)) * KB * 2 + (w & 1)) * 64;
+    it.image = ((int64_t)it.bh * a.n_tb + min(it.tb, a.n_tb - 1)) * KB * 128;
     return it;
   };
   const unsigned lane_off = lane * 16;
+  const unsigned ring_w = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)(&ring[0]) + w * 1024;
   auto request = [&](const Item &it, int kb, int slot) {
-    const int h = it.bh % a.H;
-    const bf16x8 *w1 = X ? a.w1f + (int64_t)h * (a.K * D / 8) + kb * KS * 64 : nullptr;
-    const bf16x8 *wm = a.wf + (int64_t)h * ((int64_t)a.NOUT * a.K / 8);
+    const bf16x8 *wm = it.wm + kb * 128;
 #pragma unroll
     for (int i = 0; i < PW; ++i) {
-      const int c = i * NW + w;
-      const int cc = c - (X ? KS : 0);
-      const bf16x8 *gp = X && c < KS ? w1 + c * 64 : wm + (((int64_t)(it.ob0 + (cc >> 1)) * KB + kb) * 2 + (cc & 1)) * 64;
-      const unsigned l = __builtin_amdgcn_readfirstlane(
-          (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)(&ring[slot * SLOT + c * 64]));
+      const bf16x8 *gp = X && i == 0 ? it.w1 + kb * (KS * 64) : wm + (int64_t)(i - (X ? 1 : 0)) * (4 * 128) * KB;
+      const unsigned l = __builtin_amdgcn_readfirstlane(ring_w + (slot * SLOT + i * NW * 64) * 16);
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(gp) : "memory");
     }
   };
   Item cur = item_of(i_lo), nxt = cur;
-  int slot = 0, ahead = NBUF - 1;                  // slot of the current slab; slot the next request goes to
+  int slot = 0;                                    // slot of the current slab
   bool stored = false;                             // this wave wrote its outputs at the end of the item before
-  // Barrier ahead of a slab: this wave's share has landed and so has everybody's, and everybody is done with the slab
-  // before it, whose slot takes the request NBUF - 1 slabs ahead.  Newer than the slab's own request are at least the
-  // NBUF - 2 requests after it (and from HBM as many groups of four image loads), and, for slabs requested before this
-  // wave's outputs, those 4 NT stores (loads and stores retire in order).
-  constexpr int FLY = (NBUF - 2) * (PW + (X ? 0 : 4));
+  // Barrier ahead of slab kb: this wave's shares of slabs kb and kb + 1 have landed and so have everybody's, and everybody is
+  // done with slab kb - 1, whose slot takes the request NBUF - 1 slabs ahead.  (Slab kb itself was there a barrier ago, so that
+  // its first fragments are read ahead of this barrier, under the products of slab kb - 1; all reads of slab kb - 1 have been
+  // used by then.)  Newer than the request of slab kb + 1 are at least NBUF - 3 requests (and from HBM NBUF - 2 groups of four
+  // image loads), and, where that request came before this wave's outputs, those 4 NT stores (loads and stores retire in order).
+  constexpr int FLY = (NBUF - 3) * PW + (X ? 0 : (NBUF - 2) * 4);
   static_assert(FLY + 4 * NT < 63, "vmcnt immediate too large");
   auto advance = [&](int kb) {
-    if (stored && kb < NBUF - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FLY + 4 * NT) : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FLY) : "memory");
-    __syncthreads();
+    if (stored && kb < NBUF - 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FLY + 4 * NT) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FLY) : "memory");
     const int s = kb + NBUF - 1;
-    request(s < KB ? cur : nxt, s < KB ? s : s - KB, ahead);                   // (past the last item: a slab nobody reads)
-    ahead = ahead + 1 == NBUF ? 0 : ahead + 1;
+    request(s < KB ? cur : nxt, s < KB ? s : s - KB, slot == 0 ? NBUF - 1 : slot - 1);   // (past the last item: a slab nobody reads)
   };
-  auto next_slab = [&]() {
-    const lds_frag_ptr sl = (lds_frag_ptr)&ring[slot * SLOT];
-    slot = slot + 1 == NBUF ? 0 : slot + 1;
-    return sl;
-  };
+  auto slab = [&](int s) { return (lds_frag_ptr)&ring[s * SLOT]; };
+  auto next_slot = [&]() { return slot + 1 == NBUF ? 0 : slot + 1; };
 
   bf16x8 xf[X ? KS : 1];
   auto load_x = [&](const Item &it) {
@@ -114,25 +121,51 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
   };
   bf16x8 im_hi[X ? 1 : 4][2], im_lo[X ? 1 : 4][2];                             // input blocks kb .. kb + 3, buffer kb % 4
   auto load_image = [&](const Item &it, int kb, bf16x8 (&hi)[2], bf16x8 (&lo)[2]) {
-    const int64_t at = (((int64_t)it.bh * a.n_tb + min(it.tb, a.n_tb - 1)) * KB + kb) * 128 + lane;
+    const bf16x8 *ph = a.in_hi + it.image + kb * 128, *pl = a.in_lo + it.image + kb * 128;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      hi[s] = a.in_hi[at + s * 64];
-      lo[s] = a.in_lo[at + s * 64];
+      hi[s] = ph[s * 64 + lane];
+      lo[s] = pl[s * 64 + lane];
     }
   };
 #pragma unroll
   for (int s = 0; s < NBUF - 1; ++s) request(cur, s, s);                       // (KB >= NBUF - 1)
   if constexpr (!X) {
+    // in this order: the compiler counts the loads that may be in flight at the head of the loop over all ways into it
 #pragma unroll
-    for (int s = 0; s < 3; ++s) load_image(cur, s, im_hi[s], im_lo[s]);
+    for (int s = 0; s < 3; ++s) {
+      load_image(cur, s, im_hi[s], im_lo[s]);
+      HA_FENCE();
+    }
   }
   const float *b1 = &vecs[0], *bias = &vecs[X ? WMAX : 0];
 
-  int bh_vecs = -1;
-  for (int i = i_lo; i < i_hi; ++i) {
-    nxt = item_of(i + 1 < i_hi ? i + 1 : i);
-    if constexpr (X) load_x(cur);
+  // The products of a slab: NT groups of four, group gi = (half s, output tiles fb, fb + 1); the fragments of a group are read
+  // LA groups ahead, those of the next slab's first groups included.
+  constexpr int LA = X ? 1 : 2, NF = 2 * LA;
+  static_assert(NT % NF == 0, "the fragment buffers rotate whole within a slab");
+  bf16x8 fr[NF][2];
+  constexpr int W0 = X ? KS : 0;                                               // first weight chunk behind W1
+  auto read_group = [&](lds_frag_ptr sl, int gi) {
+    const int s = gi / (NT / 2), fb = 2 * (gi % (NT / 2));
+    fr[gi % NF][0] = frag_at(sl, W0 + 2 * fb + s, lane);
+    fr[gi % NF][1] = frag_at(sl, W0 + 2 * fb + 2 + s, lane);
+  };
+  f32x16 acc[NT];
+  auto products = [&](int gi, bf16x8 hi8, bf16x8 lo8) {
+    const int fb = 2 * (gi % (NT / 2));
+    acc[fb] = mfma32(fr[gi % NF][0], lo8, acc[fb]);
+    acc[fb + 1] = mfma32(fr[gi % NF][1], lo8, acc[fb + 1]);
+    acc[fb] = mfma32(fr[gi % NF][0], hi8, acc[fb]);
+    acc[fb + 1] = mfma32(fr[gi % NF][1], hi8, acc[fb + 1]);
+  };
+  u32x4 h_hi[2], h_lo[2];                                                      // from x: the hidden block of the current slab
+  auto hop = [](const u32x4 &t) { return __builtin_bit_cast(bf16x8, t); };
+
+  int bh_vecs = -1, x_bh = -1, x_tb = -1;
+  for (int i = i_lo; i < i_hi; i += stride) {
+    nxt = item_of(i + stride < i_hi ? i + stride : i);
+    const bool new_x = X && (cur.bh != x_bh || cur.tb != x_tb);                // workgroup-uniform
     if (cur.bh != bh_vecs) {                       // workgroup-uniform: the first item, or the head changes
       const int h = cur.bh % a.H;
       __syncthreads();                             // every wave is done with the previous head's biases
@@ -142,25 +175,75 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
       bh_vecs = cur.bh;
       __syncthreads();
     }
+    if (i == i_lo) {
+      // slab 0 is in place (from the second item on the barrier of the slab before has seen to it)
+      asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+      for (int gi = 0; gi < LA; ++gi) read_group(slab(slot), gi);
+    }
     const bool live = cur.tb < a.n_tb;             // idle waves keep staging and synchronising
-    f32x16 acc[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[j] = column_tile(bias, cur.ob0 + j, g);
     if constexpr (X) {
+      if (new_x) {                                 // the first hidden block of a tile; the others are formed on the way
+        load_x(cur);
+        hidden_block(slab(slot), b1, 0, xf, lane, g, h_hi, h_lo);
+        x_bh = cur.bh;
+        x_tb = cur.tb;
+      }
       const bool keep = a.h_hi && cur.ob0 == 0 && live;
+      constexpr int HALF = NT / 2, PER = KS / HALF;                            // groups of either half, matrix instructions of W1 per group
 #pragma unroll 1
       for (int kb = 0; kb < KB; ++kb) {
         advance(kb);
-        const lds_frag_ptr sl = next_slab();
-        u32x4 h_hi[2], h_lo[2];
-        hidden_block(sl, b1, kb, xf, lane, g, h_hi, h_lo);
         if (keep) {
           const int64_t at = (((int64_t)cur.bh * a.n_tb + cur.tb) * KB + kb) * 128 + lane;
 #pragma unroll
-          for (int s = 0; s < 2; ++s) a.h_hi[at + s * 64] = __builtin_bit_cast(bf16x8, h_hi[s]);
+          for (int s = 0; s < 2; ++s) a.h_hi[at + s * 64] = hop(h_hi[s]);
         }
-        hidden_to_outputs<NT>(sl + KS * 64, __builtin_bit_cast(bf16x8, h_hi[0]), __builtin_bit_cast(bf16x8, h_hi[1]),
-                              __builtin_bit_cast(bf16x8, h_lo[0]), __builtin_bit_cast(bf16x8, h_lo[1]), lane, acc);
+        // Under the products of this block: the next hidden block, its matrix instructions in the first half, its ReLU and
+        // hi + lo split in the second.  (Behind the last block: block 0 once more, for the tile's next output channels.)
+        const lds_frag_ptr sl = slab(slot), sn = slab(next_slot());
+        f32x16 hh = column_tile(b1, kb + 1 < KB ? kb + 1 : 0, g);
+        bf16x8 wl[2][PER];
+        u32x4 n_hi[2], n_lo[2];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) wl[0][q] = frag_at(sn, q, lane);
+#pragma unroll
+        for (int gi = 0; gi < NT; ++gi) {
+          read_group(gi + LA < NT ? sl : sn, (gi + LA) % NT);
+          if (gi + 1 < HALF) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) wl[(gi + 1) & 1][q] = frag_at(sn, (gi + 1) * PER + q, lane);
+          }
+          HA_FENCE();
+          products(gi, hop(h_hi[gi / HALF]), hop(h_lo[gi / HALF]));
+          if (gi < HALF) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) hh = mfma32(wl[gi & 1][q], xf[gi * PER + q], hh);
+          } else {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+              const int x = 2 * ((gi - HALF) * PER + q);
+              const float v0 = relu(hh[x]), v1 = relu(hh[x + 1]);
+              const unsigned p = pack_bf16(v0, v1);
+              n_hi[x >> 3][(x & 7) >> 1] = p;
+              n_lo[x >> 3][(x & 7) >> 1] = pack_bf16(v0 - __uint_as_float(p << 16), v1 - __uint_as_float(p & 0xffff0000u));
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x002, 2 * PER, 0);
+            }
+          }
+          HA_FENCE();
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          h_hi[s] = n_hi[s];
+          h_lo[s] = n_lo[s];
+        }
+        slot = next_slot();
       }
     } else {
 #pragma unroll 1
@@ -168,10 +251,18 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           advance(kb + q);
-          const lds_frag_ptr sl = next_slab();
+          const lds_frag_ptr sl = slab(slot), sn = slab(next_slot());
           const int s = kb + q + 3;
           load_image(s < KB ? cur : nxt, s < KB ? s : s - KB, im_hi[(q + 3) & 3], im_lo[(q + 3) & 3]);
-          hidden_to_outputs<NT>(sl, im_hi[q][0], im_hi[q][1], im_lo[q][0], im_lo[q][1], lane, acc);
+          HA_FENCE();
+#pragma unroll
+          for (int gi = 0; gi < NT; ++gi) {
+            read_group(gi + LA < NT ? sl : sn, (gi + LA) % NT);
+            HA_FENCE();
+            products(gi, im_hi[q][gi / (NT / 2)], im_lo[q][gi / (NT / 2)]);
+            HA_FENCE();
+          }
+          slot = next_slot();
         }
       }
     }
