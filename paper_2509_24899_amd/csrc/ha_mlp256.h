@@ -2,9 +2,10 @@
 // pass and the query side.  gfx950 only.
 //
 // A token's 256 pre-activations are eight accumulator tiles; the hidden layer is walked in blocks of 32 units, each formed
-// (8 matrix instructions), split into hi + lo and contracted into all eight tiles (32 instructions) before the next one
-// starts, so one hidden block is all that is ever held.  The operands of a hidden block form a 24 KiB slab: the 8
-// fragments of its rows of W1, then for every 32-channel output tile the two of its columns of W2.
+// (8 matrix instructions), split into hi + lo and contracted into all eight tiles (32 instructions), the next one formed under the
+// contraction, so two hidden blocks are all that is ever held.  The operands of a hidden block form a 24 KiB slab: the 8
+// fragments of its rows of W1 (state pass: of the next block's rows), then for every 32-channel output tile the two of its columns
+// of W2.
 #pragma once
 #include "ha_mlp128.h"
 
@@ -24,23 +25,30 @@ static __device__ __forceinline__ f32x16 column_tile(const float *b, int blk, in
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
 }
 
+// Registers x, x + 1 of a finished hidden tile -> ReLU -> hi + lo.
+static __device__ __forceinline__ void split2(const f32x16 &hh, int x, u32x4 (&hi)[2], u32x4 (&lo)[2]) {
+  const float v0 = relu(hh[x]), v1 = relu(hh[x + 1]);
+  const unsigned p = pack_bf16(v0, v1);
+  hi[x >> 3][(x & 7) >> 1] = p;
+  lo[x >> 3][(x & 7) >> 1] = pack_bf16(v0 - __uint_as_float(p << 16), v1 - __uint_as_float(p & 0xffff0000u));
+}
+
 // ReLU of a finished hidden tile as hi + lo bf16 pairs: the B operands of the next product.
 static __device__ __forceinline__ void relu_hi_lo(const f32x16 &t, u32x4 (&hi)[2], u32x4 (&lo)[2]) {
 #pragma unroll
-  for (int x = 0; x < 16; x += 2) {
-    const float v0 = relu(t[x]), v1 = relu(t[x + 1]);
-    const unsigned p = pack_bf16(v0, v1);
-    hi[x >> 3][(x & 7) >> 1] = p;
-    lo[x >> 3][(x & 7) >> 1] = pack_bf16(v0 - __uint_as_float(p << 16), v1 - __uint_as_float(p & 0xffff0000u));
-  }
+  for (int x = 0; x < 16; x += 2) split2(t, x, hi, lo);
 }
 
 // relu(W1[block, :] x + b1[block]) of hidden block hb from the head of its slab.
 static __device__ __forceinline__ void hidden_block(lds_frag_ptr sl, const float *b1, int hb, const bf16x8 (&xf)[8], int lane, int g,
                                                     u32x4 (&h_hi)[2], u32x4 (&h_lo)[2]) {
-  f32x16 hh = column_tile(b1, hb, g);
+  bf16x8 wl[8];
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) hh = mfma32(frag_at(sl, ks, lane), xf[ks], hh);
+  for (int ks = 0; ks < 8; ++ks) wl[ks] = frag_at(sl, ks, lane);
+  f32x16 hh = column_tile(b1, hb, g);
+  HA_FENCE();                                             // all reads on their way ahead of the chain
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) hh = mfma32(wl[ks], xf[ks], hh);
   relu_hi_lo(hh, h_hi, h_lo);
 }
 
@@ -69,6 +77,67 @@ static __device__ __forceinline__ void mlp256_hidden_block(lds_frag_ptr sl, cons
   hidden_block(sl, b1, hb, xf, lane, g, h_hi, h_lo);
   hidden_to_outputs<8>(sl + 8 * 64, __builtin_bit_cast(bf16x8, h_hi[0]), __builtin_bit_cast(bf16x8, h_hi[1]),
                        __builtin_bit_cast(bf16x8, h_lo[0]), __builtin_bit_cast(bf16x8, h_lo[1]), lane, u);
+}
+
+// The products of a hidden block come in 8 groups of four: group gi = (half s, output tiles fb, fb + 1).
+static __device__ __forceinline__ void read_group256(lds_frag_ptr wsl, int gi, int lane, bf16x8 (&fr)[2][2]) {
+  const int s = gi >> 2, fb = 2 * (gi & 3);
+  fr[gi & 1][0] = frag_at(wsl, 2 * fb + s, lane);
+  fr[gi & 1][1] = frag_at(wsl, 2 * fb + 2 + s, lane);
+}
+// u += W2[:, block] h for the hidden block in h_hi, h_lo, and, NEXT, under it the next one, nb: its matrix instructions in the
+// first half, its ReLU and hi + lo split in the second; on return h_hi, h_lo hold it.  wsl: the 16 fragments of the block's columns
+// of W2, of which group 0 has been read into fr; w1_next: the 8 of the next block's rows of W1.
+// (Formed at the head of its own block the hidden block is eight matrix instructions in series with nothing beside them.)
+template <bool NEXT>
+static __device__ __forceinline__ void hidden_block_products(lds_frag_ptr wsl, lds_frag_ptr w1_next, const float *b1,
+                                                             int nb, const bf16x8 (&xf)[8], int lane, int g, bf16x8 (&fr)[2][2],
+                                                             u32x4 (&h_hi)[2], u32x4 (&h_lo)[2], f32x16 (&u)[8]) {
+  f32x16 hh;
+  bf16x8 wl[2][2];
+  u32x4 n_hi[2], n_lo[2];
+  if constexpr (NEXT) {
+    hh = column_tile(b1, nb, g);
+    wl[0][0] = frag_at(w1_next, 0, lane);
+    wl[0][1] = frag_at(w1_next, 1, lane);
+  }
+#pragma unroll
+  for (int gi = 0; gi < 8; ++gi) {
+    if (gi < 7) read_group256(wsl, gi + 1, lane, fr);
+    if (NEXT && gi < 3) {
+      wl[(gi + 1) & 1][0] = frag_at(w1_next, 2 * gi + 2, lane);
+      wl[(gi + 1) & 1][1] = frag_at(w1_next, 2 * gi + 3, lane);
+    }
+    HA_FENCE();
+    const int s = gi >> 2, fb = 2 * (gi & 3);
+    const bf16x8 hi8 = __builtin_bit_cast(bf16x8, h_hi[s]), lo8 = __builtin_bit_cast(bf16x8, h_lo[s]);
+    u[fb] = mfma32(fr[gi & 1][0], lo8, u[fb]);
+    u[fb + 1] = mfma32(fr[gi & 1][1], lo8, u[fb + 1]);
+    u[fb] = mfma32(fr[gi & 1][0], hi8, u[fb]);
+    u[fb + 1] = mfma32(fr[gi & 1][1], hi8, u[fb + 1]);
+    if constexpr (NEXT) {
+      if (gi < 4) {
+        hh = mfma32(wl[gi & 1][0], xf[2 * gi], hh);
+        hh = mfma32(wl[gi & 1][1], xf[2 * gi + 1], hh);
+      } else {
+        split2(hh, 4 * (gi - 4), n_hi, n_lo);
+        split2(hh, 4 * (gi - 4) + 2, n_hi, n_lo);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+        }
+      }
+    }
+    HA_FENCE();
+  }
+  if constexpr (NEXT) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      h_hi[s] = n_hi[s];
+      h_lo[s] = n_lo[s];
+    }
+  }
 }
 
 // The output stage in place: positive activation over all channels, slice powers.  ACT0: softmax over the channels; otherwise

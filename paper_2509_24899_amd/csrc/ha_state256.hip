@@ -11,9 +11,10 @@
 // Every wave passes the same barriers: nine per tile and one at the end.
 //
 // Bound: matrix cores, 400 instructions of 32 cycles per SIMD and 128-token tile (12.8 k cycles), next to 5 k cycles of
-// exponentials and packing that nothing covers.  Measured at 480p / 81 frames, 12 heads, R = 4: 222 us in one role with the
-// weights staged per tile in two rounds, 128 us here (130 with the features rounded tile by tile, see phi256_output; 36 % of the
-// cycles with a matrix instruction in flight); B = 2, N = 5003, R = 3, fp32: 108 -> 66 us.
+// exponentials and packing that nothing covers.  The next hidden block is formed under the products of the current one (so a slab
+// brings the rows of W1 of the block after its own; as a chain at the head of each step: 128 and 59.5 us instead of 122 and 58 for the
+// two calls below, side by side on one box).  Measured at 480p / 81 frames, 12 heads, R = 4: 222 us in one role with the
+// weights staged per tile in two rounds, 128 -> 122 us here; B = 2, N = 5003, R = 3, fp32: 108, then 59.5 -> 58 us.
 #include "ha_mlp256.h"
 #include "ha_plan.h"
 
@@ -68,18 +69,44 @@ __global__ __launch_bounds__(512, 1) void state256_kernel(const void *__restrict
     };
     bf16x8 xf[KS];
     load_k(lt_begin, xf);
-    __syncthreads();                                   // the biases are in LDS
+    const lds_frag_ptr sl0 = (lds_frag_ptr)&slab[0][0], sl1 = (lds_frag_ptr)&slab[1][0];
+    u32x4 h_hi[2], h_lo[2];                            // the hidden block of the current step
+    f32x16 hh;
+    auto first_block = [&]() {                         // hidden block 0 of the tile in xf: its rows of W1 are with slab 7
+      bf16x8 wl[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) wl[ks] = frag_at(sl1, ks, lane);
+      hh = column_tile(b1, 0, g);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) hh = mfma32(wl[ks], xf[ks], hh);
+    };
+    auto first_split = [&]() {
+#pragma unroll
+      for (int x = 0; x < 16; x += 2) split2(hh, x, h_hi, h_lo);
+    };
+    __syncthreads();                                   // the biases and W1 of block 0 are in LDS
+    if (lt_begin < lt_end) {
+      first_block();
+      first_split();
+    }
     for (int t0 = lt_begin; t0 < lt_end; t0 += TOK) {
       f32x16 u[FB];
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb) u[fb] = column_tile(b2, fb, g);
+      bf16x8 fr[2][2];
 #pragma unroll 1
-      for (int hb = 0; hb < HB; ++hb) {
+      for (int hb = 0; hb + 1 < HB; ++hb) {
         __syncthreads();                               // slab hb is in place
-        mlp256_hidden_block((lds_frag_ptr)&slab[hb & 1][0], b1, hb, xf, lane, g, u);
+        const lds_frag_ptr sl = (hb & 1) ? sl1 : sl0;
+        read_group256(sl + KS * 64, 0, lane, fr);
+        hidden_block_products<true>(sl + KS * 64, sl, b1, hb + 1, xf, lane, g, fr, h_hi, h_lo, u);
       }
-      load_k(t0 + TOK, xf);
+      load_k(t0 + TOK, xf);                            // the next tile's rows travel under the last step and the output stage
+      __syncthreads();                                 // slab 7 is in place
+      read_group256(sl1 + KS * 64, 0, lane, fr);
+      hidden_block_products<false>(sl1 + KS * 64, nullptr, nullptr, 0, xf, lane, g, fr, h_hi, h_lo, u);
       phi256_output<ACT0, P2>(u, act, P);
+      first_block();                                   // of the next tile: its products run under the packing below
       if (t0 + TOK > lt_end) {                         // ragged end of the range: padded tokens add nothing
         // (by selection: a padded row may be a token of the next causal chunk, whose features need not be finite)
         const bool keep = t0 + tf < lt_end;
@@ -104,6 +131,7 @@ __global__ __launch_bounds__(512, 1) void state256_kernel(const void *__restrict
       for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
         for (int q = 0; q < 4; ++q) *reinterpret_cast<u32x2 *>(phi_t + at + (((4 * fb + q) ^ psw) << 4)) = four[fb][q];
+      first_split();
     }
     __syncthreads();                                   // the last tile is in place
     return;
@@ -118,16 +146,21 @@ __global__ __launch_bounds__(512, 1) void state256_kernel(const void *__restrict
 #pragma unroll
       for (int x = 0; x < 16; ++x) acc[e][i][x] = 0.f;
   const unsigned lane_off = lane * 16;
-  auto request = [&](int hb) {                         // slab hb into buffer hb % 2, six chunks per wave
+  // Slab hb into buffer hb % 2, six chunks per wave: the columns of W2 of hidden block hb, in front of them the rows of W1 of the
+  // block after it (behind the last one: of block 0, for the next tile), which is formed under this one's products.
+  auto dma = [&](const bf16x8 *gp, bf16x8 *to) {
+    const unsigned l = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)to);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(gp) : "memory");
+  };
+  auto request = [&](int hb) {
 #pragma unroll
     for (int i = 0; i < kSlabChunks / 4; ++i) {
       const int c = 4 * i + w;
-      const unsigned l = __builtin_amdgcn_readfirstlane(
-          (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)(&slab[hb & 1][c * 64]));
-      const bf16x8 *gp = slab_chunk(w1g, w2g, hb, c);
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(gp) : "memory");
+      dma(slab_chunk(w1g, w2g, i < 2 ? (hb + 1) % HB : hb, c), &slab[hb & 1][c * 64]);
     }
   };
+#pragma unroll
+  for (int i = 0; i < 2; ++i) dma(slab_chunk(w1g, w2g, 0, 4 * i + w), &slab[1][(4 * i + w) * 64]);   // W1 of block 0 for the first tile
   request(0);
   // transposing reads: lane = (group tm, row ti, columns ta); see ds_read_tr
   const int tm = lane >> 4, ti = (lane >> 2) & 3, ta = lane & 3, tg = tm >> 1;
@@ -186,7 +219,8 @@ __global__ __launch_bounds__(512, 1) void state256_kernel(const void *__restrict
 #pragma unroll
       for (int e = 0; e < 2; ++e) acc[e][cb] = mfma32(a8[e], cb < D / 32 ? b8[cb] : ones, acc[e][cb]);
   };
-  __syncthreads();                                     // the biases are in LDS
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();                                     // the biases and W1 of block 0 are in LDS
   for (int t0 = lt_begin; t0 < lt_end; t0 += TOK) {
 #pragma unroll 1
     for (int hb = 0; hb < HB; ++hb) {
@@ -202,7 +236,6 @@ __global__ __launch_bounds__(512, 1) void state256_kernel(const void *__restrict
     for (int c = 0; c < NVI / 4; ++c)
       *reinterpret_cast<bf16x8 *>(v_t + ((4 * c + w) * RPI + v_row) * VROW + (v_pp << 4)) = vreg[c];
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (a range without tokens: slab 0 is still on its way)
   __syncthreads();                                     // the last tile is in place
   if (lt_begin < lt_end)
 #pragma unroll

@@ -14,12 +14,17 @@
 // SIMD at once (57 % busy, now 66 %).  From HBM the output blocks of a tile go to neighbouring workgroups of an XCD at the same
 // time, so that its image is fetched once: one after the other in one workgroup it was fetched three times (3.8 GB, now 1.5 GB).
 //
-// Bound: matrix cores at the clock the power limit allows: 1.25 PFLOP/s of matrix instructions in both forms (66 % busy at 1.83 GHz,
-// 64 % at 1.87), where a large library product of the same type reaches 1.3.  Measured with the 768-wide three-layer maps at 480p / 81
-// frames, 12 heads, R = 8, keys and queries: from x 938 and 1038 us with the hidden block at the head of its own block, 839 and 927 us
-// here; from HBM 795 and 920 us, 771 and 874 without a wait for all loads every fourth block (the order of the first image loads),
-// 679 and 752 us with the image fetched once.  The 256-wide maps' two layers ahead of a backward pass: 111 + 174 us as
-// passes of their own, 185 us here (queries).
+// Outputs leave in a burst per item, and slabs requested behind them are not known to have landed before they have reached memory
+// (loads and stores retire in order): the ring is as long as LDS and the contraction allow, the input's next blocks are requested
+// ahead of the outputs.
+//
+// Bound: matrix cores at the power limit: 1.25 - 1.3 PFLOP/s of matrix instructions in both forms (steady slabs take 1.17 times their
+// matrix instructions' cycles; clock 1.8 - 1.9 GHz), where a large library product of the same type reaches 1.3.  Measured with the
+// 768-wide three-layer maps at 480p / 81 frames, 12 heads, R = 8, keys and queries, before and after on one box: from x 856 and 925 us
+// with the hidden block at the head of its own block, 806 and 891 us here; from HBM 777 and 892 us with a wait for all loads every
+// fourth block and the image fetched three times, 632 and 703 us here.  Two slabs per barrier took 9.4 k cycles instead of 9.7 k for
+// four slabs and no less time.  The 256-wide maps' two layers ahead of a backward pass: 111 + 174 us as passes of their own, 185 us
+// here (queries).
 #include "ha_mlp256.h"
 #include "ha_plan.h"
 
@@ -42,10 +47,11 @@ struct WideMlpArgs {
 };
 
 // SRC: 0 from x in bf16, 1 from x in fp32, 2 from HBM.  LAST: fp32 pre-activations out; otherwise relu, hi + lo bf16.
-template <int NT, int SRC, bool LAST>
+// NBUF: slabs in the ring, at most K / 32 + 1.
+template <int NT, int SRC, bool LAST, int NBUF>
 __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
   constexpr bool X = SRC != 2;
-  constexpr int D = 128, KS = D / 16, NW = 8, NBUF = 5;
+  constexpr int D = 128, KS = D / 16, NW = 8;
   constexpr int CH = (X ? KS : 0) + 2 * NT, PW = CH / NW, SLOT = CH * 64;      // 1 KiB chunks per slab, per wave
   constexpr int WMAX = 768;
   static_assert(CH % NW == 0 && KS == NW, "slabs are dealt evenly, the first chunk of a wave from W1");
@@ -99,12 +105,16 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
   // done with slab kb - 1, whose slot takes the request NBUF - 1 slabs ahead.  (Slab kb itself was there a barrier ago, so that
   // its first fragments are read ahead of this barrier, under the products of slab kb - 1; all reads of slab kb - 1 have been
   // used by then.)  Newer than the request of slab kb + 1 are at least NBUF - 3 requests (and from HBM NBUF - 2 groups of four
-  // image loads), and, where that request came before this wave's outputs, those 4 NT stores (loads and stores retire in order).
-  constexpr int FLY = (NBUF - 3) * PW + (X ? 0 : (NBUF - 2) * 4);
-  static_assert(FLY + 4 * NT < 63, "vmcnt immediate too large");
+  // image loads), and, where that request came before this wave's outputs, those 4 NT stores (loads and stores retire in order, so
+  // that the ring's length is what the outputs have to reach memory in).  The slabs requested ahead of the first item are waited
+  // for together.
+  constexpr int FLY = (NBUF - 3) * PW + (X ? 0 : (NBUF - 2) * 4), FLY_OUT = FLY + 4 * NT < 63 ? FLY + 4 * NT : 63;
+  static_assert(FLY < 63, "vmcnt immediate too large");
   auto advance = [&](int kb) {
-    if (stored && kb < NBUF - 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FLY + 4 * NT) : "memory");
+    if (stored && kb < NBUF - 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FLY_OUT) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FLY) : "memory");
+  };
+  auto refill = [&](int kb) {                      // (behind a slab's first products, under which its scalar instructions pass)
     const int s = kb + NBUF - 1;
     request(s < KB ? cur : nxt, s < KB ? s : s - KB, slot == 0 ? NBUF - 1 : slot - 1);   // (past the last item: a slab nobody reads)
   };
@@ -133,7 +143,7 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
   if constexpr (!X) {
     // in this order: the compiler counts the loads that may be in flight at the head of the loop over all ways into it
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
+    for (int s = 0; s < 4; ++s) {
       load_image(cur, s, im_hi[s], im_lo[s]);
       HA_FENCE();
     }
@@ -218,18 +228,17 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
           }
           HA_FENCE();
           products(gi, hop(h_hi[gi / HALF]), hop(h_lo[gi / HALF]));
+          if (gi == 0) {
+            HA_FENCE();
+            refill(kb);
+            HA_FENCE();
+          }
           if (gi < HALF) {
 #pragma unroll
             for (int q = 0; q < PER; ++q) hh = mfma32(wl[gi & 1][q], xf[gi * PER + q], hh);
           } else {
 #pragma unroll
-            for (int q = 0; q < PER; ++q) {
-              const int x = 2 * ((gi - HALF) * PER + q);
-              const float v0 = relu(hh[x]), v1 = relu(hh[x + 1]);
-              const unsigned p = pack_bf16(v0, v1);
-              n_hi[x >> 3][(x & 7) >> 1] = p;
-              n_lo[x >> 3][(x & 7) >> 1] = pack_bf16(v0 - __uint_as_float(p << 16), v1 - __uint_as_float(p & 0xffff0000u));
-            }
+            for (int q = 0; q < PER; ++q) split2(hh, 2 * ((gi - HALF) * PER + q), n_hi, n_lo);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -252,16 +261,20 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
         for (int q = 0; q < 4; ++q) {
           advance(kb + q);
           const lds_frag_ptr sl = slab(slot), sn = slab(next_slot());
-          const int s = kb + q + 3;
-          load_image(s < KB ? cur : nxt, s < KB ? s : s - KB, im_hi[(q + 3) & 3], im_lo[(q + 3) & 3]);
-          HA_FENCE();
 #pragma unroll
           for (int gi = 0; gi < NT; ++gi) {
             read_group(gi + LA < NT ? sl : sn, (gi + LA) % NT);
             HA_FENCE();
             products(gi, im_hi[q][gi / (NT / 2)], im_lo[q][gi / (NT / 2)]);
             HA_FENCE();
+            if (gi == 0) {
+              refill(kb + q);
+              HA_FENCE();
+            }
           }
+          const int s = kb + q + 4;                // (ahead of this wave's outputs, where they follow)
+          load_image(s < KB ? cur : nxt, s < KB ? s : s - KB, im_hi[q], im_lo[q]);
+          HA_FENCE();
           slot = next_slot();
         }
       }
@@ -270,6 +283,11 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
     if (live) {
       const int64_t blk0 = ((int64_t)cur.bh * a.n_tb + cur.tb) * OB + cur.ob0;
       if constexpr (LAST) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int x4 = 0; x4 < 4; ++x4)
+            a.out_u[((blk0 + j) * 4 + x4) * 64 + lane] = f32x4{acc[j][4 * x4], acc[j][4 * x4 + 1], acc[j][4 * x4 + 2], acc[j][4 * x4 + 3]};
         // per token and 128 channels: their maximum and the sum of exponentials against it, so that the output stage can
         // form the softmax over all channels with a single sweep over the pre-activations
 #pragma unroll
@@ -291,11 +309,6 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
           st[0] = m;
           st[64] = sum;
         }
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-          for (int x4 = 0; x4 < 4; ++x4)
-            a.out_u[((blk0 + j) * 4 + x4) * 64 + lane] = f32x4{acc[j][4 * x4], acc[j][4 * x4 + 1], acc[j][4 * x4 + 2], acc[j][4 * x4 + 3]};
       } else {
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
@@ -362,13 +375,20 @@ hipError_t launch_wide_mlp(const Plan &pl, const WideMlpLayer &l, hipStream_t st
     a.first = launches[i].first;
     a.total = launches[i].total;
     const int nwg = a.total < 256 ? (a.total + 7) / 8 * 8 : 256;               // one workgroup per CU
-#define HA_WIDE_MLP(NT, SRC) \
+    // the longest ring that fits LDS and the shortest contraction of its instance
+#define HA_WIDE_MLP(NT, SRC, NBUF) \
   do { \
-    if (l.out_u) wide_mlp_kernel<NT, SRC, true><<<nwg, 512, 0, st>>>(a); \
-    else wide_mlp_kernel<NT, SRC, false><<<nwg, 512, 0, st>>>(a); \
+    if (l.out_u) wide_mlp_kernel<NT, SRC, true, NBUF><<<nwg, 512, 0, st>>>(a); \
+    else wide_mlp_kernel<NT, SRC, false, NBUF><<<nwg, 512, 0, st>>>(a); \
   } while (0)
-    if (launches[i].nt == 8) { if (src == 0) HA_WIDE_MLP(8, 0); else if (src == 1) HA_WIDE_MLP(8, 1); else HA_WIDE_MLP(8, 2); }
-    else { if (src == 0) HA_WIDE_MLP(4, 0); else if (src == 1) HA_WIDE_MLP(4, 1); else HA_WIDE_MLP(4, 2); }
+#define HA_WIDE_MLP_SRC(NT, NBUF_X, NBUF_HBM) \
+  do { \
+    if (src == 0) HA_WIDE_MLP(NT, 0, NBUF_X); else if (src == 1) HA_WIDE_MLP(NT, 1, NBUF_X); else HA_WIDE_MLP(NT, 2, NBUF_HBM); \
+  } while (0)
+    if (a.K >= 256) { if (launches[i].nt == 8) HA_WIDE_MLP_SRC(8, 6, 9); else HA_WIDE_MLP_SRC(4, 9, 9); }
+    else if (launches[i].nt == 8) HA_WIDE_MLP_SRC(8, 5, 5);
+    else HA_WIDE_MLP_SRC(4, 5, 5);
+#undef HA_WIDE_MLP_SRC
 #undef HA_WIDE_MLP
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
