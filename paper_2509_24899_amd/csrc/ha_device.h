@@ -89,6 +89,29 @@ struct LinearMap {
   }
 };
 
+// Slice powers of the output stage: channel c is raised to 1 + c / Dp, Dp = 32 NB / P.
+template <int NB>
+static __device__ __forceinline__ void feature_powers(f32x16 (&u)[NB], int P) {
+  if (P > 1) {
+    // slice p = c / Dp (0-based) gets p extra multiplications by the activation value
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int extra = ((32 * b + 8 * q) * P) / (32 * NB);   // = channel / Dp without a run-time division; wave-uniform
+        if (extra > 0) {
+          const float t0 = u[b][4 * q], t1 = u[b][4 * q + 1], t2 = u[b][4 * q + 2], t3 = u[b][4 * q + 3];
+          for (int i = 0; i < extra; ++i) {
+            u[b][4 * q] *= t0;
+            u[b][4 * q + 1] *= t1;
+            u[b][4 * q + 2] *= t2;
+            u[b][4 * q + 3] *= t3;
+          }
+        }
+      }
+  }
+}
+
 // Feature-map output stage on one C column held as NB row blocks of 16 registers (plus the same in
 // lane ^ 32): positive activation over all channels, then channel c is raised to 1 + c / Dp.
 //   act 0: softmax over the F = 32*NB channels;  1: exp;  2: relu.
@@ -130,24 +153,7 @@ static __device__ __forceinline__ void feature_activation(f32x16 (&u)[NB], int g
 #pragma unroll
       for (int v = 0; v < 16; ++v) u[b][v] = fmaxf(u[b][v], 0.f);
   }
-  if (P > 1) {
-    // slice p = c / Dp (0-based) gets p extra multiplications by the activation value
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int extra = ((32 * b + 8 * q) * P) / (32 * NB);   // = channel / Dp without a run-time division; wave-uniform
-        if (extra > 0) {
-          const float t0 = u[b][4 * q], t1 = u[b][4 * q + 1], t2 = u[b][4 * q + 2], t3 = u[b][4 * q + 3];
-          for (int i = 0; i < extra; ++i) {
-            u[b][4 * q] *= t0;
-            u[b][4 * q + 1] *= t1;
-            u[b][4 * q + 2] *= t2;
-            u[b][4 * q + 3] *= t3;
-          }
-        }
-      }
-  }
+  feature_powers<NB>(u, P);
 }
 
 // Two-layer feature-map MLP on one 32-token column block, all in registers.

@@ -48,6 +48,19 @@ def test_emptier_last_rounds(d, width, H, N, R, dtype):
     check(w.name, W.make_inputs(w), rows=np.unique(np.r_[0, 127, 128, 255, 256, N // 2, N - 130:N - 126, N - 1]))
 
 
+# 128-query tiles with a CU each (256 of them, 264 / 258 just beyond; two rows; a ragged last tile; no softmax keys at d = 64; rate 1; a
+# precomputed linear part with a loop long enough), every activation and several degrees: the map is evaluated by other code there
+@pytest.mark.parametrize("d,width,H,N,R,P", ((128, 128, 8, 4096, 4, 2), (128, 128, 8, 4097, 4, 2), (128, 128, 6, 2, 2, 2), (128, 128, 6, 131, 3, 4),
+                                             (128, 128, 7, 700, 4, 1), (64, 64, 2, 16384, 16, 2), (64, 64, 2, 16385, 16, 2), (64, 64, 3, 333, 0, 4),
+                                             (64, 0, 3, 333, 1, 2), (128, 256, 6, 1500, 2, 2), (128, 0, 16, 2048, 1, 2)))
+@pytest.mark.parametrize("dtype", ("bf16", "f32"))
+def test_one_workgroup_per_cu(d, width, H, N, R, P, dtype):
+    w = W.Workload(f"alone_d{d}_F{width}_H{H}_N{N}_{dtype}", 1, H, N, d, dtype, 128, R, width or d, width or d, poly_degree=P, seed=N)
+    rows = np.unique(np.r_[0, 127, 128, N // 2, N - 130:N - 126, N - 1]) if N > 600 else None
+    for act in ((0, 1, 2) if N < 1000 and R != 1 else (0,)):
+        check(w.name, W.make_inputs(w), rows=rows, act=act, layout="bnhd" if act == 1 else "bhnd")
+
+
 def test_one_more_row_of_tiles_is_not_one_more_round():
     """250 workgroups of 256 queries are one round on 256 CUs (122 us).  1.6 % more queries make 260 of them, a second round for
     ten (194 us, 1.57 times as long), or 510 of 128, one round of two per CU (145 us; by the cost model of the rule, 7.7 against
