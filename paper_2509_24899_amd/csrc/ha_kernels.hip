@@ -42,20 +42,13 @@ struct WeightPrep {
   __bf16 *w1f, *w2f;
   int HD, F;
 };
+// One 32-key block; vt: LDS, 32 rows of D + 8.
 template <int D, bool F32>
-__global__ __launch_bounds__(256) void compact_kernel(const void *__restrict__ k, const void *__restrict__ v,
-                                                      bf16x8 *__restrict__ ks_frag, bf16x8 *__restrict__ vs_frag,
-                                                      int H, int NS, int R, int G, int n_kblocks, int64_t sb,
-                                                      int64_t sh, int64_t sn, int BH, WeightPrep wp) {
+static __device__ __forceinline__ void compact_body(const void *__restrict__ k, const void *__restrict__ v, bf16x8 *__restrict__ ks_frag,
+                                                    bf16x8 *__restrict__ vs_frag, int H, int NS, int R, int G, int n_kblocks, int64_t sb,
+                                                    int64_t sh, int64_t sn, int kb, int bh, __bf16 (*vt)[D + 8]) {
   constexpr int CPR = D / 8;            // 16-byte chunks per row
   constexpr int FRAG = D * 4;           // bf16x8 per 32-key block (= D*32*2/16)
-  __shared__ __align__(16) __bf16 vt[32][D + 8];
-  const int kb = blockIdx.x, bh = blockIdx.y;
-  if (bh >= BH) {
-    weight_prep_body<F32>(wp.w1, wp.w2, wp.w1f, wp.w2f, D, wp.HD, wp.F, bh - BH, blockIdx.x * 256 + threadIdx.x);
-    return;
-  }
-  if (kb >= n_kblocks) return;
   const int64_t base = (int64_t)(bh / H) * sb + (int64_t)(bh % H) * sh;
   bf16x8 *kdst = ks_frag + ((int64_t)bh * n_kblocks + kb) * FRAG;
   bf16x8 *vdst = vs_frag + ((int64_t)bh * n_kblocks + kb) * FRAG;
@@ -81,9 +74,23 @@ __global__ __launch_bounds__(256) void compact_kernel(const void *__restrict__ k
     vdst[c] = o;
   }
 }
+template <int D, bool F32>
+__global__ __launch_bounds__(256) void compact_kernel(const void *__restrict__ k, const void *__restrict__ v,
+                                                      bf16x8 *__restrict__ ks_frag, bf16x8 *__restrict__ vs_frag,
+                                                      int H, int NS, int R, int G, int n_kblocks, int64_t sb,
+                                                      int64_t sh, int64_t sn, int BH, WeightPrep wp) {
+  __shared__ __align__(16) __bf16 vt[32][D + 8];
+  const int kb = blockIdx.x, bh = blockIdx.y;
+  if (bh >= BH) {
+    weight_prep_body<F32>(wp.w1, wp.w2, wp.w1f, wp.w2f, D, wp.HD, wp.F, bh - BH, blockIdx.x * 256 + threadIdx.x);
+    return;
+  }
+  if (kb >= n_kblocks) return;
+  compact_body<D, F32>(k, v, ks_frag, vs_frag, H, NS, R, G, n_kblocks, sb, sh, sn, kb, bh, vt);
+}
 
 // ------------------------------------------------------------------------------------------------
-// state_kernel (d = 64; ha_state.hip and ha_state256.hip serve d = 128): grid (n_chunks, B*H), 4 waves.  A chunk is CH linear tokens, walked in tiles of 128.
+// state_kernel (d = 64; ha_state.hip and ha_state256.hip serve d = 128): grid n_chunks * B*H (and compaction, below), 4 waves.  A chunk is CH linear tokens, walked in tiles of 128.
 // Per tile every wave runs the phi_k MLP on its 32 tokens (tokens are C columns), the four waves
 // park phi_k(k)^T and V^T in LDS with tokens contiguous, then the output tiles of
 // [S | z] = phi_k(K)^T [V | 1] are dealt round-robin to the waves and contracted over the tokens.
@@ -98,12 +105,22 @@ __global__ __launch_bounds__(256) void compact_kernel(const void *__restrict__ k
 // dz = sum_i dden_i phi_q(q_i) over all query tokens): `k` holds the queries, `v` a dense bf16 [B*H][NL][D]
 // tensor, token i's feature row is multiplied by rs[i] before it is rounded, and the "1" column becomes the pair
 // of columns (hi, lo) of wp[i].
+//
+// The weights are fetched from the caller's row-major tensors (WEIGHTED: as prepared fragments), and the workgroups behind the
+// chunks compact the softmax keys, a 32-key block each: as a launch of its own ahead of this one, with the weights' preparation, that
+// took 2.9 of 22.7 us of a call with H = 2, N = 1024, fp32.
+struct StateCompact {
+  bf16x8 *ks_frag, *vs_frag;
+  int NS, n_kblocks, BH, total;       // total: workgroups that have work
+};
+// (a grid dimension holds less than 2^32 threads)
+static inline dim3 state_grid(int total) { return dim3(total < 1 << 20 ? total : 1 << 20, (total + (1 << 20) - 1) >> 20); }
 template <int D, int HD, int F, bool F32, bool WEIGHTED = false>
 __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ k, const void *__restrict__ v,
-                                                       const bf16x8 *w1f_all, const bf16x8 *w2f_all,
+                                                       const void *__restrict__ w1_all, const void *__restrict__ w2_all,
                                                        const float *__restrict__ b1_all, const float *__restrict__ b2_all,
                                                        float *__restrict__ part, int H, int NL, int R, int G, int CH, int P,
-                                                       int act, int64_t sb, int64_t sh, int64_t sn,
+                                                       int act, int64_t sb, int64_t sh, int64_t sn, int n_chunks, StateCompact sc,
                                                        const float *__restrict__ rs_all = nullptr,
                                                        const float *__restrict__ wp_all = nullptr, int N = 0, int CC = 0,
                                                        int nsub = 1) {
@@ -115,19 +132,36 @@ __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ 
   constexpr int CG = D / 32;                  // groups of four 16-byte chunks per V row
   constexpr int VPT = (TOK / 16) * CG / 4;    // V chunks per thread per tile
   // the MLP weight fragments of this head live in LDS next to the two transposing arrays
-  static_assert((HD * D + F * HD) * 2 <= 64 * 1024, "the weights live in LDS");
+  static_assert((HD * D + F * HD) * 2 <= 64 * 1024 && HD * D % 2048 == 0 && F * HD % 2048 == 0, "the weights live in LDS");
   __shared__ __align__(16) __bf16 ft_s[F][PITCH];
   __shared__ __align__(16) __bf16 vt_s[D][PITCH];
   __shared__ bf16x8 wlds[(HD * D + F * HD) / 8];
   __shared__ __align__(16) __bf16 et[WEIGHTED ? 2 : 1][WEIGHTED ? PITCH : 8];
-  const int chunk = blockIdx.x, bh = blockIdx.y, h = bh % H;
+  const int BH = sc.BH, n_state = n_chunks * BH, id = blockIdx.y * gridDim.x + blockIdx.x;
+  if (id >= sc.total) return;
+  const bool compacting = !WEIGHTED && id >= n_state;
+  const int per_bh = compacting ? sc.n_kblocks : n_chunks, at = compacting ? id - n_state : id;
+  const int bh = at / per_bh, chunk = at - bh * per_bh, h = bh % H;
   const int64_t base = (int64_t)(bh / H) * sb + (int64_t)h * sh;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, kept scalar
-  const bf16x8 *w1g = w1f_all + (int64_t)h * (HD * D / 8);
-  const bf16x8 *w2g = w2f_all + (int64_t)h * (F * HD / 8);
-  for (int i = tid; i < HD * D / 8; i += 256) wlds[i] = w1g[i];
-  for (int i = tid; i < F * HD / 8; i += 256) wlds[HD * D / 8 + i] = w2g[i];
+  if constexpr (!WEIGHTED) {
+    if (compacting) {
+      static_assert(F >= 32 && PITCH >= D + 8, "the staging rows fit the feature tile");
+      compact_body<D, F32>(k, v, sc.ks_frag, sc.vs_frag, H, sc.NS, R, G, sc.n_kblocks, sb, sh, sn, chunk, bh,
+                           reinterpret_cast<__bf16 (*)[D + 8]>(&ft_s[0][0]));
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < HD * D / 8; i += 256) wlds[i + tid] = weight_piece<F32, false>(w1_all, (int64_t)h * (HD * D), D, i + tid);
+#pragma unroll
+    for (int i = 0; i < F * HD / 8; i += 256) wlds[HD * D / 8 + i + tid] = weight_piece<F32, true>(w2_all, (int64_t)h * (F * HD), HD, i + tid);
+  } else {
+    const bf16x8 *w1g = static_cast<const bf16x8 *>(w1_all) + (int64_t)h * (HD * D / 8);
+    const bf16x8 *w2g = static_cast<const bf16x8 *>(w2_all) + (int64_t)h * (F * HD / 8);
+    for (int i = tid; i < HD * D / 8; i += 256) wlds[i] = w1g[i];
+    for (int i = tid; i < F * HD / 8; i += 256) wlds[HD * D / 8 + i] = w2g[i];
+  }
   const lds_frag_ptr w1f = (lds_frag_ptr)&wlds[0], w2f = (lds_frag_ptr)&wlds[HD * D / 8];
   // the biases of this head sit in LDS (zeros when absent): their reads queue up with the weight reads
   // instead of exposing a vector-memory round trip in front of every chain of matrix instructions
@@ -291,7 +325,7 @@ __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ 
     __syncthreads();
   }
   if (w < GW) {
-    float *dst = part + ((int64_t)bh * gridDim.x + chunk) * NT * 1024 + (int64_t)w * TPW * 1024;
+    float *dst = part + ((int64_t)bh * n_chunks + chunk) * NT * 1024 + (int64_t)w * TPW * 1024;
 #pragma unroll
     for (int i = 0; i < TPW; ++i)
 #pragma unroll
@@ -495,12 +529,14 @@ hipError_t launch_state(const Plan &pl, const void *k, const void *v, const ha_f
                         hipStream_t st) {
   if (state_uses_pipelined_kernel(pl)) return launch_state_pipelined(pl, k, v, fm, ws, st);   // ha_state.hip
   if (pl.D == 128) return launch_state256(pl, k, v, fm, ws, st);                              // ha_state256.hip
-  dim3 grid(pl.n_chunks, pl.B * pl.H);
-  const bf16x8 *w1f = ws_ptr<bf16x8>(ws, pl.off_w1k), *w2f = ws_ptr<bf16x8>(ws, pl.off_w2k);
+  const int total = (pl.n_chunks + (state_compacts_softmax_keys(pl) ? pl.n_kblocks : 0)) * pl.B * pl.H;
+  const StateCompact sc = {ws_ptr<bf16x8>(ws, pl.off_ks), ws_ptr<bf16x8>(ws, pl.off_vs), pl.NS, pl.n_kblocks, pl.B * pl.H, total};
+  const dim3 grid = state_grid(total);
   float *part = ws_ptr<float>(ws, pl.off_part);
 #define HA_STATE(DD, HH, FF, F32) \
-  state_kernel<DD, HH, FF, F32><<<grid, 256, 0, st>>>(k, v, w1f, w2f, fm.b1, fm.b2, part, pl.H, pl.NL, pl.R, pl.G, pl.CH, \
-                                                     pl.P, pl.act_k, pl.sb, pl.sh, pl.sn, nullptr, nullptr, pl.N, pl.CC, pl.nsub)
+  state_kernel<DD, HH, FF, F32><<<grid, 256, 0, st>>>(k, v, fm.w1, fm.w2, fm.b1, fm.b2, part, pl.H, pl.NL, pl.R, pl.G, pl.CH, \
+                                                     pl.P, pl.act_k, pl.sb, pl.sh, pl.sn, pl.n_chunks, sc, nullptr, nullptr, pl.N, \
+                                                     pl.CC, pl.nsub)
   if (pl.f32) HA_STATE(64, 64, 64, true); else HA_STATE(64, 64, 64, false);
 #undef HA_STATE
   return hipGetLastError();
@@ -512,11 +548,11 @@ hipError_t launch_weighted_state(const Plan &pl, const void *q, const void *gsig
                                  int n_chunks, hipStream_t st) {
   if (state_uses_pipelined_kernel(pl))
     return launch_state_pipelined_weighted(pl, q, gsign, rs, wp, fm, w1f_, w2f_, part, CH, n_chunks, st);
-  dim3 grid(n_chunks, pl.B * pl.H);
-  const bf16x8 *w1f = static_cast<const bf16x8 *>(w1f_), *w2f = static_cast<const bf16x8 *>(w2f_);
+  const dim3 grid = state_grid(n_chunks * pl.B * pl.H);
+  const StateCompact sc = {nullptr, nullptr, 0, 0, pl.B * pl.H, n_chunks * pl.B * pl.H};
 #define HA_WSTATE(DD, F32) \
-  state_kernel<DD, DD, DD, F32, true><<<grid, 256, 0, st>>>(q, gsign, w1f, w2f, fm.b1, fm.b2, part, pl.H, pl.N, 0, 1, CH, pl.P, \
-                                                            pl.act_q, pl.sb, pl.sh, pl.sn, rs, wp)
+  state_kernel<DD, DD, DD, F32, true><<<grid, 256, 0, st>>>(q, gsign, w1f_, w2f_, fm.b1, fm.b2, part, pl.H, pl.N, 0, 1, CH, pl.P, \
+                                                            pl.act_q, pl.sb, pl.sh, pl.sn, n_chunks, sc, rs, wp)
   if (pl.f32) HA_WSTATE(64, true); else HA_WSTATE(64, false);
 #undef HA_WSTATE
   return hipGetLastError();
