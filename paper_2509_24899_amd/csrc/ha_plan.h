@@ -169,6 +169,7 @@ struct WideMlpLayer {
   void *h_hi, *out_hi, *out_lo, *out_u;
   float *out_stat;
   int K, NOUT, n_tok, R;
+  bool channel_lanes;      // last layer: a channel per lane and the tokens in the registers (what the state pass reads)
 };
 hipError_t launch_wide_mlp(const Plan &pl, const WideMlpLayer &l, hipStream_t st);
 // ha_wide.hip / ha_wide_grad.hip.  keep_hidden: leave the first hidden layer's image in the workspace (a backward pass

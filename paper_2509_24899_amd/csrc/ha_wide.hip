@@ -8,7 +8,7 @@
 //                          layer: fp32 pre-activations); h' as hi + lo bf16
 //   (output stage)         softmax / exp / relu over all channels of a token, slice powers, bf16: applied by the two
 //                          consumers below while they read the pre-activations, so phi never visits HBM
-//   wide_state_kernel      [S | z] += phi_k^T [V | 1], one 128-channel slab of S per workgroup
+//   wide_state_kernel      [S | z] += phi_k^T [V | 1], a slab of 256 or 128 features per workgroup
 //   wide_lin_kernel        n_i = phi_q(q_i) S   (fp32, in the layout of the query kernel's accumulators), e_i = phi_q(q_i).z
 // The query kernel then adds n_i and e_i in its epilogue instead of evaluating phi_q itself.
 //
@@ -16,7 +16,8 @@
 //   activations   bf16x8 [bh][tb][W/32][2][64]   piece (block c, half s) = channels 32 c + crow(8 s + t, g), t = 0..7,
 //                                                i.e. the B operand ("chained" order) of the next product
 //   fp32 tiles    f32x4  [bh][tb][W/32][4][64]   piece (block c, quad x) = channels 32 c + crow(4 x + j, g), j = 0..3
-#include "ha_device.h"
+//   the same for the state pass: lane = 32 g + r owns channel 32 c + r, piece (block c, quad x) = tokens 32 tb + crow(4 x + j, g)
+#include "ha_mlp128.h"
 #include "ha_plan.h"
 
 namespace ha {
@@ -95,94 +96,161 @@ static __device__ __forceinline__ void wide_phi_tile(const f32x4 (&raw)[4], int 
     out[s] = __builtin_convertvector(t8, bf16x8);
   }
 }
-static __device__ __forceinline__ void wide_load_tile(const f32x4 *__restrict__ src, int fb, f32x4 (&raw)[4]) {
-#pragma unroll
-  for (int x4 = 0; x4 < 4; ++x4) raw[x4] = src[(fb * 4 + x4) * 64];
-}
-static __device__ __forceinline__ void wide_phi_tile(const f32x4 *__restrict__ src, int fb, const WideOutStage &o, bool valid,
-                                                     bf16x8 (&out)[2]) {
-  f32x4 raw[4];
-  wide_load_tile(src, fb, raw);
-  wide_phi_tile(raw, fb, o, valid, out);
-}
 
 // ------------------------------------------------------------------------------------------------
-// wide_state_kernel: grid (n_chunks, B*H, F / 128), 4 waves.  As the contraction half of state_kernel, with
-// phi_k formed from the fp32 pre-activations of the last layer as they are read; workgroup z owns feature rows
-// 128 z .. 128 z + 127 of [S | z], wave w row block w of those.  Partial tiles go where state_kernel puts them
-// (part[bh][chunk][row block * NCB + column block][v][lane]), so state_reduce_kernel serves both.
-template <int D, bool F32>
-__global__ __launch_bounds__(256, 1) void wide_state_kernel(const f32x4 *__restrict__ u_img, const float *__restrict__ stat,
-                                                            const void *__restrict__ v, float *__restrict__ part, int H,
-                                                            int NL, int R, int G, int CH, int F, int n_tb, int act, int P,
-                                                            int64_t sb, int64_t sh, int64_t sn) {
-  constexpr int TOK = 128, PITCH = TOK + 8, NCB = D / 32 + 1;
-  constexpr int CG = D / 32, VPT = (TOK / 16) * CG / 4;
-  __shared__ __align__(16) __bf16 ft[128][PITCH];
-  __shared__ __align__(16) __bf16 vt[D][PITCH];
-  const int chunk = blockIdx.x, bh = blockIdx.y, zb = blockIdx.z, h = bh % H;
+// wide_state_kernel: [S | z] += phi_k^T [V | 1] of one chunk of tokens, one (batch, head) and 32 NW features, a 32-row block of them
+// per wave.  The pre-activations arrive with a channel per lane and the tokens in the registers (WideMlpLayer::channel_lanes), so
+// phi_k, formed as they are read, is the A operand of the contraction as it stands; only the V rows go through LDS (row-major,
+// double buffered, 64 tokens at a time, one barrier per 64; transposing reads), and with them what the output stage needs per token.
+// Both travel a tile ahead, the pre-activations a tile ahead in registers.  The workgroups of a chunk are consecutive on one XCD,
+// so that its V rows leave HBM once.
+// Partial tiles go where state_kernel puts them (part[bh][chunk][row block * NCB + column block][v][lane]), so state_reduce_kernel
+// serves both.
+// Bound: HBM, the fp32 pre-activations.  768 wide, 480p / 81 frames, R = 8, 12 heads (1.06 GB of them): 467 us with phi transposed
+// through LDS two bytes at a time by workgroups of 128 features (8 % matrix cores, 67 % of the wave cycles waiting; 465 with V
+// fetched once), 512 with the statistics waited for where they are requested, 265 us here (4.4 TB/s).
+template <int NW, bool F32>
+__global__ __launch_bounds__(64 * NW, 2) void wide_state_kernel(const f32x4 *__restrict__ u_img, const float *__restrict__ stat,
+                                                                const void *__restrict__ v, float *__restrict__ part, int H,
+                                                                int NL, int R, int G, int CH, int F, int n_tb, int act, int P,
+                                                                int64_t sb, int64_t sh, int64_t sn, int n_chunks, int n_pairs) {
+  constexpr int D = 128, TOK = 64, NCB = D / 32 + 1;
+  typedef RowTile<D> RT;
+  constexpr int VROW = RT::ROWB, PPR = RT::PPR, VPT = TOK * PPR / (64 * NW);
+  __shared__ __align__(16) char v_t[2][TOK * VROW];
+  __shared__ __align__(16) float tok_off[2][TOK], tok_inv[2][TOK];
+  const int FB = F / 32, nz = FB / NW;
+  const int in_xcd = blockIdx.x >> 3, pair = (in_xcd / nz) * 8 + (blockIdx.x & 7), zb = in_xcd % nz;
+  if (pair >= n_pairs) return;
+  const int bh = pair / n_chunks, chunk = pair - bh * n_chunks, h = bh % H;
   const int64_t base = (int64_t)(bh / H) * sb + (int64_t)h * sh;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int FB = F / 32;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), fb = zb * NW + w;
   const LinearMap lmap(R, G);
+  const int lt_begin = chunk * CH, lt_end = min(lt_begin + CH, NL);
+
+  // V rows of a tile and (wave 0) the statistics of its tokens, on their way in registers
+  constexpr int MAXB = WIDE_FMAX / 128;
+  const int nblk = F / 128;
+  bf16x8 vreg[VPT];
+  float st_m[MAXB], st_s[MAXB];
+  auto load_tile = [&](int t0) {
+#pragma unroll
+    for (int c = 0; c < VPT; ++c) {
+      const int i = c * 64 * NW + tid, row = i / PPR, pp = i % PPR;
+      const int tok = lmap.token(min(t0 + row, NL - 1));
+      vreg[c] = load8<F32>(v, base + (int64_t)tok * sn + (pp ^ RT::sw(row)) * 8);
+    }
+    if (act == 0 && w == 0) {
+      const int tb = min(t0 / 32 + (lane >> 5), n_tb - 1);
+      const float *st = stat + ((int64_t)bh * n_tb + tb) * nblk * 128 + r;
+#pragma unroll
+      for (int b = 0; b < MAXB; ++b) {                 // (blocks there are not repeat the first)
+        st_m[b] = st[(b < nblk ? b : 0) * 128];
+        st_s[b] = st[(b < nblk ? b : 0) * 128 + 64];
+      }
+    }
+  };
+  // (fragment 32-token block tb, quad x4): tokens crow(4 x4 + j, g) of channel 32 fb + r
+  f32x4 raw[2][4];
+  auto load_u = [&](int t0, int blk) {
+    const f32x4 *src = u_img + (((int64_t)bh * n_tb + min(t0 / 32 + blk, n_tb - 1)) * FB + fb) * 256 + lane;
+#pragma unroll
+    for (int x4 = 0; x4 < 4; ++x4) raw[blk][x4] = src[x4 * 64];
+  };
   f32x16 acc[NCB];
 #pragma unroll
   for (int i = 0; i < NCB; ++i)
 #pragma unroll
     for (int x = 0; x < 16; ++x) acc[i][x] = 0.f;
-  const int tf = w * 32 + r;
-  int fcol[4];
+  // slice power - 1 of this lane's channel = (8-channel group) / (groups per slice); exact in fp32 for these sizes
+  const int extra = (int)(((float)(4 * fb + (r >> 3)) + 0.5f) * (8.0f * (float)P / (float)F));
+  // transposing reads: lane = (group tm, row ti, columns ta); slot (g, t) of half s holds token 16 s + crow(t, g) (see ds_read_tr)
+  const int tm = lane >> 4, ti = (lane >> 2) & 3, ta = lane & 3, tg = tm >> 1;
+  int v_base[D / 32];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) fcol[q] = (4 * g) * PITCH + ((((tf >> 3) ^ (2 * q)) << 3) | (tf & 7));
-  const int vsw = (lane >> 4) << 1;
-  const int vrow0 = 8 * (lane >> 4) * PITCH;
-  const int rsw = ((r >> 3) & 3) << 1;
-  __bf16 *ftp = &ft[0][0];
-  __bf16 *vtp = &vt[0][0];
-  const __bf16 one = static_cast<__bf16>(r == 0 ? 1.0f : 0.0f);
+  for (int cb = 0; cb < D / 32; ++cb)
+    v_base[cb] = (4 * tg + ti) * VROW + (((4 * cb + 2 * (tm & 1) + (ta >> 1)) ^ RT::sw(ti)) << 4) + 8 * (ta & 1);
+  const __bf16 one = static_cast<__bf16>(r == 0 ? 1.0f : 0.0f);     // the "1" column that yields z
   const bf16x8 ones = bf16x8{one, one, one, one, one, one, one, one};
-  const int lt_begin = chunk * CH, lt_end = min(lt_begin + CH, NL);
-  for (int t0 = lt_begin; t0 < lt_end; t0 += TOK) {
-    bf16x8 vreg[VPT];
+
+  load_tile(lt_begin);
+  HA_FENCE();                                          // (in the loop's order: the compiler counts what may be in flight over both ways in)
+  load_u(lt_begin, 0);
+  HA_FENCE();
+  load_u(lt_begin, 1);
+  int buf = 0;
+  for (int t0 = lt_begin; t0 < lt_end; t0 += TOK, buf ^= 1) {
+    // (this buffer was last read two tiles ago: every wave has passed the barrier of the tile between since)
 #pragma unroll
-    for (int p = 0; p < VPT; ++p) {
-      const int trow = 16 * ((4 * p + w) & 7) + (lane & 15), c8 = 4 * (p >> 1) + (lane >> 4);
-      const int tok = lmap.token(min(t0 + trow, NL - 1));
-      vreg[p] = load8<F32>(v, base + (int64_t)tok * sn + c8 * 8);
+    for (int c = 0; c < VPT; ++c) {
+      const int i = c * 64 * NW + tid;
+      *reinterpret_cast<bf16x8 *>(&v_t[buf][i * 16]) = vreg[c];
     }
-    const int tb = min(t0 / 32 + w, n_tb - 1);            // blocks past the end: clamped, their tokens are not valid
-    const bool valid = t0 + tf < NL;
-    const WideOutStage os = wide_out_stage(stat, (int64_t)bh * n_tb + tb, F, act, P, lane);
-    const f32x4 *usrc = u_img + ((int64_t)bh * n_tb + tb) * FB * 256 + lane;
-    bf16x8 ph[4][2];
+    if (act == 0 && w == 0) {
+      float m = st_m[0], sum = 0.f;
 #pragma unroll
-    for (int fb = 0; fb < 4; ++fb) wide_phi_tile(usrc, 4 * zb + fb, os, valid, ph[fb]);
+      for (int b = 1; b < MAXB; ++b) m = fmaxf(m, st_m[b]);
 #pragma unroll
-    for (int fb = 0; fb < 4; ++fb)
-#pragma unroll
-      for (int x = 0; x < 16; ++x) ftp[(32 * fb + 8 * (x >> 2) + (x & 3)) * PITCH + fcol[x >> 2]] = ph[fb][x >> 3][x & 7];
-#pragma unroll
-    for (int p = 0; p < VPT; ++p) {
-      const int trow = 16 * ((4 * p + w) & 7) + (lane & 15);
-      const int col = (((trow >> 3) ^ vsw) << 3) | (trow & 7);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) vtp[(32 * (p >> 1) + i) * PITCH + vrow0 + col] = vreg[p][i];
+      for (int b = 0; b < MAXB; ++b) sum += b < nblk ? st_s[b] * fast_exp2((st_m[b] - m) * kLog2e) : 0.f;
+      tok_off[buf][lane] = -m * kLog2e;
+      tok_inv[buf][lane] = 1.0f / sum;
     }
     __syncthreads();
+    const int t1 = t0 + TOK < lt_end ? t0 + TOK : t0;
+    load_tile(t1);
+    HA_FENCE();
 #pragma unroll
-    for (int ks = 0; ks < TOK / 16; ++ks) {
-      const int col = ((2 * ks + g) ^ rsw) << 3;
-      const bf16x8 af = *reinterpret_cast<const bf16x8 *>(&ftp[(32 * w + r) * PITCH + col]);
+    for (int blk = 0; blk < 2; ++blk) {
+      f32x16 u;
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        const bf16x8 bfr = cb < D / 32 ? *reinterpret_cast<const bf16x8 *>(&vtp[(32 * cb + r) * PITCH + col]) : ones;
-        acc[cb] = mfma32(af, bfr, acc[cb]);
+      for (int x4 = 0; x4 < 4; ++x4)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[4 * x4 + j] = raw[blk][x4][j];
+      load_u(t1, blk);
+      if (act == 0) {                                            // one branch per block, not one per value
+#pragma unroll
+        for (int x4 = 0; x4 < 4; ++x4) {
+          const f32x4 o4 = *reinterpret_cast<const f32x4 *>(&tok_off[buf][32 * blk + 8 * x4 + 4 * g]);
+          const f32x4 i4 = *reinterpret_cast<const f32x4 *>(&tok_inv[buf][32 * blk + 8 * x4 + 4 * g]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) u[4 * x4 + j] = fast_exp2(__builtin_fmaf(u[4 * x4 + j], kLog2e, o4[j])) * i4[j];
+        }
+      } else if (act == 1) {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) u[x] = fast_exp2(u[x] * kLog2e);
+      } else {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) u[x] = fmaxf(u[x], 0.f);
+      }
+      if (P > 1) {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+          const float a0 = u[x], a2 = a0 * a0;
+          float t = (extra & 1) ? a2 : a0;                       // a0^(extra + 1), extra in 0..7
+          t = (extra & 2) ? t * a2 : t;
+          u[x] = (extra & 4) ? t * (a2 * a2) : t;
+        }
+      }
+      if (t0 + 32 * (blk + 1) > lt_end) {                        // padded tokens of a ragged tile add nothing, whatever they hold
+#pragma unroll
+        for (int x = 0; x < 16; ++x) u[x] = t0 + 32 * blk + crow(x, g) < lt_end ? u[x] : 0.f;
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        f32x8 t8;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t8[i] = u[8 * s + i];
+        const bf16x8 phi = __builtin_convertvector(t8, bf16x8);
+        const char *vt = &v_t[buf][(32 * blk + 16 * s) * VROW];
+#pragma unroll
+        for (int cb = 0; cb < D / 32; ++cb)
+          acc[cb] = mfma32(phi, join(ds_read_tr(vt, v_base[cb]), ds_read_tr(vt, v_base[cb] + 8 * VROW)), acc[cb]);
+        acc[D / 32] = mfma32(phi, ones, acc[D / 32]);
       }
     }
-    __syncthreads();
   }
-  float *dst = part + (((int64_t)bh * gridDim.x + chunk) * FB + 4 * zb + w) * NCB * 1024;
+  float *dst = part + ((int64_t)pair * FB + fb) * NCB * 1024;
 #pragma unroll
   for (int i = 0; i < NCB; ++i)
 #pragma unroll
@@ -365,6 +433,7 @@ hipError_t launch_wide_map(const Plan &pl, const WidePlan &wp, const void *x, co
   l.NOUT = pl.F;
   l.out_u = ws_ptr<void>(ws, wp.off_u);
   l.out_stat = ws_ptr<float>(ws, wp.off_stat);
+  l.channel_lanes = !is_query && !keep_hidden;         // (a backward pass reads a token per lane, as the query side does)
   return launch_wide_mlp(pl, l, st);
 }
 
@@ -373,15 +442,16 @@ hipError_t launch_wide_key_side(const Plan &pl, const WidePlan &wp, const void *
                                 void *ws, hipStream_t st) {
   hipError_t e = launch_wide_map(pl, wp, k, phi_k, false, ws, st, false);
   if (e != hipSuccess) return e;
-  dim3 grid(pl.n_chunks, pl.B * pl.H, pl.F / 128);
-  if (pl.f32)
-    wide_state_kernel<128, true><<<grid, 256, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat), v,
-                                                       ws_ptr<float>(ws, pl.off_part), pl.H, pl.NL, pl.R, pl.G, pl.CH, pl.F,
-                                                       wp.n_tb_k, pl.act_k, pl.P, pl.sb, pl.sh, pl.sn);
-  else
-    wide_state_kernel<128, false><<<grid, 256, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat), v,
-                                                        ws_ptr<float>(ws, pl.off_part), pl.H, pl.NL, pl.R, pl.G, pl.CH, pl.F,
-                                                        wp.n_tb_k, pl.act_k, pl.P, pl.sb, pl.sh, pl.sn);
+  // eight row blocks per workgroup where the width has them: V is fetched for half as many, and a barrier serves twice the work
+  const int n_pairs = pl.n_chunks * pl.B * pl.H, nw = pl.F % 256 == 0 ? 8 : 4;
+  const dim3 grid((n_pairs + 7) / 8 * 8 * (pl.F / 32 / nw));
+#define HA_WIDE_STATE(NW, F32) \
+  wide_state_kernel<NW, F32><<<grid, 64 * NW, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat), v, \
+                                                       ws_ptr<float>(ws, pl.off_part), pl.H, pl.NL, pl.R, pl.G, pl.CH, pl.F, \
+                                                       wp.n_tb_k, pl.act_k, pl.P, pl.sb, pl.sh, pl.sn, pl.n_chunks, n_pairs)
+  if (nw == 8) { if (pl.f32) HA_WIDE_STATE(8, true); else HA_WIDE_STATE(8, false); }
+  else { if (pl.f32) HA_WIDE_STATE(4, true); else HA_WIDE_STATE(4, false); }
+#undef HA_WIDE_STATE
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return launch_state_reduce(pl, ws, st);
 }

@@ -46,11 +46,35 @@ struct WideMlpArgs {
   int64_t sb, sh, sn;
 };
 
-// SRC: 0 from x in bf16, 1 from x in fp32, 2 from HBM.  LAST: fp32 pre-activations out; otherwise relu, hi + lo bf16.
+// Maximum and sum over the 32 lanes of a half wave, in every one of them.
+template <int CTRL>
+static __device__ __forceinline__ float dpp(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+static __device__ __forceinline__ float half_max(float x) {
+  x = fmaxf(x, dpp<0xB1>(x));                      // lane ^ 1, lane ^ 2, then mirrored eights and sixteens
+  x = fmaxf(x, dpp<0x4E>(x));
+  x = fmaxf(x, dpp<0x141>(x));
+  x = fmaxf(x, dpp<0x140>(x));
+  const u32x2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+static __device__ __forceinline__ float half_sum(float x) {
+  x += dpp<0xB1>(x);
+  x += dpp<0x4E>(x);
+  x += dpp<0x141>(x);
+  x += dpp<0x140>(x);
+  const u32x2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
+// SRC: 0 from x in bf16, 1 from x in fp32, 2 from HBM.  OUT: 0 relu, hi + lo bf16 (a hidden layer); 1 fp32 pre-activations (the last
+// layer), a token per lane; 2 the same with a channel per lane and the tokens in the registers, for the state pass, whose
+// contraction over the tokens takes them as they are: the operands of every product change places, nothing else.
 // NBUF: slabs in the ring, at most K / 32 + 1.
-template <int NT, int SRC, bool LAST, int NBUF>
+template <int NT, int SRC, int OUT, int NBUF>
 __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
-  constexpr bool X = SRC != 2;
+  constexpr bool X = SRC != 2, LAST = OUT != 0, TR = OUT == 2;
   constexpr int D = 128, KS = D / 16, NW = 8;
   constexpr int CH = (X ? KS : 0) + 2 * NT, PW = CH / NW, SLOT = CH * 64;      // 1 KiB chunks per slab, per wave
   constexpr int WMAX = 768;
@@ -164,10 +188,11 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
   f32x16 acc[NT];
   auto products = [&](int gi, bf16x8 hi8, bf16x8 lo8) {
     const int fb = 2 * (gi % (NT / 2));
-    acc[fb] = mfma32(fr[gi % NF][0], lo8, acc[fb]);
-    acc[fb + 1] = mfma32(fr[gi % NF][1], lo8, acc[fb + 1]);
-    acc[fb] = mfma32(fr[gi % NF][0], hi8, acc[fb]);
-    acc[fb + 1] = mfma32(fr[gi % NF][1], hi8, acc[fb + 1]);
+    auto mul = [](bf16x8 wgt, bf16x8 h, f32x16 c) { return TR ? mfma32(h, wgt, c) : mfma32(wgt, h, c); };
+    acc[fb] = mul(fr[gi % NF][0], lo8, acc[fb]);
+    acc[fb + 1] = mul(fr[gi % NF][1], lo8, acc[fb + 1]);
+    acc[fb] = mul(fr[gi % NF][0], hi8, acc[fb]);
+    acc[fb + 1] = mul(fr[gi % NF][1], hi8, acc[fb + 1]);
   };
   u32x4 h_hi[2], h_lo[2];                                                      // from x: the hidden block of the current slab
   auto hop = [](const u32x4 &t) { return __builtin_bit_cast(bf16x8, t); };
@@ -193,7 +218,18 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
     }
     const bool live = cur.tb < a.n_tb;             // idle waves keep staging and synchronising
 #pragma unroll
-    for (int j = 0; j < NT; ++j) acc[j] = column_tile(bias, cur.ob0 + j, g);
+    for (int j = 0; j < NT; ++j) {
+      if constexpr (TR) {
+        float b = bias[32 * (cur.ob0 + j) + r];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          asm volatile("" : "+v"(b));           // (sixteen copies: known to be one value, the tile was kept twice, in scratch)
+          acc[j][v] = b;
+        }
+      } else {
+        acc[j] = column_tile(bias, cur.ob0 + j, g);
+      }
+    }
     if constexpr (X) {
       if (new_x) {                                 // the first hidden block of a tile; the others are formed on the way
         load_x(cur);
@@ -288,6 +324,34 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
 #pragma unroll
           for (int x4 = 0; x4 < 4; ++x4)
             a.out_u[((blk0 + j) * 4 + x4) * 64 + lane] = f32x4{acc[j][4 * x4], acc[j][4 * x4 + 1], acc[j][4 * x4 + 2], acc[j][4 * x4 + 3]};
+        if constexpr (TR) {
+          // per token (register v of half g: token crow(v, g) of the block) the maximum over this item's channels and the sum of exponentials
+          // against it, in the statistics of the first 128 of them; a second 128 hold nothing more
+          f32x4 m = {0.f, 0.f, 0.f, 0.f}, sum = m;           // lane r < 4 keeps registers 4 r .. 4 r + 3: tokens 8 r + 4 g .. + 3
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            float t = acc[0][v];
+#pragma unroll
+            for (int j = 1; j < NT; ++j) t = fmaxf(t, acc[j][v]);
+            const float mv = half_max(t), off = -mv * kLog2e;
+            t = 0.f;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) t += fast_exp2(__builtin_fmaf(acc[j][v], kLog2e, off));
+            const float sv = half_sum(t);
+            m[v & 3] = r == v / 4 ? mv : m[v & 3];
+            sum[v & 3] = r == v / 4 ? sv : sum[v & 3];
+            if (v % 2) HA_FENCE();                           // (two chains at a time: the registers are full)
+          }
+          if (r < 4) {
+            float *st = a.out_stat + ((((int64_t)cur.bh * a.n_tb + cur.tb) * (OB / 4) + cur.ob0 / 4) * 2) * 64 + 8 * r + 4 * g;
+            *reinterpret_cast<f32x4 *>(st) = m;
+            *reinterpret_cast<f32x4 *>(st + 64) = sum;
+            if constexpr (NT == 8) {
+              *reinterpret_cast<f32x4 *>(st + 128) = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+              *reinterpret_cast<f32x4 *>(st + 192) = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+          }
+        } else {
         // per token and 128 channels: their maximum and the sum of exponentials against it, so that the output stage can
         // form the softmax over all channels with a single sweep over the pre-activations
 #pragma unroll
@@ -308,6 +372,7 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
           float *st = a.out_stat + ((((int64_t)cur.bh * a.n_tb + cur.tb) * (OB / 4) + (cur.ob0 + j0) / 4) * 2) * 64 + lane;
           st[0] = m;
           st[64] = sum;
+        }
         }
       } else {
 #pragma unroll
@@ -378,8 +443,9 @@ hipError_t launch_wide_mlp(const Plan &pl, const WideMlpLayer &l, hipStream_t st
     // the longest ring that fits LDS and the shortest contraction of its instance
 #define HA_WIDE_MLP(NT, SRC, NBUF) \
   do { \
-    if (l.out_u) wide_mlp_kernel<NT, SRC, true, NBUF><<<nwg, 512, 0, st>>>(a); \
-    else wide_mlp_kernel<NT, SRC, false, NBUF><<<nwg, 512, 0, st>>>(a); \
+    if (l.out_u && l.channel_lanes) wide_mlp_kernel<NT, SRC, 2, NBUF><<<nwg, 512, 0, st>>>(a); \
+    else if (l.out_u) wide_mlp_kernel<NT, SRC, 1, NBUF><<<nwg, 512, 0, st>>>(a); \
+    else wide_mlp_kernel<NT, SRC, 0, NBUF><<<nwg, 512, 0, st>>>(a); \
   } while (0)
 #define HA_WIDE_MLP_SRC(NT, NBUF_X, NBUF_HBM) \
   do { \
