@@ -3,7 +3,7 @@
 // all its output channels in registers, which ends at 256 channels.  Here every layer is a pass of its own and
 // activations travel through HBM, in exactly the register image the next product wants:
 //
-//   wide_prep_kernel       one weight matrix -> A-operand fragments (natural order for layer 1, chained after it)
+//   wide_prep_kernel       weight matrices -> A-operand fragments (natural order for layer 1, chained after it)
 //   (ha_wide_mlp.hip)      h^T = relu(W1 x^T + b1) on the way into  h'^T = relu(W h^T + b)  or  u^T = W h^T + b  (last
 //                          layer: fp32 pre-activations); h' as hi + lo bf16
 //   (output stage)         softmax / exp / relu over all channels of a token, slice powers, bf16: applied by the two
@@ -23,12 +23,26 @@
 namespace ha {
 
 // ------------------------------------------------------------------------------------------------
-// wide_prep_kernel: grid (ceil(NOUT*K / 2048), H).  W [H][NOUT][K] (io dtype) -> fragments, see weight_piece
-template <bool F32, bool CHAINED>
-__global__ __launch_bounds__(256) void wide_prep_kernel(const void *__restrict__ wsrc, bf16x8 *__restrict__ wf, int NOUT, int K) {
-  const int piece = blockIdx.x * 256 + threadIdx.x;
-  const int64_t n = (int64_t)NOUT * K, base = blockIdx.y * n;
-  if (piece < n / 8) wf[base / 8 + piece] = weight_piece<F32, CHAINED>(wsrc, base, K, piece);
+// wide_prep_kernel: grid (2048 weights each, H).  W [H][NOUT][K] (io dtype) of all layers of a map -> fragments, see weight_piece.
+// (A launch per layer takes 5 - 8 us each, one behind the other: three layers at 768, 12 heads, 21 us, in one launch 14; whole calls with two
+// layers, H = 2, N = 2000, 384 wide 100.5 -> 97.2, H = 1, N = 300, 768 wide 140.3 -> 136.6.)
+struct WidePrepLayer {
+  const void *w;
+  bf16x8 *frags;
+  int NOUT, K, first;                 // first: the layer's first column of the grid
+  bool chained;
+};
+struct WidePrepMap {
+  WidePrepLayer layer[3];
+};
+template <bool F32>
+__global__ __launch_bounds__(256) void wide_prep_kernel(WidePrepMap m) {
+  const int col = blockIdx.x;
+  const WidePrepLayer l = col >= m.layer[2].first ? m.layer[2] : col >= m.layer[1].first ? m.layer[1] : m.layer[0];
+  const int piece = (col - l.first) * 256 + threadIdx.x;
+  const int64_t n = (int64_t)l.NOUT * l.K, base = blockIdx.y * n;
+  if (piece >= n / 8) return;
+  l.frags[base / 8 + piece] = l.chained ? weight_piece<F32, true>(l.w, base, l.K, piece) : weight_piece<F32, false>(l.w, base, l.K, piece);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -391,20 +405,19 @@ hipError_t launch_wide_map(const Plan &pl, const WidePlan &wp, const void *x, co
   const int KL = pl.DM > 0 ? pl.DM : pl.HD;
   // weight fragments of this map
   {
-    auto prep = [&](const void *wsrc, size_t off, int nout, int kdim, bool chained) {
-      dim3 grid((nout * kdim / 8 + 255) / 256, pl.H);
-      bf16x8 *dst = ws_ptr<bf16x8>(ws, off);
-      if (pl.f32) {
-        if (chained) wide_prep_kernel<true, true><<<grid, 256, 0, st>>>(wsrc, dst, nout, kdim);
-        else wide_prep_kernel<true, false><<<grid, 256, 0, st>>>(wsrc, dst, nout, kdim);
-      } else {
-        if (chained) wide_prep_kernel<false, true><<<grid, 256, 0, st>>>(wsrc, dst, nout, kdim);
-        else wide_prep_kernel<false, false><<<grid, 256, 0, st>>>(wsrc, dst, nout, kdim);
-      }
+    WidePrepMap m;
+    int n = 0, cols = 0;
+    auto layer = [&](const void *w, size_t off, int nout, int kdim, bool chained) {
+      m.layer[n++] = WidePrepLayer{w, ws_ptr<bf16x8>(ws, off), nout, kdim, cols, chained};
+      cols += (nout * kdim / 8 + 255) / 256;
     };
-    prep(fm.w1, wp.off_w1, pl.HD, pl.D, false);
-    if (pl.DM > 0) prep(fm.w_mid, wp.off_wm, pl.DM, pl.HD, true);
-    prep(fm.w2, wp.off_w2, pl.F, KL, true);
+    layer(fm.w1, wp.off_w1, pl.HD, pl.D, false);
+    if (pl.DM > 0) layer(fm.w_mid, wp.off_wm, pl.DM, pl.HD, true);
+    layer(fm.w2, wp.off_w2, pl.F, KL, true);
+    if (n == 2) m.layer[2] = m.layer[1];
+    const dim3 grid(cols, pl.H);
+    if (pl.f32) wide_prep_kernel<true><<<grid, 256, 0, st>>>(m);
+    else wide_prep_kernel<false><<<grid, 256, 0, st>>>(m);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   // x -> first hidden layer (-> middle layer, hi + lo images) -> fp32 pre-activations and softmax statistics
