@@ -42,13 +42,9 @@ static __device__ __forceinline__ void relu_hi_lo(const f32x16 &t, u32x4 (&hi)[2
 // relu(W1[block, :] x + b1[block]) of hidden block hb from the head of its slab.
 static __device__ __forceinline__ void hidden_block(lds_frag_ptr sl, const float *b1, int hb, const bf16x8 (&xf)[8], int lane, int g,
                                                     u32x4 (&h_hi)[2], u32x4 (&h_lo)[2]) {
-  bf16x8 wl[8];
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) wl[ks] = frag_at(sl, ks, lane);
   f32x16 hh = column_tile(b1, hb, g);
-  HA_FENCE();                                             // all reads on their way ahead of the chain
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) hh = mfma32(wl[ks], xf[ks], hh);
+  for (int ks = 0; ks < 8; ++ks) hh = mfma32(frag_at(sl, ks, lane), xf[ks], hh);
   relu_hi_lo(hh, h_hi, h_lo);
 }
 
