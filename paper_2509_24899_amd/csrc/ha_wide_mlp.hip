@@ -352,27 +352,27 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
             }
           }
         } else {
-        // per token and 128 channels: their maximum and the sum of exponentials against it, so that the output stage can
-        // form the softmax over all channels with a single sweep over the pre-activations
+          // per token and 128 channels: their maximum and the sum of exponentials against it, so that the output stage can
+          // form the softmax over all channels with a single sweep over the pre-activations
 #pragma unroll
-        for (int j0 = 0; j0 < NT; j0 += 4) {
-          float m = acc[j0][0];
+          for (int j0 = 0; j0 < NT; j0 += 4) {
+            float m = acc[j0][0];
 #pragma unroll
-          for (int j = j0; j < j0 + 4; ++j)
+            for (int j = j0; j < j0 + 4; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; v += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, acc[j][v]), acc[j][v + 1]);
-          m = xhalf_max(m);
-          const float off = -m * kLog2e;
-          float sum = 0.f;
+              for (int v = 0; v < 16; v += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, acc[j][v]), acc[j][v + 1]);
+            m = xhalf_max(m);
+            const float off = -m * kLog2e;
+            float sum = 0.f;
 #pragma unroll
-          for (int j = j0; j < j0 + 4; ++j)
+            for (int j = j0; j < j0 + 4; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sum += fast_exp2(__builtin_fmaf(acc[j][v], kLog2e, off));
-          sum = xhalf_sum(sum);
-          float *st = a.out_stat + ((((int64_t)cur.bh * a.n_tb + cur.tb) * (OB / 4) + (cur.ob0 + j0) / 4) * 2) * 64 + lane;
-          st[0] = m;
-          st[64] = sum;
-        }
+              for (int v = 0; v < 16; ++v) sum += fast_exp2(__builtin_fmaf(acc[j][v], kLog2e, off));
+            sum = xhalf_sum(sum);
+            float *st = a.out_stat + ((((int64_t)cur.bh * a.n_tb + cur.tb) * (OB / 4) + (cur.ob0 + j0) / 4) * 2) * 64 + lane;
+            st[0] = m;
+            st[64] = sum;
+          }
         }
       } else {
 #pragma unroll
