@@ -59,6 +59,12 @@ static __device__ __forceinline__ float relu(float x) { return __builtin_amdgcn_
 
 static __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// Lower bound of the maximum that a part of the channels is exponentiated against before the overall maximum is known.  A part
+// whose channels are all switched off (biases of -inf, -FLT_MAX, -1e30) would otherwise have a maximum m whose -m log2 e does not cancel
+// u log2 e in exp2(u log2 e - m log2 e): -inf + inf, an overflow, or a rounding error beyond 128.  Below the bound the part's exponentials
+// are zero instead; down to it |m log2 e| < 2^31, so that the rounding error stays within 64.
+static constexpr float kMaxFloor = -1.48e9f;
+
 // 8 consecutive elements of a row in the io dtype -> 8 bf16 (fp32 is rounded to nearest even).
 template <bool F32>
 static __device__ __forceinline__ bf16x8 load8(const void *base, int64_t elem_off) {

@@ -154,7 +154,7 @@ static __device__ __forceinline__ void mlp128_pipelined(const bf16x8 (&xf)[8], l
               float t = m0;
 #pragma unroll
               for (int x = 0; x < 16; x += 2) t = __builtin_fmaxf(__builtin_fmaxf(t, u[1][x]), u[1][x + 1]);
-              m0 = xhalf_max(t);
+              m0 = __builtin_fmaxf(xhalf_max(t), kMaxFloor);
               off0 = -m0 * kLog2e;
             } else {
               auto ex = [&](int i) {
