@@ -366,7 +366,7 @@ static __device__ __forceinline__ void feature_mlp_layer2(const bf16x8 (&h_hi)[H
 // ("chained" order) of a product contracted over the channels.
 template <int FB>
 struct PhiState {
-  float m_run = -INFINITY, sum = 0.f, mref[FB];
+  float m_run = kMaxFloor, sum = 0.f, mref[FB];
 };
 
 // Tiles FB0 .. FB1 - 1.  Fragment (fb, hb, s) of W2 is read at index (fb * HB + hb) * 2 + s - frag_bias, so a
@@ -416,7 +416,7 @@ static __device__ __forceinline__ void feature_layer2_phi_tiles(const bf16x8 (&h
 #pragma unroll
       for (int v = 1; v < 16; ++v) t = fmaxf(t, acc[v]);
       const float m_new = fmaxf(st.m_run, xhalf_max(t));
-      st.sum *= fast_exp2((st.m_run - m_new) * kLog2e);          // exp2(-inf) = 0 on the first tile
+      st.sum *= fast_exp2((st.m_run - m_new) * kLog2e);          // (the sum is 0 on the first tile)
       const float off = -m_new * kLog2e;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {

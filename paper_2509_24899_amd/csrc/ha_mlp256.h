@@ -144,14 +144,14 @@ template <bool ACT0, bool P2>
 static __device__ __forceinline__ void phi256_output(f32x16 (&u)[8], int act, int P) {
   float factor[8];
   if constexpr (ACT0) {
-    float m_run = -INFINITY, sum = 0.f;
+    float m_run = kMaxFloor, sum = 0.f;
 #pragma unroll
     for (int fb = 0; fb < 8; ++fb) {
       float t = u[fb][0];
 #pragma unroll
       for (int x = 1; x < 16; ++x) t = fmaxf(t, u[fb][x]);
       const float m_new = fmaxf(m_run, xhalf_max(t));
-      sum *= fast_exp2((m_run - m_new) * kLog2e);         // exp2(-inf) = 0 on the first tile
+      sum *= fast_exp2((m_run - m_new) * kLog2e);         // (the sum is 0 on the first tile)
       const float off = -m_new * kLog2e;
 #pragma unroll
       for (int x = 0; x < 16; x += 2) {

@@ -1,6 +1,6 @@
 """Feature maps some of whose output channels are switched off by a bias that stands for minus infinity (for degree 2, the first
 or the last half: a whole slice), under the softmax activation: such a channel's feature is zero and nothing else changes, so a channel
-softmax that is put together from parts (pairs of tiles) must not form its exponentials
+softmax that is put together from parts (pairs of tiles, tiles) must not form its exponentials
 against a maximum that is such a value.
 
 From -1e9 down exp(u - max) is zero in float64 as well, so one reference serves all values.  Tolerance: the bars of
@@ -34,7 +34,8 @@ def work(name, d, width, H, N, R, **kw):
 PATHS = (
     work("one_wave_per_simd", 128, 128, 6, 131, 2), work("linear_pass", 128, 128, 2, 300, 4), work("rate_0", 128, 128, 6, 300, 0),
     work("large_tiles", 128, 128, 96, 300, 4), work("f32", 128, 128, 6, 131, 4, dtype="f32"), work("d64", 64, 64, 3, 300, 4),
-    work("chunk_causal_128", 128, 128, 2, 600, 4, causal_chunk=256),
+    work("chunk_causal_128", 128, 128, 2, 600, 4, causal_chunk=256), work("phi256", 128, 256, 2, 300, 4),
+    work("chunk_causal_256", 128, 256, 2, 600, 4, causal_chunk=256),
 )
 
 
