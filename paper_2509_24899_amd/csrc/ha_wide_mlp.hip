@@ -333,7 +333,7 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
             float t = acc[0][v];
 #pragma unroll
             for (int j = 1; j < NT; ++j) t = fmaxf(t, acc[j][v]);
-            const float mv = half_max(t), off = -mv * kLog2e;
+            const float mv = __builtin_fmaxf(half_max(t), kMaxFloor), off = -mv * kLog2e;
             t = 0.f;
 #pragma unroll
             for (int j = 0; j < NT; ++j) t += fast_exp2(__builtin_fmaf(acc[j][v], kLog2e, off));
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
             for (int j = j0; j < j0 + 4; ++j)
 #pragma unroll
               for (int v = 0; v < 16; v += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, acc[j][v]), acc[j][v + 1]);
-            m = xhalf_max(m);
+            m = __builtin_fmaxf(xhalf_max(m), kMaxFloor);
             const float off = -m * kLog2e;
             float sum = 0.f;
 #pragma unroll

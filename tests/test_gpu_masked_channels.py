@@ -1,6 +1,6 @@
 """Feature maps some of whose output channels are switched off by a bias that stands for minus infinity (for degree 2, the first
 or the last half: a whole slice), under the softmax activation: such a channel's feature is zero and nothing else changes, so a channel
-softmax that is put together from parts (pairs of tiles, tiles) must not form its exponentials
+softmax that is put together from parts (pairs of tiles, tiles, blocks of 128 channels) must not form its exponentials
 against a maximum that is such a value.
 
 From -1e9 down exp(u - max) is zero in float64 as well, so one reference serves all values.  Tolerance: the bars of
@@ -35,7 +35,9 @@ PATHS = (
     work("one_wave_per_simd", 128, 128, 6, 131, 2), work("linear_pass", 128, 128, 2, 300, 4), work("rate_0", 128, 128, 6, 300, 0),
     work("large_tiles", 128, 128, 96, 300, 4), work("f32", 128, 128, 6, 131, 4, dtype="f32"), work("d64", 64, 64, 3, 300, 4),
     work("chunk_causal_128", 128, 128, 2, 600, 4, causal_chunk=256), work("phi256", 128, 256, 2, 300, 4),
-    work("chunk_causal_256", 128, 256, 2, 600, 4, causal_chunk=256),
+    work("chunk_causal_256", 128, 256, 2, 600, 4, causal_chunk=256), work("phi384", 128, 384, 1, 300, 2, poly_degree=3),
+    work("phi512", 128, 512, 2, 200, 2, hidden=128), work("phi768x3", 128, 768, 1, 300, 4, d_mid=768),
+    work("phi512_rounds", 128, 512, 40, 700, 0, hidden=128),
 )
 
 
@@ -66,7 +68,7 @@ def test_forward_with_masked_channels(w, channels):
         p.b2[...] = kept
 
 
-@pytest.mark.parametrize("width,d_mid", ((64, 0), (128, 0)))
+@pytest.mark.parametrize("width,d_mid", ((64, 0), (128, 0), (256, 0), (384, 0), (512, 128)))
 @pytest.mark.parametrize("channels", sorted(CHANNELS))
 def test_gradient_with_masked_channels(width, d_mid, channels):
     d = min(width, 128)
