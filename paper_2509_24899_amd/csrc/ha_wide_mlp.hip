@@ -130,10 +130,11 @@ __global__ __launch_bounds__(512, 2) void wide_mlp_kernel(WideMlpArgs a) {
   // its first fragments are read ahead of this barrier, under the products of slab kb - 1; all reads of slab kb - 1 have been
   // used by then.)  Newer than the request of slab kb + 1 are at least NBUF - 3 requests (and from HBM NBUF - 2 groups of four
   // image loads), and, where that request came before this wave's outputs, those 4 NT stores (loads and stores retire in order, so
-  // that the ring's length is what the outputs have to reach memory in).  The slabs requested ahead of the first item are waited
-  // for together.
-  constexpr int FLY = (NBUF - 3) * PW + (X ? 0 : (NBUF - 2) * 4), FLY_OUT = FLY + 4 * NT < 63 ? FLY + 4 * NT : 63;
-  static_assert(FLY < 63, "vmcnt immediate too large");
+  // that the ring's length is what the outputs have to reach memory in).  The counter ends at 63 operations, so that a wait for 63
+  // is none: where more than 62 are newer (NT = 8 with nine slabs: 72), the wait is for all but 62.  The slabs requested ahead of the
+  // first item are waited for together.
+  constexpr int FLY = (NBUF - 3) * PW + (X ? 0 : (NBUF - 2) * 4), FLY_OUT = FLY + 4 * NT < 62 ? FLY + 4 * NT : 62;
+  static_assert(FLY <= 62, "a wait that the counter can hold");
   auto advance = [&](int kb) {
     if (stored && kb < NBUF - 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FLY_OUT) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FLY) : "memory");
