@@ -284,9 +284,10 @@ static ha_status run_key_side(const Plan &pl, const void *k, const void *v, cons
                               const ha_feature_map *prep_q = nullptr, bool *prep_q_done = nullptr) {
   hipError_t e;
   if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return device_error(e);
-  // (for the 128-wide bf16 maps the state pass compacts the softmax keys on its way: one pass over K and V)
+  // (for the 128-wide bf16 maps the state pass compacts the softmax keys on its way, one pass over K and V, and for the 64-wide heads
+  // workgroups behind its own do)
   const bool fused_compaction = !wide && phi_k && state_compacts_softmax_keys(pl);
-  // (the pipelined state pass of the 128-wide bf16 maps gathers the weights from the caller's tensors itself)
+  // (some state passes gather the weights from the caller's tensors themselves)
   const bool prep_k = pl.NL > 0 && !wide && !state_reads_raw_weights(pl), compact = pl.NS > 0 && !fused_compaction;
   if (compact && (e = launch_compact(pl, k, v, ws, st, prep_k ? phi_k : nullptr)) != hipSuccess) return device_error(e);
   if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return device_error(e);

@@ -106,16 +106,16 @@ __global__ __launch_bounds__(256) void compact_kernel(const void *__restrict__ k
 // tensor, token i's feature row is multiplied by rs[i] before it is rounded, and the "1" column becomes the pair
 // of columns (hi, lo) of wp[i].
 //
-// The weights are fetched from the caller's row-major tensors (WEIGHTED: as prepared fragments), and the workgroups behind the
-// chunks compact the softmax keys, a 32-key block each: as a launch of its own ahead of this one, with the weights' preparation, that
-// took 2.9 of 22.7 us of a call with H = 2, N = 1024, fp32.
+// RAW: the weights are fetched from the caller's row-major tensors, and the workgroups behind the chunks compact the softmax keys, a
+// 32-key block each: as a launch of its own ahead of this one, with the weights' preparation, that took 2.9 of 22.7 us of a call with
+// H = 2, N = 1024, fp32.  Otherwise (state_reads_raw_weights) they come as prepared fragments.
 struct StateCompact {
   bf16x8 *ks_frag, *vs_frag;
   int NS, n_kblocks, BH, total;       // total: workgroups that have work
 };
 // (a grid dimension holds less than 2^32 threads)
 static inline dim3 state_grid(int total) { return dim3(total < 1 << 20 ? total : 1 << 20, (total + (1 << 20) - 1) >> 20); }
-template <int D, int HD, int F, bool F32, bool WEIGHTED = false>
+template <int D, int HD, int F, bool F32, bool RAW, bool WEIGHTED = false>
 __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ k, const void *__restrict__ v,
                                                        const void *__restrict__ w1_all, const void *__restrict__ w2_all,
                                                        const float *__restrict__ b1_all, const float *__restrict__ b2_all,
@@ -139,13 +139,14 @@ __global__ __launch_bounds__(256, 1) void state_kernel(const void *__restrict__ 
   __shared__ __align__(16) __bf16 et[WEIGHTED ? 2 : 1][WEIGHTED ? PITCH : 8];
   const int BH = sc.BH, n_state = n_chunks * BH, id = blockIdx.y * gridDim.x + blockIdx.x;
   if (id >= sc.total) return;
-  const bool compacting = !WEIGHTED && id >= n_state;
+  const bool compacting = RAW && id >= n_state;
   const int per_bh = compacting ? sc.n_kblocks : n_chunks, at = compacting ? id - n_state : id;
   const int bh = at / per_bh, chunk = at - bh * per_bh, h = bh % H;
   const int64_t base = (int64_t)(bh / H) * sb + (int64_t)h * sh;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, kept scalar
-  if constexpr (!WEIGHTED) {
+  static_assert(!(RAW && WEIGHTED));
+  if constexpr (RAW) {
     if (compacting) {
       static_assert(F >= 32 && PITCH >= D + 8, "the staging rows fit the feature tile");
       compact_body<D, F32>(k, v, sc.ks_frag, sc.vs_frag, H, sc.NS, R, G, sc.n_kblocks, sb, sh, sn, chunk, bh,
@@ -533,11 +534,14 @@ hipError_t launch_state(const Plan &pl, const void *k, const void *v, const ha_f
   const StateCompact sc = {ws_ptr<bf16x8>(ws, pl.off_ks), ws_ptr<bf16x8>(ws, pl.off_vs), pl.NS, pl.n_kblocks, pl.B * pl.H, total};
   const dim3 grid = state_grid(total);
   float *part = ws_ptr<float>(ws, pl.off_part);
-#define HA_STATE(DD, HH, FF, F32) \
-  state_kernel<DD, HH, FF, F32><<<grid, 256, 0, st>>>(k, v, fm.w1, fm.w2, fm.b1, fm.b2, part, pl.H, pl.NL, pl.R, pl.G, pl.CH, \
-                                                     pl.P, pl.act_k, pl.sb, pl.sh, pl.sn, pl.n_chunks, sc, nullptr, nullptr, pl.N, \
-                                                     pl.CC, pl.nsub)
-  if (pl.f32) HA_STATE(64, 64, 64, true); else HA_STATE(64, 64, 64, false);
+  const bool raw = state_reads_raw_weights(pl);
+  const void *w1 = raw ? fm.w1 : ws_ptr<void>(ws, pl.off_w1k), *w2 = raw ? fm.w2 : ws_ptr<void>(ws, pl.off_w2k);
+#define HA_STATE(DD, F32, RAW) \
+  state_kernel<DD, DD, DD, F32, RAW><<<grid, 256, 0, st>>>(k, v, w1, w2, fm.b1, fm.b2, part, pl.H, pl.NL, pl.R, pl.G, pl.CH, \
+                                                           pl.P, pl.act_k, pl.sb, pl.sh, pl.sn, pl.n_chunks, sc, nullptr, nullptr, pl.N, \
+                                                           pl.CC, pl.nsub)
+  if (raw) { if (pl.f32) HA_STATE(64, true, true); else HA_STATE(64, false, true); }
+  else { if (pl.f32) HA_STATE(64, true, false); else HA_STATE(64, false, false); }
 #undef HA_STATE
   return hipGetLastError();
 }
@@ -551,7 +555,7 @@ hipError_t launch_weighted_state(const Plan &pl, const void *q, const void *gsig
   const dim3 grid = state_grid(n_chunks * pl.B * pl.H);
   const StateCompact sc = {nullptr, nullptr, 0, 0, pl.B * pl.H, n_chunks * pl.B * pl.H};
 #define HA_WSTATE(DD, F32) \
-  state_kernel<DD, DD, DD, F32, true><<<grid, 256, 0, st>>>(q, gsign, w1f_, w2f_, fm.b1, fm.b2, part, pl.H, pl.N, 0, 1, CH, pl.P, \
+  state_kernel<DD, DD, DD, F32, false, true><<<grid, 256, 0, st>>>(q, gsign, w1f_, w2f_, fm.b1, fm.b2, part, pl.H, pl.N, 0, 1, CH, pl.P, \
                                                             pl.act_q, pl.sb, pl.sh, pl.sn, n_chunks, sc, rs, wp)
   if (pl.f32) HA_WSTATE(64, true); else HA_WSTATE(64, false);
 #undef HA_WSTATE

@@ -84,9 +84,16 @@ struct WideGradPlan {
       off_dpre, off_part, total;
 };
 
-// Which kernels read bf16 feature-map weights straight from the caller's tensors (no weight_prep_kernel launch needed).
+// Which state passes read the feature map's weights straight from the caller's tensors (no preparation needed): the 128-wide
+// maps' in bf16; that of the 64-wide heads but for the chunk-causal variant with softmax keys, whose compaction is a launch of its own
+// and prepares the weights as well.  (There its many short chunks pay for fetching them row by row: raw / as fragments, whole calls, us:
+// B = 2, H = 6, N = 5583, R = 4, chunks of 256, bf16  67.1 / 66.4; H = 12, N = 20000  260.6 / 259.9; without softmax keys, H = 8, N = 4000,
+// chunks of 128, fp32, where the preparation is one launch more  41.7 / 44.0.  Local window, H = 8, N = 4000  51.3 / 51.9.)
 static inline bool state_uses_pipelined_kernel(const Plan &pl) { return pl.D == 128 && pl.HD == 128 && pl.F == 128; }
-static inline bool state_reads_raw_weights(const Plan &pl) { return pl.D == 64 || (state_uses_pipelined_kernel(pl) && !pl.f32); }
+static inline bool state_reads_raw_weights(const Plan &pl) {
+  if (pl.D == 64) return pl.CC == 0 || pl.LW > 0 || pl.NS == 0;
+  return state_uses_pipelined_kernel(pl) && !pl.f32;
+}
 // ... and compacts the softmax keys on the way (no compact_kernel launch): bf16 or d = 64, the plain operator with both kinds of tokens
 static inline bool state_compacts_softmax_keys(const Plan &pl) {
   return state_reads_raw_weights(pl) && pl.CC == 0 && pl.LW == 0 && pl.NS > 0 && pl.NL > 0 && pl.n_chunks > 0;
