@@ -121,47 +121,46 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
     else merge_kernel<false><<<mgrid, 256, 0, st>>>(a);
     return hipGetLastError();
   }
-  // Two tilings of one computation (every query column sees the same keys in the same order): 8 waves x
-  // 32 queries with a ring of 8 key blocks and a barrier every 64 keys, one workgroup per CU, or 4 waves x 32 queries
-  // with a ring of 4 and a barrier every 32 keys, two workgroups per CU.  The variants' tiles are part of their
-  // definition, so block_size decides there; for the plain operator the sizes do.
-  //   d = 128, maps in the epilogue: the 4-wave kernel reads their operands from L2 instead of LDS and fetches every key block
-  // twice as often, so it is better only where its last round of workgroups is emptier.  In us: a round of 256 large
+  // Three tilings of one computation (every query column sees the same keys in the same order): 4 waves x 32 queries, one wave per
+  // SIMD, with a ring of 8 key blocks (ha_query_alone.hip); 8 waves x 32 queries with that ring and a barrier every 64 keys, one
+  // workgroup per CU; and 4 waves x 32 queries with a ring of 4 and a barrier every 32 keys, two workgroups per CU.  The variants'
+  // tiles are part of their definition, so block_size decides there between the latter two; for the plain operator the sizes do.
+  //   128-query tiles that do not outnumber the CUs: a workgroup has a CU to itself, so that one wave per SIMD with the long ring and
+  // all operands in LDS is best.  Whole calls, us, better one of the other two / alone: H = 12, R = 4, d = 128: N = 300 (B = 2)
+  // 35.7 / 31.2, 1560  43.1 / 36.2, 2600  47.4 / 42.0; H = 8, N = 3900, R = 2  69 / 58.8; one workgroup of 128 more than CUs (H = 6,
+  // N = 5400, R = 3)  67.5 / 89; d = 64: H = 2, N = 1024, fp32  26.0 / 24.3, H = 12, N = 2600, R = 2  46.4 / 39.9; rate 1: H = 8,
+  // N = 4000  77 / 72.8, d = 64, H = 4, N = 4000  56 / 48.  With the linear part precomputed a short loop is as long either way
+  // (6 key blocks 72.4 / 73.2, 13 68.5 / 68.5), a long one shorter (94: 106.1 / 104.1).
+  const auto wgs = [&](int qt) { return (int64_t)((pl.N + qt - 1) / qt) * pl.B * pl.H; };
+  const int64_t nblk = (pl.NS + 31) / 32;
+  const bool alone = pl.CC == 0 && pl.LW == 0 && wgs(128) <= 256 && (!lin || nblk >= 20);
+  //   Otherwise, d = 128, maps in the epilogue: the 4-wave kernel reads their operands from L2 instead of LDS and fetches every key
+  // block twice as often, so it is better only where its last round of workgroups is emptier.  In us: a round of 256 large
   // workgroups takes 0.50 per key block and 14 beside, one of 512 small ones 0.52 and 24, a last one of at most 256 small ones
   // 0.30 and 26 (877 problems timed with both, R = 2 .. 16, both dtypes: 63 of them take the small tiles; none is more than
   // 0.4 % slower than with large ones throughout, none more than 2.3 % than with small ones).  Whole calls, large / small:
   // H = 10, N = 6500, R = 2 (260 / 510 workgroups) 196 / 149; H = 20, N = 3200, R = 4 (260 / 500) 94 / 81; H = 12, N = 5504, R = 2
-  // (264 / 516) 175 / 175; H = 64, N = 5556, R = 2 (1408 / 2816) 577 / 614.  Within one round of large ones they are better.
+  // (264 / 516) 175 / 175; H = 64, N = 5556, R = 2 (1408 / 2816) 577 / 614.  Within one round of large ones those are better.
   //   d = 128, linear part precomputed or absent: no operands to fetch.  In hundredths of a key block a round of large workgroups
   // takes 100 per block, one of small ones 105, a last one of at most 256 small ones 65; a short loop's start costs the large
   // ones 65 more, and 250 with every further round (small workgroups start where one has ended).  (660 problems timed with both:
   // the choice is on average 0.1 % off the better one, at most 4.6 %.)  Large / small, R = 1: H = 250, N = 457 (500 / 1000)
-  // 71.7 / 63.6; H = 100, N = 494 (200 / 400) 32.7 / 34.6; H = 128, N = 268 (256 / 384) 35.2 / 33.3; H = 86, N = 3975, fp32
-  // (1376 / 2752) 725 / 759; 256-wide maps: H = 48, N = 4818, R = 16 (912 / 1824) 342 / 323.
+  // 71.7 / 63.6; H = 128, N = 268 (256 / 384) 35.2 / 33.3; H = 86, N = 3975, fp32 (1376 / 2752) 725 / 759; 256-wide maps: H = 48,
+  // N = 4818, R = 16 (912 / 1824) 342 / 323.
   //   d = 64: everything is small, and two independent workgroups per CU fill each other's gaps once there is more than one round
-  // of large ones (R = 2 .. 16: large takes 0.85 - 0.97 of small's time within one round of them, 0.96 - 1.24, on average 1.06, beyond),
-  // or where small ones are at most one per CU and the loop is long (H = 1, N = 18432, R = 2, fp32: 154 / 139; 64 key blocks
-  // and less: 0.87 - 1.04).
-  const auto wgs = [&](int qt) { return (int64_t)((pl.N + qt - 1) / qt) * pl.B * pl.H; };
-  const int64_t nblk = (pl.NS + 31) / 32, rounds = (wgs(256) + 255) / 256, full = wgs(128) / 512, tail = wgs(128) % 512;
+  // of large ones (R = 2 .. 16: large takes 0.85 - 0.97 of small's time within one round of them, 0.96 - 1.24, on average 1.06, beyond).
+  const int64_t rounds = (wgs(256) + 255) / 256, full = wgs(128) / 512, tail = wgs(128) % 512;
   bool big;
-  if (pl.LW > 0 || pl.CC > 0) big = pl.KT == 128;
-  else if ((lin || pl.NL == 0) && (pl.D == 128 || wgs(128) <= 256)) {
+  if (alone) big = false;
+  else if (pl.LW > 0 || pl.CC > 0) big = pl.KT == 128;
+  else if (pl.D == 64) big = wgs(256) <= 256;
+  else if (lin || pl.NL == 0) {
     const int64_t len = nblk > 0 ? nblk : 1024;              // (rate 0: the rounds alone count)
     big = rounds * (100 * len + 250) - 185 <= full * 105 * len + (tail == 0 ? 0 : tail <= 256 ? 65 : 105) * len;
-  } else if (pl.D == 64) big = wgs(256) <= 256 && (wgs(128) > 256 || nblk <= 64);
-  else {
+  } else {
     const int64_t last = tail == 0 ? 0 : tail <= 256 ? 30 * nblk + 2600 : 52 * nblk + 2400;
     big = wgs(256) <= 256 || rounds * (50 * nblk + 1400) <= full * (52 * nblk + 2400) + last;
   }
-  //   Plain operator, 128-query tiles that do not outnumber the CUs: a workgroup has a CU to itself, so the small tiles run as
-  // workgroups of one wave per SIMD with the long ring and all operands in LDS (ha_query_alone.hip).  Whole calls, better one of the two
-  // above / alone: H = 12, R = 4, d = 128: N = 300 (B = 2)  35.7 / 31.2, 1560  43.1 / 36.2, 2600  47.4 / 42.0; H = 8, N = 3900, R = 2
-  // 69 / 58.8; one workgroup of 128 more than CUs (H = 6, N = 5400, R = 3)  67.5 / 89; d = 64: H = 2, N = 1024, fp32  26.0 / 24.3, H = 12,
-  // N = 2600, R = 2  46.4 / 39.9; rate 1: H = 8, N = 4000  77 / 72.8, d = 64, H = 4, N = 4000  56 / 48.  With the linear part
-  // precomputed a short loop is as long either way (6 key blocks 72.4 / 73.2, 13 68.5 / 68.5), a long one shorter (94: 106.1 / 104.1).
-  const bool alone = pl.CC == 0 && pl.LW == 0 && wgs(128) <= 256 && (!lin || nblk >= 20);
-  if (alone) big = false;
   const int qt = big ? 256 : 128;
   a.n_qtiles = (pl.N + qt - 1) / qt;
   a.total_wg = a.n_qtiles * pl.B * pl.H;

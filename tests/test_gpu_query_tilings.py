@@ -37,8 +37,8 @@ def test_both_sides_of_the_tiling_rules(d, width, H, N, dtype):
 
 
 # d = 128 with the maps in the epilogue: small tiles where the large ones' last round is nearly empty (260 / 510 and 520 / 1020
-# workgroups; 260 / 520 stays large), rate 1 with short loops and many heads (500 / 1000, 384), d = 64 with a long loop and
-# few workgroups (84 small ones)
+# workgroups; 260 / 520 stays large), rate 1 with short loops and many heads (500 / 1000, 384), d = 64 with a long loop on both sides of
+# a CU for every 128-query tile (84 and 266 of them)
 @pytest.mark.parametrize("d,width,H,N,R", ((128, 128, 10, 6500, 2), (128, 128, 20, 6500, 4), (128, 128, 10, 6656, 2), (128, 0, 250, 457, 1),
                                            (128, 0, 128, 300, 1), (128, 256, 48, 1200, 16), (64, 64, 1, 10722, 2), (64, 64, 2, 17000, 4)))
 @pytest.mark.parametrize("dtype", ("bf16", "f32"))
