@@ -89,53 +89,6 @@ static ha_status validate(const ha_problem *p, const ha_feature_map *phi_q, cons
   return HA_OK;
 }
 
-// Estimated time, in us, of the plain operator's softmax loop with the keys in n ranges.  A tile of 256 queries is one workgroup, so
-// a problem of few tiles leaves CUs idle for the whole loop; with n ranges it has n times the workgroups, each with 1 / n of the
-// keys, at the price of a pass that merges the partial sums (520 bytes per query and range written and read).  From measured
-// times: a 32-key step takes 0.5 (0.42 in the tiling of an unsplit problem), the rest of a workgroup 5; the merging pass 5 and
-// its traffic at 4 TB/s.
-static double split_cost(const Plan &pl, int n) {
-  const double tiles = (double)((pl.N + 255) / 256) * pl.B * pl.H, rows = (double)pl.N * pl.B * pl.H;
-  const double rounds = std::ceil(tiles * n / 256.0), blocks = ((pl.NS + 31) / 32 + n - 1) / n;
-  const double loop = rounds * (blocks * (n == 1 ? 0.42 : 0.5) + 5.0);
-  return n == 1 ? loop : loop + 5.0 + rows * n * 1032.0 / 4.0e6;
-}
-
-// Into how many ranges the keys are split: the estimate has to be 10 % better than one range.  (Where the query kernel evaluates
-// the maps in its epilogue, there is no pass that could merge.)  Whole calls, one range / split, us:
-//   R = 1:  H = 1, N = 1200  24.4 / 20.5;  2000  35.4 / 24.1;  8000  112 / 50;  20000  265 / 190;  32000  503 / 445;  H = 2, N = 4500  68.5 / 40.5;
-//   H = 5, N = 3000  52.3 / 42.2;  256-wide maps, R = 4, H = 1:  N = 8000  84 / 76;  20000  127 / 116.  It is wrong where five ranges fill two rounds:
-//   R = 1, H = 1, N = 26000  366 / 407.
-static int choose_split(const Plan &pl, bool lin) {
-  if (pl.D != 128 || pl.CC > 0 || pl.LW > 0 || pl.NS == 0 || (pl.NL > 0 && !lin)) return 1;
-  const double tiles = (double)((pl.N + 255) / 256) * pl.B * pl.H;
-  // From half the CUs on the loop is left whole.  Above 128 tiles the estimate is wrong and splitting loses (R = 1, one range /
-  // split: H = 1, N = 33500  601 / 745, 36000  646 / 798, 42000  819 / 937; at other rates the estimate takes one range itself).
-  // At 128 tiles exactly it would gain at R = 1 (H = 1, N = 32760  520 / 450; H = 2, N = 16300  267 / 238; H = 4, N = 8100  142 / 131), which
-  // is given up: one head of a 480p clip (32760 tokens) on its own then has the softmax outputs it has among others, bit for
-  // bit, and with them the signs that a distillation gradient is made of.
-  if (tiles >= 128.0) return 1;
-  const int nblk = (pl.NS + 31) / 32;
-  int best = 1;
-  double least = 0.9 * split_cost(pl, 1);
-  for (int n = 2; n <= 8 && 2 * n <= nblk; ++n)      // (the merging kernel takes up to eight)
-    if (split_cost(pl, n) < least) {
-      least = split_cost(pl, n);
-      best = n;
-    }
-  return best;
-}
-
-// The ranges of a plan of `base` bytes without the linear pass's results: fewer than would be best where not all of their partial sums
-// have room (route_has_room).
-static int split_with_room(const Plan &pl, bool lin, size_t base) {
-  const size_t rows = (size_t)pl.B * pl.H * ((pl.N + 255) / 256) * 256;
-  const size_t lin_bytes = pl.split_linear ? rows * (pl.D + 1) * 4 : 0, per = rows * (pl.D + 2) * 4;
-  int n = choose_split(pl, lin);
-  while (n > 1 && !route_has_room(pl, base, lin_bytes + n * per)) --n;
-  return n;
-}
-
 void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl, size_t limit) {
   std::memset(&pl, 0, sizeof(pl));
   pl.B = p.B; pl.H = p.H; pl.N = p.N; pl.D = p.d_head; pl.R = p.hybrid_rate;
@@ -225,17 +178,16 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
   const size_t tile = BH * 256 * (pl.D + 1) * 4, tiles = ((size_t)pl.N + 255) / 256;
   const bool plain = has_linear && pl.DM == 0 && pl.CC == 0 && pl.LW == 0 && pl.D == 128;
   pl.split_linear = plain && pl.HD == 256 && pl.F == 256;
-  // With the 128-wide maps a pass of its own is one more launch, about 3 us, and pays where it lets the query kernel split the keys and
-  // that is estimated to save 4 us.  Whole calls, epilogue / pass, us: R = 2, H = 1, N = 500  29.5 / 32.9; 2000  39.7 / 40.5; 3000  47.2 / 45.0;
-  // 4500  57.8 / 52.7; 12000  108 / 77; 32000  280 / 284; H = 2, N = 3000  48.1 / 49.8; 4500  58.8 / 55.4; 8000  82.8 / 74.2; H = 3, N = 6900  78.4 / 78.2;
-  // H = 5, N = 3000  52.2 / 55.7; R = 4, H = 1, N = 6500  50.1 / 52.2; 8000  56.1 / 54.1; 20000  97.6 / 91.5; H = 2, N = 8000  58.0 / 61.7; H = 4, N = 2000
-  // 34.8 / 38.4; R = 16, H = 1, N = 8000  31.4 / 34.3; H = 5, N = 6500  43.4 / 50.4.  (547 problems timed with both, R = 2 .. 16, one to twelve heads:
-  // the choice is on average 0.1 % off the better one, at most 7 %.)
-  if (plain && pl.HD == 128 && pl.F == 128 && pl.NS > 0) {
+  // With the 128-wide maps the query kernel's epilogue is 11 us at the end of every workgroup; a pass of its own over blocks
+  // of 32 queries is one more launch, but leaves the query kernel free to split the keys and to use small tiles.  Whole calls,
+  // epilogue / pass, us: R = 4, H = 1, N = 2000  38.3 / 35.3; 8000  70 / 50 (keys split; 61 without); 20000  127 / 91 (109); H = 2,
+  // N = 5000  56.0 / 49.6; H = 5, N = 3000  48.5 / 44.0; R = 16  39.1 / 36.0; R = 2  63.2 / 56.1.  From six (batch, head) pairs on it
+  // is a gain at low rates and a loss at high ones: H = 8, N = 3000  R = 2  63.3 / 58.9, R = 4  48.5 / 47.3, R = 16  38.4 / 39.9;
+  // H = 10, N = 3000, R = 16  40.0 / 42.5; H = 12, N = 1560  R = 2  52.2 / 48.7, R = 4  43.5 / 42.2, N = 2600, R = 16  40.0 / 42.6.  Five is the
+  // largest number at which no measured problem loses.  Nor does it pay once 128-query tiles are more than one per CU.
+  if (plain && pl.HD == 128 && pl.F == 128 && pl.NS > 0 && BH <= 5 && ((size_t)pl.N + 127) / 128 * BH <= 256 &&
+      route_has_room(pl, off, tiles * tile))
     pl.split_linear = true;
-    const int n = split_with_room(pl, true, off);
-    pl.split_linear = n > 1 && split_cost(pl, 1) - split_cost(pl, n) >= 4.0;
-  }
   if (pl.split_linear) {
     pl.lin_rows = pl.N;
     pl.off_lin = off;
@@ -259,6 +211,39 @@ static bool needs_wide_path(const Plan &pl) {
   return pl.NL > 0 && ((!square && !paper_width) || pl.DM > 0);
 }
 
+// Into how many ranges the keys of the plain operator's softmax loop are split.  A tile of 256 queries is one workgroup, so
+// a problem of few tiles leaves CUs idle for the whole loop; with n ranges it has n times the workgroups, each with 1 / n
+// of the keys, at the price of a pass that merges the partial sums (520 bytes per query and range written and read).  The
+// estimate, in us, from measured times: a 32-key step takes 0.5 (0.42 in the small tiling of an unsplit problem), the rest
+// of a workgroup 5; the merging pass 5 and its traffic at 4 TB/s.  It has to be 10 % better than one range.  (Where the query
+// kernel would evaluate the maps in its epilogue, there is no pass that could merge.)  Whole calls, one range / split, us:
+//   R = 1:  H = 1, N = 2000  37.4 / 23.4;  N = 8000  123 / 49;  N = 20000  291 / 189;  N = 32500  517 / 448;  H = 2, N = 5000  81 / 44;
+//   H = 5, N = 3000  54.7 / 41.9;  R = 4, H = 1:  N = 20000  109 / 91 (128-wide maps), 134 / 115 (256-wide);  N = 8000  61 / 50, 86 / 75.
+static int choose_split(const Plan &pl, bool lin) {
+  if (pl.D != 128 || pl.CC > 0 || pl.LW > 0 || pl.NS == 0 || (pl.NL > 0 && !lin)) return 1;
+  const double tiles = (double)((pl.N + 255) / 256) * pl.B * pl.H, rows = (double)pl.N * pl.B * pl.H;
+  // From half the CUs on the loop is left whole.  Above 128 tiles the estimate is wrong and splitting loses (R = 1, one range /
+  // split: H = 1, N = 33500  601 / 745, 36000  646 / 798, 42000  819 / 937; at other rates the estimate takes one range itself).
+  // At 128 tiles exactly it would gain at R = 1 (H = 1, N = 32760  520 / 450; H = 2, N = 16300  267 / 238; H = 4, N = 8100  142 / 131), which
+  // is given up: one head of a 480p clip (32760 tokens) on its own then has the softmax outputs it has among others, bit for
+  // bit, and with them the signs that a distillation gradient is made of.
+  if (tiles >= 128.0) return 1;
+  const int nblk = (pl.NS + 31) / 32;
+  auto cost = [&](int n) {
+    const double rounds = std::ceil(tiles * n / 256.0), blocks = (nblk + n - 1) / n;
+    const double loop = rounds * (blocks * (n == 1 ? 0.42 : 0.5) + 5.0);
+    return n == 1 ? loop : loop + 5.0 + rows * n * 1032.0 / 4.0e6;
+  };
+  int best = 1;
+  double least = 0.9 * cost(1);
+  for (int n = 2; n <= 8 && 2 * n <= nblk; ++n)      // (the merging kernel takes up to eight)
+    if (cost(n) < least) {
+      least = cost(n);
+      best = n;
+    }
+  return best;
+}
+
 // Plan of the forward plus, where needed, the layer-by-layer path's buffers behind it; returns the workspace size.
 static size_t full_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, Plan &pl, WidePlan &wp,
                         bool &wide, size_t limit = SIZE_MAX) {
@@ -273,7 +258,9 @@ static size_t full_plan(const ha_problem &p, const ha_feature_map *phi_q, const 
   // partials' place, a part of the queries at a time: see make_plan; the keys are in one range then)
   const size_t BH = (size_t)pl.B * pl.H, rows = BH * ((pl.N + 255) / 256) * 256;
   const size_t lin = pl.split_linear ? rows * (pl.D + 1) * 4 : 0, per = rows * (pl.D + 2) * 4;
-  pl.n_split = split_with_room(pl, wide || pl.split_linear, lin && pl.off_lin != pl.off_part ? total - lin : total);
+  const size_t base = lin && pl.off_lin != pl.off_part ? total - lin : total;
+  pl.n_split = choose_split(pl, wide || pl.split_linear);
+  while (pl.n_split > 1 && !route_has_room(pl, base, lin + pl.n_split * per)) --pl.n_split;
   if (pl.n_split > 1) {
     pl.n_tb_split = (pl.N + 255) / 256 * 8;
     pl.off_po = total;

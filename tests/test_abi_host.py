@@ -398,7 +398,7 @@ def key_ranges(H, N, R, width, dtype="bf16"):
         sizes += [H * F * D * 2, H * F * F * 2, H * n_tb * 32 * F * 4, H * n_tb * (F // 128) * 512, H * n_tb * 32 * D * 4, H * N * 4]
     unsplit = sum((x + 255) // 256 * 256 for x in sizes)
     per = rows * (D + 2) * 4
-    for lin in (0, rows * (D + 1) * 4):       # the linear part as a pass of its own: always with 256, with 128 if the keys are split
+    for lin in (0, rows * (D + 1) * 4):       # the linear part as a pass of its own: always with 256, with 128 for few heads
         if need == unsplit + lin:
             return 1
         if (need - unsplit - lin) % per == 0 and need > unsplit + lin:
@@ -418,23 +418,3 @@ def test_split_shapes_are_split(lib, dtype):
     n = [key_ranges(H, N, R, width, dtype) for N, R, width, H in SPLIT_SHAPES]
     assert set(n) == set(range(2, 9)), n
     assert key_ranges(12, 32760, 4, 128) == key_ranges(1, 32760, 1, 128) == key_ranges(12, 1560, 4, 256) == 1
-
-
-# (N, R, H) of the 128-wide maps: the smallest N at which the keys are split and the linear part is a pass of its own
-LINEAR_PASS_BORDERS = ((2433, 2, 1), (3521, 2, 2), (7041, 4, 1))
-
-
-@pytest.mark.parametrize("dtype", ("bf16", "f32"))
-def test_the_linear_part_of_the_narrow_maps_goes_ahead_only_with_split_keys(lib, dtype):
-    for N, R, H in LINEAR_PASS_BORDERS:
-        assert [key_ranges(H, n, R, 128, dtype) > 1 for n in (300, N - 1, N)] == [False, False, True]
-    fm, code = _map(128, 128), ha.HA_BF16 if dtype == "bf16" else ha.HA_F32
-    for H in (1, 2, 3, 5, 6, 12):
-        for R in (2, 3, 4, 16):
-            for N in range(129, 34000, 307):
-                if key_ranges(H, N, R, 128, dtype) == 1:        # ... nothing beyond the plan without it
-                    n_s, tiles = -(-N // R), -(-(N - -(-N // R)) // 128)
-                    chunks = -(-(N - n_s) // (-(-tiles // min(tiles, max(256 // H, 1))) * 128))
-                    sizes = [H * 32768] * 4 + [H * -(-n_s // 128) * 32768] * 2 + [H * chunks * 81920, H * 65536, H * 512, H * 32768, H * 32768]
-                    need = ha.hybrid_attn_workspace_bytes(_problem(H=H, N=N, R=R, dtype=code), fm, fm)
-                    assert need == sum(-(-x // 256) * 256 for x in sizes), (H, R, N)

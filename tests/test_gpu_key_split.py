@@ -14,7 +14,7 @@ import torch
 from oracle import hybrid_attn_oracle as O
 from paper_2509_24899_amd import hybrid_attn as ha
 from paper_2509_24899_amd import workloads as W
-from test_abi_host import LINEAR_PASS_BORDERS, SPLIT_SHAPES
+from test_abi_host import SPLIT_SHAPES
 from test_gpu_parity import check, oracle_map
 
 pytestmark = pytest.mark.gpu
@@ -75,22 +75,10 @@ def test_row_denominators(width):
         assert np.abs(den[0, h].double().cpu().numpy() / ref - 1).max() <= 4e-3     # (exp of a rounded logit: 2^-9 at most twice)
 
 
-# Where the 128-wide maps' linear part goes ahead of the query kernel (keys in ranges) and the last size at which it is left to the
-# epilogue (test_abi_host.py checks that this is so): degrees, activations.
-@pytest.mark.parametrize("N,R,H", LINEAR_PASS_BORDERS)
-@pytest.mark.parametrize("P,act,dtype", ((1, 0, "bf16"), (4, 0, "f32"), (8, 1, "bf16"), (2, 2, "f32")))
-def test_linear_part_ahead_of_the_query_kernel(N, R, H, P, act, dtype):
-    for n in (N - 1, N):
-        w = W.replace(work(n, R, H=H, dtype=dtype, seed=n), poly_degree=P)
-        rows = np.unique(np.r_[0:3, 31, 32, 255, 256, np.linspace(0, n - 1, 24).astype(int), n - 34:n])
-        check(f"ks_ahead_H{H}_N{n}_R{R}_P{P}_a{act}", W.make_inputs(w), act=act, rows=rows)
-
-
-@pytest.mark.parametrize("H", (5, 6))
+@pytest.mark.parametrize("H", (5, 6))                  # five heads: linear part ahead of the query kernel; six: in its epilogue
 @pytest.mark.parametrize("N,P,act", ((1, 2, 0), (33, 1, 0), (257, 4, 0), (6528, 2, 0), (6529, 2, 0), (300, 8, 1), (300, 2, 2)))
 def test_linear_part_of_the_narrow_maps(N, P, act, H):
-    """One key range, linear part in the epilogue (rate 0: a kernel of its own); 51 and 52 tiles of 128 queries per head are on both
-    sides of a CU for every tile at five heads."""
+    """51 and 52 tiles of 128 queries per head: the border of the rule at five heads."""
     w = W.replace(work(N, 4 if N > 4 else 0, H=H, seed=N), poly_degree=P)
     check(f"ks_lin128_H{H}_N{N}_P{P}_a{act}", W.make_inputs(w), act=act, rows=W.sample_rows(w, n_random=16) if N > 600 else None)
 
