@@ -178,13 +178,14 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
   const size_t tile = BH * 256 * (pl.D + 1) * 4, tiles = ((size_t)pl.N + 255) / 256;
   const bool plain = has_linear && pl.DM == 0 && pl.CC == 0 && pl.LW == 0 && pl.D == 128;
   pl.split_linear = plain && pl.HD == 256 && pl.F == 256;
-  // With the 128-wide maps the query kernel's epilogue is 11 us at the end of every workgroup; a pass of its own over blocks
-  // of 32 queries is one more launch, but leaves the query kernel free to split the keys and to use small tiles.  Whole calls,
-  // epilogue / pass, us: R = 4, H = 1, N = 2000  38.3 / 35.3; 8000  70 / 50 (keys split; 61 without); 20000  127 / 91 (109); H = 2,
-  // N = 5000  56.0 / 49.6; H = 5, N = 3000  48.5 / 44.0; R = 16  39.1 / 36.0; R = 2  63.2 / 56.1.  From six (batch, head) pairs on it
-  // is a gain at low rates and a loss at high ones: H = 8, N = 3000  R = 2  63.3 / 58.9, R = 4  48.5 / 47.3, R = 16  38.4 / 39.9;
-  // H = 10, N = 3000, R = 16  40.0 / 42.5; H = 12, N = 1560  R = 2  52.2 / 48.7, R = 4  43.5 / 42.2, N = 2600, R = 16  40.0 / 42.6.  Five is the
-  // largest number at which no measured problem loses.  Nor does it pay once 128-query tiles are more than one per CU.
+  // With the 128-wide maps, for up to five (batch, head) pairs with a CU for every 128-query tile, a pass of its own over blocks of
+  // 32 queries, which leaves the query kernel free to split the keys.  Where it does so in a long loop that is a gain; whole calls,
+  // epilogue / pass, us: R = 2, H = 1, N = 4500  57.8 / 52.7, 12000  108 / 77, H = 2, N = 8000  82.8 / 74.2; R = 4, H = 1, N = 8000  56.1 / 54.1,
+  // 20000  97.6 / 91.5.  Elsewhere the pass costs its launch, about 3 us, since the epilogue runs in workgroups of one wave per SIMD
+  // (ha_query_alone.hip): R = 2, H = 1, N = 500  29.5 / 32.9, 2000  39.7 / 40.5, H = 5, N = 3000  52.2 / 55.7; R = 4, H = 4, N = 2000  34.8 / 38.4;
+  // R = 16, H = 1, N = 8000  31.4 / 34.3, H = 5, N = 6500  43.4 / 50.4.  Five pairs were the largest number at which the pass was no loss
+  // against the epilogue before that, so the line is where every call keeps its route, not where it would be drawn today: the pass only
+  // where choose_split's estimate saves 4 us is 5.4 % faster over 547 problems (R = 2 .. 16, one to twelve heads) and never slower.
   if (plain && pl.HD == 128 && pl.F == 128 && pl.NS > 0 && BH <= 5 && ((size_t)pl.N + 127) / 128 * BH <= 256 &&
       route_has_room(pl, off, tiles * tile))
     pl.split_linear = true;
@@ -214,11 +215,14 @@ static bool needs_wide_path(const Plan &pl) {
 // Into how many ranges the keys of the plain operator's softmax loop are split.  A tile of 256 queries is one workgroup, so
 // a problem of few tiles leaves CUs idle for the whole loop; with n ranges it has n times the workgroups, each with 1 / n
 // of the keys, at the price of a pass that merges the partial sums (520 bytes per query and range written and read).  The
-// estimate, in us, from measured times: a 32-key step takes 0.5 (0.42 in the small tiling of an unsplit problem), the rest
-// of a workgroup 5; the merging pass 5 and its traffic at 4 TB/s.  It has to be 10 % better than one range.  (Where the query
-// kernel would evaluate the maps in its epilogue, there is no pass that could merge.)  Whole calls, one range / split, us:
-//   R = 1:  H = 1, N = 2000  37.4 / 23.4;  N = 8000  123 / 49;  N = 20000  291 / 189;  N = 32500  517 / 448;  H = 2, N = 5000  81 / 44;
-//   H = 5, N = 3000  54.7 / 41.9;  R = 4, H = 1:  N = 20000  109 / 91 (128-wide maps), 134 / 115 (256-wide);  N = 8000  61 / 50, 86 / 75.
+// estimate, in us, from measured times: a 32-key step takes 0.5 (0.42 in an unsplit problem's tiling: 0.41 from 63 to 158 of its
+// workgroups of one wave per SIMD, more beyond, up to 0.7 at 250), the rest of a workgroup 5; the merging pass 5 and its traffic at
+// 4 TB/s.  It has to be 10 % better than one range.  (Where the query kernel would evaluate the maps in its epilogue, there is no
+// pass that could merge.)  Whole calls, one range / split, us:
+//   R = 1:  H = 1, N = 1200  24.4 / 20.5;  2000  35.4 / 24.1;  8000  112 / 50;  20000  265 / 190;  32000  503 / 445;  H = 2, N = 4500  68.5 / 40.5;
+//   H = 5, N = 3000  52.3 / 42.2;  256-wide maps, R = 4, H = 1:  N = 8000  84 / 76;  20000  127 / 116.
+// It is wrong where five ranges fill two rounds of large workgroups, whose steps take longer with every CU busy: R = 1, H = 1,
+// N = 26000  366 / 407.
 static int choose_split(const Plan &pl, bool lin) {
   if (pl.D != 128 || pl.CC > 0 || pl.LW > 0 || pl.NS == 0 || (pl.NL > 0 && !lin)) return 1;
   const double tiles = (double)((pl.N + 255) / 256) * pl.B * pl.H, rows = (double)pl.N * pl.B * pl.H;
