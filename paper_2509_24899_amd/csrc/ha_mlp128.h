@@ -146,7 +146,7 @@ static __device__ __forceinline__ void mlp128_pipelined(const bf16x8 (&xf)[8], l
           } else if constexpr (ACT0) {
             // softmax of tiles 0, 1: their maximum in the first two slots, then one exponential per slot
             if (n == 0) {
-              float t = fmaxf(u[0][0], u[0][1]);
+              float t = __builtin_fmaxf(__builtin_fmaxf(u[0][0], u[0][1]), kMaxFloor);
 #pragma unroll
               for (int x = 2; x < 16; x += 2) t = __builtin_fmaxf(__builtin_fmaxf(t, u[0][x]), u[0][x + 1]);
               m0 = t;
@@ -154,7 +154,7 @@ static __device__ __forceinline__ void mlp128_pipelined(const bf16x8 (&xf)[8], l
               float t = m0;
 #pragma unroll
               for (int x = 0; x < 16; x += 2) t = __builtin_fmaxf(__builtin_fmaxf(t, u[1][x]), u[1][x + 1]);
-              m0 = __builtin_fmaxf(xhalf_max(t), kMaxFloor);
+              m0 = xhalf_max(t);
               off0 = -m0 * kLog2e;
             } else {
               auto ex = [&](int i) {
