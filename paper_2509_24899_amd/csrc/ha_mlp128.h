@@ -1,12 +1,13 @@
 // The feature map phi of Sec. 3.2 for the widths 128 -> 128 -> 128 on one 32-token column block, as the hand-placed
-// software pipeline the state pass and the gradient pass share.  gfx950 only.
+// software pipeline that the state pass, the gradient pass, the linear query side (ha_linear.hip) and the query kernel's workgroups of one
+// wave per SIMD (ha_query_alone.hip) share.  gfx950 only.
 //   * Layer 1 runs two row blocks at a time (two independent accumulator chains, their matrix instructions
 //     alternate); the fragments of the second pair arrive four k-steps ahead of their use, and its matrix
 //     instructions carry the ReLU / hi + lo conversion of the first pair.
 //   * Layer 2 runs two output tiles at a time in steps of one hidden block; the fragments of the next step are
 //     requested behind the step's first matrix instruction.  Under the steps: first the conversion of layer-1 blocks
-//     2, 3, later (softmax output) the exponentials of the finished pair of tiles against their own maximum; the
-//     second pair is exponentiated against the overall maximum, one factor per pair at the end.
+//     2, 3, later (softmax output) the exponentials of the finished pair of tiles against their own maximum (bounded from
+//     below, see kMaxFloor); the second pair is exponentiated against the overall maximum, one factor per pair at the end.
 #pragma once
 #include "ha_device.h"
 

@@ -2,10 +2,13 @@
 // pass and the query side.  gfx950 only.
 //
 // A token's 256 pre-activations are eight accumulator tiles; the hidden layer is walked in blocks of 32 units, each formed
-// (8 matrix instructions), split into hi + lo and contracted into all eight tiles (32 instructions), the next one formed under the
-// contraction, so two hidden blocks are all that is ever held.  The operands of a hidden block form a 24 KiB slab: the 8
-// fragments of its rows of W1 (state pass: of the next block's rows), then for every 32-channel output tile the two of its columns
-// of W2.
+// (8 matrix instructions), split into hi + lo and contracted into all eight tiles (32 instructions).  The operands of a step form a
+// 24 KiB slab: the 8 fragments of a block's rows of W1, then for every 32-channel output tile the two of the block's columns of W2.
+// Two forms:
+//   query side (mlp256_hidden_block)     a block is formed at the head of its own step and is all that is held; its slab brings
+//                                        its own rows of W1
+//   state pass (hidden_block_products)   the next block is formed under the current one's products, two blocks are held; a slab
+//                                        brings the rows of W1 of the block after its own
 #pragma once
 #include "ha_mlp128.h"
 

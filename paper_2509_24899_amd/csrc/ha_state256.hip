@@ -12,9 +12,9 @@
 //
 // Bound: matrix cores, 400 instructions of 32 cycles per SIMD and 128-token tile (12.8 k cycles), next to 5 k cycles of
 // exponentials and packing that nothing covers.  The next hidden block is formed under the products of the current one (so a slab
-// brings the rows of W1 of the block after its own; as a chain at the head of each step: 128 and 59.5 us instead of 122 and 58 for the
-// two calls below, side by side on one box).  Measured at 480p / 81 frames, 12 heads, R = 4: 222 us in one role with the
-// weights staged per tile in two rounds, 128 -> 122 us here; B = 2, N = 5003, R = 3, fp32: 108, then 59.5 -> 56.5 us.
+// brings the rows of W1 of the block after its own).  Measured in traces of 60 forwards, one box, with the next block as a chain at the
+// head of its own step / here: 480p / 81 frames, 12 heads, R = 4  143 / 130 us; B = 2, N = 5003, R = 3, fp32  61 / 59 us.  (One role with
+// the weights staged per tile in two rounds had taken 222 and 108 where the first form with two roles took 128 and 66.)
 #include "ha_mlp256.h"
 #include "ha_plan.h"
 
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(512, 1) void state256_kernel(const void *__restrict
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int w = wave & 3;                              // index within the role
   const bf16x8 *w1g = w1f_all + (int64_t)h * (HD * D / 8), *w2g = w2f_all + (int64_t)h * (F * HD / 8);
-  // (requested ahead of everything, written to LDS behind the request of the first K rows: B = 2, N = 5003, fp32 58.2 -> 56.5 us)
+  // (requested ahead of everything, written to LDS behind the request of the first K rows: B = 2, N = 5003, fp32 3 % of this kernel)
   float bias1 = 0.f, bias2 = 0.f;
   static_assert(HD == 256 && F == 256, "the first four waves write them");
   if (tid < 256) {

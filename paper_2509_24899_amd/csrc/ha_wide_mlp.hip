@@ -11,7 +11,7 @@
 // share; requests run ahead across items, one barrier per block.  A slab is in place a block before its turn, so that under the
 // products of a block the next block's first fragments are read and (from x) the next hidden block is formed: formed at the head
 // of its own block, as eight products in series each behind an LDS read of its own, it left the matrix cores idle in both waves of a
-// SIMD at once (57 % busy, now 66 %).  From HBM the output blocks of a tile go to neighbouring workgroups of an XCD at the same
+// SIMD at once (57 % busy, now 64 %; from HBM 50 %, now 58 - 64 %).  From HBM the output blocks of a tile go to neighbouring workgroups of an XCD at the same
 // time, so that its image is fetched once: one after the other in one workgroup it was fetched three times (3.8 GB, now 1.5 GB).
 //
 // Outputs leave in a burst per item, and slabs requested behind them are not known to have landed before they have reached memory
