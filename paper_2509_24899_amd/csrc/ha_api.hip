@@ -574,23 +574,28 @@ ha_status hybrid_attn_value_distill_loss(const ha_problem *p, const void *q, con
   return HA_OK;
 }
 
-// Workspace of the gradient: the loss's layout, then the backward pass's buffers.  Maps other than d -> d -> d take
-// the pass-per-step backward, which brings image buffers of its own (`layered`).
+// Workspace of the gradient: the loss's layout, then the backward pass's buffers.  128 -> 256 -> 256 maps have passes of their own
+// (`maps256`), other maps than d -> d -> d take the pass-per-step backward, which brings image buffers of its own (`layered`).
 struct GradLayout {
   ha::Plan teacher, student;
   ha::GradPlan gp;
   ha::WidePlan wp;
   ha::WideGradPlan wgp;
+  ha::Grad256Plan gp256;
   size_t off_partial, total;
-  bool layered;
+  bool layered, maps256;
 };
 
 static void grad_layout(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, GradLayout &gl) {
   const size_t base = distill_layout(p, phi_q, phi_k, gl.teacher, gl.student, gl.off_partial);
   gl.layered = phi_q->d_hidden != p.d_head || phi_q->d_out != p.d_head || phi_q->w_mid;
+  gl.maps256 = p.d_head == 128 && phi_q->d_hidden == 256 && phi_q->d_out == 256 && !phi_q->w_mid;
   gl.total = base;
   if (gl.student.NL == 0) return;
-  if (gl.layered) {
+  if (gl.maps256) {
+    ha::make_grad256_plan(gl.student, base, gl.gp256);
+    gl.total = gl.gp256.total;
+  } else if (gl.layered) {
     ha::make_wide_plan(gl.student, base, gl.wp, true);
     ha::make_wide_grad_plan(gl.student, gl.wp, gl.wp.total, gl.wgp);
     gl.total = gl.wgp.total;
@@ -688,7 +693,10 @@ ha_status hybrid_attn_value_distill_grad(const ha_problem *p, const void *q, con
     }
     return HA_OK;
   }
-  if (gl.layered)
+  if (gl.maps256)
+    e = ha::launch_value_distill_backward256(ps, gl.gp256, q, k, v, *phi_q, *phi_k, y_teacher, y_student, row_den, *grad_q, *grad_k,
+                                             workspace, st, loss_with_rows ? partial : nullptr, loss);
+  else if (gl.layered)
     e = ha::launch_wide_value_distill_backward(ps, gl.wp, gl.wgp, q, k, v, *phi_q, *phi_k, y_teacher, y_student, row_den,
                                                *grad_q, *grad_k, workspace, st, loss_with_rows ? partial : nullptr, loss);
   else

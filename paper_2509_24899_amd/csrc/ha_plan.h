@@ -84,6 +84,15 @@ struct WideGradPlan {
       off_dpre, off_part, total;
 };
 
+// Workspace of the value-distillation gradient of the maps 128 -> 256 -> 256 (ha_grad256.hip), [0] query side, [1] key side: fragments of the
+// weights, of W2^T and of S or dS, the bf16 images of 32-token blocks that the passes leave to the products over the tokens, and those
+// products' partial tiles over nc[side][product] ranges of blocks.
+struct Grad256Plan {
+  int n_tb[2], nc[2][3];
+  size_t off_w1[2], off_w2[2], off_w2t[2], off_mhi[2], off_mlo[2], off_dz, off_gsign, off_rs, off_wp, off_h, off_du, off_dpre, off_phi,
+      off_x, off_part, total;
+};
+
 // Which state passes read the feature map's weights straight from the caller's tensors (no preparation needed): the 128-wide
 // maps' in bf16; that of the 64-wide heads but for the chunk-causal variant with softmax keys, whose compaction is a launch of its own
 // and prepares the weights as well.  (There its many short chunks pay for fetching them row by row: raw / as fragments, whole calls, us:
@@ -189,6 +198,13 @@ hipError_t launch_wide_value_distill_backward(const Plan &pl, const WidePlan &wp
                                               const ha_feature_map &phi_k, const void *y_teacher, const void *y_student,
                                               const float *row_den, const ha_feature_map_grad &gq, const ha_feature_map_grad &gk,
                                               void *ws, hipStream_t st, double *l1_partial = nullptr, double *loss = nullptr);
+// ha_grad256.hip: the same for the maps 128 -> 256 -> 256
+void make_grad256_plan(const Plan &pl, size_t base_off, Grad256Plan &gp);
+hipError_t launch_value_distill_backward256(const Plan &pl, const Grad256Plan &gp, const void *q, const void *k, const void *v,
+                                            const ha_feature_map &phi_q, const ha_feature_map &phi_k, const void *y_teacher,
+                                            const void *y_student, const float *row_den, const ha_feature_map_grad &gq,
+                                            const ha_feature_map_grad &gk, void *ws, hipStream_t st, double *l1_partial = nullptr,
+                                            double *loss = nullptr);
 hipError_t launch_mfma_probe(float *sink, int workgroups, int iters, int random_operands, hipStream_t st);
 
 }  // namespace ha

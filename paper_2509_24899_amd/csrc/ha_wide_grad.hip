@@ -1,6 +1,6 @@
 // Gradient of the value-distillation loss (Attention Surgery, Sec. 3.3: Eq. "vd_loss", update line of Alg. "distil")
-// for two-layer feature maps of any width the layer-by-layer forward handles (Tab. "phi": the default 256-wide map,
-// P = 3, 4, ...), gfx950.  Same mathematics as ha_grad.hip; here every step is a pass of its own over register
+// for two-layer feature maps of any width the layer-by-layer forward handles (Tab. "phi":
+// P = 3, 4, ...), gfx950 (128 -> 256 -> 256 has passes of its own in ha_grad256.hip).  Same mathematics as ha_grad.hip; here every step is a pass of its own over register
 // images in HBM (layout: ha_wide.hip), per side (queries, then linear keys) right after that side's forward passes
 // have been re-run so that its hidden activations h, pre-activations u and phi are in the workspace:
 //
