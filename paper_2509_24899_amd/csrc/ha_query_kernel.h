@@ -222,6 +222,133 @@ static __device__ __forceinline__ void query_epilogue(const QueryArgs &a, int bh
   store_tile<D, F32>(a, base, lane, o, 1.0f / den, stage, q_first);
 }
 
+// The second role of a workgroup of few queries: n = phi_q(q) S and e = phi_q(q) . z of 32 queries per wave, while the other waves walk the
+// keys.  A barrier is the whole workgroup's, so the evaluation is cut into pieces of about a step of the key loop with a barrier (tick) behind
+// each.  The operands arrive in two areas: W1, then S lo in its place; W2, then S hi.
+template <int D, int HD, int F, int NW>
+struct MapRole {
+  static constexpr int KS = D / 16, RB = D / 32, HB = HD / 32, FB = F / 32;
+  static constexpr int NW1 = HD * D / 8, NW2 = F * HD / 8, NST = D * F / 8;
+  static constexpr int A1 = NW1 > NST ? NW1 : NST, OPS = A1 + (NW2 > NST ? NW2 : NST);
+  static constexpr int E_AT = HD + 2 * F, VECS = E_AT + 32 * NW;
+  static constexpr int TICKS = 2 + (HB + 1) / 2 + HB + 3 + (RB + 1) / 2 * 2;
+  template <typename LoadQ>
+  static __device__ __forceinline__ void run(const QueryArgs &a, int bh, int h, int w, int lane, int r, int g, const bf16x8 (&qf)[D / 16],
+                                             LoadQ load_q, bf16x8 *ops, float *vecs, f32x4 *out, int n_bar) {
+    const lds_frag_ptr a0 = (lds_frag_ptr)ops, a1 = (lds_frag_ptr)(ops + A1);
+    const float *b1 = vecs, *b2 = vecs + HD, *zz = vecs + HD + F;
+    dma_to_lds(a.w1f + (int64_t)h * NW1, ops, NW1 / 64, w, NW, lane);
+    dma_to_lds(a.w2f + (int64_t)h * NW2, ops + A1, NW2 / 64, w, NW, lane);
+    const int tid = 64 * w + lane;
+    static_assert(HD <= 64 * NW && F <= 64 * NW, "an element of each vector per thread");
+    float v1 = 0.f, v2 = 0.f, vz = 0.f;
+    if (tid < HD && a.b1) v1 = a.b1[(int64_t)h * HD + tid];
+    if (tid < F && a.b2) v2 = a.b2[(int64_t)h * F + tid];
+    if (tid < F) vz = a.z[(int64_t)bh * F + tid];
+    load_q();
+    int left = n_bar;
+    auto tick = [&]() {
+      --left;
+      __syncthreads();
+    };
+    tick();                                               // (the key loop's first blocks do not wait for the operands)
+    if (tid < HD) vecs[tid] = v1;
+    if (tid < F) {
+      vecs[HD + tid] = v2;
+      vecs[HD + F + tid] = vz;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    tick();                                               // W1, W2 and the vectors are in place
+    bf16x8 h_hi[HB][2], h_lo[HB][2];
+#pragma unroll
+    for (int hp = 0; hp < HB; hp += 2) {
+#pragma unroll
+      for (int hb = hp; hb < hp + 2 && hb < HB; ++hb) {
+        bf16x8 wf[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) wf[ks] = frag_at(a0, hb * KS + ks, lane);
+        f32x16 hh;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) hh[v] = b1[32 * hb + crow(v, g)];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) hh = mfma32(wf[ks], qf[ks], hh);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          f32x8 t, lo;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) t[i] = relu(hh[8 * s + i]);
+          h_hi[hb][s] = __builtin_convertvector(t, bf16x8);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) lo[i] = t[i] - static_cast<float>(h_hi[hb][s][i]);
+          h_lo[hb][s] = __builtin_convertvector(lo, bf16x8);
+        }
+      }
+      tick();
+    }
+    dma_to_lds(a.st_lo + (int64_t)bh * NST, ops, NST / 64, w, NW, lane);          // (every wave is done with W1)
+    f32x16 u[FB];
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) u[fb][v] = b2[32 * fb + crow(v, g)];
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        bf16x8 wf[FB];
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb) wf[fb] = frag_at(a1, (fb * HB + hb) * 2 + s, lane);
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb) u[fb] = mfma32(wf[fb], h_lo[hb][s], u[fb]);
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb) u[fb] = mfma32(wf[fb], h_hi[hb][s], u[fb]);
+      }
+      tick();
+    }
+    dma_to_lds(a.st_hi + (int64_t)bh * NST, ops + A1, NST / 64, w, NW, lane);     // (and with W2)
+    bf16x8 gb[FB][2];
+    feature_activation<FB>(u, g, a.act, 1, F);
+    tick();
+    feature_powers<FB>(u, a.P);
+    round_tiles<FB>(u, gb);
+    tick();
+    const float e = xhalf_sum(dot_z<FB>(gb, zz, g));
+    constexpr int HI_REQ = NST / 64 / NW;
+    static_assert(NST % (64 * NW) == 0, "requests are dealt evenly");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(HI_REQ) : "memory");
+    tick();                                               // S lo is in place
+    f32x16 n[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int x = 0; x < 16; ++x) n[rb][x] = 0.f;
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {                // lo, then hi
+      const lds_frag_ptr st = part ? a1 : a0;
+#pragma unroll
+      for (int rp = 0; rp < RB; rp += 2) {
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int rb = rp; rb < rp + 2 && rb < RB; ++rb) n[rb] = mfma32(frag_at(st, (rb * FB + fb) * 2 + s, lane), gb[fb][s], n[rb]);
+        if (part == 0 && rp + 2 >= RB) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        tick();                                           // (behind the last part of lo: S hi is in place)
+      }
+    }
+    for (; left > 0; --left) __syncthreads();
+    // the key loop is over: results through the ring, in the registers' own order
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int x4 = 0; x4 < 4; ++x4)
+        out[(rb * 4 + x4) * 64 + lane] = f32x4{n[rb][4 * x4], n[rb][4 * x4 + 1], n[rb][4 * x4 + 2], n[rb][4 * x4 + 3]};
+    if (g == 0) vecs[E_AT + 32 * w + r] = e;
+    __syncthreads();
+  }
+};
+
 // ------------------------------------------------------------------------------------------------
 // query_kernel_ring: the softmax tile loop as a software pipeline.  NW waves, each owning one column block
 // of 32 queries.
@@ -240,8 +367,10 @@ static __device__ __forceinline__ void query_epilogue(const QueryArgs &a, int bh
 // the usual kernel carries none of it.
 // MODE 1: the chunk-causal variant, 2: the local-window variant; likewise variants of their own.  MODE 3: the keys are split
 // into ranges, a workgroup walks one of them and leaves partial sums for the pass that merges them.
-template <int D, int HD, int F, int NW, int NB, int G, bool F32, bool LIN = false, int MODE = 0>
-__global__ __launch_bounds__(64 * NW, NW == 4 && NB == 8 ? 1 : 2) void query_kernel_ring(QueryArgs a) {
+// ROLES: the workgroup has as many waves again, which evaluate phi_q and its product with the state for the same queries while the first
+// NW walk the keys (map_role).
+template <int D, int HD, int F, int NW, int NB, int G, bool F32, bool LIN = false, int MODE = 0, bool ROLES = false>
+__global__ __launch_bounds__(64 * NW * (ROLES ? 2 : 1), NW == 4 && NB == 8 && !ROLES ? 1 : 2) void query_kernel_ring(QueryArgs a) {
   static_assert(G <= 2 && NB >= 2 * G + 2 && (NB & (NB - 1)) == 0, "ring too short for the barrier period");
   constexpr int KS = D / 16, RB = D / 32;
   constexpr int FRAG = D * 4;                 // bf16x8 per 32-key block per tensor
@@ -256,9 +385,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && NB == 8 ? 1 : 2) void query_ker
   // layer-1 weights of phi_q in an area of their own, fetched at kernel start; the layer-2 weights and the
   // state (hi + lo) in the ring once the loop has ended.
   constexpr int NW1 = HD * D / 8, NW2 = F * HD / 8, NST = D * F / 8;   // bf16x8 per head / per (batch, head)
-  constexpr bool ELDS = !LIN && NB == 8 && NW1 * 16 <= 32 * 1024 && (NW2 + 2 * NST) <= 2 * NB * FRAG &&
+  constexpr bool ELDS = !LIN && !ROLES && NB == 8 && NW1 * 16 <= 32 * 1024 && (NW2 + 2 * NST) <= 2 * NB * FRAG &&
                         NW1 % (64 * NW) == 0 && NW2 % (64 * NW) == 0 && NST % (64 * NW) == 0;
   __shared__ bf16x8 w1_lds[ELDS ? NW1 : 1];
+  typedef MapRole<D, HD, F, NW> Map;
+  __shared__ bf16x8 map_ops[ROLES ? Map::OPS : 1];
+  __shared__ __align__(16) float map_vecs[ROLES ? Map::VECS : 1];
   constexpr bool ALONE = ELDS && NW == 4;           // one workgroup of one wave per SIMD on a CU
   static_assert(!ALONE || (HD + F <= 64 * NW && (NW2 + 2 * NST) * 16 + (HD + 2 * F) * 4 <= 2 * NB * FRAG * 16), "the vectors fit behind the operands");
   float *vecs = reinterpret_cast<float *>(&ring[NW2 + 2 * NST]);
@@ -288,7 +420,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && NB == 8 ? 1 : 2) void query_ker
   const int h = bh % a.H;
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)h * a.sh;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, kept scalar
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, kept scalar
+  const int w = ROLES ? wave % NW : wave;
   const int q0 = qtile * QT + w * 32;
   if constexpr (CAUSAL) {
     // chunk-causal variant: this tile lies inside causal chunk cc (chunks are whole query tiles); it sees the softmax
@@ -344,10 +477,20 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && NB == 8 ? 1 : 2) void query_ker
   }
 
   bf16x8 qf[KS];
-  {
+  auto load_q = [&]() {
     const int qi = min(q0 + r, a.N - 1);   // rows past the end repeat the last query and are not stored
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qf[ks] = load8<F32>(a.q, base + (int64_t)qi * a.sn + 16 * ks + 8 * g);
+  };
+  if constexpr (!ROLES) load_q();          // (otherwise behind the requests of the operands)
+  // barriers ahead of the exchange of results: one before, one per step and one behind the loop below, or as many as the map takes
+  const int n_bar = ROLES ? max(nblk > 0 ? 2 + nblk : 0, Map::TICKS) : 0;
+  if constexpr (ROLES) {
+    static_assert(!LIN && MODE == 0 && G == 1, "the plain operator, a barrier per step");
+    if (wave >= NW) {
+      Map::run(a, bh, h, w, lane, r, g, qf, load_q, map_ops, map_vecs, reinterpret_cast<f32x4 *>(&ring[0]) + w * (2 * NB * FRAG / NW), n_bar);
+      return;
+    }
   }
   f32x16 o[RB];
   // m_true: exact running maximum c_i over the keys this lane has seen, i.e. over its half of every key block (the
@@ -420,6 +563,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && NB == 8 ? 1 : 2) void query_ker
     // and its weights are zero), so every ring slot must hold finite data before it is read: requests past
     // the end re-fetch the last block of the (zero padded) fragment arrays.
     for (int b = 0; b < LEAD; ++b) request(min(b, kb_last));
+    if constexpr (ROLES) load_q();
     ring_barrier(std::false_type{});
 
     const float c = a.scale_log2e;
@@ -534,13 +678,31 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && NB == 8 ? 1 : 2) void query_ker
     // Trips whose blocks j + 1, j + 2 consist of real keys only skip the padding mask.
     const int n_full = a.NS >> 5;
     int j = 0;
-    for (; j + 2 < n_full; j += 2) {
+    // (a workgroup in roles has a short loop as a rule: one form of the step, whose code is fetched once, and no step of padding)
+    if constexpr (ROLES) {
+      if (nblk > 32)
+        for (; j + 2 < n_full; j += 2) {
+          step(j, s_a, s_b, k_a, k_b, Fa{});
+          ring_barrier(T{});
+          step(j + 1, s_b, s_a, k_b, k_a, Fa{});
+          ring_barrier(T{});
+        }
+      for (; j < nblk; j += 2) {
+        step(j, s_a, s_b, k_a, k_b, T{});
+        ring_barrier(T{});
+        if (j + 1 == nblk) break;
+        step(j + 1, s_b, s_a, k_b, k_a, T{});
+        ring_barrier(T{});
+      }
+      j = nblk;
+    }
+    for (; !ROLES && j + 2 < n_full; j += 2) {
       step(j, s_a, s_b, k_a, k_b, Fa{});
       if (G == 1) ring_barrier(T{});
       step(j + 1, s_b, s_a, k_b, k_a, Fa{});
       ring_barrier(T{});
     }
-    for (; j < nblk; j += 2) {
+    for (; !ROLES && j < nblk; j += 2) {
       step(j, s_a, s_b, k_a, k_b, T{});
       if (G == 1) ring_barrier(T{});
       step(j + 1, s_b, s_a, k_b, k_a, T{});
@@ -575,6 +737,23 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && NB == 8 ? 1 : 2) void query_ker
     return;
   }
   char *stage = reinterpret_cast<char *>(&ring[0]) + w * (2 * NB * FRAG * 16 / NW);
+  if constexpr (ROLES) {
+    for (int i = nblk > 0 ? 2 + nblk : 0; i < n_bar; ++i) __syncthreads();
+    __syncthreads();                          // phi_q S and phi_q . z of this wave's queries are in its share of the ring
+    const f32x4 *n = reinterpret_cast<const f32x4 *>(stage) + lane;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int x4 = 0; x4 < 4; ++x4) {
+        const f32x4 t = n[(rb * 4 + x4) * 64];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[rb][4 * x4 + j] += t[j];
+      }
+    const float den = xhalf_sum(lsum) + map_vecs[Map::E_AT + w * 32 + r];
+    store_den(a, bh, lane, den, q0);
+    store_tile<D, F32>(a, base, lane, o, 1.0f / den, stage, q0);
+    return;
+  }
   if constexpr (LIN) {
     // linear part computed by the wide-map passes: add it to the accumulators, which share its register layout
     float den = xhalf_sum(lsum);
