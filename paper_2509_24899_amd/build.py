@@ -28,11 +28,28 @@ FILE_FLAGS = {"ha_grad.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"], "ha_grad256
               "ha_wide_mlp.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
+BINDING_PATH = os.path.join(LIB_DIR, "hybridattn_binding.so")
+
+
+def binding_command() -> list:
+    """g++ line of the compiled marshalling (csrc/ha_binding.cpp): host code over torch's headers and the C ABI's."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include", f"-I{sysconfig.get_paths()['include']}",
+            os.path.join(CSRC, "ha_binding.cpp"), "-o", BINDING_PATH, f"-L{root}/lib", "-lc10", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PATH, tag: str = "") -> str:
-    """Compile every source and link the shared library (libhybridattn.so by default); returns its path."""
+    """Compile every source and link the shared library (libhybridattn.so by default); returns its path.  With the default path the
+    compiled marshalling is built beside it."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(LIB_DIR, exist_ok=True)
     objs, procs = [], []
+    if out_path == LIB_PATH:
+        procs.append(("ha_binding.cpp", subprocess.Popen(binding_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src in SOURCES:
         obj = os.path.join(LIB_DIR, src.replace(".hip", tag + ".o"))
         cmd = [hipcc, *HIPCC_FLAGS, *FILE_FLAGS.get(src, []), *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
@@ -44,7 +61,7 @@ def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PAT
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l and l.strip())
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
+            raise RuntimeError(f"compiling {src} failed:\n{out}")
         if verbose and out:
             print(out, flush=True)
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", out_path]
