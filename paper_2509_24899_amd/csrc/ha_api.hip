@@ -525,25 +525,59 @@ ha_status hybrid_attn_mfma_probe(int random_operands, int iters, int launches, v
   return HA_OK;
 }
 
-// Workspace of the loss: the larger of the two forwards' workspaces, then the reduction partials.
-static size_t distill_layout(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k,
-                             ha::Plan &teacher, ha::Plan &student, size_t &off_partial) {
+// Workspace of the loss: the larger of the two forwards' workspaces, then the reduction partials.  Where the two query kernels run as one
+// launch (off_teacher > 0) the teacher has a workspace of its own behind these, up to end_teacher; with less room the forwards run one after
+// the other.
+struct DistillLayout {
+  ha::Plan teacher, student;
+  size_t off_partial, total, off_teacher, end_teacher;
+};
+static void distill_layout(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, DistillLayout &l) {
   ha_problem pt = p;
   pt.hybrid_rate = 1;
   ha::WidePlan wp;
   bool wide;
-  const size_t teacher_total = ha::full_plan(pt, nullptr, nullptr, teacher, wp, wide);
-  const size_t student_total = ha::full_plan(p, phi_q, phi_k, student, wp, wide);
-  off_partial = ha::align256(teacher_total > student_total ? teacher_total : student_total);
-  return off_partial + ha::align256(ha::l1_partial_bytes(student));
+  const size_t teacher_total = ha::full_plan(pt, nullptr, nullptr, l.teacher, wp, wide);
+  const size_t student_total = ha::full_plan(p, phi_q, phi_k, l.student, wp, wide);
+  l.off_partial = ha::align256(teacher_total > student_total ? teacher_total : student_total);
+  l.total = l.off_partial + ha::align256(ha::l1_partial_bytes(l.student));
+  l.off_teacher = l.end_teacher = 0;
+  if (!wide && ha::query_pair_fits(l.teacher, l.student)) {
+    l.off_teacher = l.total;
+    l.end_teacher = l.off_teacher + teacher_total;
+  }
+}
+
+// Both forwards of a distillation step.
+static ha_status teacher_and_student(const ha_problem *p, const DistillLayout &l, const void *q, const void *k, const void *v,
+                                     const ha_feature_map *phi_q, const ha_feature_map *phi_k, void *y_teacher, void *y_student,
+                                     float *row_den, void *workspace, size_t workspace_bytes, void *hip_stream) {
+  ha_status s;
+  const bool plain = ha::aligned16(q) && ha::aligned16(k) && ha::aligned16(v) && !(reinterpret_cast<uintptr_t>(workspace) & 255u);
+  if (l.off_teacher && workspace_bytes >= l.end_teacher && plain && !ha::prof_events()) {
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    void *ws_teacher = static_cast<char *>(workspace) + l.off_teacher;
+    bool prep_q_done = false;
+    if ((s = ha::run_key_side(l.teacher, k, v, nullptr, ws_teacher, st)) != HA_OK) return s;
+    if ((s = ha::run_key_side(l.student, k, v, phi_k, workspace, st, nullptr, nullptr, phi_q, &prep_q_done)) != HA_OK) return s;
+    hipError_t e;
+    if (!prep_q_done && (e = ha::launch_weight_prep(l.student, *phi_q, true, workspace, st)) != hipSuccess) return ha::device_error(e);
+    if ((e = ha::launch_query_pair(l.teacher, l.student, q, *phi_q, y_teacher, y_student, row_den, ws_teacher, workspace, st)) != hipSuccess)
+      return ha::device_error(e);
+    return HA_OK;
+  }
+  ha_problem teacher = *p;
+  teacher.hybrid_rate = 1;     // Eq. "softmax": every token is a softmax token
+  if ((s = hybrid_attn_forward(&teacher, q, k, v, nullptr, nullptr, y_teacher, workspace, workspace_bytes, hip_stream)) != HA_OK) return s;
+  return forward_impl(p, q, k, v, phi_q, phi_k, y_student, row_den, workspace, workspace_bytes, hip_stream);
 }
 
 size_t hybrid_attn_value_distill_workspace_bytes(const ha_problem *p, const ha_feature_map *phi_q,
                                                  const ha_feature_map *phi_k) {
   if (ha::validate(p, phi_q, phi_k) != HA_OK) return 0;
-  ha::Plan t, s;
-  size_t off;
-  return distill_layout(*p, phi_q, phi_k, t, s, off);
+  DistillLayout l;
+  distill_layout(*p, phi_q, phi_k, l);
+  return l.end_teacher > l.total ? l.end_teacher : l.total;
 }
 
 ha_status hybrid_attn_value_distill_loss(const ha_problem *p, const void *q, const void *k, const void *v,
@@ -556,19 +590,14 @@ ha_status hybrid_attn_value_distill_loss(const ha_problem *p, const void *q, con
   if (!q || !k || !v || !y_teacher || !y_student || !loss) return HA_ERR_NULL;
   if (!ha::aligned16(y_teacher) || !ha::aligned16(y_student) || (reinterpret_cast<uintptr_t>(loss) & 7u)) return HA_ERR_ALIGN;
   if (y_teacher == y_student) return HA_ERR_SHAPE;
-  ha::Plan pt, ps;
-  size_t off_partial;
-  const size_t need = distill_layout(*p, phi_q, phi_k, pt, ps, off_partial);
-  if (!workspace || workspace_bytes < need) return HA_ERR_WORKSPACE;
-  if (!teacher_is_cached) {
-    ha_problem teacher = *p;
-    teacher.hybrid_rate = 1;     // Eq. "softmax": every token is a softmax token
-    s = hybrid_attn_forward(&teacher, q, k, v, nullptr, nullptr, y_teacher, workspace, workspace_bytes, hip_stream);
-    if (s != HA_OK) return s;
-  }
-  s = hybrid_attn_forward(p, q, k, v, phi_q, phi_k, y_student, workspace, workspace_bytes, hip_stream);
+  DistillLayout l;
+  distill_layout(*p, phi_q, phi_k, l);
+  if (!workspace || workspace_bytes < l.total) return HA_ERR_WORKSPACE;
+  if (teacher_is_cached) s = hybrid_attn_forward(p, q, k, v, phi_q, phi_k, y_student, workspace, workspace_bytes, hip_stream);
+  else s = teacher_and_student(p, l, q, k, v, phi_q, phi_k, y_teacher, y_student, nullptr, workspace, workspace_bytes, hip_stream);
   if (s != HA_OK) return s;
-  double *partial = reinterpret_cast<double *>(static_cast<char *>(workspace) + off_partial);
+  const ha::Plan &ps = l.student;
+  double *partial = reinterpret_cast<double *>(static_cast<char *>(workspace) + l.off_partial);
   hipError_t e = ha::launch_l1_distance(ps, y_teacher, y_student, partial, loss, static_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return ha::device_error(e);
   return HA_OK;
@@ -577,30 +606,32 @@ ha_status hybrid_attn_value_distill_loss(const ha_problem *p, const void *q, con
 // Workspace of the gradient: the loss's layout, then the backward pass's buffers.  128 -> 256 -> 256 maps have passes of their own
 // (`maps256`), other maps than d -> d -> d take the pass-per-step backward, which brings image buffers of its own (`layered`).
 struct GradLayout {
-  ha::Plan teacher, student;
+  DistillLayout fwd;
   ha::GradPlan gp;
   ha::WidePlan wp;
   ha::WideGradPlan wgp;
   ha::Grad256Plan gp256;
-  size_t off_partial, total;
+  size_t total;
   bool layered, maps256;
 };
 
 static void grad_layout(const ha_problem &p, const ha_feature_map *phi_q, const ha_feature_map *phi_k, GradLayout &gl) {
-  const size_t base = distill_layout(p, phi_q, phi_k, gl.teacher, gl.student, gl.off_partial);
+  distill_layout(p, phi_q, phi_k, gl.fwd);
+  const size_t base = gl.fwd.total;            // (where the teacher's keys are too, spent before the backward pass begins)
+  const ha::Plan &student = gl.fwd.student;
   gl.layered = phi_q->d_hidden != p.d_head || phi_q->d_out != p.d_head || phi_q->w_mid;
   gl.maps256 = p.d_head == 128 && phi_q->d_hidden == 256 && phi_q->d_out == 256 && !phi_q->w_mid;
   gl.total = base;
-  if (gl.student.NL == 0) return;
+  if (student.NL == 0) return;
   if (gl.maps256) {
-    ha::make_grad256_plan(gl.student, base, gl.gp256);
+    ha::make_grad256_plan(student, base, gl.gp256);
     gl.total = gl.gp256.total;
   } else if (gl.layered) {
-    ha::make_wide_plan(gl.student, base, gl.wp, true);
-    ha::make_wide_grad_plan(gl.student, gl.wp, gl.wp.total, gl.wgp);
+    ha::make_wide_plan(student, base, gl.wp, true);
+    ha::make_wide_grad_plan(student, gl.wp, gl.wp.total, gl.wgp);
     gl.total = gl.wgp.total;
   } else {
-    ha::make_grad_plan(gl.student, base, gl.gp);
+    ha::make_grad_plan(student, base, gl.gp);
     gl.total = gl.gp.total;
   }
 }
@@ -625,7 +656,7 @@ size_t hybrid_attn_value_distill_grad_workspace_bytes(const ha_problem *p, const
   if (check_grad_maps(p, phi_q, phi_k) != HA_OK) return 0;
   GradLayout gl;
   grad_layout(*p, phi_q, phi_k, gl);
-  return gl.total;
+  return gl.fwd.end_teacher > gl.total ? gl.fwd.end_teacher : gl.total;
 }
 
 ha_status hybrid_attn_value_distill_grad(const ha_problem *p, const void *q, const void *k, const void *v,
@@ -650,12 +681,15 @@ ha_status hybrid_attn_value_distill_grad(const ha_problem *p, const void *q, con
   if (y_teacher == y_student) return HA_ERR_SHAPE;
   GradLayout gl;
   grad_layout(*p, phi_q, phi_k, gl);
-  const ha::Plan &ps = gl.student;
-  const size_t off_partial = gl.off_partial;
+  const ha::Plan &ps = gl.fwd.student;
+  const size_t off_partial = gl.fwd.off_partial;
   if (!workspace || workspace_bytes < gl.total) return HA_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return HA_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  if (!teacher_is_cached) {
+  if (!teacher_is_cached && !student_is_cached) {
+    s = teacher_and_student(p, gl.fwd, q, k, v, phi_q, phi_k, y_teacher, y_student, row_den, workspace, workspace_bytes, hip_stream);
+    if (s != HA_OK) return s;
+  } else if (!teacher_is_cached) {
     ha_problem teacher = *p;
     teacher.hybrid_rate = 1;
     s = hybrid_attn_forward(&teacher, q, k, v, nullptr, nullptr, y_teacher, workspace, workspace_bytes, hip_stream);
@@ -663,7 +697,7 @@ ha_status hybrid_attn_value_distill_grad(const ha_problem *p, const void *q, con
   }
   hipError_t e;
   if (!student_is_cached) {
-    s = forward_impl(p, q, k, v, phi_q, phi_k, y_student, row_den, workspace, workspace_bytes, hip_stream);
+    if (teacher_is_cached) s = forward_impl(p, q, k, v, phi_q, phi_k, y_student, row_den, workspace, workspace_bytes, hip_stream);
     if (s != HA_OK) return s;
   } else if (ps.NL > 0) {
     // the backward pass needs S, z of the current phi_k in the workspace

@@ -146,6 +146,10 @@ hipError_t launch_state_reduce(const Plan &pl, void *ws, hipStream_t st);
 hipError_t launch_state_reduce_with_prep(const Plan &pl, const ha_feature_map &phi_q, void *ws, hipStream_t st);
 hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi_q, void *out, float *row_den, void *ws,
                         hipStream_t st, const WidePlan *wide = nullptr);
+// Teacher (rate 1) and student of one problem whose query kernels take the same tiling: both in one launch, each with a workspace of its own
+bool query_pair_fits(const Plan &teacher, const Plan &student);
+hipError_t launch_query_pair(const Plan &teacher, const Plan &student, const void *q, const ha_feature_map &phi_q, void *y_teacher,
+                             void *y_student, float *row_den, void *ws_teacher, void *ws_student, hipStream_t st);
 // ha_linear.hip: the query side where there is no softmax token at all; with pl.split_linear its n = phi_q(q) S and e only
 hipError_t launch_linear_query(const Plan &pl, const void *q, const ha_feature_map &phi_q, void *out, float *row_den, void *ws,
                                hipStream_t st);

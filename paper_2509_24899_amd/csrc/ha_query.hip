@@ -80,9 +80,8 @@ __global__ __launch_bounds__(256) void merge_kernel(QueryArgs a) {
   }
 }
 
-hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi_q, void *out, float *row_den, void *ws,
-                        hipStream_t st, const WidePlan *wide) {
-  if (!wide && query_side_is_linear(pl)) return launch_linear_query(pl, q, *phi_q, out, row_den, ws, st);
+static QueryArgs query_args(const Plan &pl, const void *q, const ha_feature_map *phi_q, void *out, float *row_den, void *ws,
+                            const WidePlan *wide) {
   const bool lin = wide || pl.split_linear;               // the linear part arrives precomputed
   QueryArgs a;
   a.q = q;
@@ -107,20 +106,11 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
   a.sb = pl.sb; a.sh = pl.sh; a.sn = pl.sn;
   a.scale_log2e = pl.scale * kLog2e;
   a.sp = SplitArgs{nullptr, nullptr, nullptr, 1, 0, 0, 0.f};
-  if (pl.n_split > 1) {
-    // (choose_split says when)
-    a.sp = split_args(pl, ws);
-    a.n_qtiles = (pl.N + 255) / 256;
-    a.total_wg = a.n_qtiles * pl.B * pl.H * pl.n_split;
-    const dim3 grid((a.total_wg + 7) / 8 * 8), mgrid((pl.N + 31) / 32, pl.B * pl.H);
-    if (pl.f32) query_kernel_ring<128, 128, 128, 8, 8, 2, true, true, 3><<<grid, 512, 0, st>>>(a);
-    else query_kernel_ring<128, 128, 128, 8, 8, 2, false, true, 3><<<grid, 512, 0, st>>>(a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (pl.f32) merge_kernel<true><<<mgrid, 256, 0, st>>>(a);
-    else merge_kernel<false><<<mgrid, 256, 0, st>>>(a);
-    return hipGetLastError();
-  }
+  return a;
+}
+
+enum class Tiling { kAlone, kSmall, kLarge };
+static Tiling tiling_of(const Plan &pl, bool lin) {
   // Three tilings of one computation (every query column sees the same keys in the same order): 4 waves x 32 queries, one wave per
   // SIMD, with a ring of 8 key blocks (ha_query_alone.hip); 8 waves x 32 queries with that ring and a barrier every 64 keys, one
   // workgroup per CU; and 4 waves x 32 queries with a ring of 4 and a barrier every 32 keys, two workgroups per CU.  The variants'
@@ -161,11 +151,35 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
     const int64_t last = tail == 0 ? 0 : tail <= 256 ? 30 * nblk + 2600 : 52 * nblk + 2400;
     big = wgs(256) <= 256 || rounds * (50 * nblk + 1400) <= full * (52 * nblk + 2400) + last;
   }
+  return alone ? Tiling::kAlone : big ? Tiling::kLarge : Tiling::kSmall;
+}
+
+hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi_q, void *out, float *row_den, void *ws,
+                        hipStream_t st, const WidePlan *wide) {
+  if (!wide && query_side_is_linear(pl)) return launch_linear_query(pl, q, *phi_q, out, row_den, ws, st);
+  const bool lin = wide || pl.split_linear;
+  QueryArgs a = query_args(pl, q, phi_q, out, row_den, ws, wide);
+  if (pl.n_split > 1) {
+    // (choose_split says when)
+    a.sp = split_args(pl, ws);
+    a.n_qtiles = (pl.N + 255) / 256;
+    a.total_wg = a.n_qtiles * pl.B * pl.H * pl.n_split;
+    const dim3 grid((a.total_wg + 7) / 8 * 8), mgrid((pl.N + 31) / 32, pl.B * pl.H);
+    if (pl.f32) query_kernel_ring<128, 128, 128, 8, 8, 2, true, true, 3><<<grid, 512, 0, st>>>(a);
+    else query_kernel_ring<128, 128, 128, 8, 8, 2, false, true, 3><<<grid, 512, 0, st>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (pl.f32) merge_kernel<true><<<mgrid, 256, 0, st>>>(a);
+    else merge_kernel<false><<<mgrid, 256, 0, st>>>(a);
+    return hipGetLastError();
+  }
+  const Tiling tiling = tiling_of(pl, lin);
+  const bool big = tiling == Tiling::kLarge;
   const int qt = big ? 256 : 128;
   a.n_qtiles = (pl.N + qt - 1) / qt;
   a.total_wg = a.n_qtiles * pl.B * pl.H;
   dim3 grid(((a.total_wg + 7) / 8) * 8);
-  if (alone) return launch_query_alone(pl, a, grid, st);
+  if (tiling == Tiling::kAlone) return launch_query_alone(pl, a, grid, st);
 #define HA_QUERY(DD, HH, FF, F32) \
   do { \
     if (pl.LW > 0) { \
@@ -194,6 +208,75 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
   else if (pl.HD == 128) { if (pl.f32) HA_QUERY(128, 128, 128, true); else HA_QUERY(128, 128, 128, false); }
   else { if (pl.f32) HA_QUERY(128, 256, 256, true); else HA_QUERY(128, 256, 256, false); }
 #undef HA_QUERY
+  return hipGetLastError();
+}
+
+// Two forwards of one problem, the softmax teacher's and the student's, as one launch: the student's workgroups start on the CUs that the
+// teacher's last round leaves idle.
+// Estimated, in us, for n workgroups each: a key block 0.50 (d = 64: 0.30), 0.42 (0.25) in a round of up to 150 workgroups, more towards
+// 256; beside the loop 5 (4) for the teacher, 14 (7) for the student, whose epilogue evaluates the map.  One after the other: whole
+// rounds.  In one launch: every CU takes the next workgroup when it is free.  The estimate has to be 4 % better, and the keys of the
+// heads that an XCD works on must not outgrow its 4 MiB of L2 by the student's share alone (H = 12, N = 3500: 155.7 / 163.1 at R = 3).
+// Whole losses, one after the other / in one launch, us: H = 12, N = 2900, R = 8 122 / 107; H = 12, N = 9361, R = 8 626 / 603; H = 8, N = 5000, R = 3
+// 189 / 164; H = 5, N = 7000, R = 5 214 / 188; d = 64, H = 12, N = 4000, R = 5 108.5 / 94.6; not taken: H = 5, N = 9361, R = 2 353 / 378; H = 8, N = 15000,
+// R = 5 976 / 997; H = 12, N = 5000, R = 5 (240 workgroups) 218.6 / 215.4.  (81 sizes; the estimate was off by 10 us where it did not hold.)
+static int64_t large_tiles(const Plan &pl) { return (int64_t)((pl.N + 255) / 256) * pl.B * pl.H; }
+bool query_pair_fits(const Plan &teacher, const Plan &student) {
+  const bool square = student.HD == student.D && student.F == student.D && student.DM == 0;
+  if (student.NL == 0 || student.NS == 0 || !square || student.split_linear || student.CC > 0 || student.LW > 0) return false;
+  // (beyond four rounds a last one that is not full is little, and the teacher's keys would be held beside the student's for it)
+  if (teacher.n_split > 1 || student.n_split > 1 || large_tiles(teacher) > 1024 || tiling_of(teacher, false) != Tiling::kLarge ||
+      tiling_of(student, false) != Tiling::kLarge)
+    return false;
+  const int n = (int)large_tiles(teacher), whole = n / 256, rest = n % 256;
+  const bool d64 = teacher.D == 64;
+  const double full = d64 ? 0.30 : 0.50, light = d64 ? 0.25 : 0.42;
+  const double last = light + (full - light) * (rest > 150 ? (rest - 150) / 106.0 : 0.0);
+  const int blocks[2] = {(teacher.NS + 31) / 32, (student.NS + 31) / 32};
+  const double beside[2] = {d64 ? 4.0 : 5.0, d64 ? 7.0 : 14.0};
+  double apart = 2.0, one[2];                             // (a launch more)
+  for (int i = 0; i < 2; ++i) {
+    one[i] = full * blocks[i] + beside[i];
+    apart += whole * one[i] + (rest ? last * blocks[i] + beside[i] : 0.0);
+  }
+  // together: 256 - rest CUs are free for the student after `whole` rounds of the teacher, the others a round later
+  const double at[2] = {whole * one[0], (whole + (rest ? 1 : 0)) * one[0]};
+  auto done = [&](double t) {                             // workgroups of the student that have ended by then
+    int64_t c = 0;
+    for (int i = 0; i < 2; ++i)
+      if (t >= at[i]) c += (i ? rest : 256 - rest) * (int64_t)((t - at[i]) / one[1] + 1e-6);
+    return c;
+  };
+  double together = 1e30;
+  for (double start : at) {
+    double t = start;
+    while (done(t) < n) t += one[1];
+    together = t < together ? t : together;
+  }
+  if (together < at[1]) together = at[1];
+  const int64_t per_head = (teacher.N + 255) / 256, heads = ((n + 7) / 8 + per_head - 1) / per_head, l2 = 4 << 20;
+  const int64_t keys = heads * teacher.N * (4 * teacher.D);   // K and V of those heads in bf16
+  if (keys <= l2 && keys + heads * student.NS * (4 * student.D) > l2) return false;
+  return together <= 0.96 * apart;
+}
+hipError_t launch_query_pair(const Plan &teacher, const Plan &student, const void *q, const ha_feature_map &phi_q, void *y_teacher,
+                             void *y_student, float *row_den, void *ws_teacher, void *ws_student, hipStream_t st) {
+  QueryPair p;
+  p.a[0] = query_args(teacher, q, nullptr, y_teacher, nullptr, ws_teacher, nullptr);
+  p.a[1] = query_args(student, q, &phi_q, y_student, row_den, ws_student, nullptr);
+  for (QueryArgs &a : p.a) {
+    a.n_qtiles = (teacher.N + 255) / 256;
+    a.total_wg = (int)large_tiles(teacher);
+  }
+  p.n_first = (p.a[0].total_wg + 7) / 8 * 8;
+  const dim3 grid(2 * p.n_first);
+  if (teacher.D == 64) {
+    if (teacher.f32) query_pair_kernel<64, true><<<grid, 512, 0, st>>>(p);
+    else query_pair_kernel<64, false><<<grid, 512, 0, st>>>(p);
+  } else {
+    if (teacher.f32) query_pair_kernel<128, true><<<grid, 512, 0, st>>>(p);
+    else query_pair_kernel<128, false><<<grid, 512, 0, st>>>(p);
+  }
   return hipGetLastError();
 }
 

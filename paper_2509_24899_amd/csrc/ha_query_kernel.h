@@ -369,8 +369,9 @@ struct MapRole {
 // into ranges, a workgroup walks one of them and leaves partial sums for the pass that merges them.
 // ROLES: the workgroup has as many waves again, which evaluate phi_q and its product with the state for the same queries while the first
 // NW walk the keys (map_role).
-template <int D, int HD, int F, int NW, int NB, int G, bool F32, bool LIN = false, int MODE = 0, bool ROLES = false>
-__global__ __launch_bounds__(64 * NW * (ROLES ? 2 : 1), NW == 4 && NB == 8 && !ROLES ? 1 : 2) void query_kernel_ring(QueryArgs a) {
+// block: the workgroup's number in the launch of this problem.
+template <int D, int HD, int F, int NW, int NB, int G, bool F32, bool LIN, int MODE, bool ROLES>
+static __device__ __forceinline__ void query_ring_body(QueryArgs a, unsigned block) {
   static_assert(G <= 2 && NB >= 2 * G + 2 && (NB & (NB - 1)) == 0, "ring too short for the barrier period");
   constexpr int KS = D / 16, RB = D / 32;
   constexpr int FRAG = D * 4;                 // bf16x8 per 32-key block per tensor
@@ -400,9 +401,9 @@ __global__ __launch_bounds__(64 * NW * (ROLES ? 2 : 1), NW == 4 && NB == 8 && !R
                           NW1 % 64 == 0 && (NW2 / 2) % 64 == 0 && NST % 64 == 0 && (F / 32) % 2 == 0;
 
   const int per_xcd = (a.total_wg + 7) >> 3;
-  int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  int logical = (block & 7) * per_xcd + (block >> 3);
   constexpr bool CAUSAL = MODE == 1;
-  if constexpr (CAUSAL) logical = blockIdx.x;
+  if constexpr (CAUSAL) logical = block;
   if (logical >= a.total_wg) return;
   int range = 0;
   if constexpr (MODE == 3) {
@@ -838,6 +839,23 @@ __global__ __launch_bounds__(64 * NW * (ROLES ? 2 : 1), NW == 4 && NB == 8 && !R
                                                 global_frags(w2g, NW2 * 16), global_frags(sthg, NST * 16),
                                                 global_frags(stlg, NST * 16), nullptr, stage, q0);
   }
+}
+
+template <int D, int HD, int F, int NW, int NB, int G, bool F32, bool LIN = false, int MODE = 0, bool ROLES = false>
+__global__ __launch_bounds__(64 * NW * (ROLES ? 2 : 1), NW == 4 && NB == 8 && !ROLES ? 1 : 2) void query_kernel_ring(QueryArgs a) {
+  query_ring_body<D, HD, F, NW, NB, G, F32, LIN, MODE, ROLES>(a, blockIdx.x);
+}
+
+// Two problems of one tiling in one launch, the workgroups of the first ahead of those of the second (whose number, n_first, is a multiple
+// of 8): the last, partly empty round of the first is filled by the second.
+struct QueryPair {
+  QueryArgs a[2];
+  unsigned n_first;
+};
+template <int D, bool F32>
+__global__ __launch_bounds__(512, 2) void query_pair_kernel(QueryPair p) {
+  const int i = blockIdx.x >= p.n_first;
+  query_ring_body<D, D, D, 8, 8, 2, F32, false, 0, false>(p.a[i], blockIdx.x - (i ? p.n_first : 0));
 }
 
 // The instances for problems whose 128-query tiles have a CU each (ha_query_alone.hip).
