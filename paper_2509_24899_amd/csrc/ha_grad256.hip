@@ -9,7 +9,7 @@
 //   reduce256_kernel    fixed-order sum of the partial tiles; dS as operand fragments for the key side
 //   prep256_kernel      weight fragments of both maps, W2^T and S as fragments, in one launch
 // (the layer-by-layer passes of ha_wide_grad.hip, 14 launches more, took 1520 us behind the forward at 480p / 81 frames, 12 heads, R = 4; these
-// take 935.  H = 1, N = 200, R = 2: the whole step 208 -> 146 us; B = 2, H = 8, N = 2000, R = 8: 381 -> 240.)
+// take 875.  H = 1, N = 200, R = 2: the whole step 208 -> 146 us; B = 2, H = 8, N = 2000, R = 8: 381 -> 240.)
 #include <type_traits>
 
 #include "ha_mlp256.h"
@@ -372,9 +372,10 @@ __global__ __launch_bounds__(256, 2) void back256_kernel(Back256Args a) {
 // of 32 tokens, 16 bytes per token and lane group) or as rows.  The token-contiguous fragments come out through transposing reads: four
 // consecutive channels of a token are 8 contiguous bytes in both.  Lane slot r of an image's chunk holds token r ^ 4 g ^ 8 (chunk % 2), so that the 32 lanes of
 // half a read fall on all banks.
-// Bound: HBM, every image once (1.0 GB over the queries at 480p / 81 frames, 12 heads: 236 us, three launches of wide_contract_kernel took 300;
-// linear keys 118 and 162).  256 x 256 or 256 x 128 outputs per workgroup, so that no operand is read twice.  The tiles are taken in the order
-// that finds the last written ones in the 256 MB memory-side cache: 250 -> 236 and 127 -> 118 us against ascending order.  All fragments of a
+// Bound: HBM, every image once (1.0 GB over the queries at 480p / 81 frames, 12 heads: 197 us, three launches of wide_contract_kernel took 300;
+// linear keys 102 and 162).  256 x 256 or 256 x 128 outputs per workgroup, so that no operand is read twice.  The tiles are taken in the order
+// that finds the last written ones in the 256 MB memory-side cache: 250 -> 236 and 127 -> 118 us against ascending order, and
+// read non-temporally, so that what has been used makes no room at the cost of what has not (ONCE): 197 and 102 us, 5.2 TB/s.  All fragments of a
 // block requested at once, whole rows per request and an uneven offset between the images changed nothing.
 struct Contract256Args {
   const bf16x8 *du, *h, *dpre, *phi;  // images [B*H][n_tb][8][2][64]
@@ -399,7 +400,7 @@ static __host__ __device__ inline int64_t part256_base(const int (&nc)[3], int B
 }
 
 // PRODUCT 0: du x [h | 1], wave = 64 rows x 128 columns; 1: dpre x [x | 1], 2: phi x [g | wp], wave = 32 rows x 128 columns.
-template <int PRODUCT>
+template <int PRODUCT, bool ONCE>
 static __device__ __forceinline__ void contract256(const Contract256Args &a, bf16x8 *ring, float *wcol, int bh, int range) {
   constexpr int NST = 4, ACH = 16, BCH = PRODUCT == 0 ? 16 : 8, STG = (ACH + BCH) * 64;
   constexpr int NRB = PRODUCT == 0 ? 2 : 1, PER = (ACH + BCH) / 8;
@@ -433,7 +434,8 @@ static __device__ __forceinline__ void contract256(const Contract256Args &a, bf1
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
   auto dma = [&](const void *gp, unsigned voff, bf16x8 *to) {
     const unsigned l = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)to);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff), "s"(gp) : "memory");
+    if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(voff), "s"(gp) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff), "s"(gp) : "memory");
   };
   // chunk c of a block: lane slot (g, r) takes the piece of token r ^ 4 g ^ 8 (c % 2)
   const unsigned img_off[2] = {(unsigned)(32 * g + (r ^ (4 * g))) * 16, (unsigned)(32 * g + (r ^ (4 * g) ^ 8)) * 16};
@@ -461,7 +463,8 @@ static __device__ __forceinline__ void contract256(const Contract256Args &a, bf1
       else row = a.x + base + (int64_t)lmap.token(i) * a.sn;
       const __bf16 *piece = row + 8 * ((lane & 15) ^ RowTile<128>::sw(tok));
       const unsigned l = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)(sb + w * 64));
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(l), "v"(piece) : "memory");
+      if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(l), "v"(piece) : "memory");
+      else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(l), "v"(piece) : "memory");
       if constexpr (PRODUCT == 2) {
         if (w == 0) {                                     // the extra column's 32 values (twice)
           const float *src = a.wp + (int64_t)bh * a.N + min(32 * b + r, a.n_tok - 1);
@@ -554,14 +557,15 @@ static __device__ __forceinline__ void contract256(const Contract256Args &a, bf1
     }
 }
 
+template <bool ONCE>
 __global__ __launch_bounds__(512, 2) void contract256_kernel(Contract256Args a) {
   __shared__ bf16x8 ring[4 * 32 * 64];
   __shared__ __align__(16) float wcol[4 * 64];
   const int per = a.nc[0] + a.nc[1] + a.nc[2];
   const int bh = blockIdx.x / per, j = blockIdx.x % per;
-  if (j < a.nc[0]) contract256<0>(a, ring, wcol, bh, j);
-  else if (j < a.nc[0] + a.nc[1]) contract256<1>(a, ring, wcol, bh, j - a.nc[0]);
-  else contract256<2>(a, ring, wcol, bh, j - a.nc[0] - a.nc[1]);
+  if (j < a.nc[0]) contract256<0, ONCE>(a, ring, wcol, bh, j);
+  else if (j < a.nc[0] + a.nc[1]) contract256<1, ONCE>(a, ring, wcol, bh, j - a.nc[0]);
+  else contract256<2, ONCE>(a, ring, wcol, bh, j - a.nc[0] - a.nc[1]);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -797,7 +801,12 @@ hipError_t launch_value_distill_backward256(const Plan &pl, const Grad256Plan &g
     c.H = pl.H; c.BH = BH; c.N = pl.N; c.n_tok = n_tok; c.n_tb = a.n_tb; c.n_tiles = a.n_tiles; c.run = a.run; c.R = a.R; c.G = a.G;
     c.sb = pl.sb; c.sh = pl.sh; c.sn = pl.sn;
     for (int p = 0; p < 3; ++p) c.nc[p] = gp.nc[side][p];
-    contract256_kernel<<<BH * (c.nc[0] + c.nc[1] + c.nc[2]), 512, 0, st>>>(c);
+    // Images of more than a quarter of the memory-side cache are read non-temporally.  12 heads, both forms in turn, the whole step:
+    // 38 MB of them over the queries 208 us (non-temporal 213), 123 MB 348 (342), 1.0 GB 2702 (2665).
+    const int64_t image_bytes = (int64_t)BH * a.n_tb * 32 * 512 * (is_query ? 4 : 3);
+    const dim3 grid(BH * (c.nc[0] + c.nc[1] + c.nc[2]));
+    if (image_bytes > kMemorySideCache / 4) contract256_kernel<true><<<grid, 512, 0, st>>>(c);
+    else contract256_kernel<false><<<grid, 512, 0, st>>>(c);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     Reduce256Args ra;
     ra.part = c.part;

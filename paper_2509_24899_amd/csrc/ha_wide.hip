@@ -122,8 +122,9 @@ static __device__ __forceinline__ void wide_phi_tile(const f32x4 (&raw)[4], int 
 // serves both.
 // Bound: HBM, the fp32 pre-activations.  768 wide, 480p / 81 frames, R = 8, 12 heads (1.06 GB of them): 467 us with phi transposed
 // through LDS two bytes at a time by workgroups of 128 features (8 % matrix cores, 67 % of the wave cycles waiting; 465 with V
-// fetched once), 512 with the statistics waited for where they are requested, 265 us here (4.4 TB/s).
-template <int NW, bool F32>
+// fetched once), 512 with the statistics waited for where they are requested, 265 with them ahead, 240 us with the pre-activations
+// read non-temporally (ONCE; 4.9 TB/s).
+template <int NW, bool F32, bool ONCE>
 __global__ __launch_bounds__(64 * NW, 2) void wide_state_kernel(const f32x4 *__restrict__ u_img, const float *__restrict__ stat,
                                                                 const void *__restrict__ v, float *__restrict__ part, int H,
                                                                 int NL, int R, int G, int CH, int F, int n_tb, int act, int P,
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(64 * NW, 2) void wide_state_kernel(const f32x4 *__r
   auto load_u = [&](int t0, int blk) {
     const f32x4 *src = u_img + (((int64_t)bh * n_tb + min(t0 / 32 + blk, n_tb - 1)) * FB + fb) * 256 + lane;
 #pragma unroll
-    for (int x4 = 0; x4 < 4; ++x4) raw[blk][x4] = src[x4 * 64];
+    for (int x4 = 0; x4 < 4; ++x4) raw[blk][x4] = ONCE ? __builtin_nontemporal_load(&src[x4 * 64]) : src[x4 * 64];
   };
   f32x16 acc[NCB];
 #pragma unroll
@@ -278,11 +279,12 @@ __global__ __launch_bounds__(64 * NW, 2) void wide_state_kernel(const f32x4 *__r
 // with the rounded phi_q, as the numerator uses it.  Output: n as an fp32 C image of width D, i.e. the layout of the query
 // kernel's accumulators; e[bh][token].
 // The 16 fragments of S a 32-channel tile meets are the same for all waves: a slab of an LDS ring, one barrier per tile
-// (every wave reading its own from L2, 4.7 GB of them: 460 us at 480p / 81 frames, 768 wide, 12 heads; now 355).  The
+// (every wave reading its own from L2, 4.7 GB of them: 460 us at 480p / 81 frames, 768 wide, 12 heads; 363 so, and 354 with
+// the pre-activations read non-temporally, ONCE).  The
 // wave's own tile of pre-activations comes with it, two tiles ahead: the bound is HBM, 1.2 GB of them, and 64 KiB per CU
 // are on their way.
 // All loads of the loop are LDS-DMA so that the counts below are the only waits.
-template <int D>
+template <int D, bool ONCE>
 __global__ __launch_bounds__(512, 2) void wide_lin_kernel(const f32x4 *u_img, const float *stat, const bf16x8 *st_hi,
                                                           const bf16x8 *st_lo, const float *z, f32x4 *lin, float *e_out, int F,
                                                           int n_tok, int n_tb, int act, int P) {
@@ -305,12 +307,17 @@ __global__ __launch_bounds__(512, 2) void wide_lin_kernel(const f32x4 *u_img, co
     const unsigned l = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)to);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(from) : "memory");
   };
+  auto dma_u = [&](const void *to, const void *from) {
+    const unsigned l = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)to);
+    if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(lane_off), "s"(from) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(from) : "memory");
+  };
   // slab fb: chunk (rb, s, hi / lo) = fragment (rb, fb, s) of either array; past the last one it is fetched again, so that
   // a request is always six loads
   auto request = [&](int fb, int slot) {
     const int src = min(fb, FB - 1);
 #pragma unroll
-    for (int x4 = 0; x4 < 4; ++x4) dma(&tile[((slot * 8 + w) * 4 + x4) * 64], usrc + (src * 4 + x4) * 64);
+    for (int x4 = 0; x4 < 4; ++x4) dma_u(&tile[((slot * 8 + w) * 4 + x4) * 64], usrc + (src * 4 + x4) * 64);
 #pragma unroll
     for (int i = 0; i < RB * 4 / 8; ++i) {
       const int c = i * 8 + w;
@@ -450,6 +457,14 @@ hipError_t launch_wide_map(const Plan &pl, const WidePlan &wp, const void *x, co
   return launch_wide_mlp(pl, l, st);
 }
 
+// Pre-activations that the memory-side cache cannot hold between the writer and its reader are read non-temporally, so that they do
+// not displace what is still to be read; from a quarter above its size on, because below that the parts still in it are worth more.
+// Forward, cached / non-temporal: 12 heads, 8 blocks, 768 wide, 1.2 GB 4678 / 4660 us; 512 wide, 491 MB 974 / 946; 384 wide, 368 MB
+// 1250 / 1222; 768 wide, 307 MB 899 / 904; 512 wide, 38 MB 153 / 156.
+static bool wide_read_once(const Plan &pl, int n_tb) {
+  return (int64_t)pl.B * pl.H * n_tb * 32 * pl.F * 4 > kMemorySideCache + kMemorySideCache / 4;
+}
+
 // Key side: phi_k over the linear tokens, then [S | z] (partials + the forward's reduction).
 hipError_t launch_wide_key_side(const Plan &pl, const WidePlan &wp, const void *k, const void *v, const ha_feature_map &phi_k,
                                 void *ws, hipStream_t st) {
@@ -458,8 +473,9 @@ hipError_t launch_wide_key_side(const Plan &pl, const WidePlan &wp, const void *
   // eight row blocks per workgroup where the width has them: V is fetched for half as many, and a barrier serves twice the work
   const int n_pairs = pl.n_chunks * pl.B * pl.H, nw = pl.F % 256 == 0 ? 8 : 4;
   const dim3 grid((n_pairs + 7) / 8 * 8 * (pl.F / 32 / nw));
+  const bool once = wide_read_once(pl, wp.n_tb_k);
 #define HA_WIDE_STATE(NW, F32) \
-  wide_state_kernel<NW, F32><<<grid, 64 * NW, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat), v, \
+  (once ? wide_state_kernel<NW, F32, true> : wide_state_kernel<NW, F32, false>)<<<grid, 64 * NW, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat), v, \
                                                        ws_ptr<float>(ws, pl.off_part), pl.H, pl.NL, pl.R, pl.G, pl.CH, pl.F, \
                                                        wp.n_tb_k, pl.act_k, pl.P, pl.sb, pl.sh, pl.sn, pl.n_chunks, n_pairs)
   if (nw == 8) { if (pl.f32) HA_WIDE_STATE(8, true); else HA_WIDE_STATE(8, false); }
@@ -475,7 +491,7 @@ hipError_t launch_wide_query_side(const Plan &pl, const WidePlan &wp, const void
   hipError_t e = launch_wide_map(pl, wp, q, phi_q, true, ws, st, false);
   if (e != hipSuccess) return e;
   dim3 grid((wp.n_tb_q + 7) / 8, pl.B * pl.H);
-  wide_lin_kernel<128><<<grid, 512, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat),
+  (wide_read_once(pl, wp.n_tb_q) ? wide_lin_kernel<128, true> : wide_lin_kernel<128, false>)<<<grid, 512, 0, st>>>(ws_ptr<f32x4>(ws, wp.off_u), ws_ptr<float>(ws, wp.off_stat),
                                              ws_ptr<bf16x8>(ws, pl.off_sthi), ws_ptr<bf16x8>(ws, pl.off_stlo),
                                              ws_ptr<float>(ws, pl.off_z), ws_ptr<f32x4>(ws, wp.off_lin),
                                              ws_ptr<float>(ws, wp.off_e), pl.F, pl.N, wp.n_tb_q, pl.act_q, pl.P);

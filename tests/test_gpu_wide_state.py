@@ -33,3 +33,10 @@ def test_activations_and_degrees(act, feat, P, dtype):
 def test_more_chunks_than_chiplets():
     w = work(3000, 128, 512, 2, H=5, B=2, R=4, seed=3)
     check(w.name, W.make_inputs(w), rows=np.arange(0, 3000, 211))
+
+
+@pytest.mark.parametrize("feat,P,H,dtype", ((768, 6, 64, "bf16"), (640, 2, 80, "f32")))   # eight and four row blocks per workgroup
+def test_pre_activations_beyond_the_memory_side_cache(feat, P, H, dtype):
+    w = work(1000, 128, feat, P, H=H, B=2, R=16, dtype=dtype, seed=feat)                   # 872 linear tokens: both sides
+    assert w.B * w.H * 872 * feat * 4 > 320 << 20
+    check(w.name, W.make_inputs(w), rows=np.arange(0, 1000, 97))
