@@ -204,7 +204,7 @@ def distill_step_mode(args, w, ha, torch, q, k, v, fq, fk):
                    "step": "student forward + loss + gradient of phi_q, phi_k + AdamW update (teacher output cached)"},
         "step_ms_events": ev_full, "backward_with_state_pass_and_loss_ms": ev_bwd,
         "roofline": {"bound": "mfma", "kernel": ("grad_kernel (query pass + key pass) with its small helpers" if w.d_hidden == w.d and w.d_feat == w.d
-                                                    else "the pass-per-step backward of wider maps, all kernels"), "achieved":
+                                                    else "the backward of the wider maps, all kernels"), "achieved":
                      bwd_flops / (ev_bwd * 1e-3) / 1e12, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": bwd_flops / (ev_bwd * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, "kernel_ms": ev_bwd, "traffic": None},
         "loss": float(loss[0].item()),
