@@ -289,7 +289,8 @@ const char *hybrid_attn_status_string(ha_status s);
 /* hipError_t (as int) behind the most recent HA_ERR_DEVICE on the calling thread, 0 if none. */
 int hybrid_attn_last_device_error(void);
 
-/* Version of this ABI (bumped on any incompatible change). */
+/* Version of this ABI (bumped on any incompatible change): the library's, and the one this header describes. */
+#define HA_ABI_VERSION 7
 int hybrid_attn_abi_version(void);
 
 #ifdef __cplusplus

@@ -36,8 +36,10 @@ def binding_command() -> list:
     import sysconfig
 
     import torch
+
+    from .hybrid_attn import binding_tag
     root = os.path.dirname(torch.__file__)
-    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DHA_BINDING_TAG="{binding_tag()}"',
             f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include", f"-I{sysconfig.get_paths()['include']}",
             os.path.join(CSRC, "ha_binding.cpp"), "-o", BINDING_PATH, f"-L{root}/lib", "-lc10", "-ltorch_cpu", "-ltorch_python"]
 

@@ -756,6 +756,6 @@ const char *hybrid_attn_status_string(ha_status s) {
 
 int hybrid_attn_last_device_error(void) { return ha::g_last_device_error; }
 
-int hybrid_attn_abi_version(void) { return 7; }
+int hybrid_attn_abi_version(void) { return HA_ABI_VERSION; }
 
 }  // extern "C"

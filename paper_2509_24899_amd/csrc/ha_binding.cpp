@@ -1,7 +1,7 @@
 // Marshalling of the two calls whose host cost shows (a small forward, the update of one parameter tensor) from torch tensors to the C ABI.
 // A call that is anything but plain and right (a rate that is a tuple, a tensor of another shape, type, device or layout, a buffer
 // left to the callee) returns None and the Python code takes it, with its checks and its messages: this file decides
-// nothing, it only recognises what needs no decision.
+// nothing, it only recognises what needs no decision.  HA_BINDING_TAG: the torch and the Python it is compiled for (build.py).
 //
 // Host time per call, in Python / here: forward of d = 64, H = 2, N = 1024 19 / 8.8 us (three launches), update of one tensor 5.2 / 3.3.
 #include <Python.h>
@@ -247,5 +247,19 @@ PyMODINIT_FUNC PyInit_hybridattn_binding() {
   const char *text[] = {"w1", "b1", "w2", "b2", "w_mid", "b_mid", "poly_degree", "out_act"};
   for (int i = 0; i < 8; ++i)
     if (!(*names[i] = PyUnicode_InternFromString(text[i]))) return nullptr;
-  return PyModule_Create(&module);
+  PyObject *m = PyModule_Create(&module);
+  if (!m) return nullptr;
+  // What this file was compiled for: the Python code uses the module only where both are what it finds.
+  PyObject *abi = Py_BuildValue("(innn)", HA_ABI_VERSION, static_cast<Py_ssize_t>(sizeof(ha_problem)), static_cast<Py_ssize_t>(sizeof(ha_feature_map)),
+                                static_cast<Py_ssize_t>(sizeof(ha_optimizer)));
+  if (!abi || PyModule_AddObject(m, "abi", abi) < 0) {
+    Py_XDECREF(abi);
+    Py_DECREF(m);
+    return nullptr;
+  }
+  if (PyModule_AddStringConstant(m, "tag", HA_BINDING_TAG) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
 }

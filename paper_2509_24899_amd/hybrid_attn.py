@@ -14,6 +14,8 @@ import importlib.machinery
 import importlib.util
 import inspect
 import os
+import sys
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -132,20 +134,39 @@ BINDING_PATH = os.path.join(_HERE, "lib", "hybridattn_binding.so")
 _BINDING = None
 
 
-def _binding():
-    """The compiled marshalling of plain calls, loaded once; False where it has not been built (the code here takes every call then)."""
-    global _BINDING
-    if _BINDING is None:
-        raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw_stream is None or not os.path.exists(BINDING_PATH) or not os.path.exists(LIB_PATH):
-            return False
-        loader = importlib.machinery.ExtensionFileLoader("hybridattn_binding", BINDING_PATH)
+def binding_tag() -> str:
+    """What the compiled marshalling is tied to besides the C ABI: it reads tensors by the layout of the torch it was compiled against."""
+    return f"torch {torch.__version__} {torch.version.git_version} cpython {sys.version_info.major}.{sys.version_info.minor}"
+
+
+def _load_binding():
+    """The compiled marshalling of plain calls, or False where there is none that fits this torch, this Python and the loaded library."""
+    raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw_stream is None or not os.path.exists(BINDING_PATH):
+        return False
+    lib = _lib()
+    abi = (lib.hybrid_attn_abi_version(), *(ctypes.sizeof(s) for s in (ha_problem, ha_feature_map, ha_optimizer)))
+    loader = importlib.machinery.ExtensionFileLoader("hybridattn_binding", BINDING_PATH)
+    try:
         module = importlib.util.module_from_spec(importlib.util.spec_from_loader("hybridattn_binding", loader))
         loader.exec_module(module)
-        lib = _lib()
-        address = [ctypes.cast(f, ctypes.c_void_p).value for f in (lib.hybrid_attn_forward, lib.hybrid_attn_param_update)]
-        module.bind(*address, FeatureMap, raw_stream)
-        _BINDING = module
+        built_for = (module.tag, module.abi)
+    except (ImportError, AttributeError) as e:
+        built_for = e
+    if built_for != (binding_tag(), abi):
+        warnings.warn(f"{BINDING_PATH} does not fit and is not used, build it again: {built_for}, wanted {(binding_tag(), abi)}")
+        return False
+    address = [ctypes.cast(f, ctypes.c_void_p).value for f in (lib.hybrid_attn_forward, lib.hybrid_attn_param_update)]
+    module.bind(*address, FeatureMap, raw_stream)
+    return module
+
+
+def _binding():
+    """_load_binding's result, looked for once (the code here takes every call where it is False).  Without the library, which the call will
+    report, nothing is decided."""
+    global _BINDING
+    if _BINDING is None and os.path.exists(LIB_PATH):
+        _BINDING = _load_binding()
     return _BINDING
 
 
@@ -383,7 +404,7 @@ def hybrid_attn_forward(q, k, v, phi_q: Optional[FeatureMap], phi_k: Optional[Fe
     """Enqueue one forward of Eq. "hybrid" (Sec. 3.2) on the current (or given) stream and return
     `out` ([B, H, N, d] with q's strides and dtype).  Does not synchronise."""
     if out is not None and workspace is not None:
-        native = _BINDING or _binding()
+        native = _binding() if _BINDING is None else _BINDING
         if native:
             st = native.forward(q, k, v, phi_q, phi_k, hybrid_rate, block_size, softmax_scale, out, workspace, stream)
             if st == HA_OK:
@@ -545,7 +566,7 @@ def hybrid_attn_param_update(master, grad, lr: float, kind: int = HA_OPT_SGD, m=
     moments m, v (AdamW) and, if given, param_io (bf16 or fp32 tensor of the same shape that the forward reads)."""
     # (eight of these calls make one update of a layer: plain ones are marshalled by compiled code, 3.3 us a call;
     # with the checks below, 5.8)
-    native = _BINDING or _binding()
+    native = _binding() if _BINDING is None else _BINDING
     if native:
         st = native.param_update(master, grad, lr, kind, m, v, step, grad_scale, beta1, beta2, eps, weight_decay, param_io, stream)
         if st == HA_OK:

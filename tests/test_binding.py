@@ -26,6 +26,35 @@ def test_is_built_and_leaves_host_tensors_alone():
         ha.hybrid_attn_forward(t, t, t, None, None, 1, out=t, workspace=ws)
 
 
+@pytest.mark.parametrize("fault", ("not a module", "another torch", "another library", "absent"))
+def test_a_module_that_does_not_fit_is_not_used(fault, monkeypatch, tmp_path):
+    """A file left over from another torch or another version of the C ABI would read tensors and structs by the wrong layout: the Python
+    code takes every call, and the file is looked for once."""
+    monkeypatch.setattr(ha, "_BINDING", None)
+    if fault in ("not a module", "absent"):
+        path = tmp_path / "hybridattn_binding.so"
+        if fault == "not a module":
+            path.write_bytes(b"left over")
+        monkeypatch.setattr(ha, "BINDING_PATH", str(path))
+    elif fault == "another torch":
+        monkeypatch.setattr(torch.version, "git_version", "0" * 40)
+    else:
+        class longer(ha.ctypes.Structure):
+            _fields_ = ha.ha_problem._fields_ + [("more", ha.ctypes.c_int64)]
+        monkeypatch.setattr(ha, "ha_problem", longer)
+    if fault == "absent":
+        assert ha._binding() is False
+    else:
+        with pytest.warns(UserWarning, match="build it again"):
+            assert ha._binding() is False
+    monkeypatch.setattr(ha, "_load_binding", lambda: pytest.fail("looked for a second time"))
+    t = torch.zeros(1, 1, 8, 64)
+    with pytest.raises(RuntimeError, match="GPU only"):
+        ha.hybrid_attn_forward(t, t, t, None, None, 1, out=t, workspace=t)
+    with pytest.raises(RuntimeError, match="GPU only"):
+        ha.hybrid_attn_param_update(t, t, 1e-3)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("R,maps,dtype,layout", ((1, "none", "bf16", "bhnd"), (3, "square", "f32", "bnhd"), (4, "wide", "bf16", "bnhd"),
                                                  (2, "three", "bf16", "bhnd"), (2, "nobias", "f32", "bhnd")))
