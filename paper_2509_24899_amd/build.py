@@ -46,12 +46,11 @@ def binding_command() -> list:
 
 def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PATH, tag: str = "") -> str:
     """Compile every source and link the shared library (libhybridattn.so by default); returns its path.  With the default path the
-    compiled marshalling is built beside it."""
+    compiled marshalling is built beside it, where that can be done: the library needs hipcc alone, and calls work without the module."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(LIB_DIR, exist_ok=True)
     objs, procs = [], []
-    if out_path == LIB_PATH:
-        procs.append(("ha_binding.cpp", subprocess.Popen(binding_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    binding = _start_binding() if out_path == LIB_PATH else None
     for src in SOURCES:
         obj = os.path.join(LIB_DIR, src.replace(".hip", tag + ".o"))
         cmd = [hipcc, *HIPCC_FLAGS, *FILE_FLAGS.get(src, []), *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
@@ -63,12 +62,31 @@ def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PAT
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l and l.strip())
         if p.returncode != 0:
-            raise RuntimeError(f"compiling {src} failed:\n{out}")
+            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
         if verbose and out:
             print(out, flush=True)
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", out_path]
     subprocess.run(link, check=True)
+    if binding is not None:
+        out, _ = binding.communicate()
+        if binding.returncode != 0:
+            _without_binding(out)
     return out_path
+
+
+def _start_binding():
+    """The compiler at work on the compiled marshalling, or None where it cannot be started (no torch, no g++)."""
+    try:
+        return subprocess.Popen(binding_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    except (ImportError, OSError) as e:
+        _without_binding(e)
+        return None
+
+
+def _without_binding(why) -> None:
+    if os.path.exists(BINDING_PATH):
+        os.remove(BINDING_PATH)                           # of another build
+    print(f"{BINDING_PATH} was not built, the Python code marshals every call: {why}", file=sys.stderr, flush=True)
 
 
 # Host-side sanitizer build (AddressSanitizer + UndefinedBehaviorSanitizer on the CPU code only; the device code is

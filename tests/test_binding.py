@@ -5,6 +5,7 @@ import dataclasses
 import pytest
 import torch
 
+from paper_2509_24899_amd import build
 from paper_2509_24899_amd import hybrid_attn as ha
 from paper_2509_24899_amd import workloads as W
 
@@ -12,6 +13,19 @@ from paper_2509_24899_amd import workloads as W
 def python_only(monkeypatch):
     monkeypatch.setattr(ha, "_BINDING", None)
     monkeypatch.setattr(ha, "_binding", lambda: False)
+
+
+@pytest.mark.parametrize("fault", ("no compiler", "does not compile"))
+def test_the_library_is_built_without_it(fault, monkeypatch, tmp_path, capsys):
+    """A machine with hipcc alone builds the library; a module of an earlier build does not stay beside it."""
+    stale = tmp_path / "hybridattn_binding.so"
+    stale.write_bytes(b"of an earlier build")
+    monkeypatch.setenv("HIPCC", "true")
+    monkeypatch.setattr(build, "LIB_DIR", str(tmp_path))
+    monkeypatch.setattr(build, "BINDING_PATH", str(stale))
+    monkeypatch.setattr(build, "binding_command", lambda: [str(tmp_path / "g++")] if fault == "no compiler" else ["false"])
+    assert build.build_library() == build.LIB_PATH
+    assert not stale.exists() and "was not built" in capsys.readouterr().err
 
 
 def test_is_built_and_leaves_host_tensors_alone():
