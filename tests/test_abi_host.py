@@ -47,6 +47,18 @@ def test_struct_layout_matches_header():
     assert ha.ha_feature_map.d_hidden.offset == 32 and ha.ha_feature_map.w_mid.offset == 48 and ctypes.sizeof(ha.ha_feature_map) == 72
 
 
+def test_gradient_of_the_256_wide_maps_takes_the_workspaces_of_the_layered_passes(lib):
+    """A caller may hold a workspace of the size that the query gave out while these maps went layer by layer: whatever passes they take, they
+    ask for no more.  (B, H, N, R, fp32) -> bytes, as it was then."""
+    then = {(1, 1, 2, 0, 1): 2152448, (1, 1, 2, 2, 0): 2185216, (1, 1, 64, 2, 0): 2349824, (1, 1, 129, 4, 1): 3141888, (1, 1, 257, 2, 0): 4296448,
+            (1, 1, 1000, 4, 1): 13418496, (1, 1, 5003, 2, 0): 62673152, (2, 8, 2000, 8, 0): 314387456, (1, 12, 1560, 4, 0): 193647360,
+            (2, 90, 257, 2, 1): 590379264, (1, 12, 32760, 4, 0): 2320766208, (1, 65535, 2, 2, 0): 143159372544}
+    fm = _map(256, 256)
+    for (B, H, N, R, f32), size in then.items():
+        p = _problem(B, H, N, dtype=ha.HA_F32 if f32 else ha.HA_BF16, bs=64, R=R)
+        assert 0 < ha.hybrid_attn_value_distill_grad_workspace_bytes(p, fm, fm) <= size, (B, H, N, R, f32)
+
+
 def test_valid_problems(lib):
     fm = _map()
     assert ha.hybrid_attn_validate(_problem(), fm, fm) == ha.HA_OK
