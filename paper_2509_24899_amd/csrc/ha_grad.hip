@@ -70,18 +70,18 @@ __global__ __launch_bounds__(256) void natural_frags_kernel(const float *__restr
 }
 
 // grad_operands_kernel: the five small jobs ahead of the gradient passes of the square maps (d -> d -> d) in one
-// launch, grid (ceil(D*D / 256), 4 H + B*H): rows [0, H) and [H, 2 H) the forward fragments of phi_q's and phi_k's
+// launch, 4 H + B*H rows of ceil(D*D / 256) blocks (row0 and on, of more rows than a grid takes): rows [0, H) and [H, 2 H) the forward fragments of phi_q's and phi_k's
 // weights, [2 H, 3 H) and [3 H, 4 H) their W2^T fragments, the rest S as hi + lo natural-order fragments.
 struct GradOperands {
   const void *w1q, *w2q, *w1k, *w2k;
   __bf16 *w1qf, *w2qf, *w1kf, *w2kf, *w2tq, *w2tk;
   const float *S;
   __bf16 *s_hi, *s_lo;
-  int D, H;
+  int D, H, row0;
 };
 template <bool F32>
 __global__ __launch_bounds__(256) void grad_operands_kernel(GradOperands o) {
-  const int e = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y, D = o.D, H = o.H;
+  const int e = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y + o.row0, D = o.D, H = o.H;
   if (y < H) weight_prep_body<F32>(o.w1q, o.w2q, o.w1qf, o.w2qf, D, D, D, y, e);
   else if (y < 2 * H) weight_prep_body<F32>(o.w1k, o.w2k, o.w1kf, o.w2kf, D, D, D, y - H, e);
   else if (y < 3 * H) grad_weight_prep_body<F32>(o.w2q, o.w2tq, D, D, y - 2 * H, e);
@@ -1080,10 +1080,13 @@ hipError_t launch_value_distill_backward(const Plan &pl, const GradPlan &gp, con
     o.w2tq = ws_ptr<__bf16>(ws, gp.off_w2tq); o.w2tk = ws_ptr<__bf16>(ws, gp.off_w2tk);
     o.S = ws_ptr<float>(ws, pl.off_S); o.s_hi = ws_ptr<__bf16>(ws, gp.off_shi); o.s_lo = ws_ptr<__bf16>(ws, gp.off_slo);
     o.D = D; o.H = pl.H;
-    dim3 grid((D * D + 255) / 256, 4 * pl.H + BH);
-    if (pl.f32) grad_operands_kernel<true><<<grid, 256, 0, st>>>(o);
-    else grad_operands_kernel<false><<<grid, 256, 0, st>>>(o);
-    HA_CHECK();
+    const int rows = 4 * pl.H + BH;
+    for (o.row0 = 0; o.row0 < rows; o.row0 += kMaxGridRows) {
+      const dim3 grid((D * D + 255) / 256, rows - o.row0 < kMaxGridRows ? rows - o.row0 : kMaxGridRows);
+      if (pl.f32) grad_operands_kernel<true><<<grid, 256, 0, st>>>(o);
+      else grad_operands_kernel<false><<<grid, 256, 0, st>>>(o);
+      HA_CHECK();
+    }
   }
   // per-row factors
   if ((e = launch_vd_rows(pl, y_teacher, y_student, row_den, ws_ptr<void>(ws, gp.off_gsign), ws_ptr<float>(ws, gp.off_rs),

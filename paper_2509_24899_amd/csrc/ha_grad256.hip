@@ -626,7 +626,7 @@ __global__ __launch_bounds__(256) void reduce256_kernel(Reduce256Args a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// prep256_kernel: grid (32, 2 H + B*H), a thread per 16-byte piece.  Rows 0 .. 2 H - 1: one head's map (queries first) as fragments of W1 (4096 pieces),
+// prep256_kernel: 2 H + B*H rows of 32 blocks, in one dimension (they may be more than a second one takes), a thread per 16-byte piece.  Rows 0 .. 2 H - 1: one head's map (queries first) as fragments of W1 (4096 pieces),
 // W2 (8192) and W2^T; the rest: S as hi + lo fragments in natural order.
 struct Prep256Args {
   const void *w1[2], *w2[2];
@@ -637,7 +637,7 @@ struct Prep256Args {
 };
 template <bool F32>
 __global__ __launch_bounds__(256) void prep256_kernel(Prep256Args a) {
-  const int y = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
+  const int y = blockIdx.x >> 5, p = (blockIdx.x & 31) * 256 + threadIdx.x;
   if (y < 2 * a.H) {
     const int side = y >= a.H, h = side ? y - a.H : y;
     if (p < 4096) a.w1f[side][(int64_t)h * 4096 + p] = weight_piece<F32, false>(a.w1[side], (int64_t)h * 256 * 128, 128, p);
@@ -748,8 +748,8 @@ hipError_t launch_value_distill_backward256(const Plan &pl, const Grad256Plan &g
   pa.s_hi = ws_ptr<bf16x8>(ws, gp.off_mhi[0]);
   pa.s_lo = ws_ptr<bf16x8>(ws, gp.off_mlo[0]);
   pa.H = pl.H;
-  if (pl.f32) prep256_kernel<true><<<dim3(32, 2 * pl.H + BH), 256, 0, st>>>(pa);
-  else prep256_kernel<false><<<dim3(32, 2 * pl.H + BH), 256, 0, st>>>(pa);
+  if (pl.f32) prep256_kernel<true><<<32 * (2 * pl.H + BH), 256, 0, st>>>(pa);
+  else prep256_kernel<false><<<32 * (2 * pl.H + BH), 256, 0, st>>>(pa);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   for (int side = 0; side < 2; ++side) {
     const bool is_query = side == 0;

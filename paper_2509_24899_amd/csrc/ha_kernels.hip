@@ -509,6 +509,11 @@ hipError_t launch_weight_prep(const Plan &pl, const ha_feature_map &fm, bool is_
 }
 
 hipError_t launch_compact(const Plan &pl, const void *k, const void *v, void *ws, hipStream_t st, const ha_feature_map *prep_k) {
+  if (prep_k && pl.B * pl.H + pl.H > kMaxGridRows) {
+    const hipError_t e = launch_weight_prep(pl, *prep_k, false, ws, st);
+    if (e != hipSuccess) return e;
+    prep_k = nullptr;
+  }
   dim3 grid(pl.n_kblocks, pl.B * pl.H);
   WeightPrep wp = {};
   if (prep_k) {
@@ -563,6 +568,10 @@ hipError_t launch_weighted_state(const Plan &pl, const void *q, const void *gsig
 }
 
 hipError_t launch_state_reduce_with_prep(const Plan &pl, const ha_feature_map &phi_q, void *ws, hipStream_t st) {
+  if (pl.B * pl.H + pl.H > kMaxGridRows) {
+    const hipError_t e = launch_weight_prep(pl, phi_q, true, ws, st);
+    return e != hipSuccess ? e : launch_state_reduce(pl, ws, st);
+  }
   const int n_prep = weight_prep_blocks(pl.D, pl.HD, pl.F);
   const int n_red = pl.n_state_tiles * 1024 / 256;
   dim3 grid(n_red > n_prep ? n_red : n_prep, pl.B * pl.H + pl.H);

@@ -166,6 +166,7 @@ size_t l1_partial_bytes(const Plan &pl);
 hipError_t launch_l1_distance(const Plan &pl, const void *ya, const void *yb, double *partial, double *loss,
                               hipStream_t st);
 constexpr int64_t kMemorySideCache = 256 << 20;   // bytes, in front of HBM
+constexpr int kMaxGridRows = 65535;               // blocks along a grid's second and third dimension: B H may be as many, B H + H more
 constexpr int kL1Parts = 64;   // partial sums of the loss per (batch, head)
 hipError_t launch_l1_final(const Plan &pl, const double *partial, double *loss, hipStream_t st);
 // ha_grad.hip
