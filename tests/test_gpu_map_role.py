@@ -1,6 +1,6 @@
 """Query kernel in two roles (small problems: phi_q beside the key loop) at the lengths of its key loop where the roles' barriers could
 differ: no key block at all, one, odd and even, fewer and more than the map has pieces, the first with a separate loop of whole
-blocks (33), the longest and one more (256 / 257, which takes the other kernel); absent biases.
+blocks (33), both sides of the length from which fp32 calls take the other kernel (160 / 161), and longer ones; absent biases.
 
 Tolerance: the bars of test_gpu_parity.py."""
 import dataclasses
@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,H,N,R", ((64, 2, 200, 0), (128, 6, 40, 20), (64, 2, 66, 2), (128, 6, 385, 2), (128, 6, 960, 2), (64, 2, 1025, 4),
-                                     (128, 6, 2050, 2), (64, 1, 2110, 2), (64, 1, 16384, 2), (64, 1, 16386, 2)))
+                                     (128, 6, 2050, 2), (64, 1, 2110, 2), (64, 1, 10240, 2), (64, 1, 10242, 2), (64, 1, 16384, 2), (64, 1, 16386, 2)))
 @pytest.mark.parametrize("dtype", ("bf16", "f32"))
 def test_lengths_of_the_key_loop(d, H, N, R, dtype):
     w = W.Workload(f"roles_d{d}_H{H}_N{N}_R{R}_{dtype}", 1, H, N, d, dtype, 128, R, d, d, poly_degree=2, seed=N + R)
