@@ -137,7 +137,8 @@ size_t hybrid_attn_workspace_bytes(const ha_problem *p, const ha_feature_map *ph
  * share a workspace must be ordered on one stream.  Returns HA_OK once everything is enqueued.
  * A call's result is the same bit for bit every time, whatever the size of the workspace.  The bits of one (batch, head)
  * may depend on how many stand beside it, to rounding: B H decides how the linear tokens' sums are cut into chunks and,
- * for five (batch, head) pairs or fewer, which kernel forms the linear part; and below 128 tiles of 256 queries
+ * for five (batch, head) pairs or fewer, which kernel forms the linear part; up to 256 tiles of 128 queries
+ * (B H ceil(N / 128)) phi_q(q) S is summed in another order, apart from the softmax terms; and below 128 tiles of 256 queries
  * (B H ceil(N / 256)) into how many ranges the softmax keys are split, as far as the partial sums leave room in
  * HA_STATIC_SCRATCH_MIB. */
 ha_status hybrid_attn_forward(const ha_problem *p, const void *q, const void *k, const void *v,

@@ -1,12 +1,10 @@
-// The query kernel with one wave per SIMD, one workgroup of four waves per CU, for problems whose 128-query tiles do not outnumber the
-// CUs (launch_query's rule).  gfx950 only.
+// The query kernel where 128-query tiles do not outnumber the CUs (launch_query's rule): one workgroup per CU, its first four waves
+// with a SIMD each for the key loop.  gfx950 only.
 //
-// Bound: latency of one wave's chain.  Nothing else hides it, so the epilogue is the pipeline of the state pass (mlp128_pipelined, whose
-// 270 live registers need a wave's full 512), fragments are requested ahead of their use, and the file is compiled with the matrix
+// Bound: latency of one wave's chain.  Nothing else hides it, so fragments are requested ahead of their use and the file is compiled with the matrix
 // instructions in vector-register form (otherwise the accumulators sit in the accumulator file and every rescale, exponential and
 // output passes through copies: 1388 of them, 400 in the loop).  H = 12, N = 1560, R = 4 (156 workgroups, 13 key blocks), whole
-// call: 43.1 us with 84 workgroups of eight waves, 39.2 with four waves and the operands in LDS, 37.4 with the pipelined epilogue, 36.2 with
-// accumulators in vector registers.
+// call: 43.1 us with 84 workgroups of eight waves; with four waves of a SIMD each, the map behind the loop and its operands in LDS, 36.2.
 //   Where the call has a map, a second set of four waves evaluates phi_q and its product with the state (MapRole, ha_query_kernel.h) while the first
 // walk the keys: the epilogue is an exchange through LDS.  The same case: kernel 19.7 -> 16.5 us, whole call 36.2 -> 33.5.  Stamps (cycles): first
 // request at 2700, first blocks there at 6000, 13 steps of 1530, the exchange and the store 3300; the map's pieces, of about a step each, fill all of
@@ -25,23 +23,21 @@ namespace ha {
 constexpr int kMaxKeysBesideMapF32 = 160 * 32;
 
 hipError_t launch_query_alone(const Plan &pl, const QueryArgs &a, dim3 grid, hipStream_t st) {
-  if (a.lin) {
-    if (pl.f32) query_kernel_ring<128, 128, 128, 4, 8, 2, true, true><<<grid, 256, 0, st>>>(a);
-    else query_kernel_ring<128, 128, 128, 4, 8, 2, false, true><<<grid, 256, 0, st>>>(a);
-  } else if (a.has_linear && (!pl.f32 || pl.D == 128 || a.NS <= kMaxKeysBesideMapF32)) {
+  if (a.lin || !a.has_linear) {
     if (pl.D == 64) {
-      if (pl.f32) query_kernel_ring<64, 64, 64, 4, 8, 1, true, false, 0, true><<<grid, 512, 0, st>>>(a);
-      else query_kernel_ring<64, 64, 64, 4, 8, 1, false, false, 0, true><<<grid, 512, 0, st>>>(a);
+      if (pl.f32) query_kernel_ring<64, 64, 64, 4, 8, 2, true, true><<<grid, 256, 0, st>>>(a);
+      else query_kernel_ring<64, 64, 64, 4, 8, 2, false, true><<<grid, 256, 0, st>>>(a);
     } else {
-      if (pl.f32) query_kernel_ring<128, 128, 128, 4, 4, 1, true, false, 0, true><<<grid, 512, 0, st>>>(a);
-      else query_kernel_ring<128, 128, 128, 4, 4, 1, false, false, 0, true><<<grid, 512, 0, st>>>(a);
+      if (pl.f32) query_kernel_ring<128, 128, 128, 4, 8, 2, true, true><<<grid, 256, 0, st>>>(a);
+      else query_kernel_ring<128, 128, 128, 4, 8, 2, false, true><<<grid, 256, 0, st>>>(a);
     }
   } else if (pl.D == 64) {
-    if (pl.f32) query_kernel_ring<64, 64, 64, 4, 8, 2, true><<<grid, 256, 0, st>>>(a);
-    else query_kernel_ring<64, 64, 64, 4, 8, 2, false><<<grid, 256, 0, st>>>(a);
+    if (!pl.f32) query_kernel_ring<64, 64, 64, 4, 8, 1, false, false, 0, true><<<grid, 512, 0, st>>>(a);
+    else if (a.NS <= kMaxKeysBesideMapF32) query_kernel_ring<64, 64, 64, 4, 8, 1, true, false, 0, true><<<grid, 512, 0, st>>>(a);
+    else query_kernel_ring<64, 64, 64, 4, 8, 2, true><<<grid, 256, 0, st>>>(a);
   } else {
-    if (pl.f32) query_kernel_ring<128, 128, 128, 4, 8, 2, true><<<grid, 256, 0, st>>>(a);
-    else query_kernel_ring<128, 128, 128, 4, 8, 2, false><<<grid, 256, 0, st>>>(a);
+    if (pl.f32) query_kernel_ring<128, 128, 128, 4, 4, 1, true, false, 0, true><<<grid, 512, 0, st>>>(a);
+    else query_kernel_ring<128, 128, 128, 4, 4, 1, false, false, 0, true><<<grid, 512, 0, st>>>(a);
   }
   return hipGetLastError();
 }

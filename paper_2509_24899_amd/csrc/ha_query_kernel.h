@@ -172,8 +172,7 @@ static __device__ __forceinline__ void store_tile(const QueryArgs &a, int64_t ba
 
 // The whole epilogue with every operand array in one place for its whole duration.
 // ELDS: w2f / sth / stl sit in the ring and were requested when the loop ended (they land while layer 1 runs).
-// ALONE: one wave per SIMD, nothing else hides a latency: the 128-wide map runs as the pipeline of the state pass (vecs: b1, b2 and z in
-// LDS), fragments are requested ahead.
+// ALONE: one wave per SIMD, nothing else hides a latency: fragments are requested ahead (vecs: b1, b2 and z in LDS).
 template <int D, int HD, int F, bool F32, bool ELDS, bool ALONE, typename WP>
 static __device__ __forceinline__ void query_epilogue(const QueryArgs &a, int bh, int h, int64_t base, int lane,
                                                       const bf16x8 (&qf)[D / 16], f32x16 (&o)[D / 32], float lsum,
@@ -185,32 +184,19 @@ static __device__ __forceinline__ void query_epilogue(const QueryArgs &a, int bh
     const float *b1 = a.b1 ? a.b1 + (int64_t)h * HD : nullptr;
     const float *b2 = a.b2 ? a.b2 + (int64_t)h * F : nullptr;
     bf16x8 gb[FB][2];
-    if constexpr (ALONE && D == 128) {
-      u32x4 h_hi[4][2], h_lo[4][2];
-      f32x16 u[4];
-      const auto landed = [&]() {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-      };
-      if (a.act == 0) mlp128_pipelined<true>(qf, w1f, w2f, vecs, vecs + HD, lane, g, a.act, h_hi, h_lo, u, landed);
-      else mlp128_pipelined<false>(qf, w1f, w2f, vecs, vecs + HD, lane, g, a.act, h_hi, h_lo, u, landed);
-      feature_powers<FB>(u, a.P);
-      round_tiles<FB>(u, gb);
+    bf16x8 h_hi[HD / 32][2], h_lo[HD / 32][2];
+    feature_mlp_layer1<D, HD, ALONE>(qf, w1f, b1, lane, g, h_hi, h_lo);
+    if constexpr (ELDS) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    }
+    if constexpr (F > 128) {
+      feature_layer2_phi<HD, F, false>(h_hi, h_lo, w2f, b2, lane, g, a.act, a.P, F / a.P, gb);
     } else {
-      bf16x8 h_hi[HD / 32][2], h_lo[HD / 32][2];
-      feature_mlp_layer1<D, HD, ALONE>(qf, w1f, b1, lane, g, h_hi, h_lo);
-      if constexpr (ELDS) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-      }
-      if constexpr (F > 128) {
-        feature_layer2_phi<HD, F, false>(h_hi, h_lo, w2f, b2, lane, g, a.act, a.P, F / a.P, gb);
-      } else {
-        f32x16 u[FB];
-        feature_mlp_layer2<HD, F, ALONE>(h_hi, h_lo, w2f, b2, lane, g, u);
-        feature_activation<FB>(u, g, a.act, a.P, F / a.P);
-        round_tiles<FB>(u, gb);
-      }
+      f32x16 u[FB];
+      feature_mlp_layer2<HD, F, ALONE>(h_hi, h_lo, w2f, b2, lane, g, u);
+      feature_activation<FB>(u, g, a.act, a.P, F / a.P);
+      round_tiles<FB>(u, gb);
     }
     den += xhalf_sum(dot_z<FB>(gb, ALONE ? vecs + HD + F : a.z + (int64_t)bh * F, g));
     contract_state<D, F, ALONE>(gb, sth, stl, lane, o);
@@ -363,12 +349,12 @@ struct MapRole {
 // waiting for this wave's outstanding loads) closes every G-th step.  NB >= 2 G + 2 makes this safe:
 // the slot being refilled was last read before the latest barrier every wave has passed, and a block
 // is first read (as K(j+2)) at least one barrier after it was requested.
-// LIN: the linear part arrives precomputed (maps too wide for the epilogue below); a variant of its own so that
-// the usual kernel carries none of it.
+// LIN: the linear part arrives precomputed (maps too wide for the epilogue below) or there is none (a.lin null); a variant of its
+// own so that the usual kernel carries none of it.
 // MODE 1: the chunk-causal variant, 2: the local-window variant; likewise variants of their own.  MODE 3: the keys are split
 // into ranges, a workgroup walks one of them and leaves partial sums for the pass that merges them.
 // ROLES: the workgroup has as many waves again, which evaluate phi_q and its product with the state for the same queries while the first
-// NW walk the keys (map_role).
+// NW walk the keys (MapRole).
 // block: the workgroup's number in the launch of this problem.
 template <int D, int HD, int F, int NW, int NB, int G, bool F32, bool LIN, int MODE, bool ROLES>
 static __device__ __forceinline__ void query_ring_body(QueryArgs a, unsigned block) {
