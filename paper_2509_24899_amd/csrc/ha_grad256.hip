@@ -42,7 +42,9 @@ struct Back256Args {
 // units per step (16 KiB).  The softmax's Jacobian needs the sum of t dt over all channels before the first du: t (128 registers) and dphi
 // (128) do not fit a wave at two waves per SIMD, so M meets the rows twice, once for the sum.
 // Bound: matrix and vector instructions of a SIMD together, 704 products of 32 cycles per wave and tile (42 % of the cycles at 2.0 GHz) and 2800
-// vector instructions (30 %).  With its image stores left out it takes 272 us of 310; eight waves of one workgroup (256 tokens, ring of four
+// vector instructions (30 %).  Among these, and not counted as work: some 220 scalar registers that are spilled to lanes of vector registers (addresses
+// of slabs and images; 292 v_readlane and 220 v_writelane in the body of the measured instance, 134 null checks of the LDS pointers that the
+// requests cast), in the fp32 query instances two vector registers in scratch as well.  With its image stores left out it takes 272 us of 310; eight waves of one workgroup (256 tokens, ring of four
 // slabs) took 304 and four waves with a SIMD each 379.
 // Measured at 480p / 81 frames, 12 heads: queries 310 us, linear keys (R = 4) 240; as the three passes it replaces (the layers run again,
 // dphi, W2^T du), which passed pre-activations, du and h through HBM, 555 and 417.
