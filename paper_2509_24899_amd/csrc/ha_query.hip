@@ -217,7 +217,7 @@ hipError_t launch_query(const Plan &pl, const void *q, const ha_feature_map *phi
 // 256; beside the loop 5 (4) for the teacher, 14 (7) for the student, whose epilogue evaluates the map.  One after the other: whole
 // rounds.  In one launch: every CU takes the next workgroup when it is free.  The estimate has to be 4 % better, and the keys of the
 // heads that an XCD works on must not outgrow its 4 MiB of L2 by the student's share alone (H = 12, N = 3500: 155.7 / 163.1 at R = 3).
-// Whole losses, one after the other / in one launch, us: H = 12, N = 2900, R = 8 122 / 107; H = 12, N = 9361, R = 8 626 / 603; H = 8, N = 5000, R = 3
+// Whole losses, one after the other / in one launch, us: H = 12, N = 2900, R = 8 122 / 107; H = 12, N = 9361, R = 8 610 / 597; H = 8, N = 5000, R = 3
 // 189 / 164; H = 5, N = 7000, R = 5 214 / 188; d = 64, H = 12, N = 4000, R = 5 108.5 / 94.6; not taken: H = 5, N = 9361, R = 2 353 / 378; H = 8, N = 15000,
 // R = 5 976 / 997; H = 12, N = 5000, R = 5 (240 workgroups) 218.6 / 215.4.  (81 sizes; the estimate was off by 10 us where it did not hold.)
 static int64_t large_tiles(const Plan &pl) { return (int64_t)((pl.N + 255) / 256) * pl.B * pl.H; }
