@@ -180,12 +180,13 @@ void make_plan(const ha_problem &p, const ha_feature_map *phi_q, const ha_featur
   pl.split_linear = plain && pl.HD == 256 && pl.F == 256;
   // With the 128-wide maps, for up to five (batch, head) pairs with a CU for every 128-query tile, a pass of its own over blocks of
   // 32 queries, which leaves the query kernel free to split the keys.  Where it does so in a long loop that is a gain; whole calls,
-  // epilogue / pass, us: R = 2, H = 1, N = 4500  57.8 / 52.7, 12000  108 / 77, H = 2, N = 8000  82.8 / 74.2; R = 4, H = 1, N = 8000  56.1 / 54.1,
-  // 20000  97.6 / 91.5.  Elsewhere the pass costs its launch, about 3 us, since the epilogue runs in workgroups of one wave per SIMD
-  // (ha_query_alone.hip): R = 2, H = 1, N = 500  29.5 / 32.9, 2000  39.7 / 40.5, H = 5, N = 3000  52.2 / 55.7; R = 4, H = 4, N = 2000  34.8 / 38.4;
-  // R = 16, H = 1, N = 8000  31.4 / 34.3, H = 5, N = 6500  43.4 / 50.4.  Five pairs were the largest number at which the pass was no loss
-  // against the epilogue before that, so the line is where every call keeps its route, not where it would be drawn today: the pass only
-  // where choose_split's estimate saves 4 us is 5.4 % faster over 547 problems (R = 2 .. 16, one to twelve heads) and never slower.
+  // in the query kernel / pass, us: R = 2, H = 1, N = 4500  55.1 / 49.9, 12000  110 / 75, H = 2, N = 8000  84.2 / 71.3; R = 4, H = 1, N = 8000  53.0 / 53.1,
+  // 20000  99.1 / 87.4.  Elsewhere it costs 2 - 10 us, its launch and the map's time, since the query kernel evaluates the map beside its key loop
+  // (ha_query_alone.hip): R = 2, H = 1, N = 500  26.6 / 30.9, 2000  36.8 / 38.4, H = 5, N = 3000  49.0 / 54.3; R = 4, H = 4, N = 2000  31.2 / 37.0;
+  // R = 16, H = 1, N = 8000  32.8 / 38.2, H = 5, N = 6500  36.3 / 46.3.  Five pairs were the largest number at which the pass was no loss
+  // against a map behind the loop of workgroups of eight waves, so the line is where every call keeps its route, not where it would be drawn today:
+  // the pass only where choose_split's estimate saves 4 us was 5.4 % faster over 547 problems (R = 2 .. 16, one to twelve heads) and never
+  // slower, with the map still behind the loop.
   if (plain && pl.HD == 128 && pl.F == 128 && pl.NS > 0 && BH <= 5 && ((size_t)pl.N + 127) / 128 * BH <= 256 &&
       route_has_room(pl, off, tiles * tile))
     pl.split_linear = true;

@@ -1,6 +1,5 @@
 // The feature map phi of Sec. 3.2 for the widths 128 -> 128 -> 128 on one 32-token column block, as the hand-placed
-// software pipeline that the state pass, the gradient pass, the linear query side (ha_linear.hip) and the query kernel's workgroups of one
-// wave per SIMD (ha_query_alone.hip) share.  gfx950 only.
+// software pipeline that the state pass, the gradient pass and the linear query side (ha_linear.hip) share.  gfx950 only.
 //   * Layer 1 runs two row blocks at a time (two independent accumulator chains, their matrix instructions
 //     alternate); the fragments of the second pair arrive four k-steps ahead of their use, and its matrix
 //     instructions carry the ReLU / hi + lo conversion of the first pair.

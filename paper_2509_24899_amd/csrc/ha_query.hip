@@ -115,11 +115,11 @@ static Tiling tiling_of(const Plan &pl, bool lin) {
   // SIMD, with a ring of 8 key blocks (ha_query_alone.hip); 8 waves x 32 queries with that ring and a barrier every 64 keys, one
   // workgroup per CU; and 4 waves x 32 queries with a ring of 4 and a barrier every 32 keys, two workgroups per CU.  The variants'
   // tiles are part of their definition, so block_size decides there between the latter two; for the plain operator the sizes do.
-  //   128-query tiles that do not outnumber the CUs: a workgroup has a CU to itself, so that one wave per SIMD with the long ring and
-  // all operands in LDS is best.  Whole calls, us, better one of the other two / alone: H = 12, R = 4, d = 128: N = 300 (B = 2)
-  // 35.7 / 31.2, 1560  43.1 / 36.2, 2600  47.4 / 42.0; H = 8, N = 3900, R = 2  69 / 58.8; one workgroup of 128 more than CUs (H = 6,
-  // N = 5400, R = 3)  67.5 / 89; d = 64: H = 2, N = 1024, fp32  26.0 / 24.3, H = 12, N = 2600, R = 2  46.4 / 39.9; rate 1: H = 8,
-  // N = 4000  77 / 72.8, d = 64, H = 4, N = 4000  56 / 48.  With the linear part precomputed a short loop is as long either way
+  //   128-query tiles that do not outnumber the CUs: a workgroup has a CU to itself, so that one wave per SIMD for the keys, with the map
+  // in waves of its own, is best.  Whole calls, us, better one of the other two / alone: H = 12, R = 4, d = 128: N = 300 (B = 2)
+  // 35.3 / 30.0, 1560  43.1 / 33.9, 2600  48.5 / 39.9; H = 8, N = 3900, R = 2  69.8 / 57.4; two workgroups more than CUs (H = 6,
+  // N = 5400, R = 3)  69.0 / 86.3; d = 64: H = 2, N = 1024, fp32  22.8 / 18.5, H = 12, N = 2600, R = 2  40.0 / 32.2; rate 1: H = 8,
+  // N = 4000  76.9 / 72.6, d = 64, H = 4, N = 4000  56.4 / 47.2.  With the linear part precomputed a short loop is as long either way
   // (6 key blocks 72.4 / 73.2, 13 68.5 / 68.5), a long one shorter (94: 106.1 / 104.1).
   const auto wgs = [&](int qt) { return (int64_t)((pl.N + qt - 1) / qt) * pl.B * pl.H; };
   const int64_t nblk = (pl.NS + 31) / 32;
